@@ -260,8 +260,8 @@ int sgp_make_jacobi(sgp_ctx ctx, sgp_bsr A, sgp_prec M);
 /* Number of parallel elimination steps of a tree preconditioner (host). */
 int sgp_prec_steps(sgp_prec M, int32_t *steps);
 /* Shape of a tree factor's elimination schedule (host outputs, each may be
- * NULL): the number of steps, the first step run by the one-workgroup tail
- * (== steps when there is none), the number of leading light steps, and the
+ * NULL): the number of steps, the first step run by the one-workgroup tail or
+ * the dense top block (== steps when there is neither), the number of leading light steps, and the
  * number of vertices of every step (step_sizes: `steps` entries). */
 int sgp_prec_info(sgp_prec M, int32_t *steps, int32_t *tail_step, int32_t *light_steps, int32_t *step_sizes);
 
@@ -460,7 +460,10 @@ int sgp_mpnn_warm_start(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, sgp_bsr Gamma, con
  *  "tail_max"     the largest number of tree vertices whose last elimination
  *                 steps run as one LDS-resident workgroup in the tree sweeps
  *                 (0..65536, 0 disables, default 2200; used by factors built
- *                 afterwards)
+ *                 afterwards).  CONTRACT factors of more than 2200 cells
+ *                 (without light steps or a local forest) have no such
+ *                 steps: their last ones, of at most 256 vertices, are one
+ *                 dense product with the inverse of their Schur complement
  *  "graph"        1: each chunk of check_every CG iterations is captured once
  *                 per solve into a hipGraph and replayed (default 0)
  *  "spmv_waves"   waves per workgroup of the product: 2, 4 or 8 (default 4)
@@ -475,11 +478,12 @@ int sgp_mpnn_warm_start(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, sgp_bsr Gamma, con
  *                 rake-and-compress, default 0; used by factors built
  *                 afterwards)
  *  "light_cap"    vertices of such subtrees packed into one workgroup
- *                 (1..2^20, default 512); also the packing of the mid
- *                 steps' components (CONTRACT without light steps: the
- *                 steps between the first two and the tail, from the first
- *                 with at most 2^17 vertices left, are swept one workgroup
- *                 per group of components, in one launch per sweep)
+ *                 (1..2^20, default 512); also the largest packing of the
+ *                 mid steps' components (CONTRACT without light steps: the
+ *                 steps between the first one or two and the dense last
+ *                 ones, from the first with at most 2^17 vertices left, are
+ *                 swept one workgroup per group of components, in one or two
+ *                 launches per sweep)
  *  "fuse_step0"   1: in sgp_pcg_solve* with a tree preconditioner whose
  *                 first elimination step runs as launches of its own, that
  *                 step's forward substitution runs inside the CG's
@@ -505,9 +509,8 @@ int sgp_mpnn_warm_start(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, sgp_bsr Gamma, con
  *                 p in that pass)
  *  "prefetch"     1: the launch before the one-workgroup tail of the tree
  *                 sweeps also loads the tail's constants, from the XCD that
- *                 runs the tail, and the tail launch's other workgroups load
- *                 the backward mid steps' constants, so that those launches'
- *                 start-up loads hit in the caches (default 1; 0: off)
+ *                 runs the tail, so that its start-up loads hit in the caches
+ *                 (default 1; 0: off)
  * Unknown keys or values out of range give SGP_EINVAL.  check_every,
  * graph, fuse_step0, mid_lds, tail_side and prefetch leave every result bitwise
  * unchanged, and so does tail_max as long as the tail does not reach the first elimination

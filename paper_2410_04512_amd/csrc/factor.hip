@@ -35,6 +35,7 @@
 #include <algorithm>
 #include <climits>
 #include <mutex>
+#include <type_traits>
 
 // ---------------------------------------------------------------- W and P_ii
 
@@ -387,44 +388,48 @@ __global__ __launch_bounds__(256) void k_step_hist_sum(int nb, int32_t S, const 
     if (threadIdx.x == 0) out[s] = sw[0] + sw[1] + sw[2] + sw[3];
 }
 
-// jr[v] = v for a vertex of steps m0..m1-1, -1 otherwise
-__global__ void k_mid_init(int64_t n, const int32_t *stepv, int32_t m0, int32_t m1, int32_t *jr)
-{
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v < n) jr[v] = stepv[v] >= m0 && stepv[v] < m1 ? (int32_t)v : -1;
-}
-
-// one round of hooking along the up-links between mid vertices: where the
-// two ends carry different labels, the larger label (a vertex of the
-// component) takes the smaller one as its label.  Labels only decrease and
-// stay members of the component, so with the jumps below they converge to
-// its smallest vertex; flag: a link still joined two labels
-__global__ void k_mid_link(int64_t n, const int32_t *up0, const int32_t *up1, int32_t *jr, int32_t *flag)
+// jr[v] for a vertex of steps m0..m1-1: its up-link eliminated first when that
+// lies in the same range (the steps below `cut`, or those from it on), else v
+// itself; -1 for other vertices.  Both up-links of a vertex are joined by its
+// elimination, so the one eliminated first is connected to the other: that
+// link alone leads from any vertex of a component to its last one, by
+// ascending steps, and ceil(log2(steps)) jumps (k_light_jump) label every
+// vertex with it.
+__global__ void k_mid_init(int64_t n, const int32_t *stepv, const int32_t *up0, const int32_t *up1, int32_t m0,
+                           int32_t m1, int32_t cut, int32_t *jr)
 {
     const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= n) return;
-    const int32_t a = jr[v];
-    if (a < 0) return;
-    const int32_t u[2] = {up0[v], up1[v]};
-    for (int k = 0; k < 2; k++) {
-        if (u[k] < 0) continue;
-        const int32_t b = jr[u[k]];
-        if (b < 0 || b == a) continue;
-        if (b < a)
-            atomicMin(&jr[a], b);
-        else
-            atomicMin(&jr[b], a);
-        flag[0] = 1;
+    const int32_t sv = stepv[v];
+    int32_t j = -1;
+    if (sv >= m0 && sv < m1) {
+        j = (int32_t)v;
+        const int32_t a = up0[v], b = up1[v];
+        const int32_t sa = a >= 0 ? stepv[a] : INT32_MAX, sb = b >= 0 ? stepv[b] : INT32_MAX;
+        const int32_t e = sb < sa ? b : a, se = sb < sa ? sb : sa;
+        if (e >= 0 && se < m1 && (se < cut) == (sv < cut)) j = e;
     }
+    jr[v] = j;
 }
 
-// jr[v] = jr[jr[v]]: a label's own label is no larger
-__global__ void k_mid_jump(int64_t n, int32_t *jr)
+// component sizes of the roots of steps a..b-1, walked in the internal order,
+// and their workgroups (as k_light_vals, k_light_rootwg)
+__global__ void k_mid_vals(int64_t n, const int32_t *perm, const int32_t *jr, const int32_t *cnt,
+                           const int32_t *stepv, int32_t a, int32_t b, int32_t *val)
 {
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= n) return;
-    const int32_t a = jr[v];
-    if (a >= 0) jr[v] = jr[a];
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int32_t v = perm[i];
+    val[i] = jr[v] == v && stepv[v] >= a && stepv[v] < b ? cnt[v] : 0;
+}
+
+__global__ void k_mid_rootwg(int64_t n, const int32_t *perm, const int32_t *jr, const int32_t *stepv, int32_t a,
+                             int32_t b, const int32_t *start, int32_t cap, int32_t *wgr)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int32_t v = perm[i];
+    if (jr[v] == v && stepv[v] >= a && stepv[v] < b) wgr[v] = start[i] / cap;
 }
 
 // first q of every (step, workgroup) key in [lo, hi], at wptr[key - lo]; keys sorted
@@ -930,6 +935,9 @@ constexpr int TAIL_DEFAULT_VERTICES = 2200;   // the tail_max knob's default
 // vertices the tail holds
 constexpr int TAIL_RHS_PER_THREAD = (3 * TAIL_MAX_VERTICES + TAIL_THREADS - 1) / TAIL_THREADS;
 constexpr int64_t MID_MAX_VERTICES = 1 << 17;   // vertices left at the first mid step at most
+constexpr int64_t MID_MIN_CAP = 64;             // vertices packed into a group before it is split for balance
+constexpr int64_t MID_GROUPS = 224;             // groups aimed at: a few less than CUs, since sizes vary
+constexpr double MID_MAX_RATIO = 300.0;         // of the vertices left at a mid range's ends
 
 // The tail's constants (pivots, both coupling planes, push slots, up-links,
 // ids, in-slot bounds of its nt vertices) loaded ahead, from the XCD that
@@ -1122,72 +1130,6 @@ SGP_DEV void side_x_update(const SideX &sd, int wg, int nwg)
     }
 }
 
-// The backward mid steps' constants (ids, up-links, their local indices,
-// pivots, both coupling planes) loaded ahead, from the XCD whose k_bwd_mid
-// workgroups will sweep them (the counters show k_bwd_mid fetching as many
-// bytes from beyond L2 as without it: the gain, 14.7 -> 12.7 us at 1M cells,
-// is the last-level cache's), by this XCD's extra workgroups of
-// the tail launch (block b of a launch runs on XCD b mod 8; k_bwd_mid's
-// group of block b is xcd_block(b), so XCD x sweeps one contiguous range of
-// groups, and in every mid step their positions are contiguous).  The
-// step ranges go through LDS; each workgroup takes its share of the
-// positions, two per thread per round, every load of a round issued before
-// any is used; the sums are stored only if sd.never says so.
-template <class T>
-SGP_DEV void mid_prefetch(const SideX &sd, int32_t nside, const int32_t *elim, const int32_t *upq, const T *F,
-                          int64_t fs, const T *Dinv, int32_t *rg, T *sink)
-{
-    const int32_t b = (int32_t)blockIdx.x, x = b % NUM_XCD, L = sd.mid_L;
-    const int32_t firstb = x == 0 ? NUM_XCD : x;   // this XCD's extra workgroups: firstb, firstb + 8, ...
-    const int32_t nx = (nside - firstb) / NUM_XCD + 1, ix = (b - firstb) / NUM_XCD;
-    const int32_t nw = sd.mid_nwg, q8 = nw / NUM_XCD, r8 = nw % NUM_XCD;
-    const int32_t w0 = x < r8 ? x * (q8 + 1) : r8 * (q8 + 1) + (x - r8) * q8;
-    const int32_t w1 = w0 + q8 + (x < r8 ? 1 : 0);
-    const int tid = threadIdx.x;
-    if (tid < 2 * L) rg[tid] = sd.mid_wptr[(int64_t)(tid >> 1) * nw + ((tid & 1) ? w1 : w0)];
-    __syncthreads();
-    int32_t P = 0;
-    for (int32_t k = 0; k < L; k++) P += rg[2 * k + 1] - rg[2 * k];
-    const int32_t f0 = (int32_t)((int64_t)P * ix / nx), f1 = (int32_t)((int64_t)P * (ix + 1) / nx);
-    T acc = 0;
-    int32_t iacc = 0;
-    for (int32_t f = f0 + tid; f < f1; f += 2 * TAIL_THREADS) {
-        int32_t q[2];
-        bool on[2];
-#pragma unroll
-        for (int u = 0; u < 2; u++) {
-            int32_t l = f + TAIL_THREADS * u, k = 0;
-            on[u] = l < f1;
-            while (k < L - 1 && l >= rg[2 * k + 1] - rg[2 * k]) {
-                l -= rg[2 * k + 1] - rg[2 * k];
-                k++;
-            }
-            q[u] = on[u] ? rg[2 * k] + l : rg[0];
-        }
-        T d[2][6], g0[2][9], g1[2][9];
-        int32_t iv[2][5];
-#pragma unroll
-        for (int u = 0; u < 2; u++) {
-            const int64_t qq = q[u];
-            iv[u][0] = elim[qq];
-            iv[u][1] = upq[2 * qq];
-            iv[u][2] = upq[2 * qq + 1];
-            iv[u][3] = sd.mid_lup[2 * (qq - sd.mid_Q0)];
-            iv[u][4] = sd.mid_lup[2 * (qq - sd.mid_Q0) + 1];
-            for (int t = 0; t < 6; t++) d[u][t] = Dinv[6 * qq + t];
-            for (int t = 0; t < 9; t++) g0[u][t] = F[9 * qq + t];
-            for (int t = 0; t < 9; t++) g1[u][t] = F[fs + 9 * qq + t];
-        }
-#pragma unroll
-        for (int u = 0; u < 2; u++) {
-            for (int t = 0; t < 5; t++) iacc += iv[u][t];
-            for (int t = 0; t < 6; t++) acc += d[u][t];
-            for (int t = 0; t < 9; t++) acc += g0[u][t] + g1[u][t];
-        }
-    }
-    if (sd.never) sink[0] = acc + (T)iacc;
-}
-
 // The tail's steps fall in two parts.  Steps whose vertices all lie in the
 // last TAIL_WINDOW tail vertices (the window, from step kw on: usually most
 // of the steps, few vertices each) give vertices base + t and base +
@@ -1207,22 +1149,17 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_tail(int32_t s0, int32_t S, in
                                                        const PcgScalars *s, SideX side)
 {
     extern __shared__ unsigned char lds_raw[];
-    // workgroups past the first: the CG's x update, meanwhile, then the
-    // backward mid steps' constants into the caches
+    // workgroups past the first: the CG's x update, meanwhile
     if (blockIdx.x > 0) {
         // unless the tail's constants were prefetched (k_tail_pre),
         // wait about 7 us (2 x 127 x 64 clocks) first, so that the tail's
         // own first loads are served before these streams fill the memory
-        // queues (1M cells, without the prefetches: the tail launch with the
-        // x update 35.9 us without the wait, 33.6 us with it, 32.6 us without
-        // the x update; with both prefetches, 26.3 us without the wait and
-        // 30.3 us with it)
+        // queues
         if (side.wait) {
             __builtin_amdgcn_s_sleep(127);
             __builtin_amdgcn_s_sleep(127);
         }
         if (side.nb > 0) side_x_update<T>(side, blockIdx.x - 1, gridDim.x - 1);
-        if (side.mid_L > 0) mid_prefetch<T>(side, gridDim.x - 1, elim, upq, F, fs, Dinv, (int32_t *)lds_raw, z);
         return;
     }
     T *sv = (T *)lds_raw;
@@ -1422,6 +1359,194 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_tail(int32_t s0, int32_t S, in
     for (int32_t k = kw - 1; k >= s0; k--) bstep(k);
 }
 
+// ---------------------------------------------------------------- the top block
+//
+// The last steps of a rake-and-compress elimination hold few vertices and
+// are a pure dependency chain: ten or more steps each way, each a round of
+// LDS reads, a few dependent FP64 operations and a barrier in one workgroup
+// (~0.6 us a step; with its start-up loads and the launch that forms its
+// right-hand sides the one-workgroup tail took 24-29 us of an iteration at
+// any size, 35 % of it at 2e4 cells).  So the steps with at most TOP_MAX
+// vertices left are not swept: their Schur complement (an SPD matrix of 3 nt
+// rows, the tree's Laplacian reduced to those vertices) is inverted once per
+// factor, column by column with the sweeps themselves (k_top_inverse), and an
+// apply is one dense product over the whole chip, k_top: 6.5 us, bound by its
+// three dependent rounds of loads (ids, slots, more slots), not by its bytes
+// (at most 768^2 values, 4.7 MB, the same every apply, which come from the
+// caches); 128 vertices at most instead of 256 measured the same.  Solves of
+// 2e4 and 5e4 cells 25.0 -> 16.4 and 24.7 -> 16.6 ms, 2e5 25.0 -> 21.4 ms, 1e6 the
+// same (there the CG's x update, which had run beside the tail, is back in
+// its own pass).
+constexpr int TOP_MAX = 256;       // vertices at most
+static_assert((3 * TOP_MAX) % 256 == 0, "whole column chunks");
+
+// One vertex of the top block per workgroup, wave c: column 3 j + c of the
+// inverse, by the forward and the backward sweep of a unit vector over the
+// top steps (values and push slots in LDS).  The matrix is symmetric, so the
+// column is stored as a row; columns past 3 nt are zero.
+constexpr int TOP_INV_THREADS = 192;
+static size_t top_inv_lds(int64_t nt, int64_t ni) { return 3 * 8 * 3 * (size_t)(nt + ni); }
+
+__global__ __launch_bounds__(TOP_INV_THREADS) void k_top_inverse(int32_t s0, int32_t S, const int32_t *sp, int32_t Qt,
+                                                                 int32_t nt, int32_t ni, const int32_t *iptr,
+                                                                 const int32_t *tslot, const int32_t *upq,
+                                                                 const double *F, int64_t fs, const double *Dinv,
+                                                                 int32_t ld, double *out)
+{
+    extern __shared__ unsigned char lds_raw[];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    double *sv = (double *)lds_raw + (size_t)wv * 3 * (nt + ni);
+    double *slot = sv + 3 * nt;
+    const int32_t col = 3 * (int32_t)blockIdx.x + wv;
+    for (int32_t i = lane; i < 3 * nt; i += 64) sv[i] = i == col ? 1.0 : 0.0;
+    lds_wave_barrier();
+    for (int32_t k = s0; k < S; k++) {
+        const int32_t hi = sp[k + 1] - Qt;
+        for (int32_t i = sp[k] - Qt + lane; i < hi; i += 64) {
+            const int64_t q = Qt + i;
+            const double *d = Dinv + 6 * q;
+            double b0 = sv[3 * i], b1 = sv[3 * i + 1], b2 = sv[3 * i + 2], o0, o1, o2;
+            for (int32_t t = iptr[i]; t < iptr[i + 1]; t++) {
+                b0 = b0 - slot[3 * t];
+                b1 = b1 - slot[3 * t + 1];
+                b2 = b2 - slot[3 * t + 2];
+            }
+            sym_mv(d, b0, b1, b2, o0, o1, o2);
+            sv[3 * i] = o0;
+            sv[3 * i + 1] = o1;
+            sv[3 * i + 2] = o2;
+            for (int m = 0; m < 2; m++) {
+                const int32_t t = tslot[2 * i + m];
+                if (t < 0) continue;
+                const double *g = F + m * fs + 9 * q;
+                slot[3 * t] = g[0] * o0 + g[1] * o1 + g[2] * o2;
+                slot[3 * t + 1] = g[3] * o0 + g[4] * o1 + g[5] * o2;
+                slot[3 * t + 2] = g[6] * o0 + g[7] * o1 + g[8] * o2;
+            }
+        }
+        lds_wave_barrier();
+    }
+    for (int32_t k = S - 1; k >= s0; k--) {
+        const int32_t hi = sp[k + 1] - Qt;
+        for (int32_t i = sp[k] - Qt + lane; i < hi; i += 64) {
+            const int64_t q = Qt + i;
+            double c0 = 0, c1 = 0, c2 = 0, e0, e1, e2;
+            for (int m = 0; m < 2; m++) {
+                const int32_t a = upq[2 * q + m];
+                if (a < 0) continue;
+                const double *g = F + m * fs + 9 * q, *xs = sv + 3 * (a - Qt);
+                const double x0 = xs[0], x1 = xs[1], x2 = xs[2];
+                c0 = c0 + (g[0] * x0 + g[3] * x1 + g[6] * x2);
+                c1 = c1 + (g[1] * x0 + g[4] * x1 + g[7] * x2);
+                c2 = c2 + (g[2] * x0 + g[5] * x1 + g[8] * x2);
+            }
+            sym_mv(Dinv + 6 * q, c0, c1, c2, e0, e1, e2);
+            sv[3 * i] = sv[3 * i] - e0;
+            sv[3 * i + 1] = sv[3 * i + 1] - e1;
+            sv[3 * i + 2] = sv[3 * i + 2] - e2;
+        }
+        lds_wave_barrier();
+    }
+    for (int32_t i = lane; i < ld; i += 64) out[(int64_t)col * ld + i] = i < 3 * nt ? sv[i] : 0.0;
+}
+
+// x of the top block: the dense inverse (rows of 64 NC values) times the
+// right-hand sides, r minus the pushes from vertices eliminated before (all
+// finished by the launch boundary).  Every workgroup forms all right-hand
+// sides while its ROWS rows per wave are in flight: TOP_LANES lanes per
+// vertex, since the last vertices have many slots and a lane's chunks of them
+// would be dependent rounds of loads.  x goes to y (for the steps below) and
+// to z.
+constexpr int TOP_LANES = 4;
+template <class T, int NC, int ROWS>
+__global__ __launch_bounds__(256) void k_top(int32_t Qt, int32_t nt, const int32_t *elim, const int32_t *in_ptr,
+                                             const int32_t *iptr, const T *inv, const T *r, const T *cs, T *y, T *z,
+                                             const PcgScalars *s)
+{
+    constexpr int PER = 256 / TOP_LANES;                      // vertices per round
+    constexpr int RND = (64 * NC / 3 + PER - 1) / PER;        // rounds
+    __shared__ T b[3 * PER * RND > 64 * NC ? 3 * PER * RND : 64 * NC];
+    const int tid = threadIdx.x, lane = tid & 63, sub = tid & (TOP_LANES - 1);
+    const int32_t N = 3 * nt, row0 = ((int32_t)blockIdx.x * 4 + (tid >> 6)) * ROWS;
+    const int32_t dn = done_flag(s);
+    // ids first (the gathers wait for them), then the matrix rows (used last)
+    int64_t v[RND];
+    int32_t t0[RND], t1[RND];
+#pragma unroll
+    for (int k = 0; k < RND; k++) {
+        const int32_t i = min(tid / TOP_LANES + PER * k, nt - 1), q = Qt + i;
+        v[k] = elim[q];
+        t0[k] = in_ptr[q];
+        t1[k] = in_ptr[q + 1] - (iptr[i + 1] - iptr[i]);
+    }
+    const int64_t ov = elim[Qt + min(row0 + (lane & (ROWS - 1)), N - 1) / 3];
+    keep_loads_above();
+    T a[ROWS][NC];
+#pragma unroll
+    for (int u = 0; u < ROWS; u++)
+#pragma unroll
+        for (int c = 0; c < NC; c++) a[u][c] = inv[(int64_t)min(row0 + u, N - 1) * (64 * NC) + 64 * c + lane];
+    T g[RND][3], h[RND][2][3];
+#pragma unroll
+    for (int k = 0; k < RND; k++) {
+        for (int m = 0; m < 3; m++) g[k][m] = r[3 * v[k] + m];
+        for (int w = 0; w < 2; w++) {
+            const T *c = cs + 3 * (int64_t)max(min(t0[k] + sub + TOP_LANES * w, t1[k] - 1), t0[k]);
+            for (int m = 0; m < 3; m++) h[k][w][m] = c[m];
+        }
+    }
+    keep_loads_above();
+#pragma unroll
+    for (int k = 0; k < RND; k++) {
+        T c0 = 0, c1 = 0, c2 = 0;
+        for (int w = 0; w < 2; w++)
+            if (t0[k] + sub + TOP_LANES * w < t1[k]) {
+                c0 = c0 + h[k][w][0];
+                c1 = c1 + h[k][w][1];
+                c2 = c2 + h[k][w][2];
+            }
+        for (int32_t t = t0[k] + sub + 2 * TOP_LANES; t < t1[k]; t += TOP_LANES) {
+            const T *c = cs + 3 * (int64_t)t;
+            c0 = c0 + c[0];
+            c1 = c1 + c[1];
+            c2 = c2 + c[2];
+        }
+        for (int o = 1; o < TOP_LANES; o <<= 1) {
+            c0 = c0 + __shfl_xor(c0, o, 64);
+            c1 = c1 + __shfl_xor(c1, o, 64);
+            c2 = c2 + __shfl_xor(c2, o, 64);
+        }
+        const int32_t i = tid / TOP_LANES + PER * k;
+        if (sub < 3) {
+            const T w = sub == 0 ? g[k][0] - c0 : sub == 1 ? g[k][1] - c1 : g[k][2] - c2;
+            b[3 * i + sub] = i < nt ? w : (T)0;
+        }
+    }
+    for (int k = 3 * PER * RND + tid; k < 64 * NC; k += 256) b[k] = 0;
+    __syncthreads();
+    if (dn) return;
+    T acc[ROWS];
+#pragma unroll
+    for (int u = 0; u < ROWS; u++) acc[u] = 0;
+#pragma unroll
+    for (int c = 0; c < NC; c++) {
+        const T bc = b[64 * c + lane];
+#pragma unroll
+        for (int u = 0; u < ROWS; u++) acc[u] = acc[u] + a[u][c] * bc;
+    }
+    T o = 0;
+#pragma unroll
+    for (int u = 0; u < ROWS; u++) {
+        T w = acc[u];
+        for (int e = 32; e > 0; e >>= 1) w = w + __shfl_xor(w, e, 64);
+        o = lane == u ? w : o;
+    }
+    if (lane < ROWS && row0 + lane < N) {
+        y[3 * (int64_t)Qt + row0 + lane] = o;
+        z[3 * ov + (row0 + lane) % 3] = o;
+    }
+}
+
 // ---------------------------------------------------------------- mid steps in LDS
 
 // The mid steps (between the large first steps and the tail) split into
@@ -1429,19 +1554,16 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_tail(int32_t s0, int32_t S, in
 // (mid_ptr); every push between mid vertices, and every read of x between
 // them, stays inside a group.  The sweeps below keep a group's push slots and
 // x values in LDS: a thread takes the group's local vertices tid and tid +
-// MID_THREADS (local order: by step, then position), loads all their
+// THREADS (local order: by step, then position), loads all their
 // constants, their r and their slots filled by earlier launches at the start,
-// and then only LDS and barriers separate the steps.  Pushes to vertices
+// and then only LDS and barriers separate the steps.  THREADS x VPT local
+// vertices are held: the smallest shape that holds the range's largest group
+// is launched (mid_shape), so that small groups leave no threads idle.  Pushes to vertices
 // outside the group (later steps, the tail) and x of up-links outside it go
 // through global memory as before.  Same operations in the same order as
 // fwd_vertex / bwd_vertex, so results are bitwise unchanged.
-constexpr int MID_THREADS = 512;
-// vertices of one group at most (components are packed by their first
-// vertex's offset / light_cap, so a group can exceed light_cap by up to one
-// component less a vertex)
-constexpr int MID_LDS_MAX = 1024;
-constexpr int MID_VPT = MID_LDS_MAX / MID_THREADS;   // a thread's vertices
-static_assert(MID_VPT * MID_THREADS == MID_LDS_MAX, "whole vertices per thread");
+constexpr int MID_LDS_MAX = 1024;   // vertices of one group at most
+constexpr int MID_THREADS = 512;    // threads of k_mid_local, and of the widest sweeps
 
 // per mid vertex (index q - Q0): local index, first LDS slot and number of
 // in-entries from mid vertices; per push (2 (q - Q0) + k): its LDS slot or -1;
@@ -1451,8 +1573,7 @@ struct MidTab {
 };
 
 constexpr int MID_MAX_STEPS = 64;   // mid steps at most for the LDS sweeps
-constexpr int TAIL_EXTRA_WG = 255;   // extra workgroups of the tail launch that prefetch: one per other CU
-static_assert(2 * MID_MAX_STEPS <= TAIL_THREADS, "the step ranges load in one round");
+static_assert(2 * MID_MAX_STEPS <= 128, "the step ranges load in one round");
 
 // the group's position range of each of its L steps, rg[2k] .. rg[2k + 1],
 // loaded into LDS in one round (a walk over global memory would take a
@@ -1491,48 +1612,50 @@ __global__ void k_mid_nint(int32_t Q0, int32_t Q1, const int32_t *in_ptr, const 
 }
 
 // one workgroup per group: local indices and the first LDS slot of every
-// vertex's mid in-entries (exclusive sum in local order); flag: a group with
-// more than MID_LDS_MAX vertices or 2 MID_LDS_MAX slots
+// vertex's mid in-entries (exclusive sum in local order); maxg: the range's
+// largest group (INT32_MAX: a group of more than MID_LDS_MAX vertices, or more
+// than MID_MAX_STEPS steps).  A vertex pushes to at most two others, so a
+// group never has more than twice as many slots as vertices.
 __global__ __launch_bounds__(MID_THREADS) void k_mid_local(int32_t L, int32_t nwg, const int32_t *wptr, int32_t Q0,
                                                            const int32_t *nint, int32_t *lid, int32_t *lin0,
-                                                           int32_t *flag)
+                                                           int32_t *maxg)
 {
-    __shared__ int32_t cnt[MID_LDS_MAX], tot_sh[1], rg[2 * MID_MAX_STEPS];
+    constexpr int VPT = MID_LDS_MAX / MID_THREADS;
+    __shared__ int32_t wsum[MID_THREADS / 64], rg[2 * MID_MAX_STEPS];
     const int32_t w = blockIdx.x, tid = threadIdx.x;
     if (L > MID_MAX_STEPS) {
-        if (tid == 0) flag[0] = 1;
+        if (tid == 0) atomicMax(maxg, INT32_MAX);
         return;
     }
     mid_ranges(L, nwg, wptr, w, rg);
     int32_t tot = 0;
     for (int32_t k = 0; k < L; k++) tot += rg[2 * k + 1] - rg[2 * k];
-    if (tot > MID_LDS_MAX) {
-        if (tid == 0) flag[0] = 1;
-        return;
+    if (tid == 0) atomicMax(maxg, tot > MID_LDS_MAX ? INT32_MAX : tot);
+    if (tot > MID_LDS_MAX) return;
+    // a thread's VPT consecutive local vertices, then the sums before it
+    int32_t q[VPT], c[VPT], st, own = 0;
+    for (int u = 0; u < VPT; u++) {
+        const int32_t l = tid * VPT + u;
+        q[u] = mid_local(L, rg, l, st);
+        c[u] = l < tot ? nint[q[u] - Q0] : 0;
+        own += c[u];
     }
-    int32_t q[MID_VPT], st[MID_VPT];
-    for (int u = 0; u < MID_VPT; u++) {
-        const int32_t l = tid + MID_THREADS * u;
-        q[u] = mid_local(L, rg, l, st[u]);
-        cnt[l] = l < tot ? nint[q[u] - Q0] : 0;
+    int32_t inc = own;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int32_t up = __shfl_up(inc, o, 64);
+        if ((tid & 63) >= o) inc += up;
     }
+    if ((tid & 63) == 63) wsum[tid >> 6] = inc;
     __syncthreads();
-    if (tid == 0) {   // exclusive sum, in local order
-        int32_t s = 0;
-        for (int32_t l = 0; l < tot; l++) {
-            const int32_t c = cnt[l];
-            cnt[l] = s;
-            s += c;
+    int32_t before = inc - own;
+    for (int k = 0; k < (tid >> 6); k++) before += wsum[k];
+    for (int u = 0; u < VPT; u++) {
+        const int32_t l = tid * VPT + u;
+        if (l < tot) {
+            lid[q[u] - Q0] = l;
+            lin0[q[u] - Q0] = before;
         }
-        tot_sh[0] = s;
-        if (s > 2 * MID_LDS_MAX) flag[0] = 1;
-    }
-    __syncthreads();
-    for (int u = 0; u < MID_VPT; u++) {
-        const int32_t l = tid + MID_THREADS * u;
-        if (l >= tot) continue;
-        lid[q[u] - Q0] = l;
-        lin0[q[u] - Q0] = cnt[l];
+        before += c[u];
     }
 }
 
@@ -1562,26 +1685,26 @@ __global__ void k_mid_lup(int32_t Q0, int32_t Q1, const int32_t *upq, const int3
 
 // the forward sweep of the mid steps: y_q = Dinv_q (r_v - its slots), the
 // pushes to LDS (inside the group) or to cs (outside)
-template <class T>
-__global__ __launch_bounds__(MID_THREADS) void k_fwd_mid(int32_t L, int32_t nwg, const int32_t *wptr, int32_t Q0,
+template <class T, int THREADS, int VPT>
+__global__ __launch_bounds__(THREADS) void k_fwd_mid(int32_t L, int32_t nwg, const int32_t *wptr, int32_t Q0,
                                                          const int32_t *elim, const int32_t *in_ptr,
                                                          const int32_t *tout, const T *F, int64_t fs, const T *Dinv,
                                                          const T *r, T *y, T *cs, MidTab tab, const PcgScalars *s)
 {
-    __shared__ T sl[3 * 2 * MID_LDS_MAX];
+    __shared__ T sl[3 * 2 * THREADS * VPT];
     __shared__ int32_t rg[2 * MID_MAX_STEPS];
     if (s && s->done) return;
     const int32_t w = (int32_t)xcd_block(blockIdx.x, gridDim.x), tid = threadIdx.x;
     mid_ranges(L, nwg, wptr, w, rg);
-    int32_t q[MID_VPT], st[MID_VPT], ni[MID_VPT], l0[MID_VPT], ls[MID_VPT][2], to[MID_VPT][2], t0[MID_VPT], t1[MID_VPT];
-    int64_t v[MID_VPT];
-    T d[MID_VPT][6], f0[MID_VPT][9], f1[MID_VPT][9], b[MID_VPT][3], h[MID_VPT][12];
+    int32_t q[VPT], st[VPT], ni[VPT], l0[VPT], ls[VPT][2], to[VPT][2], t0[VPT], t1[VPT];
+    int64_t v[VPT];
+    T d[VPT][6], f0[VPT][9], f1[VPT][9], b[VPT][3], h[VPT][12];
     // two rounds of loads for both vertices: what the position gives, then
     // what those values address (r, the second coupling, the first four slots
     // filled by earlier launches, clamped); one wait between them
 #pragma unroll
-    for (int u = 0; u < MID_VPT; u++) {
-        q[u] = mid_local(L, rg, tid + MID_THREADS * u, st[u]);
+    for (int u = 0; u < VPT; u++) {
+        q[u] = mid_local(L, rg, tid + THREADS * u, st[u]);
         const int32_t qc = st[u] >= 0 ? q[u] : Q0;   // a thread without a vertex loads a valid one
         v[u] = elim[qc];
         t0[u] = in_ptr[qc];
@@ -1597,7 +1720,7 @@ __global__ __launch_bounds__(MID_THREADS) void k_fwd_mid(int32_t L, int32_t nwg,
     }
     keep_loads_above();
 #pragma unroll
-    for (int u = 0; u < MID_VPT; u++) {
+    for (int u = 0; u < VPT; u++) {
         const int32_t qc = st[u] >= 0 ? q[u] : Q0;
         b[u][0] = r[3 * v[u]];
         b[u][1] = r[3 * v[u] + 1];
@@ -1616,7 +1739,7 @@ __global__ __launch_bounds__(MID_THREADS) void k_fwd_mid(int32_t L, int32_t nwg,
     // r minus the slots filled by earlier launches (the first in-entries), in
     // slot order: the first four from h, any further ones loaded here
 #pragma unroll
-    for (int u = 0; u < MID_VPT; u++) {
+    for (int u = 0; u < VPT; u++) {
         const int32_t te = t1[u] - ni[u];
         for (int m = 0; m < 4; m++)
             if (t0[u] + m < te) {
@@ -1628,7 +1751,7 @@ __global__ __launch_bounds__(MID_THREADS) void k_fwd_mid(int32_t L, int32_t nwg,
     }
     for (int32_t k = 0; k < L; k++) {
 #pragma unroll
-        for (int u = 0; u < MID_VPT; u++) {
+        for (int u = 0; u < VPT; u++) {
             if (st[u] != k) continue;
             T c0 = b[u][0], c1 = b[u][1], c2 = b[u][2];
             for (int32_t j = 0; j < ni[u]; j++) {
@@ -1661,24 +1784,24 @@ __global__ __launch_bounds__(MID_THREADS) void k_fwd_mid(int32_t L, int32_t nwg,
 // the backward sweep of the mid steps: x_q = y_q - Dinv_q (sum over up-links
 // of F^T x), x of a mid up-link from LDS, of others from y; x written to y
 // (for the steps below) and to z
-template <class T>
-__global__ __launch_bounds__(MID_THREADS) void k_bwd_mid(int32_t L, int32_t nwg, const int32_t *wptr, int32_t Q0,
+template <class T, int THREADS, int VPT>
+__global__ __launch_bounds__(THREADS) void k_bwd_mid(int32_t L, int32_t nwg, const int32_t *wptr, int32_t Q0,
                                                          const int32_t *elim, const int32_t *upq, const T *F,
                                                          int64_t fs, const T *Dinv, T *y, T *z, MidTab tab,
                                                          const PcgScalars *s)
 {
-    __shared__ T xl[3 * MID_LDS_MAX];
+    __shared__ T xl[3 * THREADS * VPT];
     __shared__ int32_t rg[2 * MID_MAX_STEPS];
     if (s && s->done) return;
     const int32_t w = (int32_t)xcd_block(blockIdx.x, gridDim.x), tid = threadIdx.x;
     mid_ranges(L, nwg, wptr, w, rg);
-    int32_t q[MID_VPT], st[MID_VPT], lu[MID_VPT][2], ua[MID_VPT][2];
-    int64_t v[MID_VPT];
-    T d[MID_VPT][6], f0[MID_VPT][9], f1[MID_VPT][9], yo[MID_VPT][3], xo[MID_VPT][2][3];
+    int32_t q[VPT], st[VPT], lu[VPT][2], ua[VPT][2];
+    int64_t v[VPT];
+    T d[VPT][6], f0[VPT][9], f1[VPT][9], yo[VPT][3], xo[VPT][2][3];
     // two rounds of loads for both vertices, one wait between them
 #pragma unroll
-    for (int u = 0; u < MID_VPT; u++) {
-        q[u] = mid_local(L, rg, tid + MID_THREADS * u, st[u]);
+    for (int u = 0; u < VPT; u++) {
+        q[u] = mid_local(L, rg, tid + THREADS * u, st[u]);
         const int32_t qc = st[u] >= 0 ? q[u] : Q0;
         v[u] = elim[qc];
         for (int k = 0; k < 2; k++) {
@@ -1693,7 +1816,7 @@ __global__ __launch_bounds__(MID_THREADS) void k_bwd_mid(int32_t L, int32_t nwg,
     keep_loads_above();
     // x of up-links outside the group (final: swept by earlier launches)
 #pragma unroll
-    for (int u = 0; u < MID_VPT; u++) {
+    for (int u = 0; u < VPT; u++) {
         const int32_t qc = st[u] >= 0 ? q[u] : Q0;
         for (int k = 0; k < 2; k++) {
             const int64_t a = ua[u][k] >= 0 && lu[u][k] < 0 ? ua[u][k] : qc;
@@ -1702,7 +1825,7 @@ __global__ __launch_bounds__(MID_THREADS) void k_bwd_mid(int32_t L, int32_t nwg,
     }
     for (int32_t k = L - 1; k >= 0; k--) {
 #pragma unroll
-        for (int u = 0; u < MID_VPT; u++) {
+        for (int u = 0; u < VPT; u++) {
             if (st[u] != k) continue;
             T a0 = 0, a1 = 0, a2 = 0;
             for (int m = 0; m < 2; m++) {
@@ -1722,7 +1845,7 @@ __global__ __launch_bounds__(MID_THREADS) void k_bwd_mid(int32_t L, int32_t nwg,
             T e0, e1, e2;
             sym_mv(d[u], a0, a1, a2, e0, e1, e2);
             const T n0 = yo[u][0] - e0, n1 = yo[u][1] - e1, n2 = yo[u][2] - e2;
-            const int32_t l = tid + MID_THREADS * u;
+            const int32_t l = tid + THREADS * u;
             xl[3 * l] = n0;
             xl[3 * l + 1] = n1;
             xl[3 * l + 2] = n2;
@@ -1738,6 +1861,22 @@ __global__ __launch_bounds__(MID_THREADS) void k_bwd_mid(int32_t L, int32_t nwg,
         // read by no thread of this launch
         lds_barrier();
     }
+}
+
+// launches f with the smallest shape (threads, vertices per thread) that holds
+// a group of max_group vertices
+template <class Fn>
+static void mid_shape(int32_t max_group, Fn f)
+{
+    using std::integral_constant;
+    if (max_group <= 128)
+        f(integral_constant<int, 128>(), integral_constant<int, 1>());
+    else if (max_group <= 256)
+        f(integral_constant<int, 256>(), integral_constant<int, 1>());
+    else if (max_group <= 512)
+        f(integral_constant<int, 256>(), integral_constant<int, 2>());
+    else
+        f(integral_constant<int, MID_THREADS>(), integral_constant<int, MID_LDS_MAX / MID_THREADS>());
 }
 
 int tail_setup_attr(sgp_ctx ctx)
@@ -1804,8 +1943,7 @@ int32_t prec_step0_launch(sgp_prec M)
     if (!M || M->kind != PREC_TREE || M->n_wu0 <= 0 || !M->step0_sorted || M->light_steps > 0 || M->tail_step <= 0)
         return 0;
     if ((int64_t)M->h_step_ptr.size() < 2 || M->n_wu0 != M->h_step_ptr[1]) return 0;
-    const int32_t m1 = std::min(M->mid_step0 + M->mid_steps, M->tail_step);
-    if (M->mid_steps > 0 && M->mid_step0 == 0 && m1 >= 2) return 0;
+    if (M->n_mid > 0 && M->mid[0].step0 == 0) return 0;
     return M->h_step_ptr[1];
 }
 
@@ -1830,31 +1968,35 @@ static int tree_sweeps(sgp_ctx ctx, sgp_prec M, const T *F, const T *Dinv, T *y,
     // the first step from the contacts' (w, u) when it is one of these launches
     const bool step0_wu = wu0 && L == 0 && ts > 0 && M->n_wu0 == sp[1];
     const T gp = (T)M->gpar, gq = (T)M->gperp, gm = (T)M->gmed;
-    // the mid steps m0..m1-1 below the tail: one launch per sweep, a
+    // the mid ranges below the tail: one launch per sweep and range, a
     // workgroup per packed group of components
-    const int32_t m0 = M->mid_step0, m1 = std::min(M->mid_step0 + M->mid_steps, ts);
-    const bool mid = M->mid_steps > 0 && m0 >= L && m1 - m0 >= 2;
-    const int32_t *mptr = (const int32_t *)M->mid_ptr.p;
-    // the mid steps in LDS when their tables were built (knob mid_lds)
-    const bool mid_lds = mid && M->mid_lds && ctx->mid_lds && m0 >= 1;
-    MidTab mtab = {};
-    if (mid_lds) {
-        const int32_t Nm = sp[m1] - sp[m0];
-        const int32_t *tb = (const int32_t *)M->mid_tab.p;
-        mtab = {tb, tb + Nm, tb + 2 * (size_t)Nm, tb + 3 * (size_t)Nm, tb + 5 * (size_t)Nm};
-    }
+    auto range_of = [&](int k) -> const sgp_prec_::MidRange * {
+        for (int m = 0; m < M->n_mid; m++)
+            if (k >= M->mid[m].step0 && k < M->mid[m].step0 + M->mid[m].steps) return &M->mid[m];
+        return nullptr;
+    };
+    auto range_ptr = [&](const sgp_prec_::MidRange *g) {
+        return (const int32_t *)M->mid_ptr.p + (size_t)(g->step0 - M->mid[0].step0) * M->mid_stride;
+    };
+    // a range's steps in LDS when its tables were built (knob mid_lds)
+    auto range_tab = [&](const sgp_prec_::MidRange *g) {
+        const int32_t Nm = sp[g->step0 + g->steps] - sp[g->step0];
+        const int32_t *tb = (const int32_t *)M->mid_tab.p + g->tab;
+        return MidTab{tb, tb + Nm, tb + 2 * (size_t)Nm, tb + 3 * (size_t)Nm, tb + 5 * (size_t)Nm};
+    };
     for (int k = L; k < ts; k++) {
         int32_t q0 = sp[k], q1 = sp[k + 1];
-        if (mid && k == m0 && mid_lds) {
-            k_fwd_mid<T><<<M->mid_nwg, MID_THREADS, 0, st>>>(m1 - m0, M->mid_nwg, mptr, sp[m0], elim, in_ptr, tout, F,
-                                                            fs, Dinv, r, y, cs, mtab, s);
-            k = m1 - 1;
-            continue;
-        }
-        if (mid && k == m0) {
-            k_fwd_light<T><<<M->mid_nwg, 256, 0, st>>>(m1 - m0, M->mid_nwg, mptr, elim, in_ptr, tout, F, fs, Dinv, r,
-                                                       y, cs, s);
-            k = m1 - 1;
+        if (const sgp_prec_::MidRange *g = range_of(k)) {
+            if (g->lds && ctx->mid_lds)
+                mid_shape(g->max_group, [&](auto th, auto vpt) {
+                    k_fwd_mid<T, decltype(th)::value, decltype(vpt)::value><<<g->nwg, decltype(th)::value, 0, st>>>(
+                        g->steps, M->mid_stride, range_ptr(g), q0, elim, in_ptr, tout, F, fs, Dinv, r, y, cs,
+                        range_tab(g), s);
+                });
+            else
+                k_fwd_light<T><<<g->nwg, 256, 0, st>>>(g->steps, M->mid_stride, range_ptr(g), elim, in_ptr, tout, F,
+                                                       fs, Dinv, r, y, cs, s);
+            k += g->steps - 1;
             continue;
         }
         if (k == 0 && step0_wu && skip0) continue;
@@ -1865,8 +2007,25 @@ static int tree_sweeps(sgp_ctx ctx, sgp_prec M, const T *F, const T *Dinv, T *y,
             k_fwd_step<T><<<grid_for(q1 - q0, 256), 256, 0, st>>>(q0, q1, elim, in_ptr, tout, F, fs, Dinv, r, y, cs,
                                                                   s);
     }
-    if (ts < S) {
-        size_t lds = tail_lds_bytes(sizeof(T), M->tail_nt, M->tail_ni, S - ts);
+    if (ts < S && M->top) {
+        const int32_t nt = M->tail_nt;
+        const int32_t *iptr = (const int32_t *)M->tail_iptr.p;
+        const T *inv = (const T *)(sizeof(T) == 8 ? M->top_inv.p : M->top_inv32.p);
+        // about 32 matrix values per lane in flight
+        auto top = [&](auto nc, auto rows) {
+            constexpr int R = decltype(rows)::value;
+            k_top<T, decltype(nc)::value, R><<<(3 * nt + 4 * R - 1) / (4 * R), 256, 0, st>>>(
+                sp[ts], nt, elim, in_ptr, iptr, inv, r, cs, y, z, s);
+        };
+        using std::integral_constant;
+        if (M->top_ld == 256)
+            top(integral_constant<int, 4>(), integral_constant<int, 4>());
+        else if (M->top_ld == 512)
+            top(integral_constant<int, 8>(), integral_constant<int, 4>());
+        else
+            top(integral_constant<int, 12>(), integral_constant<int, 2>());
+    } else if (ts < S) {
+        const size_t lds = tail_lds_bytes(sizeof(T), M->tail_nt, M->tail_ni, S - ts);
         const int32_t nt = M->tail_nt;
         if (nt > TAIL_MAX_VERTICES) return set_err(ctx, SGP_EINVAL, "tree sweeps: tail of %d vertices", nt);
         T *tb = (T *)M->tail_b.p;
@@ -1888,18 +2047,7 @@ static int tree_sweeps(sgp_ctx ctx, sgp_prec M, const T *F, const T *Dinv, T *y,
             sd = *side;
             side->ran = true;
         }
-        // and, one per other CU, they load the backward mid steps' constants
-        // ahead of k_bwd_mid (knob prefetch)
         sd.wait = !ctx->prefetch;
-        if (ctx->prefetch && mid_lds) {
-            sd.mid_wptr = mptr;
-            sd.mid_lup = mtab.lup;
-            sd.mid_L = m1 - m0;
-            sd.mid_nwg = M->mid_nwg;
-            sd.mid_Q0 = sp[m0];
-            sd.nwg = TAIL_EXTRA_WG;
-            lds = std::max(lds, (size_t)(2 * MID_MAX_STEPS * sizeof(int32_t)));
-        }
         // the last window steps whose vertices all belong to one wave (the
         // owner of tail-local index i: i - base in the first half of the
         // window, i - base - TAIL_THREADS in the second), which sweeps them
@@ -1921,15 +2069,17 @@ static int tree_sweeps(sgp_ctx ctx, sgp_prec M, const T *F, const T *Dinv, T *y,
     }
     for (int k = ts - 1; k >= L; k--) {
         int32_t q0 = sp[k], q1 = sp[k + 1];
-        if (mid && k == m1 - 1 && mid_lds) {
-            k_bwd_mid<T><<<M->mid_nwg, MID_THREADS, 0, st>>>(m1 - m0, M->mid_nwg, mptr, sp[m0], elim, upq, F, fs, Dinv,
-                                                            y, z, mtab, s);
-            k = m0;
-            continue;
-        }
-        if (mid && k == m1 - 1) {
-            k_bwd_light<T><<<M->mid_nwg, 256, 0, st>>>(m1 - m0, M->mid_nwg, mptr, elim, upq, F, fs, Dinv, y, z, s);
-            k = m0;
+        if (const sgp_prec_::MidRange *g = range_of(k)) {
+            if (g->lds && ctx->mid_lds)
+                mid_shape(g->max_group, [&](auto th, auto vpt) {
+                    k_bwd_mid<T, decltype(th)::value, decltype(vpt)::value><<<g->nwg, decltype(th)::value, 0, st>>>(
+                        g->steps, M->mid_stride, range_ptr(g), sp[g->step0], elim, upq, F, fs, Dinv, y, z,
+                        range_tab(g), s);
+                });
+            else
+                k_bwd_light<T><<<g->nwg, 256, 0, st>>>(g->steps, M->mid_stride, range_ptr(g), elim, upq, F, fs, Dinv,
+                                                       y, z, s);
+            k = g->step0;
             continue;
         }
         if (k == 0 && step0_wu && skip0) continue;
@@ -1997,6 +2147,12 @@ int prec_make32(sgp_ctx ctx, sgp_prec M)
         SGP_TRY(ensure_t(ctx, M->cs32, 6 * n + 6, &cs32));
         k_to_f32<<<grid_for(18 * n, 256), 256, 0, st>>>(18 * n, (const double *)M->F.p, F32);
         k_to_f32<<<grid_for(6 * n, 256), 256, 0, st>>>(6 * n, (const double *)M->Dinv.p, D32);
+        if (M->top) {
+            const int64_t len = 3 * (int64_t)M->tail_nt * M->top_ld;
+            float *i32;
+            SGP_TRY(ensure_t(ctx, M->top_inv32, len, &i32));
+            k_to_f32<<<grid_for(len, 256), 256, 0, st>>>(len, (const double *)M->top_inv.p, i32);
+        }
         if (M->n_wu0 > 0) {
             float *w32;
             SGP_TRY(ensure_t(ctx, M->wu032, 8 * M->n_wu0 + 8, &w32));
@@ -2053,31 +2209,55 @@ static int tail_tables(sgp_ctx ctx, sgp_prec M, int64_t n, const int32_t *in_ptr
     return SGP_OK;
 }
 
-// the tables of the LDS mid sweeps (MidTab); flag[0] set when a group is too
-// large for them (the caller then keeps the generic workgroup sweeps)
+// the tables of the LDS mid sweeps (MidTab) of every range; flag[m]: the
+// largest group of range m (INT32_MAX: too large for them, the caller keeps
+// the generic workgroup sweeps)
 static int mid_tables(sgp_ctx ctx, sgp_prec M, const int32_t *in_ptr, const int32_t *in_src, const int32_t *upq,
                       int32_t *flag)
 {
     hipStream_t st = ctx->stream;
-    M->mid_lds_built = false;
-    if (M->mid_steps <= 0 || M->light_steps > 0) return SGP_OK;
-    const int32_t m0 = M->mid_step0, m1 = std::min(M->mid_step0 + M->mid_steps, M->tail_step);
-    // (grouped from step 0: the local forest keeps its sweeps)
-    if (m1 - m0 < 2 || m1 - m0 > MID_MAX_STEPS || m0 < 1) return SGP_OK;
-    const int32_t Q0 = M->h_step_ptr[m0], Q1 = M->h_step_ptr[m1], Nm = Q1 - Q0;
-    if (Nm <= 0) return SGP_OK;
-    int32_t *tb;
-    SGP_TRY(ensure_t(ctx, M->mid_tab, 7 * (size_t)Nm + 8, &tb));
-    int32_t *lid = tb, *lin0 = tb + Nm, *nint = tb + 2 * (size_t)Nm, *lsl = tb + 3 * (size_t)Nm,
-            *lup = tb + 5 * (size_t)Nm;
-    SGP_TRY(fill_i32(ctx, lsl, -1, 2 * (int64_t)Nm));
-    k_mid_nint<<<grid_for(Nm, 256), 256, 0, st>>>(Q0, Q1, in_ptr, in_src, nint);
-    k_mid_local<<<M->mid_nwg, MID_THREADS, 0, st>>>(m1 - m0, M->mid_nwg, (const int32_t *)M->mid_ptr.p, Q0, nint, lid,
-                                                    lin0, flag);
-    k_mid_lsl<<<grid_for(Nm, 256), 256, 0, st>>>(Q0, Q1, in_ptr, in_src, nint, lin0, lsl);
-    k_mid_lup<<<grid_for(Nm, 256), 256, 0, st>>>(Q0, Q1, upq, lid, lup);
+    size_t words = 0;
+    for (int m = 0; m < M->n_mid; m++) {
+        sgp_prec_::MidRange &g = M->mid[m];
+        const int32_t Nm = M->h_step_ptr[g.step0 + g.steps] - M->h_step_ptr[g.step0];
+        // (grouped from step 0: the local forest keeps its sweeps)
+        g.lds_built = g.step0 >= 1 && g.steps <= MID_MAX_STEPS && Nm > 0;
+        g.tab = words;
+        if (g.lds_built) words += 7 * (size_t)Nm + 8;
+    }
+    if (words == 0) return SGP_OK;
+    int32_t *base;
+    SGP_TRY(ensure_t(ctx, M->mid_tab, words, &base));
+    for (int m = 0; m < M->n_mid; m++) {
+        const sgp_prec_::MidRange &g = M->mid[m];
+        if (!g.lds_built) continue;
+        const int32_t Q0 = M->h_step_ptr[g.step0], Q1 = M->h_step_ptr[g.step0 + g.steps], Nm = Q1 - Q0;
+        int32_t *tb = base + g.tab;
+        int32_t *lid = tb, *lin0 = tb + Nm, *nint = tb + 2 * (size_t)Nm, *lsl = tb + 3 * (size_t)Nm,
+                *lup = tb + 5 * (size_t)Nm;
+        const int32_t *ptr = (const int32_t *)M->mid_ptr.p + (size_t)(g.step0 - M->mid[0].step0) * M->mid_stride;
+        SGP_TRY(fill_i32(ctx, lsl, -1, 2 * (int64_t)Nm));
+        k_mid_nint<<<grid_for(Nm, 256), 256, 0, st>>>(Q0, Q1, in_ptr, in_src, nint);
+        k_mid_local<<<g.nwg, MID_THREADS, 0, st>>>(g.steps, M->mid_stride, ptr, Q0, nint, lid, lin0, flag + m);
+        k_mid_lsl<<<grid_for(Nm, 256), 256, 0, st>>>(Q0, Q1, in_ptr, in_src, nint, lin0, lsl);
+        k_mid_lup<<<grid_for(Nm, 256), 256, 0, st>>>(Q0, Q1, upq, lid, lup);
+        LAUNCH_CHECK(ctx);
+    }
+    return SGP_OK;
+}
+
+// the top block's inverse, after the factor and its tail tables
+static int top_block(sgp_ctx ctx, sgp_prec M)
+{
+    const int32_t ts = M->tail_step, S = M->steps, nt = M->tail_nt, ni = M->tail_ni;
+    M->top_ld = (3 * nt + 255) / 256 * 256;
+    double *inv;
+    SGP_TRY(ensure_t(ctx, M->top_inv, 3 * (size_t)nt * M->top_ld, &inv));
+    k_top_inverse<<<nt, TOP_INV_THREADS, top_inv_lds(nt, ni), ctx->stream>>>(
+        ts, S, (const int32_t *)M->step_ptr.p, M->h_step_ptr[ts], nt, ni, (const int32_t *)M->tail_iptr.p,
+        (const int32_t *)M->tail_tslot.p, (const int32_t *)M->up.p, (const double *)M->F.p, 9 * M->n,
+        (const double *)M->Dinv.p, M->top_ld, inv);
     LAUNCH_CHECK(ctx);
-    M->mid_lds_built = true;
     return SGP_OK;
 }
 
@@ -2212,7 +2392,8 @@ extern "C" int sgp_factor_tree(sgp_ctx ctx, sgp_graph g, sgp_tree T, double g_pa
         }
     }
     M->steps = S;
-    M->mid_step0 = M->mid_steps = M->mid_nwg = 0;
+    M->n_mid = M->mid_stride = 0;
+    M->top = false;
     // elimination order: by (step, id)
     uint32_t *ka, *kb;
     int32_t *elim, *vb, *pos, *scnt, *sptr;
@@ -2246,78 +2427,99 @@ extern "C" int sgp_factor_tree(sgp_ctx ctx, sgp_graph g, sgp_tree T, double g_pa
     };
     M->light_steps = light;
     M->light_nwg = light ? nwg : 0;
-    // the mid steps (CONTRACT without light steps): from the first step
-    // (after the first two) with at most MID_MAX_VERTICES vertices left, up to
-    // the first step with at most the default tail size left.  Fixed by the
-    // schedule alone (not by tail_max), so the elimination order does not
-    // depend on the tail.  The step sizes come from a histogram of the steps,
-    // the components' workgroups from the labelling, and one sort orders the
+    // Mid steps and top block (CONTRACT without light steps, more cells than
+    // the one-workgroup tail holds): the top block takes the steps from the
+    // first with at most TOP_MAX vertices left, the mid steps those before it
+    // from the second step when one range can hold them (2e4 cells: 18.1 ->
+    // 16.4 ms per solve, 5e4: 18.2 -> 16.6, against a launch of its own for
+    // that step), else from the first step after the first two with at most
+    // MID_MAX_VERTICES left.  The components of a range have up to ~2 times
+    // as many vertices as the ratio of the vertices left at its ends says
+    // (2e4 - 1e6 cells, both lattices); a range whose ratio exceeds
+    // MID_MAX_RATIO is cut in two near the geometric mean, so that a group
+    // fits the LDS sweeps.  All of it is fixed by the schedule alone (not by
+    // tail_max).  The step sizes come from a histogram of the steps, the
+    // components' workgroups from the labelling, and one sort orders the
     // vertices by (step, workgroup).
-    int32_t *mw = nullptr, mnwg = 1, m0 = 2, m1 = S;
+    int32_t *mw = nullptr, mnwg = 1, tstep = S;
     // A local forest (sgp_build_forest): every push stays inside a cluster's
     // tree, so all steps are grouped by component (one launch per sweep, no
     // single-workgroup tail)
     const bool forest = T->cluster_size > 0 && !light && schedule == SGP_SCHED_CONTRACT && S >= 2;
-    if (forest) m0 = 0;
-    if (!light && schedule == SGP_SCHED_CONTRACT && ((S <= HIST_MAX_STEPS && S >= 4) || forest)) {
-        if (!forest) {
-            const int hnb = (int)std::min<int64_t>(SCHED_STAT_BLOCKS, grid_for(n, 256));
-            int32_t *hpart;
-            SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP6], (size_t)hnb * S + S + 8, &hpart));
-            int32_t *hout = hpart + (size_t)hnb * S;
-            k_step_hist<<<hnb, 256, 0, st>>>(n, stepv, S, hpart);
-            k_step_hist_sum<<<S, 256, 0, st>>>(hnb, S, hpart, hout);
-            LAUNCH_CHECK(ctx);
-            std::vector<int32_t> cnt(S);
-            SGP_TRY(readback(ctx, cnt.data(), hout, S * sizeof(int32_t)));
-            std::vector<int64_t> left(S + 1, 0);   // left[k]: vertices of steps >= k
-            for (int32_t k = S - 1; k >= 0; k--) left[k] = left[k + 1] + cnt[k];
-            while (m0 < S && left[m0] > MID_MAX_VERTICES) m0++;
-            const int tdef = std::min(TAIL_DEFAULT_VERTICES, TAIL_MAX_VERTICES);
-            while (m1 > m0 && left[m1 - 1] <= tdef) m1--;
-        }
-        if (m1 - m0 >= 2) {
-            int32_t *ja, *jb, *lcnt, *lstart, *wgr, *flag;
-            SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP3], n + 1, &ja));
-            SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP4], n + 1, &jb));
-            SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP5], n + 1, &lcnt));
-            SGP_TRY(ensure_t(ctx, ctx->ws[WS_KEY_B], 2 * n + 2, &lstart));
-            SGP_TRY(ensure_t(ctx, ctx->ws[WS_VAL_A], n + 1, &wgr));
-            SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP9], n + 1, &mw));
-            SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP6], 2 * SCHED_STAT_BLOCKS + 4, &flag));
-            k_mid_init<<<grid_for(n, 256), 256, 0, st>>>(n, stepv, m0, m1, ja);
-            LAUNCH_CHECK(ctx);
-            // hooking and jumping, four rounds per check (components are small)
-            bool converged = false;
-            for (int it = 0; it < 64 && !converged; it++) {
-                SGP_TRY(fill_i32(ctx, flag, 0, 1));
-                for (int r = 0; r < 4; r++) {
-                    k_mid_link<<<grid_for(n, 256), 256, 0, st>>>(n, up0, up1, ja, flag);
-                    k_mid_jump<<<grid_for(n, 256), 256, 0, st>>>(n, ja);
-                }
-                LAUNCH_CHECK(ctx);
-                int32_t hf;
-                SGP_TRY(readback(ctx, &hf, flag, 4));
-                // a check whose rounds found no link between two labels: every component is uniform
-                if (!hf) converged = true;
+    const bool grouped = !light && schedule == SGP_SCHED_CONTRACT && !forest && S <= HIST_MAX_STEPS && S >= 4 &&
+                         n > TAIL_DEFAULT_VERTICES;
+    std::vector<int64_t> left(S + 1, 0);   // left[k]: vertices of steps >= k
+    if (forest) {
+        left[0] = n;
+        M->n_mid = 1;
+        M->mid[0].step0 = 0;
+        M->mid[0].steps = S;
+    }
+    if (grouped) {
+        const int hnb = (int)std::min<int64_t>(SCHED_STAT_BLOCKS, grid_for(n, 256));
+        int32_t *hpart;
+        SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP6], (size_t)hnb * S + S + 8, &hpart));
+        int32_t *hout = hpart + (size_t)hnb * S;
+        k_step_hist<<<hnb, 256, 0, st>>>(n, stepv, S, hpart);
+        k_step_hist_sum<<<S, 256, 0, st>>>(hnb, S, hpart, hout);
+        LAUNCH_CHECK(ctx);
+        std::vector<int32_t> cnt(S);
+        SGP_TRY(readback(ctx, cnt.data(), hout, S * sizeof(int32_t)));
+        for (int32_t k = S - 1; k >= 0; k--) left[k] = left[k + 1] + cnt[k];
+        while (left[tstep - 1] <= TOP_MAX) tstep--;
+        const double end = (double)std::max<int64_t>(left[tstep], 1);
+        int32_t m0 = (double)left[1] <= MID_MAX_RATIO * end ? 1 : 2;
+        while (m0 < tstep && left[m0] > MID_MAX_VERTICES) m0++;
+        if (tstep - m0 >= 2) {
+            int32_t cut = tstep;
+            const double ratio = (double)left[m0] / end;
+            if (ratio > MID_MAX_RATIO && tstep - m0 >= 4) {
+                cut = m0 + 2;
+                while (cut < tstep - 2 && (double)left[cut] * left[cut] > (double)left[m0] * end) cut++;
             }
-            if (converged) {
-                SGP_TRY(fill_i32(ctx, lcnt, 0, n));
-                k_light_count<<<grid_for(n, 256), 256, 0, st>>>(n, ja, lcnt);
-                k_light_vals<<<grid_for(n, 256), 256, 0, st>>>(n, (const int32_t *)g->perm.p, ja, lcnt, jb);
-                LAUNCH_CHECK(ctx);
-                SGP_TRY(scan_exclusive(ctx, jb, lstart, n));
-                int32_t total;
-                SGP_TRY(readback(ctx, &total, lstart + n, 4));
-                const int32_t cap = std::max(forest ? std::max(ctx->light_cap, T->cluster_size) : ctx->light_cap, 1);
-                mnwg = std::max((total + cap - 1) / cap, 1);
-                k_light_rootwg<<<grid_for(n, 256), 256, 0, st>>>(n, (const int32_t *)g->perm.p, ja, lstart, cap, wgr);
-                k_light_wg<<<grid_for(n, 256), 256, 0, st>>>(n, ja, wgr, mw);
-                LAUNCH_CHECK(ctx);
-            } else {
-                mw = nullptr;
-            }
+            M->n_mid = cut < tstep ? 2 : 1;
+            M->mid[0].step0 = m0;
+            M->mid[0].steps = cut - m0;
+            M->mid[1].step0 = cut;
+            M->mid[1].steps = tstep - cut;
         }
+    }
+    if (M->n_mid > 0) {
+        const int32_t m0 = M->mid[0].step0, m1 = M->mid[M->n_mid - 1].step0 + M->mid[M->n_mid - 1].steps;
+        int32_t *ja, *jb, *lcnt, *lstart, *wgr;
+        SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP3], n + 1, &ja));
+        SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP4], n + 1, &jb));
+        SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP5], n + 1, &lcnt));
+        SGP_TRY(ensure_t(ctx, ctx->ws[WS_KEY_B], 2 * n + 2, &lstart));
+        SGP_TRY(ensure_t(ctx, ctx->ws[WS_VAL_A], n + 1, &wgr));
+        SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP9], n + 1, &mw));
+        k_mid_init<<<grid_for(n, 256), 256, 0, st>>>(n, stepv, up0, up1, m0, m1,
+                                                     M->n_mid > 1 ? M->mid[1].step0 : INT32_MAX, ja);
+        for (int span = 1; span < m1 - m0; span *= 2) {
+            k_light_jump<<<grid_for(n, 256), 256, 0, st>>>(n, ja, jb);
+            std::swap(ja, jb);
+        }
+        SGP_TRY(fill_i32(ctx, lcnt, 0, n));
+        k_light_count<<<grid_for(n, 256), 256, 0, st>>>(n, ja, lcnt);
+        for (int m = 0; m < M->n_mid; m++) {
+            sgp_prec_::MidRange &mr = M->mid[m];
+            const int32_t a = mr.step0, b = mr.step0 + mr.steps;
+            // about one group per CU, of MID_MIN_CAP to light_cap vertices
+            const int32_t cap =
+                forest ? std::max(ctx->light_cap, T->cluster_size)
+                       : (int32_t)std::min<int64_t>(ctx->light_cap,
+                                                    std::max<int64_t>(MID_MIN_CAP, (left[a] - left[b]) / MID_GROUPS + 1));
+            k_mid_vals<<<grid_for(n, 256), 256, 0, st>>>(n, (const int32_t *)g->perm.p, ja, lcnt, stepv, a, b, jb);
+            LAUNCH_CHECK(ctx);
+            SGP_TRY(scan_exclusive(ctx, jb, lstart, n));
+            k_mid_rootwg<<<grid_for(n, 256), 256, 0, st>>>(n, (const int32_t *)g->perm.p, ja, stepv, a, b, lstart, cap,
+                                                           wgr);
+            LAUNCH_CHECK(ctx);
+            mr.nwg = (int32_t)std::max<int64_t>((left[a] - left[b] + cap - 1) / cap, 1);
+            mnwg = std::max(mnwg, mr.nwg);
+        }
+        k_light_wg<<<grid_for(n, 256), 256, 0, st>>>(n, ja, wgr, mw);
+        LAUNCH_CHECK(ctx);
     }
     if (light) {
         SGP_TRY(order(wgv, nwg));
@@ -2329,24 +2531,26 @@ extern "C" int sgp_factor_tree(sgp_ctx ctx, sgp_graph g, sgp_tree T, double g_pa
     } else if (mw) {
         SGP_TRY(order(mw, mnwg));
         int32_t *wptr;
+        const int32_t m0 = M->mid[0].step0, m1 = M->mid[M->n_mid - 1].step0 + M->mid[M->n_mid - 1].steps;
         const int64_t lo = (int64_t)m0 * mnwg, hi = (int64_t)m1 * mnwg;
         SGP_TRY(ensure_t(ctx, M->mid_ptr, (size_t)(hi - lo) + 2, &wptr));
         k_mid_ptr<<<grid_for(n + 1, 256), 256, 0, st>>>(n, ka, lo, hi, wptr);
         LAUNCH_CHECK(ctx);
-        M->mid_step0 = m0;
-        M->mid_steps = m1 - m0;
-        M->mid_nwg = mnwg;
+        M->mid_stride = mnwg;
     } else {
         SGP_TRY(order(nullptr, 1));
     }
     int32_t *dsp;
     SGP_TRY(ensure_t(ctx, M->step_ptr, (size_t)S + 2, &dsp));
     HIP_TRY(ctx, hipMemcpyAsync(dsp, sptr, (S + 1) * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
-    // steps from tail_step on hold at most ctx->tail_max vertices in all (and
-    // never more than fit in LDS, TAIL_MAX_VERTICES)
-    M->tail_step = S;
+    // the last steps: the top block; for other factors the steps that hold at most
+    // ctx->tail_max vertices in all (and never more than fit in LDS,
+    // TAIL_MAX_VERTICES)
+    M->top = grouped && tstep < S;   // (not when more than TOP_MAX trees end in the last step)
+    M->tail_step = grouped ? tstep : S;
     int tmax = std::min(ctx->tail_max, TAIL_MAX_VERTICES);
-    while (!(forest && mw) && M->tail_step > light && n - M->h_step_ptr[M->tail_step - 1] <= tmax) M->tail_step--;
+    while (!grouped && !(forest && mw) && M->tail_step > light && n - M->h_step_ptr[M->tail_step - 1] <= tmax)
+        M->tail_step--;
     // up links and in-lists
     int32_t *upq, *icnt, *in_ptr, *in_src;
     SGP_TRY(ensure_t(ctx, M->up, 2 * n + 2, &upq));
@@ -2372,7 +2576,7 @@ extern "C" int sgp_factor_tree(sgp_ctx ctx, sgp_graph g, sgp_tree T, double g_pa
     double *y;
     SGP_TRY(ensure_t(ctx, M->y, 3 * n + 3, &y));
     SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP9], 4, &status));
-    SGP_TRY(fill_i32(ctx, status, 0, 3));
+    SGP_TRY(fill_i32(ctx, status, 0, 4));
     SGP_TRY(fill_f64(ctx, F, 0.0, 18 * n));
     k_tree_blocks<<<grid_for(n, 256), 256, 0, st>>>(n, (const int32_t *)T->tptr.p, (const int32_t *)T->tadje.p,
                                                   (const int32_t *)T->pedge.p, (const double4 *)g->wu.p, g_par,
@@ -2390,7 +2594,6 @@ extern "C" int sgp_factor_tree(sgp_ctx ctx, sgp_graph g, sgp_tree T, double g_pa
     // them the first step runs inside the light-subtree sweeps)
     M->n_wu0 = 0;
     M->step0_sorted = false;
-    M->mid_lds = M->mid_lds_built = false;
     M->gpar = g_par;
     M->gperp = g_perp;
     M->gmed = g_med;
@@ -2416,11 +2619,15 @@ extern "C" int sgp_factor_tree(sgp_ctx ctx, sgp_graph g, sgp_tree T, double g_pa
     LAUNCH_CHECK(ctx);
     SGP_TRY(tail_tables(ctx, M, n, in_ptr, in_src, tout));
     SGP_TRY(mid_tables(ctx, M, in_ptr, in_src, upq, status + 2));
-    SGP_TRY(readback(ctx, hbuf, status, 12));
+    if (M->top) SGP_TRY(top_block(ctx, M));
+    SGP_TRY(readback(ctx, hbuf, status, 16));
     phase_end(ctx, 3);
     if (hbuf[0]) return set_err(ctx, SGP_ENOTSPD, "factor_tree: a pivot block is not positive definite");
     M->step0_sorted = M->n_wu0 > 0 && hbuf[1] == 0;
-    M->mid_lds = M->mid_lds_built && hbuf[2] == 0;
+    for (int m = 0; m < M->n_mid; m++) {
+        M->mid[m].max_group = hbuf[2 + m];
+        M->mid[m].lds = M->mid[m].lds_built && hbuf[2 + m] <= MID_LDS_MAX;
+    }
     return SGP_OK;
 }
 

@@ -196,11 +196,24 @@ struct sgp_prec_ {
     DevBuf step_ptr;                                    // device copy of h_step_ptr
     int32_t light_steps = 0, light_nwg = 0;             // steps < light_steps: subtrees, one workgroup each
     DevBuf light_ptr;                                   // [light_steps * light_nwg + 1] first q of (step, workgroup)
-    int32_t mid_step0 = 0, mid_steps = 0, mid_nwg = 0;  // steps mid_step0.. +mid_steps: components, one workgroup each
-    DevBuf mid_ptr;                                     // [mid_steps * mid_nwg + 1] first q of (step, workgroup)
+    // ranges of steps swept one workgroup per group of components, adjacent
+    // and ascending (factor.hip, "mid steps")
+    struct MidRange {
+        int32_t step0 = 0, steps = 0, nwg = 0;
+        int32_t max_group = 0;                          // vertices of its largest group (LDS sweeps)
+        size_t tab = 0;                                 // its tables in mid_tab (MidTab)
+        bool lds_built = false, lds = false;            // tables built, and every group fits the LDS sweeps
+    };
+    MidRange mid[2];
+    int32_t n_mid = 0, mid_stride = 0;                  // ranges; workgroup keys per step
+    DevBuf mid_ptr;                                     // first q of (step from mid[0].step0 on, workgroup)
     DevBuf mid_tab;                                     // tables of the LDS mid sweeps (factor.hip, MidTab)
-    bool mid_lds_built = false, mid_lds = false;        // built, and every group fits the LDS sweeps
-    int32_t tail_step = 0;                              // steps >= tail_step run in one workgroup
+    int32_t tail_step = 0;                              // steps >= tail_step run in one launch (tail or top block)
+    // the top block: the steps >= tail_step as one dense symmetric product
+    // with the inverse of their Schur complement, [3 tail_nt][top_ld]
+    bool top = false;
+    int32_t top_ld = 0;
+    DevBuf top_inv, top_inv32;
     int32_t tail_nt = 0, tail_ni = 0;                   // tail vertices, tail-internal push slots
     DevBuf tail_iptr, tail_tslot;                       // per tail target: first internal slot; per (q,k): its slot
     DevBuf tail_b;                                      // [tail_nt][3] right-hand sides entering the tail
@@ -303,12 +316,7 @@ struct SideX {
     int32_t nb;            // vector blocks
     int32_t nwg;           // extra workgroups
     bool ran;              // set by the sweeps when the update was launched
-    // filled by the sweeps (knob prefetch): after the update, the same
-    // workgroups load the backward mid steps' constants ahead, from the XCD
-    // that will sweep them (mid_L = 0: none)
-    const int32_t *mid_wptr, *mid_lup;
-    int32_t mid_L, mid_nwg, mid_Q0, never;
-    int32_t wait;          // sleep ~7 us before either job (the tail's constants not prefetched)
+    int32_t wait;          // sleep ~7 us first (the tail's constants not prefetched)
 };
 
 // shared by several translation units
