@@ -7,18 +7,21 @@
 // root) and, for a chain vertex removed by compress, up1 (its one child).
 // With the vertices renumbered in elimination order q, P = L D L^T where row
 // q of L^T has the blocks L_{up_k(q), q} = A_{up_k, q} D_q^{-1}.  We store
-//    Dinv[q]   = D_q^{-1}            (symmetric, packed 6)
-//    F[k][q]   = A_{up_k(q), q}      (full 3x3, the coupling at elimination; two
-//                                   planes of n blocks, so the many vertices
-//                                   with one up-link never fetch a second block)
+//    Dinv[q]   = D_q^{-1}                       (symmetric, packed 6)
+//    F[k][q]   = A_{up_k(q), q} D_q^{-1}        (the block L_{up_k(q), q}, full
+//                                   3x3; two planes of n blocks, so the many
+//                                   vertices with one up-link never fetch a
+//                                   second block)
 // and solve P x = b as
-//    forward   y_q = D_q^{-1} (b_q - sum_{(u,k): up_k(u) = q} F[u][k] y_u)
-//    backward  x_q = y_q - D_q^{-1} sum_k F[q][k]^T x_{up_k(q)}
-// which is ForwardSolve, DiagSolve and BackwardSolve of Appendix B.1 with
-// the pivot solve folded into each sweep.  The forward sweep pushes: once y_u
-// is known, u writes F[u][k] y_u into the slot its target reads (the target's
-// in-list entries are contiguous), so a target sums a run of slots in a fixed
-// order instead of chasing source indices.
+//    forward   y_q = b_q - sum_{(u,k): up_k(u) = q} F[u][k] y_u
+//    backward  x_q = D_q^{-1} y_q - sum_k F[q][k]^T x_{up_k(q)}
+// which is ForwardSolve, then DiagSolve and BackwardSolve of Appendix B.1 in
+// one sweep.  (With the couplings A_{up, q} stored and the pivot solve in both
+// sweeps, the forward sweep read the pivot too, 48 of ~230 B per vertex, and
+// every step's chain held one more 3x3 product each way.)  The forward sweep
+// pushes: once y_u is known, u writes F[u][k] y_u into the slot its target
+// reads (the target's in-list entries are contiguous), so a target sums a run
+// of slots in a fixed order instead of chasing source indices.
 //
 // Schedules:
 //  LEVEL     step = max depth - depth: Alg. 2's order (decreasing distance
@@ -389,14 +392,14 @@ __global__ __launch_bounds__(256) void k_step_hist_sum(int nb, int32_t S, const 
 }
 
 // jr[v] for a vertex of steps m0..m1-1: its up-link eliminated first when that
-// lies in the same range (the steps below `cut`, or those from it on), else v
-// itself; -1 for other vertices.  Both up-links of a vertex are joined by its
+// is one of them too, else v itself; -1 for other vertices.  Both up-links of
+// a vertex are joined by its
 // elimination, so the one eliminated first is connected to the other: that
 // link alone leads from any vertex of a component to its last one, by
 // ascending steps, and ceil(log2(steps)) jumps (k_light_jump) label every
 // vertex with it.
 __global__ void k_mid_init(int64_t n, const int32_t *stepv, const int32_t *up0, const int32_t *up1, int32_t m0,
-                           int32_t m1, int32_t cut, int32_t *jr)
+                           int32_t m1, int32_t *jr)
 {
     const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= n) return;
@@ -407,29 +410,9 @@ __global__ void k_mid_init(int64_t n, const int32_t *stepv, const int32_t *up0, 
         const int32_t a = up0[v], b = up1[v];
         const int32_t sa = a >= 0 ? stepv[a] : INT32_MAX, sb = b >= 0 ? stepv[b] : INT32_MAX;
         const int32_t e = sb < sa ? b : a, se = sb < sa ? sb : sa;
-        if (e >= 0 && se < m1 && (se < cut) == (sv < cut)) j = e;
+        if (e >= 0 && se < m1) j = e;
     }
     jr[v] = j;
-}
-
-// component sizes of the roots of steps a..b-1, walked in the internal order,
-// and their workgroups (as k_light_vals, k_light_rootwg)
-__global__ void k_mid_vals(int64_t n, const int32_t *perm, const int32_t *jr, const int32_t *cnt,
-                           const int32_t *stepv, int32_t a, int32_t b, int32_t *val)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int32_t v = perm[i];
-    val[i] = jr[v] == v && stepv[v] >= a && stepv[v] < b ? cnt[v] : 0;
-}
-
-__global__ void k_mid_rootwg(int64_t n, const int32_t *perm, const int32_t *jr, const int32_t *stepv, int32_t a,
-                             int32_t b, const int32_t *start, int32_t cap, int32_t *wgr)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int32_t v = perm[i];
-    if (jr[v] == v && stepv[v] >= a && stepv[v] < b) wgr[v] = start[i] / cap;
 }
 
 // first q of every (step, workgroup) key in [lo, hi], at wptr[key - lo]; keys sorted
@@ -505,7 +488,7 @@ __global__ void k_uplinks(int64_t n, const int32_t *elim, const int32_t *pos, co
 
 // ---------------------------------------------------------------- numeric factor
 
-// One elimination step: pivots of the step's vertices, their couplings F and
+// One elimination step: pivots of the step's vertices, their blocks F and
 // their Schur contributions C[slot] (symmetric packed) to the vertices above.
 __global__ void k_factor_step(int32_t q0, int32_t q1, const int32_t *elim, const int32_t *upq,
                               const int32_t *in_ptr, const int32_t *in_src, const double *Pd, double *E,
@@ -535,8 +518,8 @@ __global__ void k_factor_step(int32_t q0, int32_t q1, const int32_t *elim, const
     if (qa >= 0) {
         double E0[9];
         for (int t = 0; t < 9; t++) E0[t] = E[9 * (int64_t)q + t];   // A_{p,v}
-        for (int t = 0; t < 9; t++) F[9 * (int64_t)q + t] = E0[t];
         mm3(E0, Di, T0);                                                // A_{p,v} D^{-1}
+        for (int t = 0; t < 9; t++) F[9 * (int64_t)q + t] = T0[t];
         double *c = C + 6 * (2 * (int64_t)q);
         // A_{p,v} D^{-1} A_{v,p}: upper triangle of T0 E0^T
         c[0] = T0[0] * E0[0] + T0[1] * E0[1] + T0[2] * E0[2];
@@ -551,8 +534,8 @@ __global__ void k_factor_step(int32_t q0, int32_t q1, const int32_t *elim, const
         for (int t = 0; t < 9; t++) E1[t] = E[9 * (int64_t)qb + t];   // A_{v,c}
         for (int a = 0; a < 3; a++)
             for (int b = 0; b < 3; b++) E1t[3 * a + b] = E1[3 * b + a];
-        for (int t = 0; t < 9; t++) F[fs + 9 * (int64_t)q + t] = E1t[t];   // A_{c,v}
         mm3(E1t, Di, T1);                                                   // A_{c,v} D^{-1}
+        for (int t = 0; t < 9; t++) F[fs + 9 * (int64_t)q + t] = T1[t];
         double *c = C + 6 * (2 * (int64_t)q + 1);
         // A_{c,v} D^{-1} A_{v,c}: upper triangle of T1 E1
         c[0] = T1[0] * E1[0] + T1[1] * E1[3] + T1[2] * E1[6];
@@ -665,9 +648,9 @@ SGP_DEV void sum_slots_early(int32_t t, int32_t te, const T *cs, T &b0, T &b1, T
     }
 }
 
-// forward substitution of one vertex q (pivot solve folded in), then the
-// push of its contributions to the vertices above it.  The loads come in
-// rounds: what depends on q alone (ids, the pivot, the first coupling
+// forward substitution of one vertex q, then the push of its contributions
+// to the vertices above it.  The loads come in
+// rounds: what depends on q alone (ids, the first coupling
 // plane), then what those ids address (r, the slots, and the second plane
 // for a vertex with a second link).  Every load precedes every store in the
 // source, so the compiler need not order a coupling's load after a push that
@@ -675,15 +658,14 @@ SGP_DEV void sum_slots_early(int32_t t, int32_t te, const T *cs, T &b0, T &b1, T
 // flag is awaited together with the loads.
 template <class T>
 SGP_DEV void fwd_vertex(int32_t q, const int32_t *elim, const int32_t *in_ptr, const int32_t *tout, const T *F,
-                        int64_t fs, const T *Dinv, const T *r, T *y, T *cs, const PcgScalars *s)
+                        int64_t fs, const T *r, T *y, T *cs, const PcgScalars *s)
 {
     const int32_t dn = done_flag(s);
     const int64_t v = elim[q];
     const int32_t t = in_ptr[q];
     const int32_t te = in_ptr[q + 1];
     const int32_t to0 = tout[2 * q], to1 = tout[2 * q + 1];
-    T d[6], f0[9], f1[9];
-    for (int k = 0; k < 6; k++) d[k] = Dinv[6 * (int64_t)q + k];
+    T f0[9], f1[9];
     for (int k = 0; k < 9; k++) f0[k] = F[9 * (int64_t)q + k];
     T b0 = r[3 * v], b1 = r[3 * v + 1], b2 = r[3 * v + 2];
     if (to1 >= 0)
@@ -691,23 +673,11 @@ SGP_DEV void fwd_vertex(int32_t q, const int32_t *elim, const int32_t *in_ptr, c
     sum_slots<T>(t, te, cs, b0, b1, b2);
     keep_loads_above();
     if (dn) return;
-    T o0, o1, o2;
-    sym_mv(d, b0, b1, b2, o0, o1, o2);
-    y[3 * (int64_t)q] = o0;
-    y[3 * (int64_t)q + 1] = o1;
-    y[3 * (int64_t)q + 2] = o2;
-    if (to0 >= 0) {
-        T *c = cs + 3 * (int64_t)to0;
-        c[0] = f0[0] * o0 + f0[1] * o1 + f0[2] * o2;
-        c[1] = f0[3] * o0 + f0[4] * o1 + f0[5] * o2;
-        c[2] = f0[6] * o0 + f0[7] * o1 + f0[8] * o2;
-    }
-    if (to1 >= 0) {
-        T *c = cs + 3 * (int64_t)to1;
-        c[0] = f1[0] * o0 + f1[1] * o1 + f1[2] * o2;
-        c[1] = f1[3] * o0 + f1[4] * o1 + f1[5] * o2;
-        c[2] = f1[6] * o0 + f1[7] * o1 + f1[8] * o2;
-    }
+    y[3 * (int64_t)q] = b0;
+    y[3 * (int64_t)q + 1] = b1;
+    y[3 * (int64_t)q + 2] = b2;
+    if (to0 >= 0) push3(cs + 3 * (int64_t)to0, f0, b0, b1, b2);
+    if (to1 >= 0) push3(cs + 3 * (int64_t)to1, f1, b0, b1, b2);
 }
 
 // backward substitution of one vertex q; y holds x for the vertices above.
@@ -734,20 +704,10 @@ SGP_DEV void bwd_vertex(int32_t q, const int32_t *elim, const int32_t *upq, cons
         for (int k = 0; k < 9; k++) f1[k] = F[fs + 9 * (int64_t)q + k];
     keep_loads_above();
     if (dn) return;
-    T a0 = 0, a1 = 0, a2 = 0;
-    if (w0 >= 0) {
-        a0 = a0 + (f0[0] * p0 + f0[3] * p1 + f0[6] * p2);
-        a1 = a1 + (f0[1] * p0 + f0[4] * p1 + f0[7] * p2);
-        a2 = a2 + (f0[2] * p0 + f0[5] * p1 + f0[8] * p2);
-    }
-    if (w1 >= 0) {
-        a0 = a0 + (f1[0] * x0 + f1[3] * x1 + f1[6] * x2);
-        a1 = a1 + (f1[1] * x0 + f1[4] * x1 + f1[7] * x2);
-        a2 = a2 + (f1[2] * x0 + f1[5] * x1 + f1[8] * x2);
-    }
-    T e0, e1, e2;
-    sym_mv(d, a0, a1, a2, e0, e1, e2);
-    const T n0 = y0 - e0, n1 = y1 - e1, n2 = y2 - e2;
+    T n0, n1, n2;
+    sym_mv(d, y0, y1, y2, n0, n1, n2);
+    if (w0 >= 0) pull3(n0, n1, n2, f0, p0, p1, p2);
+    if (w1 >= 0) pull3(n0, n1, n2, f1, x0, x1, x2);
     if (keep_x) {
         y[3 * (int64_t)q] = n0;
         y[3 * (int64_t)q + 1] = n1;
@@ -847,10 +807,10 @@ __global__ void k_bwd_step0(int32_t q1, const int32_t *elim, const int32_t *upq,
 template <class T>
 __global__ __launch_bounds__(256) void k_fwd_step(int32_t q0, int32_t q1, const int32_t *elim,
                                                   const int32_t *in_ptr, const int32_t *tout, const T *F, int64_t fs,
-                                                  const T *Dinv, const T *r, T *y, T *cs, const PcgScalars *s)
+                                                  const T *r, T *y, T *cs, const PcgScalars *s)
 {
     int32_t q = q0 + (int32_t)(xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x);
-    if (q < q1) fwd_vertex<T>(q, elim, in_ptr, tout, F, fs, Dinv, r, y, cs, s);
+    if (q < q1) fwd_vertex<T>(q, elim, in_ptr, tout, F, fs, r, y, cs, s);
 }
 
 // keep_x = false for the first elimination step (its vertices have no
@@ -873,15 +833,14 @@ __global__ __launch_bounds__(256) void k_bwd_step(int32_t q0, int32_t q1, const 
 template <class T>
 __global__ __launch_bounds__(256) void k_fwd_light(int32_t L, int32_t nwg, const int32_t *wptr, const int32_t *elim,
                                                    const int32_t *in_ptr, const int32_t *tout, const T *F,
-                                                   int64_t fs, const T *Dinv, const T *r, T *y, T *cs,
-                                                   const PcgScalars *s)
+                                                   int64_t fs, const T *r, T *y, T *cs, const PcgScalars *s)
 {
     if (s && s->done) return;
     const int32_t w = (int32_t)xcd_block(blockIdx.x, gridDim.x);
     for (int32_t k = 0; k < L; k++) {
         const int32_t q1 = wptr[(int64_t)k * nwg + w + 1];
         for (int32_t q = wptr[(int64_t)k * nwg + w] + (int32_t)threadIdx.x; q < q1; q += 256)
-            fwd_vertex<T>(q, elim, in_ptr, tout, F, fs, Dinv, r, y, cs, nullptr);
+            fwd_vertex<T>(q, elim, in_ptr, tout, F, fs, r, y, cs, nullptr);
         __syncthreads();
     }
 }
@@ -937,7 +896,7 @@ constexpr int TAIL_RHS_PER_THREAD = (3 * TAIL_MAX_VERTICES + TAIL_THREADS - 1) /
 constexpr int64_t MID_MAX_VERTICES = 1 << 17;   // vertices left at the first mid step at most
 constexpr int64_t MID_MIN_CAP = 64;             // vertices packed into a group before it is split for balance
 constexpr int64_t MID_GROUPS = 224;             // groups aimed at: a few less than CUs, since sizes vary
-constexpr double MID_MAX_RATIO = 300.0;         // of the vertices left at a mid range's ends
+constexpr int64_t MID_MAX_RATIO = 300;          // of the vertices left at the mid steps' ends
 
 // The tail's constants (pivots, both coupling planes, push slots, up-links,
 // ids, in-slot bounds of its nt vertices) loaded ahead, from the XCD that
@@ -1023,7 +982,7 @@ __global__ __launch_bounds__(64) void k_tail_pre(int32_t Qt, int32_t nt, const i
 // the per-vertex constants of one tail vertex, loaded a step ahead
 template <class T>
 struct TailPre {
-    T d[6], f0[9], f1[9];
+    T d[6], f0[9], f1[9];   // (d: backward only)
     int32_t a0, a1;   // forward: push slots; backward: up-links (elimination index)
     int32_t b0, b1;   // forward: first and end internal in-slot; backward: vertex id
 };
@@ -1041,9 +1000,14 @@ struct TailReg {
 // every load issued before it and turn the prefetch into a stall.  Both F
 // planes are read (the second is zero where there is no second link).
 template <class T>
-SGP_DEV void tail_load_common(T *d, T *f0, T *f1, int32_t q, const T *F, int64_t fs, const T *Dinv)
+SGP_DEV void tail_load_pivot(T *d, int32_t q, const T *Dinv)
 {
     for (int t = 0; t < 6; t++) d[t] = Dinv[6 * (int64_t)q + t];
+}
+
+template <class T>
+SGP_DEV void tail_load_common(T *f0, T *f1, int32_t q, const T *F, int64_t fs)
+{
     for (int t = 0; t < 9; t++) f0[t] = F[9 * (int64_t)q + t];
     for (int t = 0; t < 9; t++) f1[t] = F[fs + 9 * (int64_t)q + t];
 }
@@ -1051,13 +1015,13 @@ SGP_DEV void tail_load_common(T *d, T *f0, T *f1, int32_t q, const T *F, int64_t
 // forward: push slots and the internal in-slot range
 template <class T>
 SGP_DEV void tail_load_fwd(TailPre<T> &p, int32_t q, int32_t i, const int32_t *tslot, const int32_t *iptr,
-                           const T *F, int64_t fs, const T *Dinv)
+                           const T *F, int64_t fs)
 {
     p.a0 = tslot[2 * i];
     p.a1 = tslot[2 * i + 1];
     p.b0 = iptr[i];
     p.b1 = iptr[i + 1];
-    tail_load_common(p.d, p.f0, p.f1, q, F, fs, Dinv);
+    tail_load_common(p.f0, p.f1, q, F, fs);
 }
 
 // backward: up-links and the vertex id
@@ -1068,7 +1032,8 @@ SGP_DEV void tail_load_bwd(TailPre<T> &p, int32_t q, const int32_t *upq, const i
     p.a0 = upq[2 * q];
     p.a1 = upq[2 * q + 1];
     p.b0 = elim[q];
-    tail_load_common(p.d, p.f0, p.f1, q, F, fs, Dinv);
+    tail_load_pivot(p.d, q, Dinv);
+    tail_load_common(p.f0, p.f1, q, F, fs);
 }
 
 template <class T>
@@ -1082,7 +1047,8 @@ SGP_DEV void tail_load_reg(TailReg<T> &p, int32_t q, int32_t i, const int32_t *t
     p.up0 = upq[2 * q];
     p.up1 = upq[2 * q + 1];
     p.id = elim[q];
-    tail_load_common(p.d, p.f0, p.f1, q, F, fs, Dinv);
+    tail_load_pivot(p.d, q, Dinv);
+    tail_load_common(p.f0, p.f1, q, F, fs);
 }
 
 // x += alpha p of the CG (SideX) by workgroup wg of nwg extra workgroups of
@@ -1189,7 +1155,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_tail(int32_t s0, int32_t S, in
     TailPre<T> pa;
     {
         const int32_t q = Qt + tid < q1a - 1 ? Qt + tid : q1a - 1;
-        tail_load_fwd(pa, q, q - Qt, tslot, iptr, F, fs, Dinv);
+        tail_load_fwd(pa, q, q - Qt, tslot, iptr, F, fs);
     }
     // the step bounds and the right-hand sides with the pre-tail
     // contributions (k_tail_pre), loaded with the constants above (clamped,
@@ -1207,10 +1173,8 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_tail(int32_t s0, int32_t S, in
     for (int m = 0; m < TAIL_RHS_PER_THREAD; m++)
         if (tid + TAIL_THREADS * m < 3 * nt) sv[tid + TAIL_THREADS * m] = tbv[m];
     lds_barrier();
-    // forward: y_q = Dinv_q (b_q - its in-slots), pushes F_q y_q to its
-    // up-links' slots
-    auto fwd_one = [&](int32_t i, const T *d, const T *f0, const T *f1, int32_t a0, int32_t a1, int32_t b0,
-                       int32_t b1) {
+    // forward: y_q = b_q - its in-slots, pushes F_q y_q to its up-links' slots
+    auto fwd_one = [&](int32_t i, const T *f0, const T *f1, int32_t a0, int32_t a1, int32_t b0, int32_t b1) {
         T c0 = sv[3 * i], c1 = sv[3 * i + 1], c2 = sv[3 * i + 2];
         // in-slots in slot order, TAIL_SLOTS reads in flight at a time
         // (clamped addresses, surplus masked)
@@ -1232,24 +1196,14 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_tail(int32_t s0, int32_t S, in
                 c2 = on ? c2 - c[3 * u + 2] : c2;
             }
         }
-        T o0, o1, o2;
-        sym_mv(d, c0, c1, c2, o0, o1, o2);
-        sv[3 * i] = o0;
-        sv[3 * i + 1] = o1;
-        sv[3 * i + 2] = o2;
-        if (a0 >= 0) {
-            slot[3 * a0] = f0[0] * o0 + f0[1] * o1 + f0[2] * o2;
-            slot[3 * a0 + 1] = f0[3] * o0 + f0[4] * o1 + f0[5] * o2;
-            slot[3 * a0 + 2] = f0[6] * o0 + f0[7] * o1 + f0[8] * o2;
-        }
-        if (a1 >= 0) {
-            slot[3 * a1] = f1[0] * o0 + f1[1] * o1 + f1[2] * o2;
-            slot[3 * a1 + 1] = f1[3] * o0 + f1[4] * o1 + f1[5] * o2;
-            slot[3 * a1 + 2] = f1[6] * o0 + f1[7] * o1 + f1[8] * o2;
-        }
+        sv[3 * i] = c0;
+        sv[3 * i + 1] = c1;
+        sv[3 * i + 2] = c2;
+        if (a0 >= 0) push3(slot + 3 * a0, f0, c0, c1, c2);
+        if (a1 >= 0) push3(slot + 3 * a1, f1, c0, c1, c2);
     };
     auto fwd_pre = [&](int32_t q, const TailPre<T> &c) {
-        fwd_one(q - Qt, c.d, c.f0, c.f1, c.a0, c.a1, c.b0, c.b1);
+        fwd_one(q - Qt, c.f0, c.f1, c.a0, c.a1, c.b0, c.b1);
     };
     // A step before the window: the thread's first vertex from pa (loaded
     // ahead for the first such step, here for later ones), further ones
@@ -1257,14 +1211,14 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_tail(int32_t s0, int32_t S, in
     auto fstep = [&](int32_t k) {
         if (k > s0) {
             const int32_t q = vtx(sp, k);
-            tail_load_fwd(pa, q, q - Qt, tslot, iptr, F, fs, Dinv);
+            tail_load_fwd(pa, q, q - Qt, tslot, iptr, F, fs);
         }
         const int32_t q1 = sp[k + 1];
         int32_t q = sp[k] + tid;
         if (q < q1) fwd_pre(q, pa);
         for (q += TAIL_THREADS; q < q1; q += TAIL_THREADS) {
             TailPre<T> extra;
-            tail_load_fwd(extra, q, q - Qt, tslot, iptr, F, fs, Dinv);
+            tail_load_fwd(extra, q, q - Qt, tslot, iptr, F, fs);
             fwd_pre(q, extra);
         }
         lds_barrier();
@@ -1274,39 +1228,32 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_tail(int32_t s0, int32_t S, in
     // belong to wave wx) that wave alone, with wave-level syncs
     for (int32_t k = kw; k < kx; k++) {
         const int32_t lo = sp[k] - Qt, hi = sp[k + 1] - Qt;
-        if (ir0 >= lo && ir0 < hi) fwd_one(ir0, R0.d, R0.f0, R0.f1, R0.slot0, R0.slot1, R0.in0, R0.in1);
-        if (ir1 >= lo && ir1 < hi) fwd_one(ir1, R1.d, R1.f0, R1.f1, R1.slot0, R1.slot1, R1.in0, R1.in1);
+        if (ir0 >= lo && ir0 < hi) fwd_one(ir0, R0.f0, R0.f1, R0.slot0, R0.slot1, R0.in0, R0.in1);
+        if (ir1 >= lo && ir1 < hi) fwd_one(ir1, R1.f0, R1.f1, R1.slot0, R1.slot1, R1.in0, R1.in1);
         lds_barrier();
     }
     const bool top = (tid >> 6) == wx;
     if (top)
         for (int32_t k = kx; k < S; k++) {
             const int32_t lo = sp[k] - Qt, hi = sp[k + 1] - Qt;
-            if (ir0 >= lo && ir0 < hi) fwd_one(ir0, R0.d, R0.f0, R0.f1, R0.slot0, R0.slot1, R0.in0, R0.in1);
-            if (ir1 >= lo && ir1 < hi) fwd_one(ir1, R1.d, R1.f0, R1.f1, R1.slot0, R1.slot1, R1.in0, R1.in1);
+            if (ir0 >= lo && ir0 < hi) fwd_one(ir0, R0.f0, R0.f1, R0.slot0, R0.slot1, R0.in0, R0.in1);
+            if (ir1 >= lo && ir1 < hi) fwd_one(ir1, R1.f0, R1.f1, R1.slot0, R1.slot1, R1.in0, R1.in1);
             lds_wave_barrier();
         }
-    // backward: x_q = y_q - Dinv_q (sum over up-links of F^T x), also written
+    // backward: x_q = Dinv_q y_q - sum over up-links of F^T x, also written
     // to y (global) for the steps before the tail and to z
     auto bwd_one = [&](int32_t i, const T *d, const T *f0, const T *f1, int32_t a0, int32_t a1, int64_t v) {
-        T c0 = 0, c1 = 0, c2 = 0;
+        T x0, x1, x2;
+        sym_mv(d, sv[3 * i], sv[3 * i + 1], sv[3 * i + 2], x0, x1, x2);
         if (a0 >= 0) {
-            const int32_t wi = a0 - Qt;
-            const T x0 = sv[3 * wi], x1 = sv[3 * wi + 1], x2 = sv[3 * wi + 2];
-            c0 = c0 + (f0[0] * x0 + f0[3] * x1 + f0[6] * x2);
-            c1 = c1 + (f0[1] * x0 + f0[4] * x1 + f0[7] * x2);
-            c2 = c2 + (f0[2] * x0 + f0[5] * x1 + f0[8] * x2);
+            const T *xs = sv + 3 * (a0 - Qt);
+            const T g0[9] = {f0[6], f0[7], f0[8], f0[3], f0[4], f0[5], f0[0], f0[1], f0[2]};
+            pull3(x0, x1, x2, g0, xs[2], xs[1], xs[0]);
         }
         if (a1 >= 0) {
-            const int32_t wi = a1 - Qt;
-            const T x0 = sv[3 * wi], x1 = sv[3 * wi + 1], x2 = sv[3 * wi + 2];
-            c0 = c0 + (f1[0] * x0 + f1[3] * x1 + f1[6] * x2);
-            c1 = c1 + (f1[1] * x0 + f1[4] * x1 + f1[7] * x2);
-            c2 = c2 + (f1[2] * x0 + f1[5] * x1 + f1[8] * x2);
+            const T *xs = sv + 3 * (a1 - Qt);
+            pull3(x0, x1, x2, f1, xs[0], xs[1], xs[2]);
         }
-        T d0, d1, d2;
-        sym_mv(d, c0, c1, c2, d0, d1, d2);
-        const T x0 = sv[3 * i] - d0, x1 = sv[3 * i + 1] - d1, x2 = sv[3 * i + 2] - d2;
         sv[3 * i] = x0;
         sv[3 * i + 1] = x1;
         sv[3 * i + 2] = x2;
@@ -1366,18 +1313,19 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_tail(int32_t s0, int32_t S, in
 // LDS reads, a few dependent FP64 operations and a barrier in one workgroup
 // (~0.6 us a step; with its start-up loads and the launch that forms its
 // right-hand sides the one-workgroup tail took 24-29 us of an iteration at
-// any size, 35 % of it at 2e4 cells).  So the steps with at most TOP_MAX
-// vertices left are not swept: their Schur complement (an SPD matrix of 3 nt
+// any size, 35 % of it at 2e4 cells).  So the steps with at most
+// TOP_VERTICES vertices left are not swept: their Schur complement (an SPD matrix of 3 nt
 // rows, the tree's Laplacian reduced to those vertices) is inverted once per
 // factor, column by column with the sweeps themselves (k_top_inverse), and an
 // apply is one dense product over the whole chip, k_top: 6.5 us, bound by its
 // three dependent rounds of loads (ids, slots, more slots), not by its bytes
-// (at most 768^2 values, 4.7 MB, the same every apply, which come from the
-// caches); 128 vertices at most instead of 256 measured the same.  Solves of
+// (768^2 values at 256 vertices, 4.7 MB, the same every apply, which come
+// from the caches); 128 vertices at most instead of 256 measured the same.  Solves of
 // 2e4 and 5e4 cells 25.0 -> 16.4 and 24.7 -> 16.6 ms, 2e5 25.0 -> 21.4 ms, 1e6 the
 // same (there the CG's x update, which had run beside the tail, is back in
 // its own pass).
-constexpr int TOP_MAX = 256;       // vertices at most
+constexpr int TOP_VERTICES = 256;  // vertices at most where the mid steps reach down to it
+constexpr int TOP_MAX = 512;       // vertices at most
 static_assert((3 * TOP_MAX) % 256 == 0, "whole column chunks");
 
 // One vertex of the top block per workgroup, wave c: column 3 j + c of the
@@ -1404,24 +1352,18 @@ __global__ __launch_bounds__(TOP_INV_THREADS) void k_top_inverse(int32_t s0, int
         const int32_t hi = sp[k + 1] - Qt;
         for (int32_t i = sp[k] - Qt + lane; i < hi; i += 64) {
             const int64_t q = Qt + i;
-            const double *d = Dinv + 6 * q;
-            double b0 = sv[3 * i], b1 = sv[3 * i + 1], b2 = sv[3 * i + 2], o0, o1, o2;
+            double b0 = sv[3 * i], b1 = sv[3 * i + 1], b2 = sv[3 * i + 2];
             for (int32_t t = iptr[i]; t < iptr[i + 1]; t++) {
                 b0 = b0 - slot[3 * t];
                 b1 = b1 - slot[3 * t + 1];
                 b2 = b2 - slot[3 * t + 2];
             }
-            sym_mv(d, b0, b1, b2, o0, o1, o2);
-            sv[3 * i] = o0;
-            sv[3 * i + 1] = o1;
-            sv[3 * i + 2] = o2;
+            sv[3 * i] = b0;
+            sv[3 * i + 1] = b1;
+            sv[3 * i + 2] = b2;
             for (int m = 0; m < 2; m++) {
                 const int32_t t = tslot[2 * i + m];
-                if (t < 0) continue;
-                const double *g = F + m * fs + 9 * q;
-                slot[3 * t] = g[0] * o0 + g[1] * o1 + g[2] * o2;
-                slot[3 * t + 1] = g[3] * o0 + g[4] * o1 + g[5] * o2;
-                slot[3 * t + 2] = g[6] * o0 + g[7] * o1 + g[8] * o2;
+                if (t >= 0) push3(slot + 3 * t, F + m * fs + 9 * q, b0, b1, b2);
             }
         }
         lds_wave_barrier();
@@ -1430,20 +1372,17 @@ __global__ __launch_bounds__(TOP_INV_THREADS) void k_top_inverse(int32_t s0, int
         const int32_t hi = sp[k + 1] - Qt;
         for (int32_t i = sp[k] - Qt + lane; i < hi; i += 64) {
             const int64_t q = Qt + i;
-            double c0 = 0, c1 = 0, c2 = 0, e0, e1, e2;
+            double x0, x1, x2;
+            sym_mv(Dinv + 6 * q, sv[3 * i], sv[3 * i + 1], sv[3 * i + 2], x0, x1, x2);
             for (int m = 0; m < 2; m++) {
                 const int32_t a = upq[2 * q + m];
                 if (a < 0) continue;
-                const double *g = F + m * fs + 9 * q, *xs = sv + 3 * (a - Qt);
-                const double x0 = xs[0], x1 = xs[1], x2 = xs[2];
-                c0 = c0 + (g[0] * x0 + g[3] * x1 + g[6] * x2);
-                c1 = c1 + (g[1] * x0 + g[4] * x1 + g[7] * x2);
-                c2 = c2 + (g[2] * x0 + g[5] * x1 + g[8] * x2);
+                const double *xs = sv + 3 * (a - Qt);
+                pull3(x0, x1, x2, F + m * fs + 9 * q, xs[0], xs[1], xs[2]);
             }
-            sym_mv(Dinv + 6 * q, c0, c1, c2, e0, e1, e2);
-            sv[3 * i] = sv[3 * i] - e0;
-            sv[3 * i + 1] = sv[3 * i + 1] - e1;
-            sv[3 * i + 2] = sv[3 * i + 2] - e2;
+            sv[3 * i] = x0;
+            sv[3 * i + 1] = x1;
+            sv[3 * i + 2] = x2;
         }
         lds_wave_barrier();
     }
@@ -1562,7 +1501,7 @@ __global__ __launch_bounds__(256) void k_top(int32_t Qt, int32_t nt, const int32
 // outside the group (later steps, the tail) and x of up-links outside it go
 // through global memory as before.  Same operations in the same order as
 // fwd_vertex / bwd_vertex, so results are bitwise unchanged.
-constexpr int MID_LDS_MAX = 1024;   // vertices of one group at most
+constexpr int MID_LDS_MAX = 1536;   // vertices of one group at most
 constexpr int MID_THREADS = 512;    // threads of k_mid_local, and of the widest sweeps
 
 // per mid vertex (index q - Q0): local index, first LDS slot and number of
@@ -1683,13 +1622,13 @@ __global__ void k_mid_lup(int32_t Q0, int32_t Q1, const int32_t *upq, const int3
     }
 }
 
-// the forward sweep of the mid steps: y_q = Dinv_q (r_v - its slots), the
+// the forward sweep of the mid steps: y_q = r_v - its slots, the
 // pushes to LDS (inside the group) or to cs (outside)
 template <class T, int THREADS, int VPT>
 __global__ __launch_bounds__(THREADS) void k_fwd_mid(int32_t L, int32_t nwg, const int32_t *wptr, int32_t Q0,
                                                          const int32_t *elim, const int32_t *in_ptr,
-                                                         const int32_t *tout, const T *F, int64_t fs, const T *Dinv,
-                                                         const T *r, T *y, T *cs, MidTab tab, const PcgScalars *s)
+                                                         const int32_t *tout, const T *F, int64_t fs, const T *r,
+                                                         T *y, T *cs, MidTab tab, const PcgScalars *s)
 {
     __shared__ T sl[3 * 2 * THREADS * VPT];
     __shared__ int32_t rg[2 * MID_MAX_STEPS];
@@ -1698,7 +1637,7 @@ __global__ __launch_bounds__(THREADS) void k_fwd_mid(int32_t L, int32_t nwg, con
     mid_ranges(L, nwg, wptr, w, rg);
     int32_t q[VPT], st[VPT], ni[VPT], l0[VPT], ls[VPT][2], to[VPT][2], t0[VPT], t1[VPT];
     int64_t v[VPT];
-    T d[VPT][6], f0[VPT][9], f1[VPT][9], b[VPT][3], h[VPT][12];
+    T f0[VPT][9], f1[VPT][9], b[VPT][3], h[VPT][12];
     // two rounds of loads for both vertices: what the position gives, then
     // what those values address (r, the second coupling, the first four slots
     // filled by earlier launches, clamped); one wait between them
@@ -1715,7 +1654,6 @@ __global__ __launch_bounds__(THREADS) void k_fwd_mid(int32_t L, int32_t nwg, con
             to[u][k] = tout[2 * qc + k];
             ls[u][k] = tab.lsl[2 * (int64_t)(qc - Q0) + k];
         }
-        for (int t = 0; t < 6; t++) d[u][t] = Dinv[6 * (int64_t)qc + t];
         for (int t = 0; t < 9; t++) f0[u][t] = F[9 * (int64_t)qc + t];
     }
     keep_loads_above();
@@ -1760,19 +1698,14 @@ __global__ __launch_bounds__(THREADS) void k_fwd_mid(int32_t L, int32_t nwg, con
                 c1 = c1 - c[1];
                 c2 = c2 - c[2];
             }
-            T o0, o1, o2;
-            sym_mv(d[u], c0, c1, c2, o0, o1, o2);
             const int64_t qq = q[u];
-            y[3 * qq] = o0;
-            y[3 * qq + 1] = o1;
-            y[3 * qq + 2] = o2;
+            y[3 * qq] = c0;
+            y[3 * qq + 1] = c1;
+            y[3 * qq + 2] = c2;
             for (int m = 0; m < 2; m++) {
                 if (to[u][m] < 0) continue;
-                const T *g = m == 0 ? f0[u] : f1[u];
                 T *c = ls[u][m] >= 0 ? sl + 3 * ls[u][m] : cs + 3 * (int64_t)to[u][m];
-                c[0] = g[0] * o0 + g[1] * o1 + g[2] * o2;
-                c[1] = g[3] * o0 + g[4] * o1 + g[5] * o2;
-                c[2] = g[6] * o0 + g[7] * o1 + g[8] * o2;
+                push3(c, m == 0 ? f0[u] : f1[u], c0, c1, c2);
             }
         }
         // LDS only: the global stores (y, z, pushes out of the group) are
@@ -1781,8 +1714,8 @@ __global__ __launch_bounds__(THREADS) void k_fwd_mid(int32_t L, int32_t nwg, con
     }
 }
 
-// the backward sweep of the mid steps: x_q = y_q - Dinv_q (sum over up-links
-// of F^T x), x of a mid up-link from LDS, of others from y; x written to y
+// the backward sweep of the mid steps: x_q = Dinv_q y_q - sum over up-links
+// of F^T x, x of a mid up-link from LDS, of others from y; x written to y
 // (for the steps below) and to z
 template <class T, int THREADS, int VPT>
 __global__ __launch_bounds__(THREADS) void k_bwd_mid(int32_t L, int32_t nwg, const int32_t *wptr, int32_t Q0,
@@ -1823,14 +1756,19 @@ __global__ __launch_bounds__(THREADS) void k_bwd_mid(int32_t L, int32_t nwg, con
             for (int t = 0; t < 3; t++) xo[u][k][t] = y[3 * a + t];
         }
     }
+    // Dinv_q y_q ahead of the steps
+#pragma unroll
+    for (int u = 0; u < VPT; u++) {
+        const T y0 = yo[u][0], y1 = yo[u][1], y2 = yo[u][2];
+        sym_mv(d[u], y0, y1, y2, yo[u][0], yo[u][1], yo[u][2]);
+    }
     for (int32_t k = L - 1; k >= 0; k--) {
 #pragma unroll
         for (int u = 0; u < VPT; u++) {
             if (st[u] != k) continue;
-            T a0 = 0, a1 = 0, a2 = 0;
+            T n0 = yo[u][0], n1 = yo[u][1], n2 = yo[u][2];
             for (int m = 0; m < 2; m++) {
                 if (ua[u][m] < 0) continue;
-                const T *g = m == 0 ? f0[u] : f1[u];
                 T x0 = xo[u][m][0], x1 = xo[u][m][1], x2 = xo[u][m][2];
                 if (lu[u][m] >= 0) {
                     const T *xs = xl + 3 * lu[u][m];
@@ -1838,13 +1776,8 @@ __global__ __launch_bounds__(THREADS) void k_bwd_mid(int32_t L, int32_t nwg, con
                     x1 = xs[1];
                     x2 = xs[2];
                 }
-                a0 = a0 + (g[0] * x0 + g[3] * x1 + g[6] * x2);
-                a1 = a1 + (g[1] * x0 + g[4] * x1 + g[7] * x2);
-                a2 = a2 + (g[2] * x0 + g[5] * x1 + g[8] * x2);
+                pull3(n0, n1, n2, m == 0 ? f0[u] : f1[u], x0, x1, x2);
             }
-            T e0, e1, e2;
-            sym_mv(d[u], a0, a1, a2, e0, e1, e2);
-            const T n0 = yo[u][0] - e0, n1 = yo[u][1] - e1, n2 = yo[u][2] - e2;
             const int32_t l = tid + THREADS * u;
             xl[3 * l] = n0;
             xl[3 * l + 1] = n1;
@@ -1875,6 +1808,8 @@ static void mid_shape(int32_t max_group, Fn f)
         f(integral_constant<int, 256>(), integral_constant<int, 1>());
     else if (max_group <= 512)
         f(integral_constant<int, 256>(), integral_constant<int, 2>());
+    else if (max_group <= 1024)
+        f(integral_constant<int, MID_THREADS>(), integral_constant<int, 2>());
     else
         f(integral_constant<int, MID_THREADS>(), integral_constant<int, MID_LDS_MAX / MID_THREADS>());
 }
@@ -1887,6 +1822,9 @@ int tail_setup_attr(sgp_ctx ctx)
                                      TAIL_LDS_BYTES));
     HIP_TRY(ctx, hipFuncSetAttribute((const void *)k_tail<float>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                      TAIL_LDS_BYTES));
+    // (at most 2 push slots per vertex)
+    HIP_TRY(ctx, hipFuncSetAttribute((const void *)k_top_inverse, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)top_inv_lds(TOP_MAX, 2 * TOP_MAX)));
     done = true;
     return SGP_OK;
 }
@@ -1943,7 +1881,7 @@ int32_t prec_step0_launch(sgp_prec M)
     if (!M || M->kind != PREC_TREE || M->n_wu0 <= 0 || !M->step0_sorted || M->light_steps > 0 || M->tail_step <= 0)
         return 0;
     if ((int64_t)M->h_step_ptr.size() < 2 || M->n_wu0 != M->h_step_ptr[1]) return 0;
-    if (M->n_mid > 0 && M->mid[0].step0 == 0) return 0;
+    if (M->mid.steps > 0 && M->mid.step0 == 0) return 0;
     return M->h_step_ptr[1];
 }
 
@@ -1963,40 +1901,34 @@ static int tree_sweeps(sgp_ctx ctx, sgp_prec M, const T *F, const T *Dinv, T *y,
     const int64_t fs = 9 * M->n;   // second plane of F
     const int32_t *wptr = (const int32_t *)M->light_ptr.p;
     if (L > 0)
-        k_fwd_light<T><<<M->light_nwg, 256, 0, st>>>(L, M->light_nwg, wptr, elim, in_ptr, tout, F, fs, Dinv, r, y,
-                                                    cs, s);
+        k_fwd_light<T><<<M->light_nwg, 256, 0, st>>>(L, M->light_nwg, wptr, elim, in_ptr, tout, F, fs, r, y, cs, s);
     // the first step from the contacts' (w, u) when it is one of these launches
     const bool step0_wu = wu0 && L == 0 && ts > 0 && M->n_wu0 == sp[1];
     const T gp = (T)M->gpar, gq = (T)M->gperp, gm = (T)M->gmed;
-    // the mid ranges below the tail: one launch per sweep and range, a
-    // workgroup per packed group of components
-    auto range_of = [&](int k) -> const sgp_prec_::MidRange * {
-        for (int m = 0; m < M->n_mid; m++)
-            if (k >= M->mid[m].step0 && k < M->mid[m].step0 + M->mid[m].steps) return &M->mid[m];
-        return nullptr;
-    };
-    auto range_ptr = [&](const sgp_prec_::MidRange *g) {
-        return (const int32_t *)M->mid_ptr.p + (size_t)(g->step0 - M->mid[0].step0) * M->mid_stride;
-    };
-    // a range's steps in LDS when its tables were built (knob mid_lds)
-    auto range_tab = [&](const sgp_prec_::MidRange *g) {
-        const int32_t Nm = sp[g->step0 + g->steps] - sp[g->step0];
-        const int32_t *tb = (const int32_t *)M->mid_tab.p + g->tab;
-        return MidTab{tb, tb + Nm, tb + 2 * (size_t)Nm, tb + 3 * (size_t)Nm, tb + 5 * (size_t)Nm};
-    };
+    // the mid steps below the last ones: one launch per sweep, a workgroup per
+    // packed group of components, in LDS when their tables were built (knob
+    // mid_lds)
+    const sgp_prec_::MidRange &g = M->mid;
+    const int32_t m0 = g.step0, m1 = g.step0 + g.steps;
+    const int32_t *mptr = (const int32_t *)M->mid_ptr.p;
+    const bool mid_lds = g.lds && ctx->mid_lds;
+    MidTab mtab = {};
+    if (mid_lds) {
+        const int32_t Nm = sp[m1] - sp[m0];
+        const int32_t *tb = (const int32_t *)M->mid_tab.p;
+        mtab = {tb, tb + Nm, tb + 2 * (size_t)Nm, tb + 3 * (size_t)Nm, tb + 5 * (size_t)Nm};
+    }
     for (int k = L; k < ts; k++) {
         int32_t q0 = sp[k], q1 = sp[k + 1];
-        if (const sgp_prec_::MidRange *g = range_of(k)) {
-            if (g->lds && ctx->mid_lds)
-                mid_shape(g->max_group, [&](auto th, auto vpt) {
-                    k_fwd_mid<T, decltype(th)::value, decltype(vpt)::value><<<g->nwg, decltype(th)::value, 0, st>>>(
-                        g->steps, M->mid_stride, range_ptr(g), q0, elim, in_ptr, tout, F, fs, Dinv, r, y, cs,
-                        range_tab(g), s);
+        if (k == m0 && g.steps > 0) {
+            if (mid_lds)
+                mid_shape(g.max_group, [&](auto th, auto vpt) {
+                    k_fwd_mid<T, decltype(th)::value, decltype(vpt)::value><<<g.nwg, decltype(th)::value, 0, st>>>(
+                        g.steps, g.nwg, mptr, q0, elim, in_ptr, tout, F, fs, r, y, cs, mtab, s);
                 });
             else
-                k_fwd_light<T><<<g->nwg, 256, 0, st>>>(g->steps, M->mid_stride, range_ptr(g), elim, in_ptr, tout, F,
-                                                       fs, Dinv, r, y, cs, s);
-            k += g->steps - 1;
+                k_fwd_light<T><<<g.nwg, 256, 0, st>>>(g.steps, g.nwg, mptr, elim, in_ptr, tout, F, fs, r, y, cs, s);
+            k = m1 - 1;
             continue;
         }
         if (k == 0 && step0_wu && skip0) continue;
@@ -2004,26 +1936,27 @@ static int tree_sweeps(sgp_ctx ctx, sgp_prec M, const T *F, const T *Dinv, T *y,
             k_fwd_step0<T><<<grid_for(q1, 256), 256, 0, st>>>(q1, elim, tout, wu0, 4 * (int64_t)q1, gp, gq, gm, Dinv,
                                                               r, y, cs, s);
         else if (q1 > q0)
-            k_fwd_step<T><<<grid_for(q1 - q0, 256), 256, 0, st>>>(q0, q1, elim, in_ptr, tout, F, fs, Dinv, r, y, cs,
-                                                                  s);
+            k_fwd_step<T><<<grid_for(q1 - q0, 256), 256, 0, st>>>(q0, q1, elim, in_ptr, tout, F, fs, r, y, cs, s);
     }
     if (ts < S && M->top) {
         const int32_t nt = M->tail_nt;
         const int32_t *iptr = (const int32_t *)M->tail_iptr.p;
         const T *inv = (const T *)(sizeof(T) == 8 ? M->top_inv.p : M->top_inv32.p);
-        // about 32 matrix values per lane in flight
-        auto top = [&](auto nc, auto rows) {
-            constexpr int R = decltype(rows)::value;
-            k_top<T, decltype(nc)::value, R><<<(3 * nt + 4 * R - 1) / (4 * R), 256, 0, st>>>(
-                sp[ts], nt, elim, in_ptr, iptr, inv, r, cs, y, z, s);
+        // at most 32 matrix values per lane in flight
+        auto top = [&](auto nc) {
+            constexpr int NC = decltype(nc)::value, R = NC <= 8 ? 4 : NC <= 16 ? 2 : 1;
+            k_top<T, NC, R><<<(3 * nt + 4 * R - 1) / (4 * R), 256, 0, st>>>(sp[ts], nt, elim, in_ptr, iptr, inv, r, cs,
+                                                                           y, z, s);
         };
         using std::integral_constant;
-        if (M->top_ld == 256)
-            top(integral_constant<int, 4>(), integral_constant<int, 4>());
-        else if (M->top_ld == 512)
-            top(integral_constant<int, 8>(), integral_constant<int, 4>());
-        else
-            top(integral_constant<int, 12>(), integral_constant<int, 2>());
+        switch (M->top_ld / 256) {
+        case 1: top(integral_constant<int, 4>()); break;
+        case 2: top(integral_constant<int, 8>()); break;
+        case 3: top(integral_constant<int, 12>()); break;
+        case 4: top(integral_constant<int, 16>()); break;
+        case 5: top(integral_constant<int, 20>()); break;
+        default: top(integral_constant<int, 24>()); break;
+        }
     } else if (ts < S) {
         const size_t lds = tail_lds_bytes(sizeof(T), M->tail_nt, M->tail_ni, S - ts);
         const int32_t nt = M->tail_nt;
@@ -2069,17 +2002,15 @@ static int tree_sweeps(sgp_ctx ctx, sgp_prec M, const T *F, const T *Dinv, T *y,
     }
     for (int k = ts - 1; k >= L; k--) {
         int32_t q0 = sp[k], q1 = sp[k + 1];
-        if (const sgp_prec_::MidRange *g = range_of(k)) {
-            if (g->lds && ctx->mid_lds)
-                mid_shape(g->max_group, [&](auto th, auto vpt) {
-                    k_bwd_mid<T, decltype(th)::value, decltype(vpt)::value><<<g->nwg, decltype(th)::value, 0, st>>>(
-                        g->steps, M->mid_stride, range_ptr(g), sp[g->step0], elim, upq, F, fs, Dinv, y, z,
-                        range_tab(g), s);
+        if (k == m1 - 1 && g.steps > 0) {
+            if (mid_lds)
+                mid_shape(g.max_group, [&](auto th, auto vpt) {
+                    k_bwd_mid<T, decltype(th)::value, decltype(vpt)::value><<<g.nwg, decltype(th)::value, 0, st>>>(
+                        g.steps, g.nwg, mptr, sp[m0], elim, upq, F, fs, Dinv, y, z, mtab, s);
                 });
             else
-                k_bwd_light<T><<<g->nwg, 256, 0, st>>>(g->steps, M->mid_stride, range_ptr(g), elim, upq, F, fs, Dinv,
-                                                       y, z, s);
-            k = g->step0;
+                k_bwd_light<T><<<g.nwg, 256, 0, st>>>(g.steps, g.nwg, mptr, elim, upq, F, fs, Dinv, y, z, s);
+            k = m0;
             continue;
         }
         if (k == 0 && step0_wu && skip0) continue;
@@ -2209,40 +2140,31 @@ static int tail_tables(sgp_ctx ctx, sgp_prec M, int64_t n, const int32_t *in_ptr
     return SGP_OK;
 }
 
-// the tables of the LDS mid sweeps (MidTab) of every range; flag[m]: the
-// largest group of range m (INT32_MAX: too large for them, the caller keeps
-// the generic workgroup sweeps)
+// the tables of the LDS mid sweeps (MidTab); maxg: the largest group
+// (INT32_MAX: too large for them, the caller keeps the generic workgroup
+// sweeps)
 static int mid_tables(sgp_ctx ctx, sgp_prec M, const int32_t *in_ptr, const int32_t *in_src, const int32_t *upq,
-                      int32_t *flag)
+                      int32_t *maxg)
 {
     hipStream_t st = ctx->stream;
-    size_t words = 0;
-    for (int m = 0; m < M->n_mid; m++) {
-        sgp_prec_::MidRange &g = M->mid[m];
-        const int32_t Nm = M->h_step_ptr[g.step0 + g.steps] - M->h_step_ptr[g.step0];
-        // (grouped from step 0: the local forest keeps its sweeps)
-        g.lds_built = g.step0 >= 1 && g.steps <= MID_MAX_STEPS && Nm > 0;
-        g.tab = words;
-        if (g.lds_built) words += 7 * (size_t)Nm + 8;
-    }
-    if (words == 0) return SGP_OK;
-    int32_t *base;
-    SGP_TRY(ensure_t(ctx, M->mid_tab, words, &base));
-    for (int m = 0; m < M->n_mid; m++) {
-        const sgp_prec_::MidRange &g = M->mid[m];
-        if (!g.lds_built) continue;
-        const int32_t Q0 = M->h_step_ptr[g.step0], Q1 = M->h_step_ptr[g.step0 + g.steps], Nm = Q1 - Q0;
-        int32_t *tb = base + g.tab;
-        int32_t *lid = tb, *lin0 = tb + Nm, *nint = tb + 2 * (size_t)Nm, *lsl = tb + 3 * (size_t)Nm,
-                *lup = tb + 5 * (size_t)Nm;
-        const int32_t *ptr = (const int32_t *)M->mid_ptr.p + (size_t)(g.step0 - M->mid[0].step0) * M->mid_stride;
-        SGP_TRY(fill_i32(ctx, lsl, -1, 2 * (int64_t)Nm));
-        k_mid_nint<<<grid_for(Nm, 256), 256, 0, st>>>(Q0, Q1, in_ptr, in_src, nint);
-        k_mid_local<<<g.nwg, MID_THREADS, 0, st>>>(g.steps, M->mid_stride, ptr, Q0, nint, lid, lin0, flag + m);
-        k_mid_lsl<<<grid_for(Nm, 256), 256, 0, st>>>(Q0, Q1, in_ptr, in_src, nint, lin0, lsl);
-        k_mid_lup<<<grid_for(Nm, 256), 256, 0, st>>>(Q0, Q1, upq, lid, lup);
-        LAUNCH_CHECK(ctx);
-    }
+    sgp_prec_::MidRange &g = M->mid;
+    g.lds_built = false;
+    // (grouped from step 0: the local forest keeps its sweeps)
+    if (g.steps < 1 || g.step0 < 1 || g.steps > MID_MAX_STEPS) return SGP_OK;
+    const int32_t Q0 = M->h_step_ptr[g.step0], Q1 = M->h_step_ptr[g.step0 + g.steps], Nm = Q1 - Q0;
+    if (Nm <= 0) return SGP_OK;
+    int32_t *tb;
+    SGP_TRY(ensure_t(ctx, M->mid_tab, 7 * (size_t)Nm + 8, &tb));
+    int32_t *lid = tb, *lin0 = tb + Nm, *nint = tb + 2 * (size_t)Nm, *lsl = tb + 3 * (size_t)Nm,
+            *lup = tb + 5 * (size_t)Nm;
+    SGP_TRY(fill_i32(ctx, lsl, -1, 2 * (int64_t)Nm));
+    k_mid_nint<<<grid_for(Nm, 256), 256, 0, st>>>(Q0, Q1, in_ptr, in_src, nint);
+    k_mid_local<<<g.nwg, MID_THREADS, 0, st>>>(g.steps, g.nwg, (const int32_t *)M->mid_ptr.p, Q0, nint, lid, lin0,
+                                               maxg);
+    k_mid_lsl<<<grid_for(Nm, 256), 256, 0, st>>>(Q0, Q1, in_ptr, in_src, nint, lin0, lsl);
+    k_mid_lup<<<grid_for(Nm, 256), 256, 0, st>>>(Q0, Q1, upq, lid, lup);
+    LAUNCH_CHECK(ctx);
+    g.lds_built = true;
     return SGP_OK;
 }
 
@@ -2392,7 +2314,7 @@ extern "C" int sgp_factor_tree(sgp_ctx ctx, sgp_graph g, sgp_tree T, double g_pa
         }
     }
     M->steps = S;
-    M->n_mid = M->mid_stride = 0;
+    M->mid = {};
     M->top = false;
     // elimination order: by (step, id)
     uint32_t *ka, *kb;
@@ -2429,18 +2351,18 @@ extern "C" int sgp_factor_tree(sgp_ctx ctx, sgp_graph g, sgp_tree T, double g_pa
     M->light_nwg = light ? nwg : 0;
     // Mid steps and top block (CONTRACT without light steps, more cells than
     // the one-workgroup tail holds): the top block takes the steps from the
-    // first with at most TOP_MAX vertices left, the mid steps those before it
-    // from the second step when one range can hold them (2e4 cells: 18.1 ->
-    // 16.4 ms per solve, 5e4: 18.2 -> 16.6, against a launch of its own for
-    // that step), else from the first step after the first two with at most
-    // MID_MAX_VERTICES left.  The components of a range have up to ~2 times
-    // as many vertices as the ratio of the vertices left at its ends says
-    // (2e4 - 1e6 cells, both lattices); a range whose ratio exceeds
-    // MID_MAX_RATIO is cut in two near the geometric mean, so that a group
-    // fits the LDS sweeps.  All of it is fixed by the schedule alone (not by
-    // tail_max).  The step sizes come from a histogram of the steps, the
-    // components' workgroups from the labelling, and one sort orders the
-    // vertices by (step, workgroup).
+    // first with at most TOP_VERTICES vertices left, the mid steps those
+    // before it, from the second step or else the first after it with at most
+    // MID_MAX_VERTICES left (from the second step: 2e4 cells 18.1 -> 16.4 ms
+    // per solve, 5e4 18.2 -> 16.6, against a launch of its own for that step).
+    // The components of the mid steps have up to ~2.2 times as many vertices
+    // as the ratio of the vertices left at the range's ends says (2e4 - 1e6
+    // cells, both lattices), and must fit a group of the LDS sweeps: where the
+    // ratio exceeds MID_MAX_RATIO the second step stays a launch of its own,
+    // and if it still does the top block takes up to TOP_MAX vertices.  All of
+    // it is fixed by the schedule alone (not by tail_max).  The step sizes
+    // come from a histogram of the steps, the components' workgroups from the
+    // labelling, and one sort orders the vertices by (step, workgroup).
     int32_t *mw = nullptr, mnwg = 1, tstep = S;
     // A local forest (sgp_build_forest): every push stays inside a cluster's
     // tree, so all steps are grouped by component (one launch per sweep, no
@@ -2451,9 +2373,7 @@ extern "C" int sgp_factor_tree(sgp_ctx ctx, sgp_graph g, sgp_tree T, double g_pa
     std::vector<int64_t> left(S + 1, 0);   // left[k]: vertices of steps >= k
     if (forest) {
         left[0] = n;
-        M->n_mid = 1;
-        M->mid[0].step0 = 0;
-        M->mid[0].steps = S;
+        M->mid.steps = S;
     }
     if (grouped) {
         const int hnb = (int)std::min<int64_t>(SCHED_STAT_BLOCKS, grid_for(n, 256));
@@ -2466,26 +2386,20 @@ extern "C" int sgp_factor_tree(sgp_ctx ctx, sgp_graph g, sgp_tree T, double g_pa
         std::vector<int32_t> cnt(S);
         SGP_TRY(readback(ctx, cnt.data(), hout, S * sizeof(int32_t)));
         for (int32_t k = S - 1; k >= 0; k--) left[k] = left[k + 1] + cnt[k];
-        while (left[tstep - 1] <= TOP_MAX) tstep--;
-        const double end = (double)std::max<int64_t>(left[tstep], 1);
-        int32_t m0 = (double)left[1] <= MID_MAX_RATIO * end ? 1 : 2;
+        while (left[tstep - 1] <= TOP_VERTICES) tstep--;
+        int32_t m0 = 1;
+        auto wide = [&]() { return left[m0] > MID_MAX_RATIO * std::max<int64_t>(left[tstep], 1); };
+        if (wide()) m0 = 2;
         while (m0 < tstep && left[m0] > MID_MAX_VERTICES) m0++;
+        while (m0 < tstep && wide() && left[tstep - 1] <= TOP_MAX) tstep--;
         if (tstep - m0 >= 2) {
-            int32_t cut = tstep;
-            const double ratio = (double)left[m0] / end;
-            if (ratio > MID_MAX_RATIO && tstep - m0 >= 4) {
-                cut = m0 + 2;
-                while (cut < tstep - 2 && (double)left[cut] * left[cut] > (double)left[m0] * end) cut++;
-            }
-            M->n_mid = cut < tstep ? 2 : 1;
-            M->mid[0].step0 = m0;
-            M->mid[0].steps = cut - m0;
-            M->mid[1].step0 = cut;
-            M->mid[1].steps = tstep - cut;
+            M->mid.step0 = m0;
+            M->mid.steps = tstep - m0;
         }
     }
-    if (M->n_mid > 0) {
-        const int32_t m0 = M->mid[0].step0, m1 = M->mid[M->n_mid - 1].step0 + M->mid[M->n_mid - 1].steps;
+    if (M->mid.steps > 0) {
+        sgp_prec_::MidRange &mr = M->mid;
+        const int32_t m0 = mr.step0, m1 = mr.step0 + mr.steps;
         int32_t *ja, *jb, *lcnt, *lstart, *wgr;
         SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP3], n + 1, &ja));
         SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP4], n + 1, &jb));
@@ -2493,33 +2407,25 @@ extern "C" int sgp_factor_tree(sgp_ctx ctx, sgp_graph g, sgp_tree T, double g_pa
         SGP_TRY(ensure_t(ctx, ctx->ws[WS_KEY_B], 2 * n + 2, &lstart));
         SGP_TRY(ensure_t(ctx, ctx->ws[WS_VAL_A], n + 1, &wgr));
         SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP9], n + 1, &mw));
-        k_mid_init<<<grid_for(n, 256), 256, 0, st>>>(n, stepv, up0, up1, m0, m1,
-                                                     M->n_mid > 1 ? M->mid[1].step0 : INT32_MAX, ja);
+        k_mid_init<<<grid_for(n, 256), 256, 0, st>>>(n, stepv, up0, up1, m0, m1, ja);
         for (int span = 1; span < m1 - m0; span *= 2) {
             k_light_jump<<<grid_for(n, 256), 256, 0, st>>>(n, ja, jb);
             std::swap(ja, jb);
         }
         SGP_TRY(fill_i32(ctx, lcnt, 0, n));
         k_light_count<<<grid_for(n, 256), 256, 0, st>>>(n, ja, lcnt);
-        for (int m = 0; m < M->n_mid; m++) {
-            sgp_prec_::MidRange &mr = M->mid[m];
-            const int32_t a = mr.step0, b = mr.step0 + mr.steps;
-            // about one group per CU, of MID_MIN_CAP to light_cap vertices
-            const int32_t cap =
-                forest ? std::max(ctx->light_cap, T->cluster_size)
-                       : (int32_t)std::min<int64_t>(ctx->light_cap,
-                                                    std::max<int64_t>(MID_MIN_CAP, (left[a] - left[b]) / MID_GROUPS + 1));
-            k_mid_vals<<<grid_for(n, 256), 256, 0, st>>>(n, (const int32_t *)g->perm.p, ja, lcnt, stepv, a, b, jb);
-            LAUNCH_CHECK(ctx);
-            SGP_TRY(scan_exclusive(ctx, jb, lstart, n));
-            k_mid_rootwg<<<grid_for(n, 256), 256, 0, st>>>(n, (const int32_t *)g->perm.p, ja, stepv, a, b, lstart, cap,
-                                                           wgr);
-            LAUNCH_CHECK(ctx);
-            mr.nwg = (int32_t)std::max<int64_t>((left[a] - left[b] + cap - 1) / cap, 1);
-            mnwg = std::max(mnwg, mr.nwg);
-        }
+        k_light_vals<<<grid_for(n, 256), 256, 0, st>>>(n, (const int32_t *)g->perm.p, ja, lcnt, jb);
+        LAUNCH_CHECK(ctx);
+        SGP_TRY(scan_exclusive(ctx, jb, lstart, n));
+        // about one group per CU, of MID_MIN_CAP to light_cap vertices
+        const int64_t total = left[m0] - left[m1];
+        const int32_t cap = forest ? std::max(ctx->light_cap, T->cluster_size)
+                                   : (int32_t)std::min<int64_t>(ctx->light_cap,
+                                                                std::max<int64_t>(MID_MIN_CAP, total / MID_GROUPS + 1));
+        k_light_rootwg<<<grid_for(n, 256), 256, 0, st>>>(n, (const int32_t *)g->perm.p, ja, lstart, cap, wgr);
         k_light_wg<<<grid_for(n, 256), 256, 0, st>>>(n, ja, wgr, mw);
         LAUNCH_CHECK(ctx);
+        mr.nwg = mnwg = (int32_t)std::max<int64_t>((total + cap - 1) / cap, 1);
     }
     if (light) {
         SGP_TRY(order(wgv, nwg));
@@ -2531,12 +2437,11 @@ extern "C" int sgp_factor_tree(sgp_ctx ctx, sgp_graph g, sgp_tree T, double g_pa
     } else if (mw) {
         SGP_TRY(order(mw, mnwg));
         int32_t *wptr;
-        const int32_t m0 = M->mid[0].step0, m1 = M->mid[M->n_mid - 1].step0 + M->mid[M->n_mid - 1].steps;
+        const int32_t m0 = M->mid.step0, m1 = m0 + M->mid.steps;
         const int64_t lo = (int64_t)m0 * mnwg, hi = (int64_t)m1 * mnwg;
         SGP_TRY(ensure_t(ctx, M->mid_ptr, (size_t)(hi - lo) + 2, &wptr));
         k_mid_ptr<<<grid_for(n + 1, 256), 256, 0, st>>>(n, ka, lo, hi, wptr);
         LAUNCH_CHECK(ctx);
-        M->mid_stride = mnwg;
     } else {
         SGP_TRY(order(nullptr, 1));
     }
@@ -2576,7 +2481,7 @@ extern "C" int sgp_factor_tree(sgp_ctx ctx, sgp_graph g, sgp_tree T, double g_pa
     double *y;
     SGP_TRY(ensure_t(ctx, M->y, 3 * n + 3, &y));
     SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP9], 4, &status));
-    SGP_TRY(fill_i32(ctx, status, 0, 4));
+    SGP_TRY(fill_i32(ctx, status, 0, 3));
     SGP_TRY(fill_f64(ctx, F, 0.0, 18 * n));
     k_tree_blocks<<<grid_for(n, 256), 256, 0, st>>>(n, (const int32_t *)T->tptr.p, (const int32_t *)T->tadje.p,
                                                   (const int32_t *)T->pedge.p, (const double4 *)g->wu.p, g_par,
@@ -2620,14 +2525,12 @@ extern "C" int sgp_factor_tree(sgp_ctx ctx, sgp_graph g, sgp_tree T, double g_pa
     SGP_TRY(tail_tables(ctx, M, n, in_ptr, in_src, tout));
     SGP_TRY(mid_tables(ctx, M, in_ptr, in_src, upq, status + 2));
     if (M->top) SGP_TRY(top_block(ctx, M));
-    SGP_TRY(readback(ctx, hbuf, status, 16));
+    SGP_TRY(readback(ctx, hbuf, status, 12));
     phase_end(ctx, 3);
     if (hbuf[0]) return set_err(ctx, SGP_ENOTSPD, "factor_tree: a pivot block is not positive definite");
     M->step0_sorted = M->n_wu0 > 0 && hbuf[1] == 0;
-    for (int m = 0; m < M->n_mid; m++) {
-        M->mid[m].max_group = hbuf[2 + m];
-        M->mid[m].lds = M->mid[m].lds_built && hbuf[2 + m] <= MID_LDS_MAX;
-    }
+    M->mid.max_group = hbuf[2];
+    M->mid.lds = M->mid.lds_built && hbuf[2] <= MID_LDS_MAX;
     return SGP_OK;
 }
 

@@ -196,17 +196,14 @@ struct sgp_prec_ {
     DevBuf step_ptr;                                    // device copy of h_step_ptr
     int32_t light_steps = 0, light_nwg = 0;             // steps < light_steps: subtrees, one workgroup each
     DevBuf light_ptr;                                   // [light_steps * light_nwg + 1] first q of (step, workgroup)
-    // ranges of steps swept one workgroup per group of components, adjacent
-    // and ascending (factor.hip, "mid steps")
+    // steps swept one workgroup per group of components (factor.hip, "mid steps")
     struct MidRange {
         int32_t step0 = 0, steps = 0, nwg = 0;
         int32_t max_group = 0;                          // vertices of its largest group (LDS sweeps)
-        size_t tab = 0;                                 // its tables in mid_tab (MidTab)
         bool lds_built = false, lds = false;            // tables built, and every group fits the LDS sweeps
     };
-    MidRange mid[2];
-    int32_t n_mid = 0, mid_stride = 0;                  // ranges; workgroup keys per step
-    DevBuf mid_ptr;                                     // first q of (step from mid[0].step0 on, workgroup)
+    MidRange mid;
+    DevBuf mid_ptr;                                     // [mid.steps * mid.nwg + 1] first q of (step, workgroup)
     DevBuf mid_tab;                                     // tables of the LDS mid sweeps (factor.hip, MidTab)
     int32_t tail_step = 0;                              // steps >= tail_step run in one launch (tail or top block)
     // the top block: the steps >= tail_step as one dense symmetric product
@@ -478,6 +475,26 @@ SGP_DEV void sym_mv(const T *s, T x0, T x1, T x2, T &y0, T &y1, T &y2)
     y0 = s[0] * x0 + s[1] * x1 + s[2] * x2;
     y1 = s[1] * x0 + s[3] * x1 + s[4] * x2;
     y2 = s[2] * x0 + s[4] * x1 + s[5] * x2;
+}
+
+// One vertex of the tree sweeps: the push c = f o to an up-link's slot, and
+// x -= f^T p for an up-link's x.  Fused multiply-adds (the build forms none by
+// itself): one rounding less per term, and a shorter chain in the steps that
+// wait on each other.
+template <class T>
+SGP_DEV void push3(T *c, const T *f, T o0, T o1, T o2)
+{
+    c[0] = __builtin_elementwise_fma(f[2], o2, __builtin_elementwise_fma(f[1], o1, f[0] * o0));
+    c[1] = __builtin_elementwise_fma(f[5], o2, __builtin_elementwise_fma(f[4], o1, f[3] * o0));
+    c[2] = __builtin_elementwise_fma(f[8], o2, __builtin_elementwise_fma(f[7], o1, f[6] * o0));
+}
+
+template <class T>
+SGP_DEV void pull3(T &x0, T &x1, T &x2, const T *f, T p0, T p1, T p2)
+{
+    x0 = __builtin_elementwise_fma(-f[6], p2, __builtin_elementwise_fma(-f[3], p1, __builtin_elementwise_fma(-f[0], p0, x0)));
+    x1 = __builtin_elementwise_fma(-f[7], p2, __builtin_elementwise_fma(-f[4], p1, __builtin_elementwise_fma(-f[1], p0, x1)));
+    x2 = __builtin_elementwise_fma(-f[8], p2, __builtin_elementwise_fma(-f[5], p1, __builtin_elementwise_fma(-f[2], p0, x2)));
 }
 
 // -W p for the block W = w (g_perp I + (g_par - g_perp) u u^T) of contact

@@ -236,23 +236,11 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_pcg(SmallArgs A)
                     c2 = on ? c2 - h[3 * m + 2] : c2;
                 }
             }
-            double o0, o1, o2;
-            sym_mv(c.d, c0, c1, c2, o0, o1, o2);
-            pv[3 * qq] = o0;
-            pv[3 * qq + 1] = o1;
-            pv[3 * qq + 2] = o2;
-            if (c.s0 >= 0) {
-                const double *g = c.f0;
-                slot[3 * c.s0] = g[0] * o0 + g[1] * o1 + g[2] * o2;
-                slot[3 * c.s0 + 1] = g[3] * o0 + g[4] * o1 + g[5] * o2;
-                slot[3 * c.s0 + 2] = g[6] * o0 + g[7] * o1 + g[8] * o2;
-            }
-            if (c.s1 >= 0) {
-                const double *g = g1;
-                slot[3 * c.s1] = g[0] * o0 + g[1] * o1 + g[2] * o2;
-                slot[3 * c.s1 + 1] = g[3] * o0 + g[4] * o1 + g[5] * o2;
-                slot[3 * c.s1 + 2] = g[6] * o0 + g[7] * o1 + g[8] * o2;
-            }
+            pv[3 * qq] = c0;
+            pv[3 * qq + 1] = c1;
+            pv[3 * qq + 2] = c2;
+            if (c.s0 >= 0) push3(slot + 3 * c.s0, c.f0, c0, c1, c2);
+            if (c.s1 >= 0) push3(slot + 3 * c.s1, g1, c0, c1, c2);
         }
     };
     // one elimination step of the backward sweep
@@ -272,22 +260,10 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_pcg(SmallArgs A)
             double g1[9];
             const double *gs = f1l + 9 * (int64_t)qq;
             for (int t = 0; t < 9; t++) g1[t] = gs[t];
-            double c0 = 0, c1 = 0, c2 = 0;
-            if (c.a0 >= 0) {
-                const double *g = c.f0;
-                c0 = c0 + (g[0] * p0 + g[3] * p1 + g[6] * p2);
-                c1 = c1 + (g[1] * p0 + g[4] * p1 + g[7] * p2);
-                c2 = c2 + (g[2] * p0 + g[5] * p1 + g[8] * p2);
-            }
-            if (c.a1 >= 0) {
-                const double *g = g1;
-                c0 = c0 + (g[0] * x0 + g[3] * x1 + g[6] * x2);
-                c1 = c1 + (g[1] * x0 + g[4] * x1 + g[7] * x2);
-                c2 = c2 + (g[2] * x0 + g[5] * x1 + g[8] * x2);
-            }
-            double d0, d1, d2;
-            sym_mv(c.d, c0, c1, c2, d0, d1, d2);
-            const double n0 = y0 - d0, n1 = y1 - d1, n2 = y2 - d2;
+            double n0, n1, n2;
+            sym_mv(c.d, y0, y1, y2, n0, n1, n2);
+            if (c.a0 >= 0) pull3(n0, n1, n2, c.f0, p0, p1, p2);
+            if (c.a1 >= 0) pull3(n0, n1, n2, g1, x0, x1, x2);
             pv[3 * qq] = n0;
             pv[3 * qq + 1] = n1;
             pv[3 * qq + 2] = n2;
