@@ -8,9 +8,8 @@ workload: jittered FCC ball of 1,000,000 spheres (nearest-neighbour spacing
 1.9, jitter N(0, 0.05^2)), radii U[0.95, 1.05], forces N(0, 1), seed 0.
 
 Prints ONE JSON line.  Besides the headline value it carries:
-  roofline      the CG's product Gamma p (the dominant kernel; by default the
-                edge form k_spmv_edge, from the contacts' v = sqrt(w) u and
-                the diagonal blocks): algorithmic bytes per launch / its average
+  roofline      the CG's product Gamma p (the largest kernel; by default
+                k_spmv_tile, from the cells' positions and radii): algorithmic bytes per launch / its average
                 launch time, measured with HIP events attached to sampled
                 launches on the library's stream inside the timed region;
   cpu_baseline  the FP64 CPU oracle timed on this host's cores on a bounded
@@ -48,7 +47,8 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, published
 # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, the factors that make a 512 MiB copy
 # read and write 512 MiB (summary and commands under profiles/).  Must be
 # re-measured, or set to None, whenever that kernel changes.
-SPMV_TRAFFIC_1M = {0: None, 1: 418.2e6}
+SPMV_TRAFFIC_1M = {0: None, 1: 136.8e6}
+TILE_MIN_CELLS = 8192   # beyond it form 1 is the product from the cells
 
 
 def spmv_bytes(n: int, nnzb: int, form: int = 1, val_bytes: int = 48) -> int:
@@ -57,10 +57,13 @@ def spmv_bytes(n: int, nnzb: int, form: int = 1, val_bytes: int = 48) -> int:
     symmetric, 48 B in FP64) and its column index once.  Edge form (form 1):
     every off-diagonal entry's v = sqrt(w) u (24 B) and column once, every
     diagonal block's 6 entries once.  Both: the row pointers once, x once, y
-    once."""
+    once.  From the cells (form 1, more than TILE_MIN_CELLS cells): every
+    entry's 16-bit number, every cell's position and radius, x and y once."""
     if form == 0:
         return nnzb * (val_bytes + 4) + 4 * (n + 1) + 24 * n + 24 * n
     ne = nnzb - n
+    if n > TILE_MIN_CELLS:
+        return ne * 2 + n * (32 + 24 + 24)
     return ne * (24 + 4) + n * 48 + 4 * (n + 1) + 24 * n + 24 * n
 
 
@@ -506,7 +509,8 @@ def main():
         e1.record()
         torch.cuda.synchronize()
         ms = e0.elapsed_time(e1) / 20
-        print(json.dumps({"kernel": "k_spmv_edge" if ctx.tune_get("spmv_form") else "k_spmv_sym",
+        print(json.dumps({"kernel": ("k_spmv_tile" if n > TILE_MIN_CELLS else "k_spmv_edge")
+                          if ctx.tune_get("spmv_form") else "k_spmv_sym",
                           "copy_bytes": 2 * src.numel() * 8, "api_call_avg_ms": ms,
                           "bytes_per_launch": spmv_bytes(n, nnzb, ctx.tune_get("spmv_form")),
                           "note": "api_call_avg_ms includes the two permutations of sgp_spmv; the kernel alone is in the trace"}), flush=True)
@@ -554,7 +558,9 @@ def main():
                    "schedule": args.schedule, "elim_steps": M.steps(), "cg_iters": info.get("iters"),
                    "relres_true": info.get("relres_true")},
         "roofline": {"bound": "hbm",
-                     "kernel": "k_spmv_edge (Gamma p from contacts, in CG)" if form else "k_spmv_sym (block-CSR product, in CG)",
+                     "kernel": ("k_spmv_tile (Gamma p from the cells, in CG)" if n > TILE_MIN_CELLS
+                                else "k_spmv_edge (Gamma p from contacts, in CG)") if form
+                     else "k_spmv_sym (block-CSR product, in CG)",
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "traffic": SPMV_TRAFFIC_1M[form] if (args.n == 1_000_000 and ctx.tune_get("spmv_waves") == 4) else None,

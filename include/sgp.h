@@ -136,7 +136,8 @@ void sgp_bsr_free(sgp_bsr A);
  * neighbour order.  Row i holds its neighbours and itself, columns ascending.
  * g_par, g_perp > 0 and g_med >= 0, else SGP_EINVAL.  Stored in the form the
  * product reads (tune key spmv_form): the contacts' v = sqrt(w) u with the
- * diagonal blocks, and the 3x3 blocks themselves only for the block-CSR
+ * diagonal blocks, or beyond 8192 cells the cells' positions and radii, from
+ * which the product forms the contacts again; and the 3x3 blocks themselves only for the block-CSR
  * product (spmv_form 0; assembled on first use when that key changes after
  * the assembly, which needs g not collided again since: SGP_ESTALE
  * otherwise).  sgp_bsr_export always rebuilds the blocks from g. */
@@ -466,12 +467,15 @@ int sgp_mpnn_warm_start(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, sgp_bsr Gamma, con
  *                 dense product with the inverse of their Schur complement
  *  "graph"        1: each chunk of check_every CG iterations is captured once
  *                 per solve into a hipGraph and replayed (default 0)
- *  "spmv_waves"   waves per workgroup of the product: 2, 4 or 8 (default 4)
+ *  "spmv_waves"   waves per workgroup of the product: 2, 4 or 8 (default 4;
+ *                 beyond 8192 cells it shapes the block-CSR product only)
  *  "spmv_form"    how the CG forms Gamma p: 0 from the stored 3x3 blocks,
  *                 1 from the contacts, D_i p_i - sum_j W_ij p_j with
  *                 W_ij p = g_perp (v.v) p + (g_par - g_perp)(v.p) v for the
  *                 contact's v = sqrt(w) u (w u u^T = v v^T; default 1; fewer
- *                 bytes per product; sgp_spmv uses it too)
+ *                 bytes per product; sgp_spmv uses it too); beyond 8192 cells
+ *                 g_med p_i + sum_j W_ij (p_i - p_j) with W_ij formed from
+ *                 the two cells' positions and radii
  *  "light_height" CONTRACT schedule: the first light_height rounds remove
  *                 leaves only; the subtrees they remove are swept by one
  *                 workgroup each, in one launch per sweep (0..1024, 0 = plain

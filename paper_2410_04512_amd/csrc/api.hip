@@ -89,7 +89,7 @@ extern "C" void sgp_graph_free(sgp_graph g)
     if (!g) return;
     (void)hipDeviceSynchronize();
     release(g->rowptr); release(g->col); release(g->ent_edge); release(g->ei);
-    release(g->ej); release(g->wu); release(g->inst_off); release(g->inst_of); release(g->w);
+    release(g->ej); release(g->wu); release(g->inst_off); release(g->inst_of); release(g->w); release(g->cell);
     release(g->perm); release(g->inv);
     delete g;
 }
@@ -100,7 +100,7 @@ extern "C" void sgp_bsr_free(sgp_bsr A)
     (void)hipDeviceSynchronize();
     release(A->rowptr); release(A->bcol); release(A->val); release(A->val32); release(A->diagpos);
     release(A->wrow); release(A->perm); release(A->inv);
-    release(A->ecol); release(A->ew); release(A->dg); release(A->ew32); release(A->dg32); release(A->ewrow);
+    release(A->ecol); release(A->ew); release(A->dg); release(A->ew32); release(A->tile_tab); release(A->tile_idx); release(A->tile_halo); release(A->tile_pos); release(A->dg32); release(A->ewrow);
     delete A;
 }
 

@@ -190,12 +190,11 @@ extern "C" int sgp_assemble_gamma(sgp_ctx ctx, sgp_graph g, double g_par, double
     A->have_blocks = false;
     A->src_version = g->version;
     int32_t *brow, *deg, *ecol;
-    double *ew, *dg;
     const int64_t ne = 2 * g->m;
     SGP_TRY(ensure_t(ctx, A->rowptr, n + 1, &brow));
     SGP_TRY(ensure_t(ctx, A->ecol, ne + 1, &ecol));
-    SGP_TRY(ensure_t(ctx, A->ew, edge_group_size(ne) + 8, &ew));
-    SGP_TRY(ensure_t(ctx, A->dg, sym_group_size(n) + 8, &dg));
+    A->tile_rows = 0;
+    A->have_dg = false;
     A->src = g;
     A->gpar = g_par;
     A->gperp = g_perp;
@@ -205,17 +204,25 @@ extern "C" int sgp_assemble_gamma(sgp_ctx ctx, sgp_graph g, double g_par, double
         return fill_i32(ctx, brow, 0, 1);
     }
     SGP_TRY(copy_order(ctx, A->perm, A->inv, g->perm, g->inv, n));
-    // zero the padding of the last groups (read by no row, kept finite)
-    SGP_TRY(fill_f64(ctx, dg + (sym_group_size(n) - 384), 0.0, 384));
-    if (ne > 0) SGP_TRY(fill_f64(ctx, ew + (edge_group_size(ne) - 64 * EDGE_PLANES), 0.0, 64 * EDGE_PLANES));
     SGP_TRY(ensure_t(ctx, ctx->ws[WS_DEG], n + 1, &deg));
     k_int_degree<<<grid_for(n, 256), 256, 0, st>>>(n, (const int32_t *)g->rowptr.p, (const int32_t *)g->perm.p, deg);
     SGP_TRY(scan_exclusive(ctx, deg, brow, n));
-    k_assemble<<<grid_for(ASM_LANES * n, 256), 256, 0, st>>>(n, (const int32_t *)g->rowptr.p, (const int32_t *)g->col.p,
-                                                 (const int32_t *)g->ent_edge.p, (const double4 *)g->wu.p,
-                                                 (const int32_t *)g->perm.p, (const int32_t *)g->inv.p, g_par,
-                                                 g_perp, g_med, brow, nullptr, nullptr, nullptr, ecol, ew, dg);
-    LAUNCH_CHECK(ctx);
+    if (n > TILE_MIN_CELLS) {
+        SGP_TRY(tile_assemble(ctx, g, A));
+    } else {
+        double *ew, *dg;
+        SGP_TRY(ensure_t(ctx, A->ew, edge_group_size(ne) + 8, &ew));
+        SGP_TRY(ensure_t(ctx, A->dg, sym_group_size(n) + 8, &dg));
+        // zero the padding of the last groups (read by no row, kept finite)
+        SGP_TRY(fill_f64(ctx, dg + (sym_group_size(n) - 384), 0.0, 384));
+        if (ne > 0) SGP_TRY(fill_f64(ctx, ew + (edge_group_size(ne) - 64 * EDGE_PLANES), 0.0, 64 * EDGE_PLANES));
+        k_assemble<<<grid_for(ASM_LANES * n, 256), 256, 0, st>>>(
+            n, (const int32_t *)g->rowptr.p, (const int32_t *)g->col.p, (const int32_t *)g->ent_edge.p,
+            (const double4 *)g->wu.p, (const int32_t *)g->perm.p, (const int32_t *)g->inv.p, g_par, g_perp, g_med, brow,
+            nullptr, nullptr, nullptr, ecol, ew, dg);
+        LAUNCH_CHECK(ctx);
+        A->have_dg = true;
+    }
     // the 3x3 blocks only for the block-CSR product (else on first use)
     if (ctx->spmv_form == 0) SGP_TRY(bsr_blocks(ctx, A));
     SGP_TRY(bsr_prepare(ctx, A));
@@ -298,7 +305,7 @@ int bsr_make32(sgp_ctx ctx, sgp_bsr A)
         LAUNCH_CHECK(ctx);
         A->have_val32 = true;
     }
-    if (A->have32) return SGP_OK;
+    if (A->have32 || A->tile_rows > 0) return SGP_OK;   // (the tile form reads no rounded values)
     // the edge form: (w, u) and the diagonal blocks, rounded once
     float *e32, *d32;
     const int64_t elen = edge_group_size(A->nnzb - A->n), dlen = sym_group_size(A->n);

@@ -2562,6 +2562,10 @@ extern "C" int sgp_make_jacobi(sgp_ctx ctx, sgp_bsr A, sgp_prec M)
     SGP_TRY(copy_order(ctx, M->perm, M->inv, A->perm, A->inv, A->n));
     double *dinv;
     int32_t *status;
+    if (A->n > 0 && !A->have_dg) {   // the tile form's diagonal blocks, on first use
+        SGP_TRY(tile_diag(ctx, A));
+        A->have_dg = true;
+    }
     SGP_TRY(ensure_t(ctx, M->jdinv, 6 * A->n + 6, &dinv));
     SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP9], 4, &status));
     SGP_TRY(fill_i32(ctx, status, 0, 1));

@@ -56,7 +56,7 @@ SGP_DEV int vec_idx(int u, int ne) { return min((int)threadIdx.x + 256 * u, ne -
 SGP_DEV bool vec_own(int u, int ne) { return (int)threadIdx.x + 256 * u < ne; }
 
 // host-side construction: clusters are cut into blocks of rows_per_block rows
-static void build_tab(const std::vector<int64_t> &off, int rows_per_block, std::vector<int32_t> &buf,
+void build_tab(const std::vector<int64_t> &off, int rows_per_block, std::vector<int32_t> &buf,
                       int32_t &nblocks)
 {
     int64_t K = (int64_t)off.size() - 1;
@@ -761,22 +761,29 @@ struct PcgWork {
     int32_t mv_nb = 0;                   // product workgroups (one cluster: p.q partials)
     const int32_t *mv_first = nullptr;   // {0}
     const int32_t *mv_nb_dev = nullptr;  // {mv_nb}
+    // several clusters whose product forms the partials of p.q itself (the
+    // tile form, whose tiles are cut from the same clusters): per cluster its
+    // first tile and number of tiles
+    const int32_t *tile_first = nullptr, *tile_nb = nullptr;
     int64_t K = 1;
     int32_t s0_q1 = 0;               // > 0: the first elimination step runs in the vector passes
     const int32_t *s0_qr = nullptr;  // its positions per vector block
 };
 
 template <class T>
-static int spmv_t(sgp_ctx ctx, sgp_bsr A, const T *x, T *y, const PcgScalars *S, double *part, int mode);
+static int spmv_t(sgp_ctx ctx, sgp_bsr A, const T *x, T *y, const PcgScalars *S, double *part, int mode,
+                  bool per_inst = false);
 template <>
-int spmv_t<double>(sgp_ctx ctx, sgp_bsr A, const double *x, double *y, const PcgScalars *S, double *part, int mode)
+int spmv_t<double>(sgp_ctx ctx, sgp_bsr A, const double *x, double *y, const PcgScalars *S, double *part, int mode,
+                   bool per_inst)
 {
-    return spmv_f64(ctx, A, x, y, S, part, mode);
+    return spmv_f64(ctx, A, x, y, S, part, mode, per_inst);
 }
 template <>
-int spmv_t<float>(sgp_ctx ctx, sgp_bsr A, const float *x, float *y, const PcgScalars *S, double *part, int mode)
+int spmv_t<float>(sgp_ctx ctx, sgp_bsr A, const float *x, float *y, const PcgScalars *S, double *part, int mode,
+                  bool per_inst)
 {
-    return spmv_f32(ctx, A, x, y, S, part, mode);
+    return spmv_f32(ctx, A, x, y, S, part, mode, per_inst);
 }
 
 
@@ -840,6 +847,10 @@ static int pcg_chunk(sgp_ctx ctx, sgp_bsr A, sgp_prec M, Vecs<T> v, PcgWork &w, 
             SGP_TRY(spmv_t<T>(ctx, A, v.p, v.q, S, part, 1));
             if (timed) SGP_TRY(ktimer_end(ctx));
             SGP_TRY(fin(ctx, FIN_ALPHA, part, w.mv_nb, w.mv_first, w.mv_nb_dev, S, 1));
+        } else if (w.tile_first) {
+            SGP_TRY(spmv_t<T>(ctx, A, v.p, v.q, S, part, 1, true));
+            if (timed) SGP_TRY(ktimer_end(ctx));
+            SGP_TRY(fin(ctx, FIN_ALPHA, part, w.mv_nb, w.tile_first, w.tile_nb, S, K));
         } else {
             SGP_TRY(spmv_t<T>(ctx, A, v.p, v.q, nullptr, nullptr, 0));
             if (timed) SGP_TRY(ktimer_end(ctx));
@@ -1024,6 +1035,10 @@ static int prepare_work(sgp_ctx ctx, sgp_bsr A, const std::vector<int64_t> &off,
     w.vec = tab_ptrs(d, w.vec_nb, K);
     w.mv_first = d + nv - 2;
     w.mv_nb_dev = d + nv - 1;
+    if (K > 1 && spmv_tiled(ctx, A) && A->tile_off == off) {
+        w.tile_first = (const int32_t *)A->tile_tab.p + 3 * (size_t)A->n_tiles;
+        w.tile_nb = w.tile_first + K;
+    }
     const int32_t q1 = ctx->fuse_step0 ? prec_step0_launch(M) : 0;
     if (q1 > 0 && M->n == A->n) {
         int32_t *qr = d + nv + 2;

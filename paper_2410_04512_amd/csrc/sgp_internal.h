@@ -125,6 +125,9 @@ struct sgp_graph_ {
     uint64_t version = 0;   // changes whenever a collide rewrites the graph
     DevBuf rowptr, col, ent_edge, ei, ej, wu, inst_off, inst_of;
     DevBuf w;   // the contacts' w alone (dense, for passes that read only w)
+    DevBuf cell;   // double4 per cell, internal order: position and radius
+    int32_t max_deg = 0;   // contacts of a cell at most
+    bool hertz = false;    // w is the Hertz contact area
     DevBuf perm, inv;
     std::vector<int64_t> h_inst_off;
 };
@@ -151,7 +154,19 @@ struct sgp_bsr_ {
     int64_t enwaves = 0;
     int64_t nwaves = 0;
     bool have32 = false;
+    // tile form (tile.hip; more than TILE_MIN_CELLS cells, instead of the edge
+    // form's ew and dg): rows per tile (0: none), tiles, entry slots per row,
+    // the clusters the tiles are cut from, per-tile tables (several clusters),
+    // entries, halos with their counts, positions and radii
+    int32_t tile_rows = 0, n_tiles = 0, tile_w = 0;
+    bool tile_hertz = false, have_dg = false;
+    std::vector<int64_t> tile_off;
+    DevBuf tile_tab, tile_idx, tile_halo, tile_pos;
 };
+
+// cells beyond which the product takes the tile form and the internal order
+// the bricks that it needs
+constexpr int64_t TILE_MIN_CELLS = 8192;
 
 inline int64_t sym_group_size(int64_t nnzb) { return ((nnzb + 63) / 64) * 384; }   // values incl. padding
 // the edge form keeps per entry v = sqrt(w) u of its contact (w = v.v), in
@@ -344,8 +359,20 @@ int bsr_make32(sgp_ctx ctx, sgp_bsr A);
 int bsr_prepare(sgp_ctx ctx, sgp_bsr A);
 int spmv_blocks(sgp_ctx ctx, sgp_bsr A);
 uint64_t next_graph_version();   // process-wide, strictly increasing
-int spmv_f64(sgp_ctx ctx, sgp_bsr A, const double *x, double *y, const PcgScalars *S, double *part, int mode);
-int spmv_f32(sgp_ctx ctx, sgp_bsr A, const float *x, float *y, const PcgScalars *S, double *part, int mode);
+// per_inst: S per cluster of the tile form's tiles (tile_fused)
+int spmv_f64(sgp_ctx ctx, sgp_bsr A, const double *x, double *y, const PcgScalars *S, double *part, int mode,
+             bool per_inst = false);
+int spmv_f32(sgp_ctx ctx, sgp_bsr A, const float *x, float *y, const PcgScalars *S, double *part, int mode,
+             bool per_inst = false);
+int tile_assemble(sgp_ctx ctx, sgp_graph g, sgp_bsr A);
+int tile_diag(sgp_ctx ctx, sgp_bsr A);
+template <class T>
+int spmv_tile(sgp_ctx ctx, sgp_bsr A, const T *x, T *y, const PcgScalars *S, bool per_inst, double *part, int mode);
+// the product runs in the tile form
+inline bool spmv_tiled(sgp_ctx ctx, sgp_bsr A) { return ctx->spmv_form == 1 && A->tile_rows > 0; }
+// clusters cut into blocks of rows (pcg.hip): [row0][row1][cluster] per block,
+// [first block][blocks] per cluster
+void build_tab(const std::vector<int64_t> &off, int rows_per_block, std::vector<int32_t> &buf, int32_t &nblocks);
 
 // ---------------------------------------------------------------- device helpers
 

@@ -320,6 +320,7 @@ __global__ __launch_bounds__(64 * SPMV_WAVES) void k_spmv_edge(const int32_t *__
 
 int spmv_blocks(sgp_ctx ctx, sgp_bsr A)
 {
+    if (spmv_tiled(ctx, A)) return A->n_tiles;
     const int64_t nw = ctx->spmv_form ? A->enwaves : A->nwaves;
     return (int)((nw + ctx->spmv_waves - 1) / ctx->spmv_waves);
 }
@@ -378,16 +379,20 @@ static int spmv_launch(sgp_ctx ctx, sgp_bsr A, const T *val, const T *ew, const 
     return SGP_OK;
 }
 
-int spmv_f64(sgp_ctx ctx, sgp_bsr A, const double *x, double *y, const PcgScalars *S, double *part, int mode)
+int spmv_f64(sgp_ctx ctx, sgp_bsr A, const double *x, double *y, const PcgScalars *S, double *part, int mode,
+             bool per_inst)
 {
+    if (spmv_tiled(ctx, A)) return spmv_tile<double>(ctx, A, x, y, S, per_inst, part, mode);
     // the blocks are assembled on first use: before their pointer is taken
     if (!ctx->spmv_form && A->n > 0) SGP_TRY(bsr_blocks(ctx, A));
     return spmv_launch<double>(ctx, A, (const double *)A->val.p, (const double *)A->ew.p, (const double *)A->dg.p,
                                x, y, S, part, mode);
 }
 
-int spmv_f32(sgp_ctx ctx, sgp_bsr A, const float *x, float *y, const PcgScalars *S, double *part, int mode)
+int spmv_f32(sgp_ctx ctx, sgp_bsr A, const float *x, float *y, const PcgScalars *S, double *part, int mode,
+             bool per_inst)
 {
+    if (spmv_tiled(ctx, A)) return spmv_tile<float>(ctx, A, x, y, S, per_inst, part, mode);
     // the FP32 copies (and the blocks they round) before their pointers are taken
     if (A->n > 0) SGP_TRY(bsr_make32(ctx, A));
     return spmv_launch<float>(ctx, A, (const float *)A->val32.p, (const float *)A->ew32.p, (const float *)A->dg32.p,
