@@ -103,7 +103,7 @@ struct sgp_mpnn_ {
     Layout L = make_layout();
     Packed PK = make_packed();
     DevBuf theta, m1, m2, grad, wbf, wrow;   // wrow: BF16-rounded master weights as FP32 (edge arithmetic)
-    DevBuf act, efeat, part, red, sum, vq;   // vq: v_hat and Gamma v_hat (FP64, canonical order)
+    DevBuf act, efeat, part, vq;   // vq: v_hat and Gamma v_hat (FP64, canonical order)
     DevBuf irow, icol;                      // neighbour lists in the internal order (with efeat)
     const void *lists_of = nullptr;         // graph and version they were built for
     uint64_t lists_version = 0;
@@ -235,8 +235,8 @@ __global__ __launch_bounds__(256) void k_gemm(const float *A, int64_t lda, const
 
 // One layer's node update in one pass: U = [h, a] W_u + b_u as the two
 // K = 64 products of the unfused form (h against rows 0..63 of W_u plus the
-// bias, then a against rows 64..127, added in that order), kept for the
-// backward pass, and h' = h + relu(U).  The operations and their order are
+// bias, then a against rows 64..127, added in that order), kept for a
+// backward pass (U null: none follows), and h' = h + relu(U).  The operations and their order are
 // those of two k_gemm launches and the residual pass, so the results are
 // the same bit for bit; h and a are read once and U is not read back.
 __global__ __launch_bounds__(256) void k_gemm_update(const float *H, const float *Ag, const unsigned short *B,
@@ -303,105 +303,137 @@ __global__ __launch_bounds__(256) void k_gemm_update(const float *H, const float
                 if (row >= M) continue;
                 const int64_t o = row * N + 16 * nt + lr;
                 const float u = (acc1[t] + bv[nt]) + (acc2[t] + 0.f);
-                U[o] = u;
+                if (U) U[o] = u;
                 Hn[o] = hv[nt][t] + fmaxf(u, 0.f);
             }
         }
     }
 }
 
-// Weight-gradient partials over chunks of AT_ROWS rows: part[g] holds the
-// chunk's A^T D (K x N, MFMA with the row index as the reduction dimension)
-// followed by the chunk's column sums of D (N values, FP32).  A 64-row slab is
-// staged in LDS transposed and in BF16, so a lane's four reduction-index
-// values are adjacent; wave w owns the output tiles w, w + 4, ...  Every sum
-// has a fixed order.
-constexpr int AT_ROWS = 512;
+// Weight-gradient partials: workgroup g's [A | A2]^T D (K x N, the row index
+// the reduction dimension of the MFMAs) over its share of the 16-row blocks,
+// then its column sums of D (N values, FP32).  A lane's four reduction-index
+// values are four rows of one column, so the fragments come straight from
+// global memory (64-byte segments; the other tiles of the block read the rest of
+// the same lines): no LDS, no barrier, and each wave walks blocks of its own,
+// all loads of a block ahead of its MFMAs.  A wave keeps all K x N sums; the
+// workgroup adds its four waves in LDS.  Bound by memory: 60k rows, 64 x 128:
+// 118 -> 21 us (before, 512-row chunks through LDS: 118 workgroups, each
+// waiting for one slab at a time).  Every sum has a fixed order.
+constexpr int AT_GRID = 256;
 
-template <int KT>
-__global__ __launch_bounds__(256) void k_gemm_at(const float *A, int64_t lda, const float *D, int64_t ldd, int N,
-                                                 int64_t M, float *part)
+template <int KT1, int KT2, int NT>
+__global__ __launch_bounds__(256) void k_gemm_at(const float *A, int64_t lda, const float *A2, int64_t lda2,
+                                                 const float *D, int64_t ldd, int64_t M, float *part)
 {
-    constexpr int K = 16 * KT;
-    __shared__ __attribute__((aligned(16))) unsigned short sAT[K][68];
-    __shared__ __attribute__((aligned(16))) unsigned short sDT[128][68];
-    __shared__ float scs[256];
-    const int NT = N >> 4, tiles = KT * NT;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int lr = lane & 15, lg = lane >> 4;
-    const int64_t m0 = (int64_t)blockIdx.x * AT_ROWS;
-    const int64_t m1 = m0 + AT_ROWS < M ? m0 + AT_ROWS : M;
-    f32x4 acc[8];
-    for (int q = 0; q < 8; q++) acc[q] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    float cs = 0.f;   // column threadIdx.x % N (256 is a multiple of N)
-    for (int64_t rs = m0; rs < m1; rs += 64) {
-        __syncthreads();
-        for (int t = threadIdx.x; t < 64 * K; t += 256) {
-            const int r = t / K, c = t % K;
-            sAT[c][r] = f2bf(rs + r < m1 ? A[(rs + r) * lda + c] : 0.f);
+    constexpr int KT = KT1 + KT2, K = 16 * KT, N = 16 * NT;
+    __shared__ float sh[K * N + N];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, lr = lane & 15, lg = lane >> 4;
+    f32x4 acc[KT][NT];
+    float cs[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++) {
+        cs[nt] = 0.f;
+#pragma unroll
+        for (int kt = 0; kt < KT; kt++) acc[kt][nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    const int64_t nblk = (M + 15) / 16, step = 4 * (int64_t)gridDim.x;
+    for (int64_t blk = 4 * (int64_t)blockIdx.x + wv; blk < nblk; blk += step) {
+        float av[KT][4], dv[NT][4];
+        const int64_t r0 = 16 * blk + 4 * lg;
+#pragma unroll
+        for (int t = 0; t < 4; t++) {
+            const int64_t r = min(r0 + t, M - 1);
+#pragma unroll
+            for (int nt = 0; nt < NT; nt++) dv[nt][t] = D[r * ldd + 16 * nt + lr];
+#pragma unroll
+            for (int kt = 0; kt < KT1; kt++) av[kt][t] = A[r * lda + 16 * kt + lr];
+#pragma unroll
+            for (int kt = 0; kt < KT2; kt++) av[KT1 + kt][t] = A2[r * lda2 + 16 * kt + lr];
         }
-        for (int t = threadIdx.x; t < 64 * N; t += 256) {
-            const int r = t / N, c = t % N;
-            const float v = rs + r < m1 ? D[(rs + r) * ldd + c] : 0.f;
-            cs += v;
-            sDT[c][r] = f2bf(v);
+        keep_loads_above();
+        bf16x4 a[KT];
+#pragma unroll
+        for (int kt = 0; kt < KT; kt++)
+#pragma unroll
+            for (int t = 0; t < 4; t++) a[kt][t] = (short)f2bf(r0 + t < M ? av[kt][t] : 0.f);
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) {
+            bf16x4 d;
+#pragma unroll
+            for (int t = 0; t < 4; t++) {
+                const float v = r0 + t < M ? dv[nt][t] : 0.f;
+                cs[nt] += v;
+                d[t] = (short)f2bf(v);
+            }
+#pragma unroll
+            for (int kt = 0; kt < KT; kt++)
+                acc[kt][nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[kt], d, acc[kt][nt], 0, 0, 0);
         }
-        __syncthreads();
-        for (int sub = 0; sub < 4; sub++) {
-            for (int q = 0; q < 8; q++) {
-                const int tile = wv + 4 * q;
-                if (tile >= tiles) break;
-                const int kt = tile / NT, nt = tile % NT;
-                const bf16x4 a = *(const bf16x4 *)&sAT[16 * kt + lr][16 * sub + 4 * lg];
-                const bf16x4 b = *(const bf16x4 *)&sDT[16 * nt + lr][16 * sub + 4 * lg];
-                acc[q] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[q], 0, 0, 0);
+    }
+    // the four waves in order, then out
+    for (int w = 0; w < 4; w++) {
+        if (wv == w) {
+#pragma unroll
+            for (int nt = 0; nt < NT; nt++) {
+                float c = cs[nt];
+                c += __shfl_xor(c, 16, 64);
+                c += __shfl_xor(c, 32, 64);
+                if (lg == 0) sh[K * N + 16 * nt + lr] = w ? sh[K * N + 16 * nt + lr] + c : c;
+#pragma unroll
+                for (int kt = 0; kt < KT; kt++)
+#pragma unroll
+                    for (int t = 0; t < 4; t++) {
+                        float *o = sh + (16 * kt + 4 * lg + t) * N + 16 * nt + lr;
+                        *o = w ? *o + acc[kt][nt][t] : acc[kt][nt][t];
+                    }
             }
         }
+        __syncthreads();
     }
     float *P = part + (int64_t)blockIdx.x * (K * N + N);
-    for (int q = 0; q < 8; q++) {
-        const int tile = wv + 4 * q;
-        if (tile >= tiles) break;
-        const int kt = tile / NT, nt = tile % NT;
-        for (int t = 0; t < 4; t++) P[(16 * kt + 4 * lg + t) * N + 16 * nt + lr] = acc[q][t];
+    for (int t = threadIdx.x; t < K * N + N; t += 256) P[t] = sh[t];
+}
+
+// Where a sum of partials goes in the gradient: value (r, c) of the K x N
+// product to w0[r ld + c] for c < c1 and to w1[r ld + c - c1] for c1 <= c < c2
+// (rows below `rows` only), the column sums of columns below c1 to b (if any).
+struct GradOut {
+    float *w0, *w1, *b;
+    int K, N, rows, c1, c2, ld;
+};
+
+// Fixed-order sum of G partial vectors of length L: 64 values per workgroup,
+// its 16 waves a contiguous run of partials each (eight loads in flight), the
+// runs added in order, and each sum stored where it belongs: one launch instead
+// of two sums and up to three copies.
+constexpr int RED_WAVES = 16;
+__global__ __launch_bounds__(64 * RED_WAVES) void k_red_out(const float *part, int G, int L, GradOut o)
+{
+    __shared__ float sh[RED_WAVES][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int c = blockIdx.x * 64 + lane, cc = min(c, L - 1);
+    const int per = (G + RED_WAVES - 1) / RED_WAVES, p0 = min(wv * per, G), p1 = min(p0 + per, G);
+    float acc = 0.f;
+    for (int p = p0; p < p1; p += 8) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) v[u] = part[(int64_t)min(p + u, p1 - 1) * L + cc];
+#pragma unroll
+        for (int u = 0; u < 8; u++) acc += p + u < p1 ? v[u] : 0.f;
     }
-    scs[threadIdx.x] = cs;
+    sh[wv][lane] = acc;
     __syncthreads();
-    if (threadIdx.x < N) {
-        float s = 0.f;
-        for (int k = threadIdx.x; k < 256; k += N) s += scs[k];
-        P[K * N + threadIdx.x] = s;
+    if (wv != 0 || c >= L) return;
+    float s = 0.f;
+    for (int w = 0; w < RED_WAVES; w++) s += sh[w][lane];
+    const int r = c / o.N, k = c % o.N;
+    if (r >= o.K) {
+        if (o.b && k < o.c1) o.b[k] = s;
+    } else if (r < o.rows) {
+        if (k < o.c1) o.w0[r * o.ld + k] = s;
+        else if (k < o.c2) o.w1[r * o.ld + k - o.c1] = s;
     }
-}
-
-// Fixed-order reduction of G partial vectors of length L: stage 1 sums a
-// contiguous run of `per` partials per segment, stage 2 the segments in order.
-__global__ void k_red1(const float *part, int G, int L, int per, float *tmp)
-{
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= L) return;
-    const int p0 = blockIdx.y * per, p1 = p0 + per < G ? p0 + per : G;
-    float acc = 0.f;
-    for (int p = p0; p < p1; p++) acc += part[(int64_t)p * L + c];
-    tmp[(int64_t)blockIdx.y * L + c] = acc;
-}
-
-__global__ void k_red2(const float *tmp, int S, int L, float *out)
-{
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= L) return;
-    float acc = 0.f;
-    for (int s = 0; s < S; s++) acc += tmp[(int64_t)s * L + c];
-    out[c] = acc;
-}
-
-// out[r * ld + (c - c0)] = red[off + r * N + c] for r < r1, c0 <= c < c1
-__global__ void k_window(const float *red, int off, int N, int r1, int c0, int c1, float *out, int64_t ld)
-{
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= r1 * (c1 - c0)) return;
-    const int r = t / (c1 - c0), c = c0 + t % (c1 - c0);
-    out[(int64_t)r * ld + (c - c0)] = red[off + r * N + c];
 }
 
 // ---------------------------------------------------------------- elementwise
@@ -468,8 +500,7 @@ __global__ void k_add64(int64_t n, const float *a, int64_t lda, const float *b, 
     dst[i * ldd + c] = a[i * lda + c] + b[i * ldb + c];
 }
 
-// ---------------------------------------------------------------- messages (forward: 16 lanes per row, four
-// features per lane; backward: one wave per row, lane = feature)
+// ---------------------------------------------------------------- messages (16 lanes per row, four features per lane)
 
 // A row's entries are taken MSG_BATCH at a time: their column ids and edge
 // features first, then all their neighbour gathers, then the arithmetic in
@@ -522,10 +553,13 @@ __global__ __launch_bounds__(256) void k_msg_fwd(int64_t n, const int32_t *rowpt
 }
 
 // dP_i = sum over row i of dz_p, dz_p = da_i [z_p > 0]; per-workgroup partials
-// of e_p^T dz_p (4 x 64).  The grid is fixed (at most MSG_BWD_GRID workgroups);
-// workgroup b (in XCD-contiguous order) walks its own contiguous run of 4-row
+// of e_p^T dz_p (4 x 64).  Lanes and loads as in the forward messages (16 lanes
+// per row, four features per lane, a batch's loads unconditional and ahead of
+// their use; one wave per row with loads behind branches took 74 us instead of
+// 38 at 60k rows, and 63 instead of 28 in k_msg_bwd_q).  The grid is fixed (at most MSG_BWD_GRID workgroups);
+// workgroup b (in XCD-contiguous order) walks its own contiguous run of 16-row
 // blocks in order.
-constexpr int MSG_BWD_GRID = 1024;
+constexpr int MSG_BWD_GRID = 2048;
 
 __global__ __launch_bounds__(256) void k_msg_bwd_p(int64_t n, const int32_t *rowptr, const int32_t *col,
                                                    const float4 *ef, const float *PQ, const float *bm,
@@ -533,53 +567,67 @@ __global__ __launch_bounds__(256) void k_msg_bwd_p(int64_t n, const int32_t *row
                                                    float *wc_part)
 {
     __shared__ float sw[4][256];
-    const int wv = threadIdx.x >> 6, f = threadIdx.x & 63;
-    const float w0 = Wc[f], w1 = Wc[64 + f], w2 = Wc[128 + f], w3 = Wc[192 + f];
-    const float bmf = bm[f];
-    float g0 = 0.f, g1 = 0.f, g2 = 0.f, g3 = 0.f;
-    const int64_t nblk = (n + 3) / 4, per = (nblk + gridDim.x - 1) / gridDim.x;
-    const int64_t b0 = xcd_block(blockIdx.x, gridDim.x) * per;
-    const int64_t b1 = b0 + per < nblk ? b0 + per : nblk;
-    for (int64_t blk = b0; blk < b1; blk++) {
-        const int64_t i = blk * 4 + wv;
+    const int wv = threadIdx.x >> 6, f = 4 * (threadIdx.x & 15);
+    const float4 w0 = *(const float4 *)(Wc + f), w1 = *(const float4 *)(Wc + 64 + f);
+    const float4 w2 = *(const float4 *)(Wc + 128 + f), w3 = *(const float4 *)(Wc + 192 + f);
+    const float4 b4 = *(const float4 *)(bm + f);
+    float g[4][4];
+    for (int a = 0; a < 4; a++)
+        for (int k = 0; k < 4; k++) g[a][k] = 0.f;
+    const int64_t nblk = (n + 15) / 16, per = (nblk + gridDim.x - 1) / gridDim.x;
+    const int64_t k0 = xcd_block(blockIdx.x, gridDim.x) * per;
+    const int64_t k1 = k0 + per < nblk ? k0 + per : nblk;
+    for (int64_t blk = k0; blk < k1; blk++) {
+        const int64_t i = blk * 16 + (threadIdx.x >> 4);
         if (i >= n) continue;
-        const float Pi = PQ[i * 128 + f] + bmf;
-        const float dai = da[i * ldda + f];
-        float dp = 0.f;
+        const float4 pq = *(const float4 *)(PQ + i * 128 + f), d4 = *(const float4 *)(da + i * ldda + f);
+        const float P[4] = {pq.x + b4.x, pq.y + b4.y, pq.z + b4.z, pq.w + b4.w}, dai[4] = {d4.x, d4.y, d4.z, d4.w};
+        float dp[4] = {0.f, 0.f, 0.f, 0.f};
         const int32_t re = rowptr[i + 1];
         for (int32_t p = rowptr[i]; p < re; p += MSG_BATCH) {
             const int cnt = re - p < MSG_BATCH ? re - p : MSG_BATCH;
-            int64_t jj[MSG_BATCH];
-            float4 ee[MSG_BATCH];
-            float qv[MSG_BATCH];
+            int32_t jj[MSG_BATCH];
+            float4 ee[MSG_BATCH], qv[MSG_BATCH];
+#pragma unroll
+            for (int u = 0; u < MSG_BATCH; u++) {
+                const int32_t pc = min(p + u, re - 1);
+                jj[u] = col[pc];
+                ee[u] = ef[pc];
+            }
+#pragma unroll
+            for (int u = 0; u < MSG_BATCH; u++) qv[u] = *(const float4 *)(PQ + (int64_t)jj[u] * 128 + 64 + f);
+            keep_loads_above();
 #pragma unroll
             for (int u = 0; u < MSG_BATCH; u++)
                 if (u < cnt) {
-                    jj[u] = col[p + u];
-                    ee[u] = ef[p + u];
-                }
+                    const float4 e = ee[u], q = qv[u];
+                    const float z[4] = {P[0] + q.x + (e.x * w0.x + e.y * w1.x + e.z * w2.x + e.w * w3.x),
+                                        P[1] + q.y + (e.x * w0.y + e.y * w1.y + e.z * w2.y + e.w * w3.y),
+                                        P[2] + q.z + (e.x * w0.z + e.y * w1.z + e.z * w2.z + e.w * w3.z),
+                                        P[3] + q.w + (e.x * w0.w + e.y * w1.w + e.z * w2.w + e.w * w3.w)};
 #pragma unroll
-            for (int u = 0; u < MSG_BATCH; u++)
-                if (u < cnt) qv[u] = PQ[jj[u] * 128 + 64 + f];
-#pragma unroll
-            for (int u = 0; u < MSG_BATCH; u++)
-                if (u < cnt) {
-                    const float4 e = ee[u];
-                    const float z = Pi + qv[u] + (e.x * w0 + e.y * w1 + e.z * w2 + e.w * w3);
-                    const float dz = z > 0.f ? dai : 0.f;
-                    dp += dz;
-                    g0 += e.x * dz;
-                    g1 += e.y * dz;
-                    g2 += e.z * dz;
-                    g3 += e.w * dz;
+                    for (int k = 0; k < 4; k++) {
+                        const float dz = z[k] > 0.f ? dai[k] : 0.f;
+                        dp[k] += dz;
+                        g[0][k] += e.x * dz;
+                        g[1][k] += e.y * dz;
+                        g[2][k] += e.z * dz;
+                        g[3][k] += e.w * dz;
+                    }
                 }
         }
-        dPQ[i * 128 + f] = dp;
+        *(float4 *)(dPQ + i * 128 + f) = make_float4(dp[0], dp[1], dp[2], dp[3]);
     }
-    sw[wv][f] = g0;
-    sw[wv][64 + f] = g1;
-    sw[wv][128 + f] = g2;
-    sw[wv][192 + f] = g3;
+    // a wave's four row groups, then the four waves
+#pragma unroll
+    for (int a = 0; a < 4; a++)
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            float v = g[a][k];
+            v += __shfl_xor(v, 16, 64);
+            v += __shfl_xor(v, 32, 64);
+            if ((threadIdx.x & 63) < 16) sw[wv][64 * a + f + k] = v;
+        }
     __syncthreads();
     const int t = threadIdx.x;   // 256 = 4 x 64 outputs
     wc_part[(int64_t)blockIdx.x * 256 + t] = (sw[0][t] + sw[1][t]) + (sw[2][t] + sw[3][t]);
@@ -591,45 +639,47 @@ __global__ __launch_bounds__(256) void k_msg_bwd_q(int64_t n, const int32_t *row
                                                    const float4 *ef, const float *PQ, const float *bm,
                                                    const float *Wc, const float *da, int64_t ldda, float *dPQ)
 {
-    const int64_t j = xcd_block(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
-    const int f = threadIdx.x & 63;
+    constexpr int BATCH = 4;   // two gathers per entry
+    const int64_t j = xcd_block(blockIdx.x, gridDim.x) * 16 + (threadIdx.x >> 4);
+    const int f = 4 * (threadIdx.x & 15);
     if (j >= n) return;
-    const float Qj = PQ[j * 128 + 64 + f];
-    const float w0 = Wc[f], w1 = Wc[64 + f], w2 = Wc[128 + f], w3 = Wc[192 + f];
-    const float bmf = bm[f];
-    float dq = 0.f;
+    const float4 q4 = *(const float4 *)(PQ + j * 128 + 64 + f), b4 = *(const float4 *)(bm + f);
+    const float4 w0 = *(const float4 *)(Wc + f), w1 = *(const float4 *)(Wc + 64 + f);
+    const float4 w2 = *(const float4 *)(Wc + 128 + f), w3 = *(const float4 *)(Wc + 192 + f);
+    float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
     const int32_t re = rowptr[j + 1];
-    for (int32_t p = rowptr[j]; p < re; p += MSG_BATCH) {
-        const int cnt = re - p < MSG_BATCH ? re - p : MSG_BATCH;
-        int64_t ii[MSG_BATCH];
-        float4 ee[MSG_BATCH];
-        float pv[MSG_BATCH], dv[MSG_BATCH];
+    for (int32_t p = rowptr[j]; p < re; p += BATCH) {
+        const int cnt = re - p < BATCH ? re - p : BATCH;
+        int32_t ii[BATCH];
+        float4 ee[BATCH], pv[BATCH], dv[BATCH];
 #pragma unroll
-        for (int u = 0; u < MSG_BATCH; u++)
-            if (u < cnt) {
-                ii[u] = col[p + u];
-                ee[u] = ef[p + u];
-            }
+        for (int u = 0; u < BATCH; u++) {
+            const int32_t pc = min(p + u, re - 1);
+            ii[u] = col[pc];
+            ee[u] = ef[pc];
+        }
 #pragma unroll
-        for (int u = 0; u < MSG_BATCH; u++)
-            if (u < cnt) {
-                pv[u] = PQ[ii[u] * 128 + f];
-                dv[u] = da[ii[u] * ldda + f];
-            }
+        for (int u = 0; u < BATCH; u++) {
+            pv[u] = *(const float4 *)(PQ + (int64_t)ii[u] * 128 + f);
+            dv[u] = *(const float4 *)(da + (int64_t)ii[u] * ldda + f);
+        }
+        keep_loads_above();
 #pragma unroll
-        for (int u = 0; u < MSG_BATCH; u++)
+        for (int u = 0; u < BATCH; u++)
             if (u < cnt) {
-                const float4 e = ee[u];
-                const float z = (pv[u] + bmf) + Qj + (e.x * w0 - e.y * w1 - e.z * w2 - e.w * w3);
-                dq += z > 0.f ? dv[u] : 0.f;
+                const float4 e = ee[u], P = pv[u], d = dv[u];
+                a0 += (P.x + b4.x) + q4.x + (e.x * w0.x - e.y * w1.x - e.z * w2.x - e.w * w3.x) > 0.f ? d.x : 0.f;
+                a1 += (P.y + b4.y) + q4.y + (e.x * w0.y - e.y * w1.y - e.z * w2.y - e.w * w3.y) > 0.f ? d.y : 0.f;
+                a2 += (P.z + b4.z) + q4.z + (e.x * w0.z - e.y * w1.z - e.z * w2.z - e.w * w3.z) > 0.f ? d.z : 0.f;
+                a3 += (P.w + b4.w) + q4.w + (e.x * w0.w - e.y * w1.w - e.z * w2.w - e.w * w3.w) > 0.f ? d.w : 0.f;
             }
     }
-    dPQ[j * 128 + 64 + f] = dq;
+    *(float4 *)(dPQ + j * 128 + 64 + f) = make_float4(a0, a1, a2, a3);
 }
 
 // loss = mean (out - v/sV)^2 over 3n values; dout16 = 2 (out - v/sV)/(3n) in columns 0..2
-__global__ __launch_bounds__(256) void k_loss(int64_t n, const int32_t *perm, const float *out16, const double *v,
-                                              float sV, float *dout16, double *part)
+__global__ __launch_bounds__(256) void k_loss(int64_t n, const int32_t *perm, const float *out16, const float *bout,
+                                              const double *v, float sV, float *dout16, double *part)
 {
     __shared__ double sh[256];
     int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -638,7 +688,7 @@ __global__ __launch_bounds__(256) void k_loss(int64_t n, const int32_t *perm, co
         for (int a = 0; a < 16; a++) {
             float d = 0.f;
             if (a < 3) {
-                d = out16[16 * i + a] - (float)(v[3 * (int64_t)perm[i] + a] / sV);
+                d = (out16[16 * i + a] + bout[a]) - (float)(v[3 * (int64_t)perm[i] + a] / sV);
                 s += (double)d * (double)d;
                 d = 2.f * d / (float)(3 * n);
             }
@@ -725,12 +775,13 @@ __global__ void k_sum_double(const double *part, int np, double *out)
     if (threadIdx.x == 0) *out = s;
 }
 
-__global__ void k_output(int64_t n, const int32_t *perm, const float *out16, double sV, double *vhat)
+__global__ void k_output(int64_t n, const int32_t *perm, const float *out16, const float *bout, double sV,
+                         double *vhat)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int64_t u = perm[i];
-    for (int a = 0; a < 3; a++) vhat[3 * u + a] = sV * (double)out16[16 * i + a];
+    for (int a = 0; a < 3; a++) vhat[3 * u + a] = sV * (double)(out16[16 * i + a] + bout[a]);
 }
 
 __global__ void k_adam(int64_t np, float *theta, const float *g, float *m1, float *m2, float lr, float b1, float b2,
@@ -744,16 +795,6 @@ __global__ void k_adam(int64_t np, float *theta, const float *g, float *m1, floa
     m1[t] = a;
     m2[t] = b;
     theta[t] -= lr * (a / c1) / (sqrtf(b / c2) + eps);
-}
-
-// b_out added to the first three output columns
-__global__ void k_add_bias3(int64_t n, float *out16, const float *b)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    out16[16 * i] += b[0];
-    out16[16 * i + 1] += b[1];
-    out16[16 * i + 2] += b[2];
 }
 
 // ---------------------------------------------------------------- host drivers
@@ -803,47 +844,29 @@ int gemm(sgp_ctx ctx, const float *A, int64_t lda, const unsigned short *B, floa
     return SGP_OK;
 }
 
-// out[0, L) = fixed-order sum of the G partial vectors part[g][0, L)
-int reduce_parts(sgp_ctx ctx, sgp_mpnn M, const float *part, int G, int L, float *out)
+// the fixed-order sum of the G partial vectors part[g][0, L), into the gradient
+int reduce_parts(sgp_ctx ctx, const float *part, int G, int L, const GradOut &o)
 {
-    const int S = G < 32 ? G : 32;
-    const int per = (G + S - 1) / S;
-    const int segs = (G + per - 1) / per;
-    float *tmp;
-    SGP_TRY(ensure_t(ctx, M->red, (size_t)segs * L + 64, &tmp));
-    k_red1<<<dim3((unsigned)grid_for(L, 256), (unsigned)segs), 256, 0, ctx->stream>>>(part, G, L, per, tmp);
-    k_red2<<<grid_for(L, 256), 256, 0, ctx->stream>>>(tmp, segs, L, out);
+    k_red_out<<<grid_for(L, 64), 64 * RED_WAVES, 0, ctx->stream>>>(part, G, L, o);
     LAUNCH_CHECK(ctx);
     return SGP_OK;
 }
 
-// A^T D (K x N) followed by the column sums of D (N), summed over all m rows,
-// into M->sum; the caller copies windows of it into the gradient.
-int gemm_at(sgp_ctx ctx, sgp_mpnn M, const float *A, int64_t lda, int K, const float *D, int64_t ldd, int N,
-            int64_t m, float **sum)
+// [A | A2]^T D (16 (KT1 + KT2) x 16 NT) and the column sums of D over all m
+// rows, into the gradient
+template <int KT1, int KT2, int NT>
+int gemm_at(sgp_ctx ctx, sgp_mpnn M, const float *A, int64_t lda, const float *A2, int64_t lda2, const float *D,
+            int64_t ldd, int64_t m, GradOut o)
 {
-    const int G = m > 0 ? (int)((m + AT_ROWS - 1) / AT_ROWS) : 1;
-    const int L = K * N + N;
-    float *part, *out;
+    constexpr int K = 16 * (KT1 + KT2), N = 16 * NT, L = K * N + N;
+    const int G = (int)std::min<int64_t>(std::max<int64_t>((m + 63) / 64, 1), AT_GRID);
+    float *part;
     SGP_TRY(ensure_t(ctx, M->part, (size_t)G * L + 64, &part));
-    SGP_TRY(ensure_t(ctx, M->sum, (size_t)L + 64, &out));
-    hipStream_t st = ctx->stream;
-    switch (K) {
-    case 16: k_gemm_at<1><<<G, 256, 0, st>>>(A, lda, D, ldd, N, m, part); break;
-    case 64: k_gemm_at<4><<<G, 256, 0, st>>>(A, lda, D, ldd, N, m, part); break;
-    default: return set_err(ctx, SGP_EINVAL, "mpnn gemm_at: unsupported K");
-    }
+    k_gemm_at<KT1, KT2, NT><<<G, 256, 0, ctx->stream>>>(A, lda, A2, lda2, D, ldd, m, part);
     LAUNCH_CHECK(ctx);
-    SGP_TRY(reduce_parts(ctx, M, part, G, L, out));
-    *sum = out;
-    return SGP_OK;
-}
-
-int window(sgp_ctx ctx, const float *red, int off, int N, int r1, int c0, int c1, float *out, int64_t ld)
-{
-    k_window<<<grid_for((int64_t)r1 * (c1 - c0), 256), 256, 0, ctx->stream>>>(red, off, N, r1, c0, c1, out, ld);
-    LAUNCH_CHECK(ctx);
-    return SGP_OK;
+    o.K = K;
+    o.N = N;
+    return reduce_parts(ctx, part, G, L, o);
 }
 
 int prepare(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, const double *F, const double *vp, Act &A)
@@ -880,7 +903,8 @@ int prepare(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, const double *F, const double 
     return SGP_OK;
 }
 
-int forward(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, Act &A)
+// keep: pre0 and U of every layer are kept for a backward pass
+int forward(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, Act &A, bool keep)
 {
     hipStream_t st = ctx->stream;
     const int64_t n = g->n;
@@ -896,14 +920,11 @@ int forward(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, Act &A)
         SGP_TRY(gemm(ctx, A.h[l], 64, W + PK.ab[l], A.PQ, 128, n, 64, 128, nullptr, 0));
         k_msg_fwd<<<grid_for(n, 16), 256, 0, st>>>(n, rowptr, col, ef, A.PQ, wr + L.b_m[l], wr + L.W_c[l], A.a[l]);
         if (n > 0)
-            k_gemm_update<<<grid_for(n, GEMM_ROWS), 256, 0, st>>>(A.h[l], A.a[l], W + PK.u[l], wr + L.b_u[l], A.U[l],
-                                                                  A.h[l + 1], n);
+            k_gemm_update<<<grid_for(n, GEMM_ROWS), 256, 0, st>>>(A.h[l], A.a[l], W + PK.u[l], wr + L.b_u[l],
+                                                                  keep ? A.U[l] : nullptr, A.h[l + 1], n);
     }
-    SGP_TRY(gemm(ctx, A.h[NL], 64, W + PK.out16, A.out16, 16, n, 64, 16, nullptr, 0));
-    // b_out (3 entries) added by a tiny pass
-    k_add_bias3<<<grid_for(n, 256), 256, 0, st>>>(n, A.out16, wr + L.b_out);
-    LAUNCH_CHECK(ctx);
-    return SGP_OK;
+    // (b_out is added where the output is read: k_output, k_loss)
+    return gemm(ctx, A.h[NL], 64, W + PK.out16, A.out16, 16, n, 64, 16, nullptr, 0);
 }
 
 int backward(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, Act &A)
@@ -917,36 +938,31 @@ int backward(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, Act &A)
     float *G = (float *)M->grad.p;
     const int32_t *rowptr = (const int32_t *)M->irow.p, *col = (const int32_t *)M->icol.p;   // internal order
     const float4 *ef = (const float4 *)M->efeat.p;
-    float *S;
     // output layer: W_out rows 0..63 x columns 0..2 of h^T dout, b_out = column sums
-    SGP_TRY(gemm_at(ctx, M, A.h[NL], 64, 64, A.dout16, 16, 16, n, &S));
-    SGP_TRY(window(ctx, S, 0, 16, 64, 0, 3, G + L.W_out, 3));
-    SGP_TRY(window(ctx, S, 64 * 16, 16, 1, 0, 3, G + L.b_out, 3));
+    SGP_TRY((gemm_at<4, 0, 1>(ctx, M, A.h[NL], 64, nullptr, 0, A.dout16, 16, n,
+                              {G + L.W_out, nullptr, G + L.b_out, 0, 0, 64, 3, 3, 3})));
     SGP_TRY(gemm(ctx, A.dout16, 16, W + PK.out16T, A.dh, 64, n, 16, 64, nullptr, 0));
     for (int l = NL - 1; l >= 0; l--) {
         k_mask<<<grid_for(64 * n, 256), 256, 0, st>>>(64 * n, A.dh, A.U[l], A.dU);
-        SGP_TRY(gemm_at(ctx, M, A.h[l], 64, 64, A.dU, 64, 64, n, &S));
-        SGP_TRY(window(ctx, S, 0, 64, 64, 0, 64, G + L.W_u[l], 64));
-        SGP_TRY(window(ctx, S, 64 * 64, 64, 1, 0, 64, G + L.b_u[l], 64));
-        SGP_TRY(gemm_at(ctx, M, A.a[l], 64, 64, A.dU, 64, 64, n, &S));
-        SGP_TRY(window(ctx, S, 0, 64, 64, 0, 64, G + L.W_u[l] + 64 * 64, 64));
+        // W_u = [h | a]^T dU, b_u = column sums of dU
+        SGP_TRY((gemm_at<4, 4, 4>(ctx, M, A.h[l], 64, A.a[l], 64, A.dU, 64, n,
+                                  {G + L.W_u[l], nullptr, G + L.b_u[l], 0, 0, 128, 64, 64, 64})));
         SGP_TRY(gemm(ctx, A.dU, 64, W + PK.uT[l], A.dcat, 128, n, 64, 128, nullptr, 0));   // [dh part | da]
-        // messages: recompute PQ of this layer from h[l]
-        SGP_TRY(gemm(ctx, A.h[l], 64, W + PK.ab[l], A.PQ, 128, n, 64, 128, nullptr, 0));
-        const int nb = (int)std::min<int64_t>(grid_for(n, 4), MSG_BWD_GRID);
+        // messages: recompute PQ of this layer from h[l] (the last layer's is
+        // still there from the forward pass)
+        if (l < NL - 1) SGP_TRY(gemm(ctx, A.h[l], 64, W + PK.ab[l], A.PQ, 128, n, 64, 128, nullptr, 0));
+        const int nb = (int)std::min<int64_t>(grid_for(n, 16), MSG_BWD_GRID);
         float *wcp;
         SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP9], (size_t)nb * 256 + 64, &wcp));
         k_msg_bwd_p<<<nb, 256, 0, st>>>(n, rowptr, col, ef, A.PQ, wr + L.b_m[l], wr + L.W_c[l], A.dcat + 64, 128,
                                         A.dPQ, wcp);
-        k_msg_bwd_q<<<grid_for(n, 4), 256, 0, st>>>(n, rowptr, col, ef, A.PQ, wr + L.b_m[l], wr + L.W_c[l],
-                                                    A.dcat + 64, 128, A.dPQ);
+        k_msg_bwd_q<<<grid_for(n, 16), 256, 0, st>>>(n, rowptr, col, ef, A.PQ, wr + L.b_m[l], wr + L.W_c[l],
+                                                     A.dcat + 64, 128, A.dPQ);
         LAUNCH_CHECK(ctx);
-        SGP_TRY(reduce_parts(ctx, M, wcp, nb, 256, G + L.W_c[l]));   // W_c is 4 x 64 row-major
+        SGP_TRY(reduce_parts(ctx, wcp, nb, 256, {G + L.W_c[l], nullptr, nullptr, 4, 64, 4, 64, 64, 64}));   // 4 x 64
         // W_a, W_b = h^T dP, h^T dQ; b_m = column sums of dP
-        SGP_TRY(gemm_at(ctx, M, A.h[l], 64, 64, A.dPQ, 128, 128, n, &S));
-        SGP_TRY(window(ctx, S, 0, 128, 64, 0, 64, G + L.W_a[l], 64));
-        SGP_TRY(window(ctx, S, 0, 128, 64, 64, 128, G + L.W_b[l], 64));
-        SGP_TRY(window(ctx, S, 64 * 128, 128, 1, 0, 64, G + L.b_m[l], 64));
+        SGP_TRY((gemm_at<4, 0, 8>(ctx, M, A.h[l], 64, nullptr, 0, A.dPQ, 128, n,
+                                  {G + L.W_a[l], G + L.W_b[l], G + L.b_m[l], 0, 0, 64, 64, 128, 64})));
         // dh_l = dh (residual) + dcat[:, :64] + dPQ W_ab^T
         k_add64<<<grid_for(64 * n, 256), 256, 0, st>>>(n, A.dh, 64, A.dcat, 128, A.tmp, 64);
         LAUNCH_CHECK(ctx);
@@ -954,9 +970,8 @@ int backward(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, Act &A)
         std::swap(A.dh, A.tmp);
     }
     k_mask<<<grid_for(64 * n, 256), 256, 0, st>>>(64 * n, A.dh, A.pre0, A.dU);
-    SGP_TRY(gemm_at(ctx, M, A.x16, 16, 16, A.dU, 64, 64, n, &S));
-    SGP_TRY(window(ctx, S, 0, 64, 6, 0, 64, G + L.W_in, 64));
-    SGP_TRY(window(ctx, S, 16 * 64, 64, 1, 0, 64, G + L.b_in, 64));
+    SGP_TRY((gemm_at<1, 0, 4>(ctx, M, A.x16, 16, nullptr, 0, A.dU, 64, n,
+                              {G + L.W_in, nullptr, G + L.b_in, 0, 0, 6, 64, 64, 64})));
     return SGP_OK;
 }
 
@@ -995,7 +1010,7 @@ extern "C" void sgp_mpnn_free(sgp_mpnn M)
     if (!M) return;
     (void)hipDeviceSynchronize();
     release(M->theta); release(M->m1); release(M->m2); release(M->grad); release(M->wbf); release(M->wrow);
-    release(M->act); release(M->efeat); release(M->part); release(M->red); release(M->sum); release(M->vq);
+    release(M->act); release(M->efeat); release(M->part); release(M->vq);
     release(M->irow); release(M->icol);
     delete M;
 }
@@ -1042,8 +1057,9 @@ extern "C" int sgp_mpnn_forward(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, const doub
     if (!vhat) return set_err(ctx, SGP_EINVAL, "mpnn_forward: null output");
     Act A;
     SGP_TRY(prepare(ctx, M, g, F, vprev, A));
-    SGP_TRY(forward(ctx, M, g, A));
-    k_output<<<grid_for(g->n, 256), 256, 0, ctx->stream>>>(g->n, (const int32_t *)g->perm.p, A.out16, M->sV, vhat);
+    SGP_TRY(forward(ctx, M, g, A, false));
+    k_output<<<grid_for(g->n, 256), 256, 0, ctx->stream>>>(g->n, (const int32_t *)g->perm.p, A.out16,
+                                                            (const float *)M->wrow.p + M->L.b_out, M->sV, vhat);
     LAUNCH_CHECK(ctx);
     return SGP_OK;
 }
@@ -1070,13 +1086,14 @@ static int loss_grad(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, sgp_bsr Gm, const dou
     Act A;
     const int64_t n = g->n;
     SGP_TRY(prepare(ctx, M, g, F, vprev, A));
-    SGP_TRY(forward(ctx, M, g, A));
+    SGP_TRY(forward(ctx, M, g, A, true));
     double s[3];
     if (!Gm) {
         double *part;
         const int nb = (int)grid_for(n, 256);
         SGP_TRY(ensure_t(ctx, ctx->ws[WS_PART], (size_t)nb + 8, &part));
-        k_loss<<<nb, 256, 0, ctx->stream>>>(n, (const int32_t *)g->perm.p, A.out16, v, (float)M->sV, A.dout16, part);
+        k_loss<<<nb, 256, 0, ctx->stream>>>(n, (const int32_t *)g->perm.p, A.out16,
+                                            (const float *)M->wrow.p + M->L.b_out, v, (float)M->sV, A.dout16, part);
         k_sum_double<<<1, 256, 0, ctx->stream>>>(part, nb, part + nb);
         LAUNCH_CHECK(ctx);
         SGP_TRY(backward(ctx, M, g, A));
@@ -1089,7 +1106,8 @@ static int loss_grad(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, sgp_bsr Gm, const dou
     SGP_TRY(ensure_t(ctx, M->vq, (size_t)6 * n + 8, &vh));
     double *q = vh + 3 * n, *sd = vh + 6 * n;
     ds = sd;
-    k_output<<<grid_for(n, 256), 256, 0, ctx->stream>>>(n, (const int32_t *)g->perm.p, A.out16, M->sV, vh);
+    k_output<<<grid_for(n, 256), 256, 0, ctx->stream>>>(n, (const int32_t *)g->perm.p, A.out16,
+                                                      (const float *)M->wrow.p + M->L.b_out, M->sV, vh);
     LAUNCH_CHECK(ctx);
     SGP_TRY(energy_sums(ctx, M, Gm, vh, q, F, v, ds));
     k_energy_dout<<<grid_for(n, 256), 256, 0, ctx->stream>>>(n, (const int32_t *)g->perm.p, q, F, M->sV, ds,
@@ -1151,11 +1169,12 @@ extern "C" int sgp_mpnn_warm_start(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, sgp_bsr
     }
     Act A;
     SGP_TRY(prepare(ctx, M, g, F, vprev, A));
-    SGP_TRY(forward(ctx, M, g, A));
+    SGP_TRY(forward(ctx, M, g, A, false));
     double *vh;
     SGP_TRY(ensure_t(ctx, M->vq, (size_t)6 * n + 8, &vh));
     double *q = vh + 3 * n, *s = vh + 6 * n;   // s: 3 sums of the guess, 3 of v_prev (8 doubles reserved)
-    k_output<<<grid_for(n, 256), 256, 0, ctx->stream>>>(n, (const int32_t *)g->perm.p, A.out16, M->sV, vh);
+    k_output<<<grid_for(n, 256), 256, 0, ctx->stream>>>(n, (const int32_t *)g->perm.p, A.out16,
+                                                      (const float *)M->wrow.p + M->L.b_out, M->sV, vh);
     LAUNCH_CHECK(ctx);
     SGP_TRY(energy_sums(ctx, M, Gm, vh, q, F, nullptr, s));
     SGP_TRY(energy_sums(ctx, M, Gm, vprev, q, F, nullptr, s + 3));
