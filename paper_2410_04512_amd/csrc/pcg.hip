@@ -9,10 +9,13 @@
 //           z = M^{-1} r; rho' = r.z; p = z + (rho'/rho) p
 //
 // The launches of one iteration: the product (with the partials of p.q);
-// alpha; r -= alpha q (with the partials of ||r||^2); z = M^{-1} r; the
+// alpha and r -= alpha q (with the partials of ||r||^2); z = M^{-1} r; the
 // partials of r.z; one reduction for both ||r||^2 (the stopping rule) and
-// rho' (beta); then x += alpha p and p = z + beta p in one pass, which reads
-// p once for both.  The same values as the order above, bit for bit: x's
+// rho' (beta), then x += alpha p and p = z + beta p in one pass, which reads
+// p once for both.  With block Jacobi, z and the partials of r.z belong to
+// the pass that forms r.  Up to FOLD_MAX partials a cluster, alpha and beta
+// are formed by every block of the pass that uses them, beyond by a launch
+// of their own (k_fin).  The same values as the order above, bit for bit: x's
 // update only moves later.  The stopping rule is thus applied after the
 // sweeps of the last iteration instead of before them (one preconditioner
 // application more per solve, for one reduction less per iteration).  A
@@ -32,6 +35,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 // ---------------------------------------------------------------- block tables
 
@@ -161,6 +165,84 @@ SGP_DEV void sum_partials(const double *part, int64_t ns, int n, double *sh, dou
         }
 }
 
+// alpha = rho / p.q of a running cluster; false on a breakdown.  `lead` stores
+// what follows from it (with the snapshot that beta_from reads).  Every block
+// of a pass may call this with the same values while one of them stores: no
+// value read here is stored here.
+SGP_DEV bool alpha_from(PcgScalars *Sc, double pq, double rho, bool lead, double &alpha)
+{
+    if (lead) Sc->pq = pq;
+    if (!(pq > 0.0) || !isfinite(pq)) {
+        if (lead) {
+            Sc->status = SGP_EBREAKDOWN;
+            Sc->done = 1;
+        }
+        return false;
+    }
+    alpha = rho / pq;
+    if (lead) {
+        Sc->alpha = alpha;
+        Sc->rho_s = rho;
+        Sc->phi_s = Sc->phi;
+        Sc->gs_s = Sc->gs;
+        Sc->iter_s = Sc->iter;
+    }
+    return true;
+}
+
+// beta and the stopping rule from rr = ||r||^2 and rz = r.z; the mark (done)
+// that a running cluster has afterwards.  `lead` stores it all; no value read
+// here is stored here.
+SGP_DEV int32_t beta_from(PcgScalars *Sc, double rr, double rz, double alpha, bool lead, double &beta)
+{
+    const double rho = Sc->rho_s, relres2 = rr / Sc->nF2;
+    const int32_t iter = Sc->iter_s + 1;
+    beta = rz / rho;
+    double gs = 0.0, phi = 0.0, gbound = 0.0;
+    const bool err = Sc->stop == SGP_STOP_ERROR;
+    int32_t dn = 0, status = SGP_OK;
+    if (!isfinite(rr)) {
+        status = SGP_ENONFINITE;
+        dn = 1;
+    } else {
+        bool conv;
+        if (err) {
+            // the Gauss-Radau bound of the energy error after this step
+            gs = Sc->gs_s + alpha * rho;
+            phi = (Sc->phi_s - alpha) / (Sc->mu * (Sc->phi_s - alpha) + beta);
+            gbound = phi * rz;
+            conv = gbound <= Sc->tol2 * (gs + gbound);
+        } else {
+            conv = relres2 <= Sc->tol2;
+        }
+        if (Sc->fixed) {
+            dn = iter >= Sc->fixed ? 3 : 0;
+        } else if (conv) {
+            dn = 3;
+        } else if (iter >= Sc->max_iter) {
+            status = SGP_ENOCONV;
+            dn = 3;
+        }
+    }
+    if (lead) {
+        Sc->rr = rr;
+        Sc->iter = iter;
+        Sc->relres2 = relres2;
+        if (status != SGP_OK) Sc->status = status;
+        if (dn != 1) {
+            if (err) {
+                Sc->gs = gs;
+                Sc->phi = phi;
+                Sc->gbound = gbound;
+            }
+            Sc->beta = beta;
+            Sc->rho = rz;
+        }
+        if (dn) Sc->done = dn;
+    }
+    return dn;
+}
+
 // Second stage: cluster k = blockIdx.x sums its partials (np values per block,
 // stored as np arrays of stride nblk) and updates its scalars.
 __global__ __launch_bounds__(FIN_THREADS) void k_fin(int op, const double *part, int nblk, const int32_t *ifirst,
@@ -190,47 +272,14 @@ __global__ __launch_bounds__(FIN_THREADS) void k_fin(int op, const double *part,
     if (threadIdx.x != 0) return;
     const double t0 = t[0], t1 = t[1], t2 = t[2];
     switch (op) {
-    case FIN_ALPHA:
-        Sc->pq = t0;
-        if (!(t0 > 0.0) || !isfinite(t0)) {
-            Sc->status = SGP_EBREAKDOWN;
-            Sc->done = 1;
-        } else {
-            Sc->alpha = Sc->rho / t0;
-        }
+    case FIN_ALPHA: {
+        double alpha;
+        (void)alpha_from(Sc, t0, Sc->rho, true, alpha);
         break;
-    case FIN_RR_BETA: {   // t0 = ||r||^2, t1 = r.z
-        Sc->rr = t0;
-        Sc->iter = Sc->iter + 1;
-        Sc->relres2 = t0 / Sc->nF2;
-        if (!isfinite(t0)) {
-            Sc->status = SGP_ENONFINITE;
-            Sc->done = 1;
-            break;
-        }
-        bool conv;
-        if (Sc->stop == SGP_STOP_ERROR) {
-            // the Gauss-Radau bound of the energy error after this step
-            const double a = Sc->alpha, beta = t1 / Sc->rho;
-            Sc->gs = Sc->gs + a * Sc->rho;
-            Sc->phi = (Sc->phi - a) / (Sc->mu * (Sc->phi - a) + beta);
-            Sc->gbound = Sc->phi * t1;
-            conv = Sc->gbound <= Sc->tol2 * (Sc->gs + Sc->gbound);
-        } else {
-            conv = Sc->relres2 <= Sc->tol2;
-        }
-        bool stop = false;
-        if (Sc->fixed) {
-            stop = Sc->iter >= Sc->fixed;
-        } else if (conv) {
-            stop = true;
-        } else if (Sc->iter >= Sc->max_iter) {
-            Sc->status = SGP_ENOCONV;
-            stop = true;
-        }
-        Sc->beta = t1 / Sc->rho;
-        Sc->rho = t1;
-        if (stop) Sc->done = 3;
+    }
+    case FIN_RR_BETA: {
+        double beta;
+        (void)beta_from(Sc, t0, t1, Sc->alpha, true, beta);
         break;
     }
     case FIN_RHO:
@@ -263,6 +312,104 @@ __global__ __launch_bounds__(FIN_THREADS) void k_fin(int op, const double *part,
         Sc->nF2 = t1;   // ||F||^2
         break;
     }
+}
+
+// ---- the second stage inside the pass that needs its result
+//
+// With at most FOLD_MAX partials a cluster, every block of the pass after a
+// producer sums them all itself (4 loads a thread and array, in flight together
+// with the pass's own), in the order of k_fin, so with its bits; the cluster's
+// first block stores the scalars.  A launch of one workgroup per cluster and
+// the wait for it go, for at most 16 KB read from L2 by each block.  Whole
+// solves: 50k cells, tree 16.1 -> 14.4 ms; 32 clusters of 1k to 40k 23.5 -> 22.5 ms;
+// 200k cells, block Jacobi (with its passes joined) 13.0 -> 11.6 ms.  At 500k
+// cells, 1954 partials from as many blocks (8 loads a thread), 25.4 -> 26.8 ms:
+// the reading grows with the square of the size, so there k_fin stays.
+constexpr int FOLD_MAX = 1024;
+struct FinIn {
+    const double *part;           // NA arrays of stride `stride`
+    int64_t stride;
+    const int32_t *first, *nb;    // per cluster: first partial, number of partials
+    int32_t n1;                   // > 0: one cluster, its partials are 0..n1-1
+};
+
+// block-uniform results in every thread.  Partial 256 h + t is held by thread
+// t, which folds the waves of k_fin's threads 256 h + t.
+// dn (the flag, which the storing block may change under this launch's feet) is
+// made uniform too: nonzero if any wave saw it nonzero.
+template <int NA>
+SGP_DEV void fold_partials(const FinIn &in, int inst, int32_t &dn, double (&res)[NA])
+{
+    __shared__ double shw[NA][16];
+    __shared__ int32_t shd[4];
+    const int32_t f = in.n1 > 0 ? 0 : in.first[inst], n = in.n1 > 0 ? in.n1 : in.nb[inst];
+    double v[NA][4];
+#pragma unroll
+    for (int a = 0; a < NA; a++)
+#pragma unroll
+        for (int h = 0; h < 4; h++) {
+            const int k = 256 * h + (int)threadIdx.x;
+            v[a][h] = k < n ? in.part[a * in.stride + f + k] : 0.0;
+        }
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+    for (int a = 0; a < NA; a++)
+#pragma unroll
+        for (int h = 0; h < 4; h++) {
+            double t = v[a][h];
+            if (256 * h < n)
+                for (int o = 32; o > 0; o >>= 1) t = t + __shfl_xor(t, o, 64);
+            if (lane == 0) shw[a][4 * h + w] = t;
+        }
+    if (lane == 0) shd[w] = dn;
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < NA; a++) {
+        double r = 0.0;
+        for (int k = 0; k < 16; k++) r = r + shw[a][k];
+        res[a] = r;
+    }
+    for (int k = 0; k < 4; k++) dn = shd[k] ? shd[k] : dn;
+}
+
+// the head of the pass that subtracts alpha q: alpha of the block's cluster,
+// false if the cluster has stopped.  b: the block's index in the row table.
+template <bool FOLD>
+SGP_DEV bool pass_alpha(const FinIn &in, const BlockTab &tab, int b, int inst, PcgScalars *Sc, double &alpha)
+{
+    int32_t dn = Sc->done;
+    if (!FOLD) {
+        alpha = Sc->alpha;
+        return dn == 0;
+    }
+    const double rho = Sc->rho;
+    double t[1];
+    fold_partials<1>(in, inst, dn, t);
+    const bool lead = threadIdx.x == 0 && b == (in.n1 > 0 ? 0 : tab.ifirst[inst]);
+    if (dn) {
+        if (dn == 3 && lead) Sc->done = 1;   // a finishing solve (its last x update has run): finished
+        return false;
+    }
+    return alpha_from(Sc, t[0], rho, lead, alpha);
+}
+
+// the head of the pass that forms p: alpha, beta and the cluster's mark after
+// the stopping rule (nonzero before: that mark)
+template <bool FOLD>
+SGP_DEV int32_t pass_beta(const FinIn &in, const BlockTab &tab, int b, int inst, PcgScalars *Sc, double &alpha,
+                          double &beta)
+{
+    int32_t dn = Sc->done;
+    alpha = Sc->alpha;
+    if (!FOLD) {
+        beta = Sc->beta;
+        return dn;
+    }
+    double t[2];
+    fold_partials<2>(in, inst, dn, t);
+    if (dn) return dn;
+    const bool lead = threadIdx.x == 0 && b == (in.n1 > 0 ? 0 : tab.ifirst[inst]);
+    return beta_from(Sc, t[0], t[1], alpha, lead, beta);
 }
 
 // ---------------------------------------------------------------- vector kernels
@@ -338,25 +485,30 @@ SGP_DEV int block_elems(const BlockTab &tab, int b, int64_t &e0, int &inst)
     return 3 * (tab.row1[b] - tab.row0[b]);
 }
 
-// r -= alpha q; partial of ||r||^2
-template <class T>
-__global__ __launch_bounds__(256) void k_update_r(T *r, const T *q, BlockTab tab, const PcgScalars *S, double *part)
+// r -= alpha q; partial of ||r||^2, and without a preconditioner (z is r) the
+// same partial as r.z
+template <class T, bool FOLD>
+__global__ __launch_bounds__(256) void k_update_r(T *r, const T *q, BlockTab tab, PcgScalars *S, double *part,
+                                                  double *part_rz, FinIn in)
 {
     __shared__ double sh[256];
     int inst;
     int64_t e0;
     const int ne = block_elems(tab, blockIdx.x, e0, inst);
-    const PcgScalars *Sc = S + inst;
-    if (Sc->done) return;
-    const T alpha = (T)Sc->alpha;
-    double rr = 0.0;
+    if (!FOLD && S[inst].done) return;
+    T rv[VEC_EPT], qv[VEC_EPT];
     if (ne > 0) {
-        T rv[VEC_EPT], qv[VEC_EPT];
 #pragma unroll
         for (int u = 0; u < VEC_EPT; u++) {
             rv[u] = r[e0 + vec_idx(u, ne)];
             qv[u] = q[e0 + vec_idx(u, ne)];
         }
+    }
+    double al;
+    if (!pass_alpha<FOLD>(in, tab, blockIdx.x, inst, S + inst, al)) return;
+    const T alpha = (T)al;
+    double rr = 0.0;
+    if (ne > 0) {
 #pragma unroll
         for (int u = 0; u < VEC_EPT; u++)
             if (vec_own(u, ne)) {
@@ -365,7 +517,75 @@ __global__ __launch_bounds__(256) void k_update_r(T *r, const T *q, BlockTab tab
                 rr = rr + (double)ri * (double)ri;
             }
     }
+    const double s = block_sum_256(rr, sh);
+    if (threadIdx.x == 0) {
+        part[blockIdx.x] = s;
+        if (part_rz) part_rz[blockIdx.x] = s;
+    }
+}
+
+// r -= alpha q, z = the diagonal blocks' inverses times r, and the partials of
+// ||r||^2 and r.z, in one pass.  Memory bound: r, q and the 6 values of a
+// cell's inverse read, r and z written, 15 T a cell; as three launches r was
+// read three times and z twice, 24 T.
+template <class T, bool FOLD>
+__global__ __launch_bounds__(256) void k_update_r_jac(T *r, const T *q, T *z, const T *dinv, BlockTab tab,
+                                                      PcgScalars *S, double *part, double *part_rz, FinIn in)
+{
+    __shared__ double sh[256];
+    __shared__ T l[3 * VEC_ROWS];
+    int inst;
+    int64_t e0;
+    const int ne = block_elems(tab, blockIdx.x, e0, inst);
+    if (!FOLD && S[inst].done) return;
+    T rv[VEC_EPT], qv[VEC_EPT], d[6];
+    const bool mine = 3 * (int)threadIdx.x < ne;   // the thread's row
+    if (ne > 0) {
+#pragma unroll
+        for (int u = 0; u < VEC_EPT; u++) {
+            rv[u] = r[e0 + vec_idx(u, ne)];
+            qv[u] = q[e0 + vec_idx(u, ne)];
+        }
+        const T *di = dinv + 2 * e0 + 6 * (mine ? (int)threadIdx.x : 0);
+#pragma unroll
+        for (int k = 0; k < 6; k++) d[k] = di[k];
+    }
+    double al;
+    if (!pass_alpha<FOLD>(in, tab, blockIdx.x, inst, S + inst, al)) return;
+    const T alpha = (T)al;
+    double rr = 0.0, rz = 0.0;
+    if (ne > 0) {
+#pragma unroll
+        for (int u = 0; u < VEC_EPT; u++)
+            if (vec_own(u, ne)) {
+                const T ri = rv[u] - alpha * qv[u];
+                r[e0 + vec_idx(u, ne)] = ri;
+                l[threadIdx.x + 256 * u] = ri;
+                rv[u] = ri;
+                rr = rr + (double)ri * (double)ri;
+            }
+    }
+    __syncthreads();
+    if (mine) {   // a row's three values are read and replaced by its thread alone
+        T *li = l + 3 * threadIdx.x;
+        T o0, o1, o2;
+        sym_mv(d, li[0], li[1], li[2], o0, o1, o2);
+        li[0] = o0;
+        li[1] = o1;
+        li[2] = o2;
+    }
+    __syncthreads();
+    if (ne > 0) {
+#pragma unroll
+        for (int u = 0; u < VEC_EPT; u++)
+            if (vec_own(u, ne)) {
+                const T zi = l[threadIdx.x + 256 * u];
+                z[e0 + vec_idx(u, ne)] = zi;
+                rz = rz + (double)rv[u] * (double)zi;
+            }
+    }
     block_partial(rr, blockIdx.x, part, sh);
+    block_partial(rz, blockIdx.x, part_rz, sh);
 }
 
 // partial of p.q (batched solves: the product itself has no cluster split)
@@ -457,9 +677,9 @@ __global__ void k_step0_ranges(int32_t nb, BlockTab tab, const int32_t *elim, in
 // r -= alpha q with the partial of ||r||^2, then the forward substitution of
 // the block's first-step vertices: y = P_qq^{-1} r and its pushes (y itself
 // is formed again by k_rz_s0)
-template <class T>
-__global__ __launch_bounds__(256) void k_update_r_s0(T *r, const T *q, BlockTab tab, const PcgScalars *S,
-                                                     double *part, Step0Tab<T> t)
+template <class T, bool FOLD>
+__global__ __launch_bounds__(256) void k_update_r_s0(T *r, const T *q, BlockTab tab, PcgScalars *S, double *part,
+                                                     Step0Tab<T> t, FinIn in)
 {
     __shared__ double sh[256];
     __shared__ T rl[3 * VEC_ROWS];
@@ -468,8 +688,7 @@ __global__ __launch_bounds__(256) void k_update_r_s0(T *r, const T *q, BlockTab 
     // XCD-contiguous rows: the pushes of an XCD's blocks land in one region
     const int b = (int)xcd_block(blockIdx.x, gridDim.x);
     const int ne = block_elems(tab, b, e0, inst);
-    const PcgScalars *Sc = S + inst;
-    if (Sc->done) return;
+    if (!FOLD && S[inst].done) return;
     const int32_t qa = t.qr[2 * b], qb = t.qr[2 * b + 1];
     T rv[VEC_EPT], qx[VEC_EPT];
     if (ne > 0) {
@@ -493,7 +712,9 @@ __global__ __launch_bounds__(256) void k_update_r_s0(T *r, const T *q, BlockTab 
         for (int k = 0; k < 4; k++) w1[k] = t.wu[t.ws + 4 * (int64_t)qc + k];
         for (int k = 0; k < 6; k++) d[k] = t.Dinv[6 * (int64_t)qc + k];
     }
-    const T alpha = (T)Sc->alpha;
+    double al;
+    if (!pass_alpha<FOLD>(in, tab, b, inst, S + inst, al)) return;
+    const T alpha = (T)al;
     double rr = 0.0;
     if (ne > 0) {
 #pragma unroll
@@ -626,32 +847,33 @@ __global__ __launch_bounds__(256) void k_rz_s0(const T *r, T *z, BlockTab tab, c
 }
 
 // x += alpha p, then p = z + beta p (p only while the solve goes on)
-template <class T>
-__global__ __launch_bounds__(256) void k_update_xp(T *x, T *p, const T *z, BlockTab tab, const PcgScalars *S)
+template <class T, bool FOLD>
+__global__ __launch_bounds__(256) void k_update_xp(T *x, T *p, const T *z, BlockTab tab, PcgScalars *S, FinIn in)
 {
     int inst;
     int64_t e0;
     const int ne = block_elems(tab, blockIdx.x, e0, inst);
-    const PcgScalars *Sc = S + inst;
-    const int32_t dn = Sc->done;
-    if ((dn != 0 && dn != 3) || ne == 0) return;
-    const T alpha = (T)Sc->alpha;
-    T xv[VEC_EPT], pv[VEC_EPT];
+    if (!FOLD && S[inst].done != 0 && S[inst].done != 3) return;
+    T xv[VEC_EPT], pv[VEC_EPT], zv[VEC_EPT];
+    if (ne > 0) {
 #pragma unroll
-    for (int u = 0; u < VEC_EPT; u++) {
-        xv[u] = x[e0 + vec_idx(u, ne)];
-        pv[u] = p[e0 + vec_idx(u, ne)];
+        for (int u = 0; u < VEC_EPT; u++) {
+            xv[u] = x[e0 + vec_idx(u, ne)];
+            pv[u] = p[e0 + vec_idx(u, ne)];
+            zv[u] = z[e0 + vec_idx(u, ne)];
+        }
     }
+    double al, be;
+    const int32_t dn = pass_beta<FOLD>(in, tab, blockIdx.x, inst, S + inst, al, be);
+    if ((dn != 0 && dn != 3) || ne == 0) return;
+    const T alpha = (T)al;
     if (dn == 3) {   // finishing: the last x update only
 #pragma unroll
         for (int u = 0; u < VEC_EPT; u++)
             if (vec_own(u, ne)) x[e0 + vec_idx(u, ne)] = xv[u] + alpha * pv[u];
         return;
     }
-    const T beta = (T)Sc->beta;
-    T zv[VEC_EPT];
-#pragma unroll
-    for (int u = 0; u < VEC_EPT; u++) zv[u] = z[e0 + vec_idx(u, ne)];
+    const T beta = (T)be;
 #pragma unroll
     for (int u = 0; u < VEC_EPT; u++)
         if (vec_own(u, ne)) {
@@ -662,23 +884,25 @@ __global__ __launch_bounds__(256) void k_update_xp(T *x, T *p, const T *z, Block
 
 // p = z + beta p, where x += alpha p ran during the tree sweeps (SideX): a
 // finishing solve has nothing left to do
-template <class T>
-__global__ __launch_bounds__(256) void k_update_p(T *p, const T *z, BlockTab tab, const PcgScalars *S)
+template <class T, bool FOLD>
+__global__ __launch_bounds__(256) void k_update_p(T *p, const T *z, BlockTab tab, PcgScalars *S, FinIn in)
 {
     int inst;
     int64_t e0;
     const int ne = block_elems(tab, blockIdx.x, e0, inst);
-    const PcgScalars *Sc = S + inst;
     T pv[VEC_EPT], zv[VEC_EPT];
+    if (ne > 0) {
 #pragma unroll
-    for (int u = 0; u < VEC_EPT; u++) {
-        pv[u] = p[e0 + vec_idx(u, ne)];
-        // z's last read in an iteration: non-temporal, so that it does not
-        // displace p, which the product gathers next
-        zv[u] = __builtin_nontemporal_load(z + e0 + vec_idx(u, ne));
+        for (int u = 0; u < VEC_EPT; u++) {
+            pv[u] = p[e0 + vec_idx(u, ne)];
+            // z's last read in an iteration: non-temporal, so that it does not
+            // displace p, which the product gathers next
+            zv[u] = __builtin_nontemporal_load(z + e0 + vec_idx(u, ne));
+        }
     }
-    if (Sc->done || ne == 0) return;
-    const T beta = (T)Sc->beta;
+    double al, be;
+    if (pass_beta<FOLD>(in, tab, blockIdx.x, inst, S + inst, al, be) || ne == 0) return;
+    const T beta = (T)be;
 #pragma unroll
     for (int u = 0; u < VEC_EPT; u++)
         if (vec_own(u, ne)) p[e0 + vec_idx(u, ne)] = zv[u] + beta * pv[u];
@@ -765,6 +989,7 @@ struct PcgWork {
     // tile form, whose tiles are cut from the same clusters): per cluster its
     // first tile and number of tiles
     const int32_t *tile_first = nullptr, *tile_nb = nullptr;
+    int32_t mv_most = 0, vec_most = 0;   // the most partials of p.q and of r.r a cluster has
     int64_t K = 1;
     int32_t s0_q1 = 0;               // > 0: the first elimination step runs in the vector passes
     const int32_t *s0_qr = nullptr;  // its positions per vector block
@@ -821,6 +1046,15 @@ static int fin(sgp_ctx ctx, int op, const double *part, int nblk, const int32_t 
     return SGP_OK;
 }
 
+template <class F>
+static void with_fold(bool fold, F f)
+{
+    if (fold)
+        f(std::true_type{});
+    else
+        f(std::false_type{});
+}
+
 // CG iterations per timed product (at most one per chunk)
 constexpr int KT_STRIDE = 4;
 
@@ -843,46 +1077,58 @@ static int pcg_chunk(sgp_ctx ctx, sgp_bsr A, sgp_prec M, Vecs<T> v, PcgWork &w, 
         // a new stride
         const bool timed = c == std::min(2, count - 1) && it0 % KT_STRIDE < count;
         if (timed) SGP_TRY(ktimer_begin(ctx, it0 + c));
-        if (K == 1) {
-            SGP_TRY(spmv_t<T>(ctx, A, v.p, v.q, S, part, 1));
+        const bool tiles = K > 1 && w.tile_first;
+        if (K == 1 || tiles) {
+            SGP_TRY(spmv_t<T>(ctx, A, v.p, v.q, S, part, 1, tiles));
             if (timed) SGP_TRY(ktimer_end(ctx));
-            SGP_TRY(fin(ctx, FIN_ALPHA, part, w.mv_nb, w.mv_first, w.mv_nb_dev, S, 1));
-        } else if (w.tile_first) {
-            SGP_TRY(spmv_t<T>(ctx, A, v.p, v.q, S, part, 1, true));
-            if (timed) SGP_TRY(ktimer_end(ctx));
-            SGP_TRY(fin(ctx, FIN_ALPHA, part, w.mv_nb, w.tile_first, w.tile_nb, S, K));
         } else {
             SGP_TRY(spmv_t<T>(ctx, A, v.p, v.q, nullptr, nullptr, 0));
             if (timed) SGP_TRY(ktimer_end(ctx));
             k_pq<T><<<w.vec_nb, 256, 0, st>>>(v.p, v.q, w.vec, S, part);
-            SGP_TRY(fin(ctx, FIN_ALPHA, part, w.vec_nb, w.vec.ifirst, w.vec.inb, S, K));
         }
-        // partials: ||r||^2 in the first nb entries, r.z in the next nb
-        const bool s0 = M && w.s0_q1 > 0;
-        if (s0)
-            k_update_r_s0<T><<<w.vec_nb, 256, 0, st>>>(v.r, v.q, w.vec, S, part, step0_tab<T>(M, w));
-        else
-            k_update_r<T><<<w.vec_nb, 256, 0, st>>>(v.r, v.q, w.vec, S, part);
+        const FinIn pq = K == 1  ? FinIn{part, 0, w.mv_first, w.mv_nb_dev, w.mv_nb}
+                         : tiles ? FinIn{part, 0, w.tile_first, w.tile_nb, 0}
+                                 : FinIn{part, 0, w.vec.ifirst, w.vec.inb, 0};
+        const bool fa = w.mv_most <= FOLD_MAX, fb = w.vec_most <= FOLD_MAX;
+        if (!fa) SGP_TRY(fin(ctx, FIN_ALPHA, part, w.mv_nb, pq.first, pq.nb, S, K));
+        // the partials of ||r||^2 and r.z, beyond those of p.q (which the
+        // pass that writes them may still be reading)
+        double *prr = part + std::max(w.vec_nb, w.mv_nb), *prz = prr + w.vec_nb;
+        const FinIn rb = {prr, w.vec_nb, w.vec.ifirst, w.vec.inb, K == 1 ? w.vec_nb : 0};
+        const bool s0 = M && w.s0_q1 > 0, jac = M && M->kind == PREC_JACOBI;
+        with_fold(fa, [&](auto d) {
+            constexpr bool D = decltype(d)::value;
+            if (s0)
+                k_update_r_s0<T, D><<<w.vec_nb, 256, 0, st>>>(v.r, v.q, w.vec, S, prr, step0_tab<T>(M, w), pq);
+            else if (jac)
+                k_update_r_jac<T, D><<<w.vec_nb, 256, 0, st>>>(
+                    v.r, v.q, v.z, (const T *)(sizeof(T) == 8 ? M->jdinv.p : M->Dinv32.p), w.vec, S, prr, prz, pq);
+            else
+                k_update_r<T, D><<<w.vec_nb, 256, 0, st>>>(v.r, v.q, w.vec, S, prr, M ? nullptr : prz, pq);
+        });
         // x += alpha p by extra workgroups of the sweeps' one-workgroup tail
         // launch, when there is one (knob tail_side)
         SideX side = {v.x, v.p, w.vec.row0, w.vec.row1, w.vec.inst, S, w.vec_nb,
                       std::min(SIDE_NWG, (w.vec_nb + 3) / 4), false};
         SideX *sx = ctx->tail_side ? &side : nullptr;
-        if (M) {
+        if (M && !jac) {
             if (sizeof(T) == 8)
                 SGP_TRY(prec_apply_f64(ctx, M, (const double *)v.r, (double *)v.z, gate, s0, sx));
             else
                 SGP_TRY(prec_apply_f32(ctx, M, (const float *)v.r, (float *)v.z, gate, s0, sx));
         }
         if (s0)
-            k_rz_s0<T><<<w.vec_nb, 256, 0, st>>>(v.r, v.z, w.vec, S, part + w.vec_nb, step0_tab<T>(M, w));
-        else
-            k_rz<T><<<w.vec_nb, 256, 0, st>>>(v.r, v.z, w.vec, S, part + w.vec_nb);
-        SGP_TRY(fin(ctx, FIN_RR_BETA, part, w.vec_nb, w.vec.ifirst, w.vec.inb, S, K));
-        if (side.ran)
-            k_update_p<T><<<w.vec_nb, 256, 0, st>>>(v.p, v.z, w.vec, S);
-        else
-            k_update_xp<T><<<w.vec_nb, 256, 0, st>>>(v.x, v.p, v.z, w.vec, S);
+            k_rz_s0<T><<<w.vec_nb, 256, 0, st>>>(v.r, v.z, w.vec, S, prz, step0_tab<T>(M, w));
+        else if (M && !jac)
+            k_rz<T><<<w.vec_nb, 256, 0, st>>>(v.r, v.z, w.vec, S, prz);
+        if (!fb) SGP_TRY(fin(ctx, FIN_RR_BETA, prr, w.vec_nb, w.vec.ifirst, w.vec.inb, S, K));
+        with_fold(fb, [&](auto d) {
+            constexpr bool D = decltype(d)::value;
+            if (side.ran)
+                k_update_p<T, D><<<w.vec_nb, 256, 0, st>>>(v.p, v.z, w.vec, S, rb);
+            else
+                k_update_xp<T, D><<<w.vec_nb, 256, 0, st>>>(v.x, v.p, v.z, w.vec, S, rb);
+        });
         LAUNCH_CHECK(ctx);
     }
     return SGP_OK;
@@ -1039,6 +1285,9 @@ static int prepare_work(sgp_ctx ctx, sgp_bsr A, const std::vector<int64_t> &off,
         w.tile_first = (const int32_t *)A->tile_tab.p + 3 * (size_t)A->n_tiles;
         w.tile_nb = w.tile_first + K;
     }
+    for (int64_t k = 0; k < K; k++)
+        w.vec_most = std::max(w.vec_most, w.vec_buf[3 * (size_t)w.vec_nb + K + k]);
+    w.mv_most = K == 1 ? w.mv_nb : w.tile_first ? w.vec_most * (VEC_ROWS / A->tile_rows) : w.vec_most;
     const int32_t q1 = ctx->fuse_step0 ? prec_step0_launch(M) : 0;
     if (q1 > 0 && M->n == A->n) {
         int32_t *qr = d + nv + 2;

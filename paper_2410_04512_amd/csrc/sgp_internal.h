@@ -25,6 +25,10 @@ struct PcgScalars {
     int32_t iter, done, status, fixed, max_iter, stop;
     // SGP_STOP_ERROR: the Gauss-Radau node mu, phi_k, S_k and phi_k rho_k
     double mu, phi, gs, gbound;
+    // rho, phi, gs and iter as the alpha of this iteration found them: a pass
+    // that forms rr and r.z itself reads these and writes the ones above
+    double rho_s, phi_s, gs_s;
+    int32_t iter_s;
 };
 
 // The solve's stop flag, or 0 without a solve.  The address is selected
