@@ -317,15 +317,16 @@ __global__ __launch_bounds__(FIN_THREADS) void k_fin(int op, const double *part,
 // ---- the second stage inside the pass that needs its result
 //
 // With at most FOLD_MAX partials a cluster, every block of the pass after a
-// producer sums them all itself (4 loads a thread and array, in flight together
-// with the pass's own), in the order of k_fin, so with its bits; the cluster's
-// first block stores the scalars.  A launch of one workgroup per cluster and
-// the wait for it go, for at most 16 KB read from L2 by each block.  Whole
-// solves: 50k cells, tree 16.1 -> 14.4 ms; 32 clusters of 1k to 40k 23.5 -> 22.5 ms;
-// 200k cells, block Jacobi (with its passes joined) 13.0 -> 11.6 ms.  At 500k
-// cells, 1954 partials from as many blocks (8 loads a thread), 25.4 -> 26.8 ms:
-// the reading grows with the square of the size, so there k_fin stays.
-constexpr int FOLD_MAX = 1024;
+// producer sums them all itself (at most 8 loads a thread and array, in flight
+// together with the pass's own), in the order of k_fin, so with its bits; the
+// cluster's first block stores the scalars.  A launch of one workgroup per
+// cluster and the wait for it go, for at most 32 KB read from L2 by each block.
+// Whole solves: 50k cells, tree 16.1 -> 13.6 ms; 32 clusters of 1k to 40k 23.5
+// -> 22.1 ms; 200k cells, block Jacobi (with its passes joined) 13.0 -> 9.4 ms;
+// 500k cells, FP32 in refinement, 1954 partials from as many blocks, 25.1 ->
+// 24.5 ms.  The reading grows with the square of the size (244 MB an iteration
+// at 1e6 cells, for two launches of 4.8 us), so there k_fin stays.
+constexpr int FOLD_MAX = 2048;
 struct FinIn {
     const double *part;           // NA arrays of stride `stride`
     int64_t stride;
@@ -333,8 +334,11 @@ struct FinIn {
     int32_t n1;                   // > 0: one cluster, its partials are 0..n1-1
 };
 
-// block-uniform results in every thread.  Partial 256 h + t is held by thread
-// t, which folds the waves of k_fin's threads 256 h + t.
+// block-uniform results in every thread.  The 64 partials that a wave of k_fin
+// folds, 64 w + l, belong to the row of 16 threads w: its distances 32 and 16
+// are a thread's own additions, the rest stay in the row of lanes (as LDS
+// shuffles over whole waves: 200k cells, block Jacobi 11.5 instead of 9.4 ms).
+// Partials from 1024 on are the second running sum of k_fin's threads.
 // dn (the flag, which the storing block may change under this launch's feet) is
 // made uniform too: nonzero if any wave saw it nonzero.
 template <int NA>
@@ -343,25 +347,35 @@ SGP_DEV void fold_partials(const FinIn &in, int inst, int32_t &dn, double (&res)
     __shared__ double shw[NA][16];
     __shared__ int32_t shd[4];
     const int32_t f = in.n1 > 0 ? 0 : in.first[inst], n = in.n1 > 0 ? in.n1 : in.nb[inst];
+    const int w = threadIdx.x >> 4, l = threadIdx.x & 15;
     double v[NA][4];
 #pragma unroll
     for (int a = 0; a < NA; a++)
 #pragma unroll
-        for (int h = 0; h < 4; h++) {
-            const int k = 256 * h + (int)threadIdx.x;
-            v[a][h] = k < n ? in.part[a * in.stride + f + k] : 0.0;
+        for (int m = 0; m < 4; m++) {
+            const int k = 64 * w + 16 * m + l;
+            v[a][m] = k < n ? in.part[a * in.stride + f + k] : 0.0;
         }
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (n > 1024) {
+        double v2[NA][4];
 #pragma unroll
-    for (int a = 0; a < NA; a++)
+        for (int a = 0; a < NA; a++)
 #pragma unroll
-        for (int h = 0; h < 4; h++) {
-            double t = v[a][h];
-            if (256 * h < n)
-                for (int o = 32; o > 0; o >>= 1) t = t + __shfl_xor(t, o, 64);
-            if (lane == 0) shw[a][4 * h + w] = t;
-        }
-    if (lane == 0) shd[w] = dn;
+            for (int m = 0; m < 4; m++) {
+                const int k = 1024 + 64 * w + 16 * m + l;
+                v2[a][m] = k < n ? in.part[a * in.stride + f + k] : 0.0;
+            }
+#pragma unroll
+        for (int a = 0; a < NA; a++)
+#pragma unroll
+            for (int m = 0; m < 4; m++) v[a][m] = v[a][m] + v2[a][m];
+    }
+#pragma unroll
+    for (int a = 0; a < NA; a++) {
+        const double t = row_sum_16((v[a][0] + v[a][2]) + (v[a][1] + v[a][3]));
+        if (l == 0) shw[a][w] = t;
+    }
+    if ((threadIdx.x & 63) == 0) shd[threadIdx.x >> 6] = dn;
     __syncthreads();
 #pragma unroll
     for (int a = 0; a < NA; a++) {

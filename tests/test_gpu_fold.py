@@ -1,4 +1,4 @@
-"""The CG scalars formed by every block of the pass that uses them (up to 1024
+"""The CG scalars formed by every block of the pass that uses them (up to 2048
 partials a cluster) or by a launch of their own, and block Jacobi applied in
 the pass that forms r: a few iterations against NumPy's CG on the library's own
 product and apply.  Tolerance: a dot product of 3n terms carries at most
@@ -34,7 +34,7 @@ def _cg(product, apply, F):
 
 
 @pytest.mark.parametrize("prec", ["none", "jacobi", "tree"])
-@pytest.mark.parametrize("n", [8193, 65537, 262144, 262145])   # 33, 257, 1024 and 1025 blocks of rows
+@pytest.mark.parametrize("n", [8193, 65537, 262144, 262145, 524289])   # 33, 257, 1024, 1025 and 2049 blocks of rows
 def test_first_iterations(n, prec):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
