@@ -1396,6 +1396,9 @@ __global__ __launch_bounds__(TOP_INV_THREADS) void k_top_inverse(int32_t s0, int
 // vertex, since the last vertices have many slots and a lane's chunks of them
 // would be dependent rounds of loads.  x goes to y (for the steps below) and
 // to z.
+// (SLOTS per lane in flight at once, 2 to 6 as the registers allow: the last
+// vertices have up to 23 slots at 1e6 cells, and two per lane left up to four
+// dependent rounds)
 constexpr int TOP_LANES = 4;
 template <class T, int NC, int ROWS>
 __global__ __launch_bounds__(256) void k_top(int32_t Qt, int32_t nt, const int32_t *elim, const int32_t *in_ptr,
@@ -1404,6 +1407,7 @@ __global__ __launch_bounds__(256) void k_top(int32_t Qt, int32_t nt, const int32
 {
     constexpr int PER = 256 / TOP_LANES;                      // vertices per round
     constexpr int RND = (64 * NC / 3 + PER - 1) / PER;        // rounds
+    constexpr int SLOTS = RND <= 4 ? 6 : RND <= 6 ? 4 : 2;
     __shared__ T b[3 * PER * RND > 64 * NC ? 3 * PER * RND : 64 * NC];
     const int tid = threadIdx.x, lane = tid & 63, sub = tid & (TOP_LANES - 1);
     const int32_t N = 3 * nt, row0 = ((int32_t)blockIdx.x * 4 + (tid >> 6)) * ROWS;
@@ -1425,11 +1429,11 @@ __global__ __launch_bounds__(256) void k_top(int32_t Qt, int32_t nt, const int32
     for (int u = 0; u < ROWS; u++)
 #pragma unroll
         for (int c = 0; c < NC; c++) a[u][c] = inv[(int64_t)min(row0 + u, N - 1) * (64 * NC) + 64 * c + lane];
-    T g[RND][3], h[RND][2][3];
+    T g[RND], h[RND][SLOTS][3];
 #pragma unroll
     for (int k = 0; k < RND; k++) {
-        for (int m = 0; m < 3; m++) g[k][m] = r[3 * v[k] + m];
-        for (int w = 0; w < 2; w++) {
+        g[k] = r[3 * v[k] + min(sub, 2)];
+        for (int w = 0; w < SLOTS; w++) {
             const T *c = cs + 3 * (int64_t)max(min(t0[k] + sub + TOP_LANES * w, t1[k] - 1), t0[k]);
             for (int m = 0; m < 3; m++) h[k][w][m] = c[m];
         }
@@ -1438,13 +1442,13 @@ __global__ __launch_bounds__(256) void k_top(int32_t Qt, int32_t nt, const int32
 #pragma unroll
     for (int k = 0; k < RND; k++) {
         T c0 = 0, c1 = 0, c2 = 0;
-        for (int w = 0; w < 2; w++)
+        for (int w = 0; w < SLOTS; w++)
             if (t0[k] + sub + TOP_LANES * w < t1[k]) {
                 c0 = c0 + h[k][w][0];
                 c1 = c1 + h[k][w][1];
                 c2 = c2 + h[k][w][2];
             }
-        for (int32_t t = t0[k] + sub + 2 * TOP_LANES; t < t1[k]; t += TOP_LANES) {
+        for (int32_t t = t0[k] + sub + SLOTS * TOP_LANES; t < t1[k]; t += TOP_LANES) {
             const T *c = cs + 3 * (int64_t)t;
             c0 = c0 + c[0];
             c1 = c1 + c[1];
@@ -1457,7 +1461,7 @@ __global__ __launch_bounds__(256) void k_top(int32_t Qt, int32_t nt, const int32
         }
         const int32_t i = tid / TOP_LANES + PER * k;
         if (sub < 3) {
-            const T w = sub == 0 ? g[k][0] - c0 : sub == 1 ? g[k][1] - c1 : g[k][2] - c2;
+            const T w = g[k] - (sub == 0 ? c0 : sub == 1 ? c1 : c2);
             b[3 * i + sub] = i < nt ? w : (T)0;
         }
     }
@@ -1495,7 +1499,11 @@ __global__ __launch_bounds__(256) void k_top(int32_t Qt, int32_t nt, const int32
 // x values in LDS: a thread takes the group's local vertices tid and tid +
 // THREADS (local order: by step, then position), loads all their
 // constants, their r and their slots filled by earlier launches at the start,
-// and then only LDS and barriers separate the steps.  THREADS x VPT local
+// and then only LDS and barriers separate the steps.  What a vertex's indices
+// are is packed once per factor in the order of these threads (k_mid_pack): a
+// sweep starts with two rounds of loads, the packed words (with the solve's
+// flag) and what they address.  With the flag, the steps' ranges, a search for
+// the thread's vertex and its tables in turn, in four rounds, 50k cells took 13.6 instead of 13.0 ms a solve, 20k a step 14.8 instead of 12.7.  THREADS x VPT local
 // vertices are held: the smallest shape that holds the range's largest group
 // is launched (mid_shape), so that small groups leave no threads idle.  Pushes to vertices
 // outside the group (later steps, the tail) and x of up-links outside it go
@@ -1504,14 +1512,22 @@ __global__ __launch_bounds__(256) void k_top(int32_t Qt, int32_t nt, const int32
 constexpr int MID_LDS_MAX = 1536;   // vertices of one group at most
 constexpr int MID_THREADS = 512;    // threads of k_mid_local, and of the widest sweeps
 
-// per mid vertex (index q - Q0): local index, first LDS slot and number of
-// in-entries from mid vertices; per push (2 (q - Q0) + k): its LDS slot or -1;
-// per up-link: the local index of a mid up-link or -1
+// Packed words of thread slot l of group w, at w stride + l (stride: threads x
+// vertices per thread of the shape).  fwd: position, vertex, the first and the
+// end of its slots filled by earlier launches; push: step | LDS slots to read
+// << 7 | first of them << 19, the LDS slots of its two pushes (16 bits each,
+// 0xffff: none), the pushes' slots in cs (-1: none); bwd: position, vertex, and
+// per up-link its position, -2 - its local index if it is in the group, or -1.
+// A slot without a vertex has step MID_NO_STEP and addresses a valid one.
 struct MidTab {
-    const int32_t *lid, *lin0, *nint, *lsl, *lup;
+    const int4 *fwd, *push, *bwd;
+    int32_t stride;
 };
 
 constexpr int MID_MAX_STEPS = 64;   // mid steps at most for the LDS sweeps
+constexpr int MID_NO_STEP = 127;
+constexpr size_t MID_PACK_MAX = 1 << 22;   // packed words at most (x 48 B); default packings need a tenth
+static_assert(2 * MID_LDS_MAX < 4096, "slot numbers and counts fit 12 bits, and 16 with a mark");
 static_assert(2 * MID_MAX_STEPS <= 128, "the step ranges load in one round");
 
 // the group's position range of each of its L steps, rg[2k] .. rg[2k + 1],
@@ -1612,99 +1628,105 @@ __global__ void k_mid_lsl(int32_t Q0, int32_t Q1, const int32_t *in_ptr, const i
     }
 }
 
-__global__ void k_mid_lup(int32_t Q0, int32_t Q1, const int32_t *upq, const int32_t *lid, int32_t *lup)
+// the packed words of a group (MidTab), one workgroup each
+__global__ __launch_bounds__(MID_THREADS) void k_mid_pack(int32_t L, int32_t nwg, const int32_t *wptr, int32_t Q0,
+                                                          int32_t Q1, const int32_t *elim, const int32_t *in_ptr,
+                                                          const int32_t *tout, const int32_t *upq, const int32_t *lid,
+                                                          const int32_t *lin0, const int32_t *nint, const int32_t *lsl,
+                                                          int32_t stride, int4 *fwd, int4 *push, int4 *bwd)
 {
-    const int64_t q = Q0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= Q1) return;
-    for (int k = 0; k < 2; k++) {
-        const int32_t a = upq[2 * q + k];
-        lup[2 * (q - Q0) + k] = a >= Q0 && a < Q1 ? lid[a - Q0] : -1;
+    __shared__ int32_t rg[2 * MID_MAX_STEPS];
+    const int32_t w = blockIdx.x;
+    mid_ranges(L, nwg, wptr, w, rg);
+    for (int32_t l = threadIdx.x; l < stride; l += MID_THREADS) {
+        int32_t st, q = mid_local(L, rg, l, st);
+        const bool on = st >= 0;
+        q = on ? q : Q0;
+        const int32_t i = q - Q0, ni = nint[i], v = elim[q];
+        int32_t e[2];
+        for (int k = 0; k < 2; k++) {
+            const int32_t a = upq[2 * q + k];
+            e[k] = a >= Q0 && a < Q1 ? -2 - lid[a - Q0] : a;
+        }
+        const int64_t o = (int64_t)w * stride + l;
+        fwd[o] = {q, v, in_ptr[q], in_ptr[q + 1] - ni};
+        push[o] = {on ? st | ni << 7 | lin0[i] << 19 : MID_NO_STEP,
+                   (lsl[2 * (int64_t)i] & 0xffff) | lsl[2 * (int64_t)i + 1] << 16, tout[2 * q], tout[2 * q + 1]};
+        bwd[o] = {q, v, e[0], e[1]};
     }
 }
 
 // the forward sweep of the mid steps: y_q = r_v - its slots, the
 // pushes to LDS (inside the group) or to cs (outside)
 template <class T, int THREADS, int VPT>
-__global__ __launch_bounds__(THREADS) void k_fwd_mid(int32_t L, int32_t nwg, const int32_t *wptr, int32_t Q0,
-                                                         const int32_t *elim, const int32_t *in_ptr,
-                                                         const int32_t *tout, const T *F, int64_t fs, const T *r,
-                                                         T *y, T *cs, MidTab tab, const PcgScalars *s)
+__global__ __launch_bounds__(THREADS) void k_fwd_mid(int32_t L, const T *F, int64_t fs, const T *r, T *y, T *cs,
+                                                     MidTab tab, const PcgScalars *s)
 {
     __shared__ T sl[3 * 2 * THREADS * VPT];
-    __shared__ int32_t rg[2 * MID_MAX_STEPS];
-    if (s && s->done) return;
     const int32_t w = (int32_t)xcd_block(blockIdx.x, gridDim.x), tid = threadIdx.x;
-    mid_ranges(L, nwg, wptr, w, rg);
-    int32_t q[VPT], st[VPT], ni[VPT], l0[VPT], ls[VPT][2], to[VPT][2], t0[VPT], t1[VPT];
-    int64_t v[VPT];
-    T f0[VPT][9], f1[VPT][9], b[VPT][3], h[VPT][12];
-    // two rounds of loads for both vertices: what the position gives, then
-    // what those values address (r, the second coupling, the first four slots
-    // filled by earlier launches, clamped); one wait between them
+    const int32_t dn = done_flag(s);
+    int4 pf[VPT], pp[VPT];
 #pragma unroll
     for (int u = 0; u < VPT; u++) {
-        q[u] = mid_local(L, rg, tid + THREADS * u, st[u]);
-        const int32_t qc = st[u] >= 0 ? q[u] : Q0;   // a thread without a vertex loads a valid one
-        v[u] = elim[qc];
-        t0[u] = in_ptr[qc];
-        t1[u] = in_ptr[qc + 1];
-        ni[u] = tab.nint[qc - Q0];
-        l0[u] = tab.lin0[qc - Q0];
-        for (int k = 0; k < 2; k++) {
-            to[u][k] = tout[2 * qc + k];
-            ls[u][k] = tab.lsl[2 * (int64_t)(qc - Q0) + k];
-        }
-        for (int t = 0; t < 9; t++) f0[u][t] = F[9 * (int64_t)qc + t];
+        pf[u] = tab.fwd[(int64_t)w * (THREADS * VPT) + tid + THREADS * u];
+        pp[u] = tab.push[(int64_t)w * (THREADS * VPT) + tid + THREADS * u];
     }
     keep_loads_above();
+    if (dn) return;
+    T f0[VPT][9], f1[VPT][9], b[VPT][3], h[VPT][12];
+    // what the words address: r, the couplings, the first four slots filled by
+    // earlier launches (clamped)
 #pragma unroll
     for (int u = 0; u < VPT; u++) {
-        const int32_t qc = st[u] >= 0 ? q[u] : Q0;
-        b[u][0] = r[3 * v[u]];
-        b[u][1] = r[3 * v[u] + 1];
-        b[u][2] = r[3 * v[u] + 2];
-        // (the second plane is zero without a second link)
-        for (int t = 0; t < 9; t++) f1[u][t] = F[fs + 9 * (int64_t)qc + t];
-        const int32_t te = t1[u] - ni[u], last = te > t0[u] ? te - 1 : t0[u];
+        const int64_t qc = pf[u].x, v = pf[u].y;
+        b[u][0] = r[3 * v];
+        b[u][1] = r[3 * v + 1];
+        b[u][2] = r[3 * v + 2];
+        const int32_t t0 = pf[u].z, last = pf[u].w > t0 ? pf[u].w - 1 : t0;
         for (int m = 0; m < 4; m++) {
-            const T *c = cs + 3 * (int64_t)min(t0[u] + m, last);
+            const T *c = cs + 3 * (int64_t)min(t0 + m, last);
             h[u][3 * m] = c[0];
             h[u][3 * m + 1] = c[1];
             h[u][3 * m + 2] = c[2];
         }
+        for (int t = 0; t < 9; t++) f0[u][t] = F[9 * qc + t];
+        // (the second plane is zero without a second link)
+        for (int t = 0; t < 9; t++) f1[u][t] = F[fs + 9 * qc + t];
     }
     keep_loads_above();
     // r minus the slots filled by earlier launches (the first in-entries), in
     // slot order: the first four from h, any further ones loaded here
 #pragma unroll
     for (int u = 0; u < VPT; u++) {
-        const int32_t te = t1[u] - ni[u];
+        const int32_t t0 = pf[u].z, te = pf[u].w;
         for (int m = 0; m < 4; m++)
-            if (t0[u] + m < te) {
+            if (t0 + m < te) {
                 b[u][0] = b[u][0] - h[u][3 * m];
                 b[u][1] = b[u][1] - h[u][3 * m + 1];
                 b[u][2] = b[u][2] - h[u][3 * m + 2];
             }
-        if (t0[u] + 4 < te) sum_slots<T>(t0[u] + 4, te, cs, b[u][0], b[u][1], b[u][2]);
+        if (t0 + 4 < te) sum_slots<T>(t0 + 4, te, cs, b[u][0], b[u][1], b[u][2]);
     }
     for (int32_t k = 0; k < L; k++) {
 #pragma unroll
         for (int u = 0; u < VPT; u++) {
-            if (st[u] != k) continue;
+            if ((pp[u].x & 127) != k) continue;
             T c0 = b[u][0], c1 = b[u][1], c2 = b[u][2];
-            for (int32_t j = 0; j < ni[u]; j++) {
-                const T *c = sl + 3 * (l0[u] + j);
+            const int32_t ni = (pp[u].x >> 7) & 0xfff, l0 = pp[u].x >> 19;
+            for (int32_t j = 0; j < ni; j++) {
+                const T *c = sl + 3 * (l0 + j);
                 c0 = c0 - c[0];
                 c1 = c1 - c[1];
                 c2 = c2 - c[2];
             }
-            const int64_t qq = q[u];
+            const int64_t qq = pf[u].x;
             y[3 * qq] = c0;
             y[3 * qq + 1] = c1;
             y[3 * qq + 2] = c2;
             for (int m = 0; m < 2; m++) {
-                if (to[u][m] < 0) continue;
-                T *c = ls[u][m] >= 0 ? sl + 3 * ls[u][m] : cs + 3 * (int64_t)to[u][m];
+                const int32_t to = m == 0 ? pp[u].z : pp[u].w, ls = (pp[u].y >> (16 * m)) & 0xffff;
+                if (to < 0) continue;
+                T *c = ls != 0xffff ? sl + 3 * ls : cs + 3 * (int64_t)to;
                 push3(c, m == 0 ? f0[u] : f1[u], c0, c1, c2);
             }
         }
@@ -1718,44 +1740,39 @@ __global__ __launch_bounds__(THREADS) void k_fwd_mid(int32_t L, int32_t nwg, con
 // of F^T x, x of a mid up-link from LDS, of others from y; x written to y
 // (for the steps below) and to z
 template <class T, int THREADS, int VPT>
-__global__ __launch_bounds__(THREADS) void k_bwd_mid(int32_t L, int32_t nwg, const int32_t *wptr, int32_t Q0,
-                                                         const int32_t *elim, const int32_t *upq, const T *F,
-                                                         int64_t fs, const T *Dinv, T *y, T *z, MidTab tab,
-                                                         const PcgScalars *s)
+__global__ __launch_bounds__(THREADS) void k_bwd_mid(int32_t L, const T *F, int64_t fs, const T *Dinv, T *y, T *z,
+                                                     MidTab tab, const PcgScalars *s)
 {
     __shared__ T xl[3 * THREADS * VPT];
-    __shared__ int32_t rg[2 * MID_MAX_STEPS];
-    if (s && s->done) return;
     const int32_t w = (int32_t)xcd_block(blockIdx.x, gridDim.x), tid = threadIdx.x;
-    mid_ranges(L, nwg, wptr, w, rg);
-    int32_t q[VPT], st[VPT], lu[VPT][2], ua[VPT][2];
-    int64_t v[VPT];
-    T d[VPT][6], f0[VPT][9], f1[VPT][9], yo[VPT][3], xo[VPT][2][3];
-    // two rounds of loads for both vertices, one wait between them
+    const int32_t dn = done_flag(s);
+    int4 pb[VPT];
+    int32_t st[VPT];
 #pragma unroll
     for (int u = 0; u < VPT; u++) {
-        q[u] = mid_local(L, rg, tid + THREADS * u, st[u]);
-        const int32_t qc = st[u] >= 0 ? q[u] : Q0;
-        v[u] = elim[qc];
-        for (int k = 0; k < 2; k++) {
-            ua[u][k] = upq[2 * qc + k];
-            lu[u][k] = tab.lup[2 * (int64_t)(qc - Q0) + k];
-        }
-        for (int t = 0; t < 6; t++) d[u][t] = Dinv[6 * (int64_t)qc + t];
-        for (int t = 0; t < 9; t++) f0[u][t] = F[9 * (int64_t)qc + t];
-        for (int t = 0; t < 9; t++) f1[u][t] = F[fs + 9 * (int64_t)qc + t];
-        for (int t = 0; t < 3; t++) yo[u][t] = y[3 * (int64_t)qc + t];
+        pb[u] = tab.bwd[(int64_t)w * (THREADS * VPT) + tid + THREADS * u];
+        st[u] = tab.push[(int64_t)w * (THREADS * VPT) + tid + THREADS * u].x;
     }
     keep_loads_above();
-    // x of up-links outside the group (final: swept by earlier launches)
+    if (dn) return;
+    T d[VPT][6], f0[VPT][9], f1[VPT][9], yo[VPT][3], xo[VPT][2][3];
+    // what the words address; x of up-links outside the group is final (swept
+    // by earlier launches)
 #pragma unroll
     for (int u = 0; u < VPT; u++) {
-        const int32_t qc = st[u] >= 0 ? q[u] : Q0;
+        const int64_t qc = pb[u].x;
+        st[u] &= 127;
         for (int k = 0; k < 2; k++) {
-            const int64_t a = ua[u][k] >= 0 && lu[u][k] < 0 ? ua[u][k] : qc;
+            const int32_t e = k == 0 ? pb[u].z : pb[u].w;
+            const int64_t a = e >= 0 ? e : qc;
             for (int t = 0; t < 3; t++) xo[u][k][t] = y[3 * a + t];
         }
+        for (int t = 0; t < 3; t++) yo[u][t] = y[3 * qc + t];
+        for (int t = 0; t < 6; t++) d[u][t] = Dinv[6 * qc + t];
+        for (int t = 0; t < 9; t++) f0[u][t] = F[9 * qc + t];
+        for (int t = 0; t < 9; t++) f1[u][t] = F[fs + 9 * qc + t];
     }
+    keep_loads_above();
     // Dinv_q y_q ahead of the steps
 #pragma unroll
     for (int u = 0; u < VPT; u++) {
@@ -1768,10 +1785,11 @@ __global__ __launch_bounds__(THREADS) void k_bwd_mid(int32_t L, int32_t nwg, con
             if (st[u] != k) continue;
             T n0 = yo[u][0], n1 = yo[u][1], n2 = yo[u][2];
             for (int m = 0; m < 2; m++) {
-                if (ua[u][m] < 0) continue;
+                const int32_t e = m == 0 ? pb[u].z : pb[u].w;
+                if (e == -1) continue;
                 T x0 = xo[u][m][0], x1 = xo[u][m][1], x2 = xo[u][m][2];
-                if (lu[u][m] >= 0) {
-                    const T *xs = xl + 3 * lu[u][m];
+                if (e < 0) {
+                    const T *xs = xl + 3 * (-2 - e);
                     x0 = xs[0];
                     x1 = xs[1];
                     x2 = xs[2];
@@ -1782,13 +1800,13 @@ __global__ __launch_bounds__(THREADS) void k_bwd_mid(int32_t L, int32_t nwg, con
             xl[3 * l] = n0;
             xl[3 * l + 1] = n1;
             xl[3 * l + 2] = n2;
-            const int64_t qq = q[u];
+            const int64_t qq = pb[u].x, v = pb[u].y;
             y[3 * qq] = n0;
             y[3 * qq + 1] = n1;
             y[3 * qq + 2] = n2;
-            z[3 * v[u]] = n0;
-            z[3 * v[u] + 1] = n1;
-            z[3 * v[u] + 2] = n2;
+            z[3 * v] = n0;
+            z[3 * v + 1] = n1;
+            z[3 * v + 2] = n2;
         }
         // LDS only: the global stores (y, z, pushes out of the group) are
         // read by no thread of this launch
@@ -1914,17 +1932,17 @@ static int tree_sweeps(sgp_ctx ctx, sgp_prec M, const T *F, const T *Dinv, T *y,
     const bool mid_lds = g.lds && ctx->mid_lds;
     MidTab mtab = {};
     if (mid_lds) {
-        const int32_t Nm = sp[m1] - sp[m0];
-        const int32_t *tb = (const int32_t *)M->mid_tab.p;
-        mtab = {tb, tb + Nm, tb + 2 * (size_t)Nm, tb + 3 * (size_t)Nm, tb + 5 * (size_t)Nm};
+        const int4 *tb = (const int4 *)M->mid_pack.p;
+        const int64_t len = (int64_t)g.nwg * g.stride;
+        mtab = {tb, tb + len, tb + 2 * len, g.stride};
     }
     for (int k = L; k < ts; k++) {
         int32_t q0 = sp[k], q1 = sp[k + 1];
         if (k == m0 && g.steps > 0) {
             if (mid_lds)
                 mid_shape(g.max_group, [&](auto th, auto vpt) {
-                    k_fwd_mid<T, decltype(th)::value, decltype(vpt)::value><<<g.nwg, decltype(th)::value, 0, st>>>(
-                        g.steps, g.nwg, mptr, q0, elim, in_ptr, tout, F, fs, r, y, cs, mtab, s);
+                    k_fwd_mid<T, decltype(th)::value, decltype(vpt)::value>
+                        <<<g.nwg, decltype(th)::value, 0, st>>>(g.steps, F, fs, r, y, cs, mtab, s);
                 });
             else
                 k_fwd_light<T><<<g.nwg, 256, 0, st>>>(g.steps, g.nwg, mptr, elim, in_ptr, tout, F, fs, r, y, cs, s);
@@ -2005,8 +2023,8 @@ static int tree_sweeps(sgp_ctx ctx, sgp_prec M, const T *F, const T *Dinv, T *y,
         if (k == m1 - 1 && g.steps > 0) {
             if (mid_lds)
                 mid_shape(g.max_group, [&](auto th, auto vpt) {
-                    k_bwd_mid<T, decltype(th)::value, decltype(vpt)::value><<<g.nwg, decltype(th)::value, 0, st>>>(
-                        g.steps, g.nwg, mptr, sp[m0], elim, upq, F, fs, Dinv, y, z, mtab, s);
+                    k_bwd_mid<T, decltype(th)::value, decltype(vpt)::value>
+                        <<<g.nwg, decltype(th)::value, 0, st>>>(g.steps, F, fs, Dinv, y, z, mtab, s);
                 });
             else
                 k_bwd_light<T><<<g.nwg, 256, 0, st>>>(g.steps, g.nwg, mptr, elim, upq, F, fs, Dinv, y, z, s);
@@ -2140,11 +2158,12 @@ static int tail_tables(sgp_ctx ctx, sgp_prec M, int64_t n, const int32_t *in_ptr
     return SGP_OK;
 }
 
-// the tables of the LDS mid sweeps (MidTab); maxg: the largest group
+// what k_mid_pack needs for the LDS mid sweeps, in mid_tab: per mid vertex
+// (index q - Q0) its local index, first LDS slot and number of in-entries from
+// mid vertices, per push its LDS slot or -1; maxg: the largest group
 // (INT32_MAX: too large for them, the caller keeps the generic workgroup
 // sweeps)
-static int mid_tables(sgp_ctx ctx, sgp_prec M, const int32_t *in_ptr, const int32_t *in_src, const int32_t *upq,
-                      int32_t *maxg)
+static int mid_tables(sgp_ctx ctx, sgp_prec M, const int32_t *in_ptr, const int32_t *in_src, int32_t *maxg)
 {
     hipStream_t st = ctx->stream;
     sgp_prec_::MidRange &g = M->mid;
@@ -2154,17 +2173,38 @@ static int mid_tables(sgp_ctx ctx, sgp_prec M, const int32_t *in_ptr, const int3
     const int32_t Q0 = M->h_step_ptr[g.step0], Q1 = M->h_step_ptr[g.step0 + g.steps], Nm = Q1 - Q0;
     if (Nm <= 0) return SGP_OK;
     int32_t *tb;
-    SGP_TRY(ensure_t(ctx, M->mid_tab, 7 * (size_t)Nm + 8, &tb));
-    int32_t *lid = tb, *lin0 = tb + Nm, *nint = tb + 2 * (size_t)Nm, *lsl = tb + 3 * (size_t)Nm,
-            *lup = tb + 5 * (size_t)Nm;
+    SGP_TRY(ensure_t(ctx, M->mid_tab, 5 * (size_t)Nm + 8, &tb));
+    int32_t *lid = tb, *lin0 = tb + Nm, *nint = tb + 2 * (size_t)Nm, *lsl = tb + 3 * (size_t)Nm;
     SGP_TRY(fill_i32(ctx, lsl, -1, 2 * (int64_t)Nm));
     k_mid_nint<<<grid_for(Nm, 256), 256, 0, st>>>(Q0, Q1, in_ptr, in_src, nint);
     k_mid_local<<<g.nwg, MID_THREADS, 0, st>>>(g.steps, g.nwg, (const int32_t *)M->mid_ptr.p, Q0, nint, lid, lin0,
                                                maxg);
     k_mid_lsl<<<grid_for(Nm, 256), 256, 0, st>>>(Q0, Q1, in_ptr, in_src, nint, lin0, lsl);
-    k_mid_lup<<<grid_for(Nm, 256), 256, 0, st>>>(Q0, Q1, upq, lid, lup);
     LAUNCH_CHECK(ctx);
     g.lds_built = true;
+    return SGP_OK;
+}
+
+// the packed words of the LDS mid sweeps, once the largest group is known
+static int mid_pack(sgp_ctx ctx, sgp_prec M)
+{
+    sgp_prec_::MidRange &g = M->mid;
+    const int32_t Q0 = M->h_step_ptr[g.step0], Q1 = M->h_step_ptr[g.step0 + g.steps];
+    const size_t Nm = (size_t)(Q1 - Q0);
+    mid_shape(g.max_group, [&](auto th, auto vpt) { g.stride = decltype(th)::value * decltype(vpt)::value; });
+    const size_t len = (size_t)g.nwg * g.stride;
+    if (len > MID_PACK_MAX) {   // tens of thousands of groups (knob light_cap): the generic workgroup sweeps
+        g.lds = false;
+        return SGP_OK;
+    }
+    int4 *pk;
+    SGP_TRY(ensure_t(ctx, M->mid_pack, 3 * len, &pk));
+    const int32_t *tb = (const int32_t *)M->mid_tab.p;
+    k_mid_pack<<<g.nwg, MID_THREADS, 0, ctx->stream>>>(
+        g.steps, g.nwg, (const int32_t *)M->mid_ptr.p, Q0, Q1, (const int32_t *)M->elim_int.p,
+        (const int32_t *)M->in_ptr.p, (const int32_t *)M->tout.p, (const int32_t *)M->up.p, tb, tb + Nm, tb + 2 * Nm,
+        tb + 3 * Nm, g.stride, pk, pk + len, pk + 2 * len);
+    LAUNCH_CHECK(ctx);
     return SGP_OK;
 }
 
@@ -2523,14 +2563,15 @@ extern "C" int sgp_factor_tree(sgp_ctx ctx, sgp_graph g, sgp_tree T, double g_pa
     k_slot_of<<<grid_for(2 * n, 256), 256, 0, st>>>(in_ptr + n, in_src, tout);
     LAUNCH_CHECK(ctx);
     SGP_TRY(tail_tables(ctx, M, n, in_ptr, in_src, tout));
-    SGP_TRY(mid_tables(ctx, M, in_ptr, in_src, upq, status + 2));
+    SGP_TRY(mid_tables(ctx, M, in_ptr, in_src, status + 2));
     if (M->top) SGP_TRY(top_block(ctx, M));
     SGP_TRY(readback(ctx, hbuf, status, 12));
-    phase_end(ctx, 3);
-    if (hbuf[0]) return set_err(ctx, SGP_ENOTSPD, "factor_tree: a pivot block is not positive definite");
     M->step0_sorted = M->n_wu0 > 0 && hbuf[1] == 0;
     M->mid.max_group = hbuf[2];
     M->mid.lds = M->mid.lds_built && hbuf[2] <= MID_LDS_MAX;
+    if (M->mid.lds) SGP_TRY(mid_pack(ctx, M));
+    phase_end(ctx, 3);
+    if (hbuf[0]) return set_err(ctx, SGP_ENOTSPD, "factor_tree: a pivot block is not positive definite");
     return SGP_OK;
 }
 

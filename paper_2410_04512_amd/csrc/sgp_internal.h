@@ -219,11 +219,12 @@ struct sgp_prec_ {
     struct MidRange {
         int32_t step0 = 0, steps = 0, nwg = 0;
         int32_t max_group = 0;                          // vertices of its largest group (LDS sweeps)
+        int32_t stride = 0;                             // packed words per group (MidTab)
         bool lds_built = false, lds = false;            // tables built, and every group fits the LDS sweeps
     };
     MidRange mid;
     DevBuf mid_ptr;                                     // [mid.steps * mid.nwg + 1] first q of (step, workgroup)
-    DevBuf mid_tab;                                     // tables of the LDS mid sweeps (factor.hip, MidTab)
+    DevBuf mid_tab, mid_pack;                           // tables of the LDS mid sweeps (factor.hip, MidTab)
     int32_t tail_step = 0;                              // steps >= tail_step run in one launch (tail or top block)
     // the top block: the steps >= tail_step as one dense symmetric product
     // with the inverse of their Schur complement, [3 tail_nt][top_ld]
