@@ -423,6 +423,25 @@ SGP_DEV double row_sum_16(double v)
     return add_row_ror<1>(add_row_ror<2>(add_row_ror<4>(add_row_ror<8>(v))));
 }
 
+// v[l] + v[l ^ 32] and v[l] + v[l ^ 16] in every lane (gfx950's half and row
+// swaps: both halves of a value's sum from one register pair)
+SGP_DEV double add_swap_32(double v)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+SGP_DEV double add_swap_16(double v)
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+
+// sum over a wave in every lane: the pairwise tree of distances 32, 16, .., 1,
+// without LDS.  All lanes active.
+SGP_DEV double wave_sum(double v) { return row_sum_16(add_swap_16(add_swap_32(v))); }
+
 // Sum over a 256-thread block in every thread: the pairwise tree of distances
 // 128, 64, .., 1.  The distances down to 16 are the thread's own additions of
 // 16 values from LDS, the rest stay in a row of lanes: two barriers instead of

@@ -68,7 +68,7 @@ struct SmallArgs {
 };
 
 // sums of NV values over the workgroup, in a fixed order (each wave by a
-// butterfly, then the waves in order); every thread gets the totals.
+// pairwise tree, then the waves in order); every thread gets the totals.
 // Two buffers, used in turn: a buffer is reused only after the barrier of the
 // reduction between, so no barrier is needed after reading.
 template <int NV>
@@ -79,8 +79,7 @@ SGP_DEV void small_sum(double *red, int &buf, double *v)
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
     for (int a = 0; a < NV; a++) {
-        double s = v[a];
-        for (int o = 32; o > 0; o >>= 1) s = s + __shfl_xor(s, o, 64);
+        const double s = wave_sum(v[a]);
         if (lane == 0) b[a * W + wv] = s;
     }
     lds_barrier();

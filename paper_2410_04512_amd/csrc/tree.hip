@@ -30,15 +30,6 @@ __global__ void k_bv_reset(int32_t *comp, int64_t n)
     if (v < n) comp[v] = (int32_t)v;
 }
 
-__global__ void k_bv_clear_best(unsigned long long *bestw, int32_t *beste, int64_t n)
-{
-    int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v < n) {
-        bestw[v] = 0ull;
-        beste[v] = INT_MAX;
-    }
-}
-
 // atomicMax of val into slot[key] for the lanes with ok set.  Lanes of a wave
 // that share a key are combined first (up to four keys, each led by the lowest
 // pending lane); the rest use their own atomic.  Late rounds send most edges
@@ -121,11 +112,14 @@ __global__ void k_bv_first(int64_t n, const int32_t *rowptr, const int32_t *ent_
     beste[v] = be;
 }
 
+// (it also resets what the launches after it collect: mr and the jumps' flag)
 __global__ void k_bv_hook(const int32_t *ei, const int32_t *ej, int64_t n, const int32_t *comp,
-                          const int32_t *beste, int32_t *nxt, int32_t *is_tree, int32_t *flag)
+                          const int32_t *beste, int32_t *nxt, int32_t *is_tree, int32_t *mr, int32_t *flag)
 {
     int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= n) return;
+    if (c == 0) *flag = 0;
+    mr[c] = INT_MAX;
     if (comp[c] != c) return;   // representatives only
     int32_t e = beste[c];
     if (e == INT_MAX) {
@@ -140,36 +134,49 @@ __global__ void k_bv_hook(const int32_t *ei, const int32_t *ej, int64_t n, const
     }
     nxt[c] = o;
     is_tree[e] = 1;
-    *flag = 1;
 }
 
+// nxt_out = the pointer JUMP_HOPS further (fewer at a root); flag: a chain is
+// longer.  A launch of hops costs little more than one of a single jump (a few
+// dependent gathers, which most chains end at once), so two launches reach 80
+// hops where pairs of doublings took six launches for 64.
+constexpr int JUMP_HOPS = 8;
 __global__ void k_bv_jump(int64_t n, const int32_t *comp, const int32_t *nxt_in, int32_t *nxt_out, int32_t *flag)
 {
     int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= n || comp[c] != c) return;
     int32_t p = nxt_in[c];
-    int32_t pp = nxt_in[p];
-    nxt_out[c] = pp;
-    if (pp != p) *flag = 1;
+    bool root = false;
+    for (int h = 0; h < JUMP_HOPS && !root; h++) {
+        const int32_t pp = nxt_in[p];
+        root = pp == p;
+        p = pp;
+    }
+    nxt_out[c] = p;
+    if (!root) *flag = 1;
 }
 
-// smallest representative of every hook tree, at the tree's root
-__global__ void k_bv_minrep(int64_t n, const int32_t *comp, const int32_t *nxt, int32_t *mr)
+// smallest representative of every hook tree, at the tree's root (nothing
+// while a chain is unfinished: flag)
+__global__ void k_bv_minrep(int64_t n, const int32_t *comp, const int32_t *nxt, int32_t *mr, const int32_t *flag)
 {
     int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n || comp[c] != c) return;
+    if (c >= n || comp[c] != c || *flag) return;
     int32_t root = nxt[c];
     if ((int32_t)c < mr[root]) atomicMin(&mr[root], (int32_t)c);
 }
 
-__global__ void k_bv_relabel(int64_t n, int32_t *comp, const int32_t *nxt, const int32_t *mr)
+// the new components, and the best edges reset for the next round
+__global__ void k_bv_relabel(int64_t n, int32_t *comp, const int32_t *nxt, const int32_t *mr, const int32_t *flag,
+                             unsigned long long *bestw, int32_t *beste)
 {
     int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= n) return;
+    if (v >= n || *flag) return;
     comp[v] = mr[nxt[comp[v]]];
+    bestw[v] = 0ull;
+    beste[v] = INT_MAX;
 }
 
-// active-edge compaction: keep the edges that still join two components
 __global__ void k_bv_live(const int32_t *act, int64_t na, const int32_t *ei, const int32_t *ej, const int32_t *comp,
                           int32_t *flag)
 {
@@ -179,9 +186,15 @@ __global__ void k_bv_live(const int32_t *act, int64_t na, const int32_t *ei, con
     flag[k] = comp[ei[e]] != comp[ej[e]] ? 1 : 0;
 }
 
-__global__ void k_bv_pack(const int32_t *act, int64_t na, const int32_t *flag, const int32_t *off, int32_t *out)
+// the live edges, and for the host (pair) the jumps' flag and their number
+__global__ void k_bv_pack(const int32_t *act, int64_t na, const int32_t *flag, const int32_t *off, int32_t *out,
+                          const int32_t *jflag, int32_t *pair)
 {
     int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k == 0) {
+        pair[0] = *jflag;
+        pair[1] = off[na];
+    }
     if (k < na && flag[k]) out[off[k]] = act[k];
 }
 
@@ -267,17 +280,19 @@ __global__ void k_tour(int64_t nd, const int32_t *tptr, const int32_t *adj, cons
     sr[k] = make_int2(nx, nx < 0 ? 0 : 1);
 }
 
+// spans of RANK_SPAN of the last launch's: 300k cells, 20 launches of one
+// gather each 152 us, 10 of three 128
+constexpr int RANK_SPAN = 4;
 __global__ void k_rank_jump(int64_t nd, const int2 *sr_in, int2 *sr_out)
 {
     int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= nd) return;
-    const int2 a = sr_in[k];
-    if (a.x < 0) {
-        sr_out[k] = a;
-        return;
+    int2 a = sr_in[k];
+    for (int h = 1; h < RANK_SPAN && a.x >= 0; h++) {
+        const int2 b = sr_in[a.x];
+        a = make_int2(b.x, a.y + b.y);
     }
-    const int2 b = sr_in[a.x];
-    sr_out[k] = make_int2(b.x, a.y + b.y);
+    sr_out[k] = a;
 }
 
 __global__ void k_rank_unpack(int64_t nd, const int2 *sr, int32_t *rank)
@@ -414,35 +429,30 @@ static int build_forest_impl(sgp_ctx ctx, sgp_graph g, sgp_tree T, const int32_t
                                                         (const int32_t *)g->ent_edge.p, (const int32_t *)g->col.p, cl,
                                                         wonly, bestw, beste);
         } else {
-            k_bv_clear_best<<<grid_for(n, 256), 256, 0, st>>>(bestw, beste, n);
             k_bv_maxw<<<grid_for(na, 256), 256, 0, st>>>(act, na, ei, ej, wonly, comp, bestw);
             k_bv_mine<<<grid_for(na, 256), 256, 0, st>>>(act, na, ei, ej, wonly, comp, bestw, beste);
         }
-        SGP_TRY(fill_i32(ctx, flag, 0, 1));
-        k_bv_hook<<<grid_for(n, 256), 256, 0, st>>>(ei, ej, n, comp, beste, nxt, is_tree, flag);
+        k_bv_hook<<<grid_for(n, 256), 256, 0, st>>>(ei, ej, n, comp, beste, nxt, is_tree, mr, flag);
         LAUNCH_CHECK(ctx);
-        // pointer jumping: three pairs of jumps before the first check (hook
-        // chains are short: one check usually ends it), then two per check;
-        // jumps past convergence are no-ops
+        // Two launches of jumps finish almost every round, so the rest of the
+        // round is issued behind them and the host waits once, for their flag
+        // and the edges left together; with an unfinished chain the rest
+        // changed nothing, and runs again after two more.
+        int32_t hn = 0;
         for (int j = 0; j < 64; j++) {
-            for (int r = 0; r < (j == 0 ? 3 : 1); r++) {
-                if (r == (j == 0 ? 2 : 0)) SGP_TRY(fill_i32(ctx, flag, 0, 1));   // the last pair is checked
-                k_bv_jump<<<grid_for(n, 256), 256, 0, st>>>(n, comp, nxt, nxt2, flag + 1);
-                k_bv_jump<<<grid_for(n, 256), 256, 0, st>>>(n, comp, nxt2, nxt, flag);
-            }
+            if (j > 0) SGP_TRY(fill_i32(ctx, flag, 0, 1));
+            k_bv_jump<<<grid_for(n, 256), 256, 0, st>>>(n, comp, nxt, nxt2, flag + 1);
+            k_bv_jump<<<grid_for(n, 256), 256, 0, st>>>(n, comp, nxt2, nxt, flag);
+            k_bv_minrep<<<grid_for(n, 256), 256, 0, st>>>(n, comp, nxt, mr, flag);
+            k_bv_relabel<<<grid_for(n, 256), 256, 0, st>>>(n, comp, nxt, mr, flag, bestw, beste);
+            k_bv_live<<<grid_for(na, 256), 256, 0, st>>>(act, na, ei, ej, comp, lflag);
+            SGP_TRY(scan_exclusive(ctx, lflag, loff, na));
+            k_bv_pack<<<grid_for(na, 256), 256, 0, st>>>(act, na, lflag, loff, act2, flag, flag + 2);
             LAUNCH_CHECK(ctx);
-            SGP_TRY(readback(ctx, hflag, flag, 4));
+            SGP_TRY(readback(ctx, hflag, flag + 2, 8));
+            hn = hflag[1];
             if (!hflag[0]) break;
         }
-        SGP_TRY(fill_i32(ctx, mr, INT_MAX, n));
-        k_bv_minrep<<<grid_for(n, 256), 256, 0, st>>>(n, comp, nxt, mr);
-        k_bv_relabel<<<grid_for(n, 256), 256, 0, st>>>(n, comp, nxt, mr);
-        k_bv_live<<<grid_for(na, 256), 256, 0, st>>>(act, na, ei, ej, comp, lflag);
-        SGP_TRY(scan_exclusive(ctx, lflag, loff, na));
-        k_bv_pack<<<grid_for(na, 256), 256, 0, st>>>(act, na, lflag, loff, act2);
-        LAUNCH_CHECK(ctx);
-        int32_t hn;
-        SGP_TRY(readback(ctx, &hn, loff + na, 4));
         std::swap(act, act2);
         na = hn;
     }
@@ -479,7 +489,7 @@ static int build_forest_impl(sgp_ctx ctx, sgp_graph g, sgp_tree T, const int32_t
         k_tsort<<<grid_for(n, 256), 256, 0, st>>>(n, tptr, adj, adje, from);
         k_tour<<<grid_for(nd, 256), 256, 0, st>>>(nd, tptr, adj, adje, comp, twin, sra);
         LAUNCH_CHECK(ctx);
-        for (int64_t span = 1; span < nd; span *= 2) {
+        for (int64_t span = 1; span < nd; span *= RANK_SPAN) {
             k_rank_jump<<<grid_for(nd, 256), 256, 0, st>>>(nd, sra, srb);
             std::swap(sra, srb);
         }

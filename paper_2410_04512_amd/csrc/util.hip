@@ -206,6 +206,10 @@ __global__ void k_scan_tile_sums(int32_t *tile, int ntiles, int32_t *total_out)
     if (threadIdx.x == 0) *total_out = carry;
 }
 
+// The exclusive scan of a tile from the sums before it: SUMS: tile_off holds
+// the tiles' own sums, and every workgroup adds those before its own (the last
+// one stores the total), else their exclusive scan.
+template <bool SUMS>
 __global__ void k_scan_apply(const int32_t *in, int32_t *out, int64_t n, const int32_t *tile_off)
 {
     __shared__ int32_t sh[4];
@@ -216,13 +220,25 @@ __global__ void k_scan_apply(const int32_t *in, int32_t *out, int64_t n, const i
         v[k] = (base + k < n) ? in[base + k] : 0;
         s += v[k];
     }
-    int32_t tot;
-    int32_t ex = block_exscan_256(s, &tot, sh) + tile_off[blockIdx.x];
+    int32_t tot, off = 0;
+    if (SUMS) {
+        int32_t p = 0;
+        for (int32_t k = threadIdx.x; k < (int32_t)blockIdx.x; k += SCAN_T) p += tile_off[k];
+        block_exscan_256(p, &off, sh);
+    } else {
+        off = tile_off[blockIdx.x];
+    }
+    int32_t ex = block_exscan_256(s, &tot, sh) + off;
+    if (SUMS && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = off + tot;
     for (int k = 0; k < SCAN_I; k++) {
         if (base + k < n) out[base + k] = ex;
         ex += v[k];
     }
 }
+
+// tiles up to which every workgroup adds the sums before its own (at most 8
+// loads a thread) instead of a launch of one workgroup between the two
+constexpr int SCAN_FOLD = 2048;
 
 int scan_exclusive(sgp_ctx ctx, const int32_t *in, int32_t *out, int64_t n)
 {
@@ -230,9 +246,13 @@ int scan_exclusive(sgp_ctx ctx, const int32_t *in, int32_t *out, int64_t n)
     if (ntiles == 0) ntiles = 1;
     int32_t *tiles;
     SGP_TRY(ensure_t(ctx, ctx->ws[WS_TILES], (size_t)ntiles + 1, &tiles));
-    k_scan_tiles<<<ntiles, SCAN_T, 0, ctx->stream>>>(in, n, tiles);
-    k_scan_tile_sums<<<1, SCAN_T, 0, ctx->stream>>>(tiles, ntiles, out + n);
-    k_scan_apply<<<ntiles, SCAN_T, 0, ctx->stream>>>(in, out, n, tiles);
+    if (ntiles > 1) k_scan_tiles<<<ntiles, SCAN_T, 0, ctx->stream>>>(in, n, tiles);
+    if (ntiles <= SCAN_FOLD) {
+        k_scan_apply<true><<<ntiles, SCAN_T, 0, ctx->stream>>>(in, out, n, tiles);
+    } else {
+        k_scan_tile_sums<<<1, SCAN_T, 0, ctx->stream>>>(tiles, ntiles, out + n);
+        k_scan_apply<false><<<ntiles, SCAN_T, 0, ctx->stream>>>(in, out, n, tiles);
+    }
     LAUNCH_CHECK(ctx);
     return SGP_OK;
 }
