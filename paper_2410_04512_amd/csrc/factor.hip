@@ -490,20 +490,45 @@ __global__ void k_uplinks(int64_t n, const int32_t *elim, const int32_t *pos, co
 
 // One elimination step: pivots of the step's vertices, their blocks F and
 // their Schur contributions C[slot] (symmetric packed) to the vertices above.
+// Bound by the chain of loads of one thread, since most steps have few
+// vertices and a vertex up to some twenty contributions: these are read
+// FACTOR_BATCH at a time (sources, then blocks; clamped, surplus not
+// subtracted) and the vertex's own blocks with the first of them.  300k cells,
+// 21 steps: 259 -> 177 us.
+constexpr int FACTOR_BATCH = 4;
 __global__ void k_factor_step(int32_t q0, int32_t q1, const int32_t *elim, const int32_t *upq,
                               const int32_t *in_ptr, const int32_t *in_src, const double *Pd, double *E,
                               double *C, double *F, int64_t fs, double *Dinv, int32_t *status)
 {
     int32_t q = q0 + (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
     if (q >= q1) return;
-    int32_t v = elim[q];
-    double D[9];
-    for (int t = 0; t < 9; t++) D[t] = Pd[9 * (int64_t)v + t];
-    for (int32_t t = in_ptr[q]; t < in_ptr[q + 1]; t++) {
-        const double *c = C + 6 * (int64_t)in_src[t];
-        D[0] = D[0] - c[0]; D[1] = D[1] - c[1]; D[2] = D[2] - c[2];
-        D[3] = D[3] - c[1]; D[4] = D[4] - c[3]; D[5] = D[5] - c[4];
-        D[6] = D[6] - c[2]; D[7] = D[7] - c[4]; D[8] = D[8] - c[5];
+    const int32_t v = elim[q], qa = upq[2 * q], qb = upq[2 * q + 1];
+    const int32_t i0 = in_ptr[q], i1 = in_ptr[q + 1];
+    keep_loads_above();
+    double D[9], E0[9], E1[9];   // (E of q and of its second up-link; unused without the links)
+    const int64_t qe = qb >= 0 ? qb : q;
+    for (int t = 0; t < 9; t++) {
+        D[t] = Pd[9 * (int64_t)v + t];
+        E0[t] = E[9 * (int64_t)q + t];
+        E1[t] = E[9 * qe + t];
+    }
+    for (int32_t i = i0; i < i1; i += FACTOR_BATCH) {
+        int64_t src[FACTOR_BATCH];
+        double cs[FACTOR_BATCH][6];
+#pragma unroll
+        for (int m = 0; m < FACTOR_BATCH; m++) src[m] = in_src[min(i + m, i1 - 1)];
+#pragma unroll
+        for (int m = 0; m < FACTOR_BATCH; m++)
+            for (int t = 0; t < 6; t++) cs[m][t] = C[6 * src[m] + t];
+        keep_loads_above();
+#pragma unroll
+        for (int m = 0; m < FACTOR_BATCH; m++) {
+            if (i + m >= i1) break;
+            const double *c = cs[m];
+            D[0] = D[0] - c[0]; D[1] = D[1] - c[1]; D[2] = D[2] - c[2];
+            D[3] = D[3] - c[1]; D[4] = D[4] - c[3]; D[5] = D[5] - c[4];
+            D[6] = D[6] - c[2]; D[7] = D[7] - c[4]; D[8] = D[8] - c[5];
+        }
     }
     double inv[6];
     if (!spd_inverse3(D, inv)) {
@@ -513,12 +538,9 @@ __global__ void k_factor_step(int32_t q0, int32_t q1, const int32_t *elim, const
     for (int t = 0; t < 6; t++) Dinv[6 * (int64_t)q + t] = inv[t];
     double Di[9];
     sym_unpack(inv, Di);
-    int32_t qa = upq[2 * q], qb = upq[2 * q + 1];
     double T0[9];
     if (qa >= 0) {
-        double E0[9];
-        for (int t = 0; t < 9; t++) E0[t] = E[9 * (int64_t)q + t];   // A_{p,v}
-        mm3(E0, Di, T0);                                                // A_{p,v} D^{-1}
+        mm3(E0, Di, T0);   // A_{p,v} D^{-1}, A_{p,v} in E0
         for (int t = 0; t < 9; t++) F[9 * (int64_t)q + t] = T0[t];
         double *c = C + 6 * (2 * (int64_t)q);
         // A_{p,v} D^{-1} A_{v,p}: upper triangle of T0 E0^T
@@ -530,8 +552,7 @@ __global__ void k_factor_step(int32_t q0, int32_t q1, const int32_t *elim, const
         c[5] = T0[6] * E0[6] + T0[7] * E0[7] + T0[8] * E0[8];
     }
     if (qb >= 0) {
-        double E1[9], E1t[9], T1[9];
-        for (int t = 0; t < 9; t++) E1[t] = E[9 * (int64_t)qb + t];   // A_{v,c}
+        double E1t[9], T1[9];   // A_{v,c} in E1
         for (int a = 0; a < 3; a++)
             for (int b = 0; b < 3; b++) E1t[3 * a + b] = E1[3 * b + a];
         mm3(E1t, Di, T1);                                                   // A_{c,v} D^{-1}
