@@ -29,6 +29,8 @@
 
 #include <cmath>
 #include <cstring>
+#include <type_traits>
+#include <utility>
 
 namespace {
 
@@ -502,11 +504,59 @@ __global__ void k_add64(int64_t n, const float *a, int64_t lda, const float *b, 
 
 // ---------------------------------------------------------------- messages (16 lanes per row, four features per lane)
 
-// A row's entries are taken MSG_BATCH at a time: their column ids and edge
-// features first, then all their neighbour gathers, then the arithmetic in
-// entry order -- so a wave waits for memory twice per batch instead of twice
-// per entry.  The summation order is the entry order, as in a plain loop.
-constexpr int MSG_BATCH = 8;
+// A row's 16 lanes load the columns and edge features of 16 of its entries at
+// once, a lane each, and hand them round by DPP row broadcasts; the neighbour
+// gathers, which wait for the columns, go six, six and four at a time, then the
+// arithmetic in entry order, as in a plain loop.  Every lane loading every
+// entry's column and features (eight entries at a time, two waits per eight)
+// took twice the load instructions and 64 more registers: forward, 200k cells,
+// 93 -> 64 us.
+template <int U>
+SGP_DEV int row_bcast(int v)
+{
+    return __builtin_amdgcn_update_dpp(0, v, 0x150 + U, 0xf, 0xf, false);
+}
+template <int U>
+SGP_DEV float4 row_bcast(const float4 &v)
+{
+    return make_float4(__int_as_float(row_bcast<U>(__float_as_int(v.x))), __int_as_float(row_bcast<U>(__float_as_int(v.y))),
+                       __int_as_float(row_bcast<U>(__float_as_int(v.z))), __int_as_float(row_bcast<U>(__float_as_int(v.w))));
+}
+
+template <class F, int... U>
+SGP_DEV void static_for(std::integer_sequence<int, U...>, F f)
+{
+    (f(std::integral_constant<int, U>()), ...);
+}
+
+// entries OFF .. OFF + N - 1 of the lanes' 16 (cnt of them the row's, the rest
+// copies of its last): get(column) for all, then use(features, value) in order
+template <int OFF, int N, class Get, class Use>
+SGP_DEV void msg_group(int32_t jl, const float4 &el, int cnt, Get get, Use use)
+{
+    using Idx = std::make_integer_sequence<int, N>;
+    decltype(get(0)) v[N];
+    static_for(Idx(), [&](auto u) { v[u] = get(row_bcast<OFF + decltype(u)::value>(jl)); });
+    keep_loads_above();
+    static_for(Idx(), [&](auto u) {
+        const float4 e = row_bcast<OFF + decltype(u)::value>(el);
+        if (OFF + decltype(u)::value < cnt) use(e, v[u]);
+    });
+}
+
+template <class Get, class Use>
+SGP_DEV void msg_row(int32_t p, int32_t re, const int32_t *col, const float4 *ef, Get get, Use use)
+{
+    for (; p < re; p += 16) {
+        const int cnt = re - p < 16 ? re - p : 16;
+        const int32_t pc = min(p + (int)(threadIdx.x & 15), re - 1);
+        const int32_t jl = col[pc];
+        const float4 el = ef[pc];
+        msg_group<0, 6>(jl, el, cnt, get, use);
+        if (cnt > 6) msg_group<6, 6>(jl, el, cnt, get, use);
+        if (cnt > 12) msg_group<12, 4>(jl, el, cnt, get, use);
+    }
+}
 
 __global__ __launch_bounds__(256) void k_msg_fwd(int64_t n, const int32_t *rowptr, const int32_t *col,
                                                  const float4 *ef, const float *PQ, const float *bm,
@@ -522,41 +572,22 @@ __global__ __launch_bounds__(256) void k_msg_fwd(int64_t n, const int32_t *rowpt
     const float4 w0 = *(const float4 *)(Wc + f), w1 = *(const float4 *)(Wc + 64 + f);
     const float4 w2 = *(const float4 *)(Wc + 128 + f), w3 = *(const float4 *)(Wc + 192 + f);
     float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-    const int32_t re = rowptr[i + 1];
-    for (int32_t p = rowptr[i]; p < re; p += MSG_BATCH) {
-        // a batch's loads are unconditional (entries past the row's end
-        // reload its last one and are not summed) and precede every use: a
-        // load in a branch makes the compiler wait for it there
-        const int cnt = re - p < MSG_BATCH ? re - p : MSG_BATCH;
-        int32_t jj[MSG_BATCH];
-        float4 ee[MSG_BATCH], qv[MSG_BATCH];
-#pragma unroll
-        for (int u = 0; u < MSG_BATCH; u++) {
-            const int32_t pc = min(p + u, re - 1);
-            jj[u] = col[pc];
-            ee[u] = ef[pc];
-        }
-#pragma unroll
-        for (int u = 0; u < MSG_BATCH; u++) qv[u] = *(const float4 *)(PQ + (int64_t)jj[u] * 128 + 64 + f);
-        keep_loads_above();
-#pragma unroll
-        for (int u = 0; u < MSG_BATCH; u++)
-            if (u < cnt) {
-                const float4 e = ee[u], q = qv[u];
-                a0 += fmaxf(P0 + q.x + (e.x * w0.x + e.y * w1.x + e.z * w2.x + e.w * w3.x), 0.f);
-                a1 += fmaxf(P1 + q.y + (e.x * w0.y + e.y * w1.y + e.z * w2.y + e.w * w3.y), 0.f);
-                a2 += fmaxf(P2 + q.z + (e.x * w0.z + e.y * w1.z + e.z * w2.z + e.w * w3.z), 0.f);
-                a3 += fmaxf(P3 + q.w + (e.x * w0.w + e.y * w1.w + e.z * w2.w + e.w * w3.w), 0.f);
-            }
-    }
+    msg_row(
+        rowptr[i], rowptr[i + 1], col, ef, [&](int32_t j) { return *(const float4 *)(PQ + (int64_t)j * 128 + 64 + f); },
+        [&](const float4 &e, const float4 &q) {
+            a0 += fmaxf(P0 + q.x + (e.x * w0.x + e.y * w1.x + e.z * w2.x + e.w * w3.x), 0.f);
+            a1 += fmaxf(P1 + q.y + (e.x * w0.y + e.y * w1.y + e.z * w2.y + e.w * w3.y), 0.f);
+            a2 += fmaxf(P2 + q.z + (e.x * w0.z + e.y * w1.z + e.z * w2.z + e.w * w3.z), 0.f);
+            a3 += fmaxf(P3 + q.w + (e.x * w0.w + e.y * w1.w + e.z * w2.w + e.w * w3.w), 0.f);
+        });
     *(float4 *)(agg + i * 64 + f) = make_float4(a0, a1, a2, a3);
 }
 
 // dP_i = sum over row i of dz_p, dz_p = da_i [z_p > 0]; per-workgroup partials
-// of e_p^T dz_p (4 x 64).  Lanes and loads as in the forward messages (16 lanes
-// per row, four features per lane, a batch's loads unconditional and ahead of
-// their use; one wave per row with loads behind branches took 74 us instead of
-// 38 at 60k rows, and 63 instead of 28 in k_msg_bwd_q).  The grid is fixed (at most MSG_BWD_GRID workgroups);
+// of e_p^T dz_p (4 x 64).  Rows are walked as in the forward messages (60k
+// rows: 34 us, and 26 in k_msg_bwd_q; with every lane loading every entry's
+// column and features 38 and 28, one wave per row with loads behind branches 74
+// and 63).  The grid is fixed (at most MSG_BWD_GRID workgroups);
 // workgroup b (in XCD-contiguous order) walks its own contiguous run of 16-row
 // blocks in order.
 constexpr int MSG_BWD_GRID = 2048;
@@ -583,39 +614,24 @@ __global__ __launch_bounds__(256) void k_msg_bwd_p(int64_t n, const int32_t *row
         const float4 pq = *(const float4 *)(PQ + i * 128 + f), d4 = *(const float4 *)(da + i * ldda + f);
         const float P[4] = {pq.x + b4.x, pq.y + b4.y, pq.z + b4.z, pq.w + b4.w}, dai[4] = {d4.x, d4.y, d4.z, d4.w};
         float dp[4] = {0.f, 0.f, 0.f, 0.f};
-        const int32_t re = rowptr[i + 1];
-        for (int32_t p = rowptr[i]; p < re; p += MSG_BATCH) {
-            const int cnt = re - p < MSG_BATCH ? re - p : MSG_BATCH;
-            int32_t jj[MSG_BATCH];
-            float4 ee[MSG_BATCH], qv[MSG_BATCH];
+        msg_row(
+            rowptr[i], rowptr[i + 1], col, ef,
+            [&](int32_t j) { return *(const float4 *)(PQ + (int64_t)j * 128 + 64 + f); },
+            [&](const float4 &e, const float4 &q) {
+                const float z[4] = {P[0] + q.x + (e.x * w0.x + e.y * w1.x + e.z * w2.x + e.w * w3.x),
+                                    P[1] + q.y + (e.x * w0.y + e.y * w1.y + e.z * w2.y + e.w * w3.y),
+                                    P[2] + q.z + (e.x * w0.z + e.y * w1.z + e.z * w2.z + e.w * w3.z),
+                                    P[3] + q.w + (e.x * w0.w + e.y * w1.w + e.z * w2.w + e.w * w3.w)};
 #pragma unroll
-            for (int u = 0; u < MSG_BATCH; u++) {
-                const int32_t pc = min(p + u, re - 1);
-                jj[u] = col[pc];
-                ee[u] = ef[pc];
-            }
-#pragma unroll
-            for (int u = 0; u < MSG_BATCH; u++) qv[u] = *(const float4 *)(PQ + (int64_t)jj[u] * 128 + 64 + f);
-            keep_loads_above();
-#pragma unroll
-            for (int u = 0; u < MSG_BATCH; u++)
-                if (u < cnt) {
-                    const float4 e = ee[u], q = qv[u];
-                    const float z[4] = {P[0] + q.x + (e.x * w0.x + e.y * w1.x + e.z * w2.x + e.w * w3.x),
-                                        P[1] + q.y + (e.x * w0.y + e.y * w1.y + e.z * w2.y + e.w * w3.y),
-                                        P[2] + q.z + (e.x * w0.z + e.y * w1.z + e.z * w2.z + e.w * w3.z),
-                                        P[3] + q.w + (e.x * w0.w + e.y * w1.w + e.z * w2.w + e.w * w3.w)};
-#pragma unroll
-                    for (int k = 0; k < 4; k++) {
-                        const float dz = z[k] > 0.f ? dai[k] : 0.f;
-                        dp[k] += dz;
-                        g[0][k] += e.x * dz;
-                        g[1][k] += e.y * dz;
-                        g[2][k] += e.z * dz;
-                        g[3][k] += e.w * dz;
-                    }
+                for (int k = 0; k < 4; k++) {
+                    const float dz = z[k] > 0.f ? dai[k] : 0.f;
+                    dp[k] += dz;
+                    g[0][k] += e.x * dz;
+                    g[1][k] += e.y * dz;
+                    g[2][k] += e.z * dz;
+                    g[3][k] += e.w * dz;
                 }
-        }
+            });
         *(float4 *)(dPQ + i * 128 + f) = make_float4(dp[0], dp[1], dp[2], dp[3]);
     }
     // a wave's four row groups, then the four waves
@@ -639,7 +655,9 @@ __global__ __launch_bounds__(256) void k_msg_bwd_q(int64_t n, const int32_t *row
                                                    const float4 *ef, const float *PQ, const float *bm,
                                                    const float *Wc, const float *da, int64_t ldda, float *dPQ)
 {
-    constexpr int BATCH = 4;   // two gathers per entry
+    struct Two {
+        float4 p, d;
+    };
     const int64_t j = xcd_block(blockIdx.x, gridDim.x) * 16 + (threadIdx.x >> 4);
     const int f = 4 * (threadIdx.x & 15);
     if (j >= n) return;
@@ -647,33 +665,18 @@ __global__ __launch_bounds__(256) void k_msg_bwd_q(int64_t n, const int32_t *row
     const float4 w0 = *(const float4 *)(Wc + f), w1 = *(const float4 *)(Wc + 64 + f);
     const float4 w2 = *(const float4 *)(Wc + 128 + f), w3 = *(const float4 *)(Wc + 192 + f);
     float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-    const int32_t re = rowptr[j + 1];
-    for (int32_t p = rowptr[j]; p < re; p += BATCH) {
-        const int cnt = re - p < BATCH ? re - p : BATCH;
-        int32_t ii[BATCH];
-        float4 ee[BATCH], pv[BATCH], dv[BATCH];
-#pragma unroll
-        for (int u = 0; u < BATCH; u++) {
-            const int32_t pc = min(p + u, re - 1);
-            ii[u] = col[pc];
-            ee[u] = ef[pc];
-        }
-#pragma unroll
-        for (int u = 0; u < BATCH; u++) {
-            pv[u] = *(const float4 *)(PQ + (int64_t)ii[u] * 128 + f);
-            dv[u] = *(const float4 *)(da + (int64_t)ii[u] * ldda + f);
-        }
-        keep_loads_above();
-#pragma unroll
-        for (int u = 0; u < BATCH; u++)
-            if (u < cnt) {
-                const float4 e = ee[u], P = pv[u], d = dv[u];
-                a0 += (P.x + b4.x) + q4.x + (e.x * w0.x - e.y * w1.x - e.z * w2.x - e.w * w3.x) > 0.f ? d.x : 0.f;
-                a1 += (P.y + b4.y) + q4.y + (e.x * w0.y - e.y * w1.y - e.z * w2.y - e.w * w3.y) > 0.f ? d.y : 0.f;
-                a2 += (P.z + b4.z) + q4.z + (e.x * w0.z - e.y * w1.z - e.z * w2.z - e.w * w3.z) > 0.f ? d.z : 0.f;
-                a3 += (P.w + b4.w) + q4.w + (e.x * w0.w - e.y * w1.w - e.z * w2.w - e.w * w3.w) > 0.f ? d.w : 0.f;
-            }
-    }
+    msg_row(
+        rowptr[j], rowptr[j + 1], col, ef,
+        [&](int32_t i) {
+            return Two{*(const float4 *)(PQ + (int64_t)i * 128 + f), *(const float4 *)(da + (int64_t)i * ldda + f)};
+        },
+        [&](const float4 &e, const Two &v) {
+            const float4 P = v.p, d = v.d;
+            a0 += (P.x + b4.x) + q4.x + (e.x * w0.x - e.y * w1.x - e.z * w2.x - e.w * w3.x) > 0.f ? d.x : 0.f;
+            a1 += (P.y + b4.y) + q4.y + (e.x * w0.y - e.y * w1.y - e.z * w2.y - e.w * w3.y) > 0.f ? d.y : 0.f;
+            a2 += (P.z + b4.z) + q4.z + (e.x * w0.z - e.y * w1.z - e.z * w2.z - e.w * w3.z) > 0.f ? d.z : 0.f;
+            a3 += (P.w + b4.w) + q4.w + (e.x * w0.w - e.y * w1.w - e.z * w2.w - e.w * w3.w) > 0.f ? d.w : 0.f;
+        });
     *(float4 *)(dPQ + j * 128 + 64 + f) = make_float4(a0, a1, a2, a3);
 }
 
