@@ -105,6 +105,7 @@ struct sgp_mpnn_ {
     Layout L = make_layout();
     Packed PK = make_packed();
     DevBuf theta, m1, m2, grad, wbf, wrow;   // wrow: BF16-rounded master weights as FP32 (edge arithmetic)
+    DevBuf wfrag;                            // weights of the fused layers (k_pack_frag)
     DevBuf act, efeat, part, vq;   // vq: v_hat and Gamma v_hat (FP64, canonical order)
     DevBuf irow, icol;                      // neighbour lists in the internal order (with efeat)
     const void *lists_of = nullptr;         // graph and version they were built for
@@ -159,6 +160,26 @@ __global__ void k_pack(const float *theta, Layout L, Packed P, unsigned short *w
         v = r < 3 ? theta[L.W_out + c * 3 + r] : 0.f;
     }
     wbf[o] = f2bf(v);
+}
+
+// The matrices of the fused layers in fragment order (k_layer reads a lane's
+// four k-values of a 16 x 16 tile as one coalesced 8-byte load): per layer
+// W_u (halves h and a, 4 x 4 tiles each) and the matrix of the product behind
+// it, [W_a | W_b] of the next layer (4 x 8 tiles) or W_out (4 x 1).
+constexpr int FRAG_U = 2 * 4 * 4 * 64, FRAG_N = 4 * 8 * 64, FRAG_LAYER = FRAG_U + FRAG_N;
+__global__ void k_pack_frag(const unsigned short *wbf, Packed P, bf16x4 *out)
+{
+    const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (t >= NL * FRAG_LAYER) return;
+    const int l = t / FRAG_LAYER, e = t % FRAG_LAYER;
+    const bool up = e < FRAG_U, last = l == NL - 1;
+    const int f = up ? e : e - FRAG_U, lane = f & 63, NT = up ? 4 : last ? 1 : 8;
+    const int kt = (f >> 6) / NT, nt = (f >> 6) % NT, N = 16 * NT;   // (W_u: 8 k-tiles, a's after h's)
+    if (kt >= (up ? 8 : 4)) return;
+    const unsigned short *B = wbf + (up ? P.u[l] : last ? P.out16 : P.ab[l + 1]);
+    bf16x4 b;
+    for (int k = 0; k < 4; k++) b[k] = (short)B[(16 * kt + 4 * (lane >> 4) + k) * N + 16 * nt + (lane & 15)];
+    out[t] = b;
 }
 
 // ---------------------------------------------------------------- MFMA GEMM
@@ -230,83 +251,6 @@ __global__ __launch_bounds__(256) void k_gemm(const float *A, int64_t lda, const
                 const float o = accumulate ? cv[nt][t] + v : v;
                 C[row * ldc + 16 * nt + lr] = o;
                 if (R) R[row * ldc + 16 * nt + lr] = fmaxf(o, 0.f);
-            }
-        }
-    }
-}
-
-// One layer's node update in one pass: U = [h, a] W_u + b_u as the two
-// K = 64 products of the unfused form (h against rows 0..63 of W_u plus the
-// bias, then a against rows 64..127, added in that order), kept for a
-// backward pass (U null: none follows), and h' = h + relu(U).  The operations and their order are
-// those of two k_gemm launches and the residual pass, so the results are
-// the same bit for bit; h and a are read once and U is not read back.
-__global__ __launch_bounds__(256) void k_gemm_update(const float *H, const float *Ag, const unsigned short *B,
-                                                     const float *bias, float *U, float *Hn, int64_t M)
-{
-    constexpr int KT = 4, NT = 4, N = 64;
-    __shared__ bf16x4 sB[2 * KT * NT * 64];
-    for (int e = threadIdx.x; e < 2 * KT * NT * 64; e += 256) {
-        const int half = e / (KT * NT * 64), f = e % (KT * NT * 64);
-        const int ln = f & 63, tile = f >> 6, kt = tile / NT, nt = tile % NT;
-        bf16x4 b;
-        for (int t = 0; t < 4; t++)
-            b[t] = (short)B[(64 * half + 16 * kt + 4 * (ln >> 4) + t) * N + 16 * nt + (ln & 15)];
-        sB[e] = b;
-    }
-    __syncthreads();
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int lr = lane & 15, lg = lane >> 4;
-    for (int it = 0; it < GEMM_ROWS / 64; it++) {
-        const int64_t r0 = (int64_t)blockIdx.x * GEMM_ROWS + 64 * it + 16 * wv;
-        if (r0 >= M) break;
-        // Every load of the tile before any store, unconditional (rows past
-        // M read row M-1; their results are not stored): the fragments of h
-        // and a, and h at the lane's output positions for the residual.  A
-        // load behind a store, or in a branch, would wait for it.
-        const int64_t arow = min(r0 + lr, M - 1);
-        float hv[NT][4];
-#pragma unroll
-        for (int nt = 0; nt < NT; nt++)
-#pragma unroll
-            for (int t = 0; t < 4; t++) hv[nt][t] = H[min(r0 + 4 * lg + t, M - 1) * N + 16 * nt + lr];
-        float4 vh[KT], va[KT];
-#pragma unroll
-        for (int kt = 0; kt < KT; kt++) {
-            vh[kt] = *(const float4 *)(H + arow * 64 + 16 * kt + 4 * lg);
-            va[kt] = *(const float4 *)(Ag + arow * 64 + 16 * kt + 4 * lg);
-        }
-        float bv[NT];
-#pragma unroll
-        for (int nt = 0; nt < NT; nt++) bv[nt] = bias[16 * nt + lr];
-        keep_loads_above();
-        bf16x4 ah[KT], aa[KT];
-#pragma unroll
-        for (int kt = 0; kt < KT; kt++) {
-            ah[kt][0] = (short)f2bf(vh[kt].x);
-            ah[kt][1] = (short)f2bf(vh[kt].y);
-            ah[kt][2] = (short)f2bf(vh[kt].z);
-            ah[kt][3] = (short)f2bf(vh[kt].w);
-            aa[kt][0] = (short)f2bf(va[kt].x);
-            aa[kt][1] = (short)f2bf(va[kt].y);
-            aa[kt][2] = (short)f2bf(va[kt].z);
-            aa[kt][3] = (short)f2bf(va[kt].w);
-        }
-        for (int nt = 0; nt < NT; nt++) {
-            f32x4 acc1 = {0.f, 0.f, 0.f, 0.f}, acc2 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kt = 0; kt < KT; kt++) {
-                acc1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah[kt], sB[(kt * NT + nt) * 64 + lane], acc1, 0, 0, 0);
-                acc2 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(aa[kt], sB[KT * NT * 64 + (kt * NT + nt) * 64 + lane],
-                                                                 acc2, 0, 0, 0);
-            }
-            for (int t = 0; t < 4; t++) {
-                const int64_t row = r0 + 4 * lg + t;
-                if (row >= M) continue;
-                const int64_t o = row * N + 16 * nt + lr;
-                const float u = (acc1[t] + bv[nt]) + (acc2[t] + 0.f);
-                if (U) U[o] = u;
-                Hn[o] = hv[nt][t] + fmaxf(u, 0.f);
             }
         }
     }
@@ -544,43 +488,170 @@ SGP_DEV void msg_group(int32_t jl, const float4 &el, int cnt, Get get, Use use)
     });
 }
 
+// a row's up to 16 entries from p on, whose columns and features the lanes hold
+template <class Get, class Use>
+SGP_DEV void msg_16(int32_t p, int32_t re, int32_t jl, const float4 &el, Get get, Use use)
+{
+    const int cnt = re - p < 16 ? re - p : 16;
+    if (cnt > 0) msg_group<0, 6>(jl, el, cnt, get, use);
+    if (cnt > 6) msg_group<6, 6>(jl, el, cnt, get, use);
+    if (cnt > 12) msg_group<12, 4>(jl, el, cnt, get, use);
+}
+
 template <class Get, class Use>
 SGP_DEV void msg_row(int32_t p, int32_t re, const int32_t *col, const float4 *ef, Get get, Use use)
 {
     for (; p < re; p += 16) {
-        const int cnt = re - p < 16 ? re - p : 16;
         const int32_t pc = min(p + (int)(threadIdx.x & 15), re - 1);
         const int32_t jl = col[pc];
         const float4 el = ef[pc];
-        msg_group<0, 6>(jl, el, cnt, get, use);
-        if (cnt > 6) msg_group<6, 6>(jl, el, cnt, get, use);
-        if (cnt > 12) msg_group<12, 4>(jl, el, cnt, get, use);
+        msg_16(p, re, jl, el, get, use);
     }
 }
 
-__global__ __launch_bounds__(256) void k_msg_fwd(int64_t n, const int32_t *rowptr, const int32_t *col,
-                                                 const float4 *ef, const float *PQ, const float *bm,
-                                                 const float *Wc, float *agg)
+// One layer of the network in one pass: the messages a of 16 rows per wave, U =
+// [h, a] W_u + b_u as two K = 64 products (h's plus the bias, then a's, added in
+// that order), h' = h + relu(U), and the product behind it, h' [W_a | W_b] of
+// the next layer or h' W_out.  a and h' pass from one step to the next in LDS
+// (fragments want a lane's k-values of one row, results come as rows of a
+// column).  a, U (null: no backward pass follows) and h' (null: after the last
+// layer) are stored for others.  Bound by the gathers of the messages (64 us
+// alone at 200k rows); as four passes over memory (messages, update, product)
+// a layer of 200k rows took 129 us instead of 116, the last one 113 instead of
+// 79.  Four waves per SIMD fit 128 registers; with three it took 133.
+// Rows past n are computed from row n - 1 and not stored.
+constexpr int LAYER_ROWS = 64, LAYER_LD = 68;   // (16-byte rows, four banks apart)
+template <int NT2>
+__global__ __launch_bounds__(256, 4) void k_layer(int64_t n, const int32_t *rowptr, const int32_t *col, const float4 *ef,
+                                               const float *PQ, const float *bm, const float *Wc, const float *H,
+                                               const bf16x4 *Bu, const float *bias, const bf16x4 *B2, float *agg,
+                                               float *U, float *Hn, float *C, int64_t ldc)
 {
-    // 16 lanes per node, four features per lane (one 16-byte load of a
-    // neighbour's 64 features per 16 lanes), 16 nodes per workgroup
-    const int64_t i = xcd_block(blockIdx.x, gridDim.x) * 16 + (threadIdx.x >> 4);
-    const int f = 4 * (threadIdx.x & 15);
-    if (i >= n) return;
-    const float4 pq = *(const float4 *)(PQ + i * 128 + f), b4 = *(const float4 *)(bm + f);
-    const float P0 = pq.x + b4.x, P1 = pq.y + b4.y, P2 = pq.z + b4.z, P3 = pq.w + b4.w;
+    constexpr int KT = 4, NT = 4, N = 64;
+    __shared__ float st[4][16][LAYER_LD], sth[4][16][LAYER_LD];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int lr = lane & 15, lg = lane >> 4, f = 4 * lr;
+    const int64_t r0 = xcd_block(blockIdx.x, gridDim.x) * LAYER_ROWS + 16 * wv;
+    if (r0 >= n) return;
+    float(*s)[LAYER_LD] = st[wv], (*sh)[LAYER_LD] = sth[wv];
+    // messages: 16 lanes per row, four features per lane, rows 4 k + lg in turn;
+    // the ranges, then the first 16 entries' columns and features of all four
+    int32_t p0[4], p1[4], jl[4];
+    float4 el[4], pq[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        const int64_t i = min(r0 + 4 * k + lg, n - 1);
+        p0[k] = rowptr[i];
+        p1[k] = rowptr[i + 1];
+        pq[k] = *(const float4 *)(PQ + i * 128 + f);
+    }
+    const float4 b4 = *(const float4 *)(bm + f);
     const float4 w0 = *(const float4 *)(Wc + f), w1 = *(const float4 *)(Wc + 64 + f);
     const float4 w2 = *(const float4 *)(Wc + 128 + f), w3 = *(const float4 *)(Wc + 192 + f);
-    float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-    msg_row(
-        rowptr[i], rowptr[i + 1], col, ef, [&](int32_t j) { return *(const float4 *)(PQ + (int64_t)j * 128 + 64 + f); },
-        [&](const float4 &e, const float4 &q) {
+    keep_loads_above();
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        // (a row without entries: entry 0, or the rows' end less one, unused)
+        const int32_t pc = max(min(p0[k] + lr, p1[k] - 1), 0);
+        jl[k] = p1[k] > p0[k] ? col[pc] : 0;
+        el[k] = p1[k] > p0[k] ? ef[pc] : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        const float P0 = pq[k].x + b4.x, P1 = pq[k].y + b4.y, P2 = pq[k].z + b4.z, P3 = pq[k].w + b4.w;
+        float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+        auto get = [&](int32_t j) { return *(const float4 *)(PQ + (int64_t)j * 128 + 64 + f); };
+        auto use = [&](const float4 &e, const float4 &q) {
             a0 += fmaxf(P0 + q.x + (e.x * w0.x + e.y * w1.x + e.z * w2.x + e.w * w3.x), 0.f);
             a1 += fmaxf(P1 + q.y + (e.x * w0.y + e.y * w1.y + e.z * w2.y + e.w * w3.y), 0.f);
             a2 += fmaxf(P2 + q.z + (e.x * w0.z + e.y * w1.z + e.z * w2.z + e.w * w3.z), 0.f);
             a3 += fmaxf(P3 + q.w + (e.x * w0.w + e.y * w1.w + e.z * w2.w + e.w * w3.w), 0.f);
-        });
-    *(float4 *)(agg + i * 64 + f) = make_float4(a0, a1, a2, a3);
+        };
+        msg_16(p0[k], p1[k], jl[k], el[k], get, use);
+        if (p1[k] - p0[k] > 16) msg_row(p0[k] + 16, p1[k], col, ef, get, use);
+        const float4 a = make_float4(a0, a1, a2, a3);
+        *(float4 *)&s[4 * k + lg][f] = a;
+        const int64_t i = r0 + 4 * k + lg;
+        if (agg && i < n) *(float4 *)(agg + i * 64 + f) = a;
+    }
+    // update: the fragments of h and a, and h at the lane's output positions,
+    // all from LDS (whole rows in and out of memory: a lane's four values of
+    // one column are four rows, 64 bytes a row and instruction)
+    float4 hr[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) hr[k] = *(const float4 *)(H + min(r0 + 4 * k + lg, n - 1) * 64 + f);
+    float bv[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++) bv[nt] = bias[16 * nt + lr];
+#pragma unroll
+    for (int k = 0; k < 4; k++) *(float4 *)&sh[4 * k + lg][f] = hr[k];
+    lds_wave_barrier();
+    auto frag = [](const float4 &v) {
+        bf16x4 b;
+        b[0] = (short)f2bf(v.x);
+        b[1] = (short)f2bf(v.y);
+        b[2] = (short)f2bf(v.z);
+        b[3] = (short)f2bf(v.w);
+        return b;
+    };
+    bf16x4 ah[KT], aa[KT];
+#pragma unroll
+    for (int kt = 0; kt < KT; kt++) {
+        ah[kt] = frag(*(const float4 *)&sh[lr][16 * kt + 4 * lg]);
+        aa[kt] = frag(*(const float4 *)&s[lr][16 * kt + 4 * lg]);
+    }
+    lds_wave_barrier();
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++) {
+        f32x4 acc1 = {0.f, 0.f, 0.f, 0.f}, acc2 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kt = 0; kt < KT; kt++) {
+            acc1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah[kt], Bu[(kt * NT + nt) * 64 + lane], acc1, 0, 0, 0);
+            acc2 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(aa[kt], Bu[((KT + kt) * NT + nt) * 64 + lane], acc2, 0, 0,
+                                                             0);
+        }
+#pragma unroll
+        for (int t = 0; t < 4; t++) {
+            const int64_t row = r0 + 4 * lg + t, o = row * N + 16 * nt + lr;
+            const float u = (acc1[t] + bv[nt]) + (acc2[t] + 0.f);
+            if (U && row < n) U[o] = u;
+            s[4 * lg + t][16 * nt + lr] = sh[4 * lg + t][16 * nt + lr] + fmaxf(u, 0.f);
+        }
+    }
+    lds_wave_barrier();
+    // whole rows of LDS to memory
+    auto store_rows = [&](const float(*src)[LAYER_LD], float *dst, int64_t ld) {
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const int64_t i = r0 + 4 * k + lg;
+            if (i < n) *(float4 *)(dst + i * ld + f) = *(const float4 *)&src[4 * k + lg][f];
+        }
+    };
+    if (Hn) store_rows(s, Hn, 64);
+    // the product behind it
+    bf16x4 an[KT];
+#pragma unroll
+    for (int kt = 0; kt < KT; kt++) an[kt] = frag(*(const float4 *)&s[lr][16 * kt + 4 * lg]);
+#pragma unroll
+    for (int nt = 0; nt < NT2; nt++) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kt = 0; kt < KT; kt++)
+            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(an[kt], B2[(kt * NT2 + nt) * 64 + lane], acc, 0, 0, 0);
+#pragma unroll
+        for (int t = 0; t < 4; t++) {
+            const int64_t row = r0 + 4 * lg + t;
+            if (NT2 >= 4)
+                sh[4 * lg + t][16 * (nt & 3) + lr] = acc[t] + 0.f;
+            else if (row < n)
+                C[row * ldc + 16 * nt + lr] = acc[t] + 0.f;
+        }
+        if (NT2 >= 4 && (nt & 3) == 3) {   // four tiles make 64 columns of the rows
+            lds_wave_barrier();
+            store_rows(sh, C + 16 * (nt - 3), ldc);
+            lds_wave_barrier();
+        }
+    }
 }
 
 // dP_i = sum over row i of dz_p, dz_p = da_i [z_p > 0]; per-workgroup partials
@@ -919,15 +990,25 @@ int forward(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, Act &A, bool keep)
     const float4 *ef = (const float4 *)M->efeat.p;
     // input layer: pre0 kept for the backward pass, h0 = relu(pre0) in the same pass
     SGP_TRY(gemm(ctx, A.x16, 16, W + PK.in16, A.pre0, 64, n, 16, 64, wr + L.b_in, 0, A.h[0]));
-    for (int l = 0; l < NL; l++) {
-        SGP_TRY(gemm(ctx, A.h[l], 64, W + PK.ab[l], A.PQ, 128, n, 64, 128, nullptr, 0));
-        k_msg_fwd<<<grid_for(n, 16), 256, 0, st>>>(n, rowptr, col, ef, A.PQ, wr + L.b_m[l], wr + L.W_c[l], A.a[l]);
-        if (n > 0)
-            k_gemm_update<<<grid_for(n, GEMM_ROWS), 256, 0, st>>>(A.h[l], A.a[l], W + PK.u[l], wr + L.b_u[l],
-                                                                  keep ? A.U[l] : nullptr, A.h[l + 1], n);
+    SGP_TRY(gemm(ctx, A.h[0], 64, W + PK.ab[0], A.PQ, 128, n, 64, 128, nullptr, 0));
+    // the layers gather from one PQ and write the next one's to the other
+    // buffer (dPQ, free in a forward pass); the last layer's is in PQ
+    static_assert(NL % 2 == 1, "the last layer reads A.PQ");
+    const bf16x4 *B = (const bf16x4 *)M->wfrag.p;
+    const unsigned grid = (unsigned)((n + LAYER_ROWS - 1) / LAYER_ROWS);
+    for (int l = 0; l < NL && n > 0; l++, B += FRAG_LAYER) {
+        float *agg = keep ? A.a[l] : nullptr, *U = keep ? A.U[l] : nullptr;
+        const float *PQ = l % 2 ? A.dPQ : A.PQ;
+        if (l < NL - 1)
+            k_layer<8><<<grid, 256, 0, st>>>(n, rowptr, col, ef, PQ, wr + L.b_m[l], wr + L.W_c[l], A.h[l], B,
+                                             wr + L.b_u[l], B + FRAG_U, agg, U, A.h[l + 1], l % 2 ? A.PQ : A.dPQ, 128);
+        else   // (b_out is added where the output is read: k_output, k_loss)
+            k_layer<1><<<grid, 256, 0, st>>>(n, rowptr, col, ef, PQ, wr + L.b_m[l], wr + L.W_c[l], A.h[l], B,
+                                             wr + L.b_u[l], B + FRAG_U, agg, U, keep ? A.h[l + 1] : nullptr, A.out16,
+                                             16);
     }
-    // (b_out is added where the output is read: k_output, k_loss)
-    return gemm(ctx, A.h[NL], 64, W + PK.out16, A.out16, 16, n, 64, 16, nullptr, 0);
+    LAUNCH_CHECK(ctx);
+    return SGP_OK;
 }
 
 int backward(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, Act &A)
@@ -986,6 +1067,9 @@ int repack(sgp_ctx ctx, sgp_mpnn M)
     SGP_TRY(ensure_t(ctx, M->wrow, (size_t)M->L.total + 8, &wr));
     int64_t cnt = std::max<int64_t>(M->PK.total, M->L.total);
     k_pack<<<grid_for(cnt, 256), 256, 0, ctx->stream>>>((const float *)M->theta.p, M->L, M->PK, wbf, wr);
+    bf16x4 *fr;
+    SGP_TRY(ensure_t(ctx, M->wfrag, (size_t)NL * FRAG_LAYER, &fr));
+    k_pack_frag<<<grid_for(NL * FRAG_LAYER, 256), 256, 0, ctx->stream>>>(wbf, M->PK, fr);
     LAUNCH_CHECK(ctx);
     return SGP_OK;
 }
@@ -1012,7 +1096,7 @@ extern "C" void sgp_mpnn_free(sgp_mpnn M)
 {
     if (!M) return;
     (void)hipDeviceSynchronize();
-    release(M->theta); release(M->m1); release(M->m2); release(M->grad); release(M->wbf); release(M->wrow);
+    release(M->theta); release(M->m1); release(M->m2); release(M->grad); release(M->wbf); release(M->wfrag); release(M->wrow);
     release(M->act); release(M->efeat); release(M->part); release(M->vq);
     release(M->irow); release(M->icol);
     delete M;
