@@ -1501,8 +1501,7 @@ __global__ __launch_bounds__(256) void k_top(int32_t Qt, int32_t nt, const int32
     T o = 0;
 #pragma unroll
     for (int u = 0; u < ROWS; u++) {
-        T w = acc[u];
-        for (int e = 32; e > 0; e >>= 1) w = w + __shfl_xor(w, e, 64);
+        const T w = wave_sum(acc[u]);
         o = lane == u ? w : o;
     }
     if (lane < ROWS && row0 + lane < N) {

@@ -122,7 +122,7 @@ enum { FIN_ALPHA, FIN_RR_BETA, FIN_RHO, FIN_INIT, FIN_TRUE, FIN_NORM2 };
 // (one pass covers the 1M-cell product's 10k partials), so the partials,
 // just written by the producer, cost one round trip instead of one per
 // FIN_THREADS.  Each thread adds its U sums pairwise, each wave folds its
-// lanes by a butterfly and thread 0 adds the waves in order.  Results valid
+// lanes by a pairwise tree and thread 0 adds the waves in order.  Results valid
 // in thread 0.  sh holds NA * FIN_THREADS / 64 doubles.
 constexpr int FIN_THREADS = 1024;
 
@@ -152,8 +152,7 @@ SGP_DEV void sum_partials(const double *part, int64_t ns, int n, double *sh, dou
         for (int h = U / 2; h > 0; h >>= 1)
 #pragma unroll
             for (int j = 0; j < h; j++) acc[a][j] = acc[a][j] + acc[a][j + h];
-        double v = acc[a][0];
-        for (int o = 32; o > 0; o >>= 1) v = v + __shfl_xor(v, o, 64);
+        const double v = wave_sum(acc[a][0]);
         if ((threadIdx.x & 63) == 0) sh[a * (B / 64) + (threadIdx.x >> 6)] = v;
     }
     __syncthreads();

@@ -442,6 +442,20 @@ SGP_DEV double add_swap_16(double v)
 // without LDS.  All lanes active.
 SGP_DEV double wave_sum(double v) { return row_sum_16(add_swap_16(add_swap_32(v))); }
 
+template <int N>
+SGP_DEV float add_row_ror(float v)
+{
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, true));
+}
+SGP_DEV float wave_sum(float v)
+{
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_int(v), __float_as_int(v), false, false);
+    v = __int_as_float((int)a[0]) + __int_as_float((int)a[1]);
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_int(v), __float_as_int(v), false, false);
+    v = __int_as_float((int)b[0]) + __int_as_float((int)b[1]);
+    return add_row_ror<1>(add_row_ror<2>(add_row_ror<4>(add_row_ror<8>(v))));
+}
+
 // Sum over a 256-thread block in every thread: the pairwise tree of distances
 // 128, 64, .., 1.  The distances down to 16 are the thread's own additions of
 // 16 values from LDS, the rest stay in a row of lanes: two barriers instead of

@@ -364,7 +364,7 @@ __global__ __launch_bounds__(256) void k_spmv_tile(TileArgs A, const T *__restri
         d = ((double)p0 * (double)y0 + (double)p1 * (double)y1) + (double)p2 * (double)y2;
     }
     if (mode) {
-        for (int o = 32; o > 0; o >>= 1) d = d + __shfl_xor(d, o, 64);
+        d = wave_sum(d);
         if ((tid & 63) == 0) sh[tid >> 6] = d;
         __syncthreads();
         if (tid == 0) part[tile] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
