@@ -47,8 +47,14 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, published
 # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, the factors that make a 512 MiB copy
 # read and write 512 MiB (summary and commands under profiles/).  Must be
 # re-measured, or set to None, whenever that kernel changes.
-SPMV_TRAFFIC_1M = {0: None, 1: 136.8e6}
-TILE_MIN_CELLS = 8192   # beyond it form 1 is the product from the cells
+SPMV_TRAFFIC_1M = {0: None, 1: None, 2: 140.1e6}
+TILE_MIN_CELLS = 8192   # beyond it the library's edge form is the product from the cells
+
+
+def product_form(knob: int, n: int) -> int:
+    """Form of spmv_bytes that the library runs: its knob spmv_form (0 blocks,
+    1 contacts), the latter from the cells (2) beyond TILE_MIN_CELLS cells."""
+    return 2 if knob == 1 and n > TILE_MIN_CELLS else knob
 
 
 def spmv_bytes(n: int, nnzb: int, form: int = 1, val_bytes: int = 48) -> int:
@@ -57,12 +63,12 @@ def spmv_bytes(n: int, nnzb: int, form: int = 1, val_bytes: int = 48) -> int:
     symmetric, 48 B in FP64) and its column index once.  Edge form (form 1):
     every off-diagonal entry's v = sqrt(w) u (24 B) and column once, every
     diagonal block's 6 entries once.  Both: the row pointers once, x once, y
-    once.  From the cells (form 1, more than TILE_MIN_CELLS cells): every
-    entry's 16-bit number, every cell's position and radius, x and y once."""
+    once.  From the cells (form 2): every entry's 16-bit number, every cell's
+    position and radius, x and y once."""
     if form == 0:
         return nnzb * (val_bytes + 4) + 4 * (n + 1) + 24 * n + 24 * n
     ne = nnzb - n
-    if n > TILE_MIN_CELLS:
+    if form == 2:
         return ne * 2 + n * (32 + 24 + 24)
     return ne * (24 + 4) + n * 48 + 4 * (n + 1) + 24 * n + 24 * n
 
@@ -512,7 +518,7 @@ def main():
         print(json.dumps({"kernel": ("k_spmv_tile" if n > TILE_MIN_CELLS else "k_spmv_edge")
                           if ctx.tune_get("spmv_form") else "k_spmv_sym",
                           "copy_bytes": 2 * src.numel() * 8, "api_call_avg_ms": ms,
-                          "bytes_per_launch": spmv_bytes(n, nnzb, ctx.tune_get("spmv_form")),
+                          "bytes_per_launch": spmv_bytes(n, nnzb, product_form(ctx.tune_get("spmv_form"), n)),
                           "note": "api_call_avg_ms includes the two permutations of sgp_spmv; the kernel alone is in the trace"}), flush=True)
         ctx.close()
         return
@@ -537,7 +543,7 @@ def main():
     _, nnzb = A.size()
     nt, n_roots, max_depth = T.size()
     avg_spmv_ms = spmv_ms / max(spmv_launches, 1)
-    form = ctx.tune_get("spmv_form")
+    form = product_form(ctx.tune_get("spmv_form"), n)
     bytes_spmv = spmv_bytes(n, nnzb, form)
     achieved = bytes_spmv / (avg_spmv_ms * 1e-3) / 1e9
     out = {
@@ -558,9 +564,9 @@ def main():
                    "schedule": args.schedule, "elim_steps": M.steps(), "cg_iters": info.get("iters"),
                    "relres_true": info.get("relres_true")},
         "roofline": {"bound": "hbm",
-                     "kernel": ("k_spmv_tile (Gamma p from the cells, in CG)" if n > TILE_MIN_CELLS
-                                else "k_spmv_edge (Gamma p from contacts, in CG)") if form
-                     else "k_spmv_sym (block-CSR product, in CG)",
+                     "kernel": ("k_spmv_sym (block-CSR product, in CG)",
+                                "k_spmv_edge (Gamma p from contacts, in CG)",
+                                "k_spmv_tile (Gamma p from the cells, in CG)")[form],
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "traffic": SPMV_TRAFFIC_1M[form] if (args.n == 1_000_000 and ctx.tune_get("spmv_waves") == 4) else None,
