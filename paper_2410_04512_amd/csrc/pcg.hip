@@ -119,7 +119,7 @@ enum { FIN_ALPHA, FIN_RR_BETA, FIN_RHO, FIN_INIT, FIN_TRUE, FIN_NORM2 };
 // arrays (stride ns) at once: thread t owns the interleaved sequence t,
 // t+FIN_THREADS, ...; position j of a pass of U * FIN_THREADS partials goes
 // to running sum j mod U, and all U * NA loads of a pass are issued together
-// (one pass covers the 1M-cell product's 10k partials), so the partials,
+// (one pass covers 16k partials), so the partials,
 // just written by the producer, cost one round trip instead of one per
 // FIN_THREADS.  Each thread adds its U sums pairwise, each wave folds its
 // lanes by a pairwise tree and thread 0 adds the waves in order.  Results valid

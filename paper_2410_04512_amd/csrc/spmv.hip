@@ -17,7 +17,7 @@
 // in storage order.  A row is never split between waves, so every row sum has
 // one fixed order and the product is bitwise reproducible.
 //
-// Edge form (the default for the CG): the same product from the contacts
+// Edge form (the CG's up to TILE_MIN_CELLS cells; beyond, tile.hip): the same product from the contacts
 // themselves, q_i = D_i p_i - sum_j W_ij p_j with
 // W_ij p = w (g_perp p + (g_par - g_perp) (u . p) u) (eq. cell_cell_friction),
 // so an off-diagonal entry costs its (w, u) and column (36 bytes) instead of a
