@@ -184,7 +184,7 @@ __global__ void k_pack_frag(const unsigned short *wbf, Packed P, bf16x4 *out)
 
 // ---------------------------------------------------------------- MFMA GEMM
 //
-// C[M x N] (=|+=) A[M x K] B[K x N] (+ bias): A FP32 row-major (lda), B BF16
+// C[M x N] = A[M x K] B[K x N] (+ bias): A FP32 row-major (lda), B BF16
 // row-major K x N, K = 16 KT and N multiples of 16 (<= 128).
 // v_mfma_f32_16x16x16_bf16 lane layout (wave64): lane l holds
 //   A[l % 16][4 (l / 16) + t], B[4 (l / 16) + t][l % 16], D[4 (l / 16) + t][l % 16], t = 0..3.
@@ -195,10 +195,21 @@ __global__ void k_pack_frag(const unsigned short *wbf, Packed P, bf16x4 *out)
 // several tiles per wave, whose loads would wait for the previous tile).
 constexpr int GEMM_ROWS = 64;
 
-template <int KT>
+// What a product of the backward pass does with its result (BACK, N = 64, rows
+// of 64 values): add1 + add2 (null: nothing) is added, the sum goes to C (null:
+// not needed) and, where mask > 0, to dU, else 0 there.  Sums in the order of
+// passes of their own, which read and wrote the rows once more each (60k cells:
+// 13 us a mask, 10 us an addition).
+struct GemmBack {
+    const float *add1, *add2;
+    int64_t ld2;
+    const float *mask;
+    float *dU;
+};
+
+template <int KT, bool BACK>
 __global__ __launch_bounds__(256) void k_gemm(const float *A, int64_t lda, const unsigned short *B, float *C,
-                                              int64_t ldc, int64_t M, int N, const float *bias, int accumulate,
-                                              float *R)
+                                              int64_t ldc, int64_t M, int N, const float *bias, float *R, GemmBack bk)
 {
     __shared__ bf16x4 sB[KT * 8 * 64];
     const int NT = N >> 4;
@@ -221,12 +232,20 @@ __global__ __launch_bounds__(256) void k_gemm(const float *A, int64_t lda, const
         float4 av[KT];
 #pragma unroll
         for (int kt = 0; kt < KT; kt++) av[kt] = *(const float4 *)(A + arow * lda + 16 * kt + 4 * lg);
-        float bv[8], cv[8][4];
+        float bv[8], c1[BACK ? 4 : 1][4], c2[BACK ? 4 : 1][4], mk[BACK ? 4 : 1][4];
 #pragma unroll
-        for (int nt = 0; nt < 8; nt++) {
-            bv[nt] = bias && nt < NT ? bias[16 * nt + lr] : 0.f;
-            if (accumulate && nt < NT)
-                for (int t = 0; t < 4; t++) cv[nt][t] = C[min(r0 + 4 * lg + t, M - 1) * ldc + 16 * nt + lr];
+        for (int nt = 0; nt < 8; nt++) bv[nt] = bias && nt < NT ? bias[16 * nt + lr] : 0.f;
+        if (BACK) {
+#pragma unroll
+            for (int nt = 0; nt < 4; nt++)
+#pragma unroll
+                for (int t = 0; t < 4; t++) {
+                    const int64_t row = min(r0 + 4 * lg + t, M - 1);
+                    const int c = 16 * nt + lr;
+                    mk[nt][t] = bk.mask[row * 64 + c];
+                    c1[nt][t] = bk.add1 ? bk.add1[row * 64 + c] : 0.f;
+                    c2[nt][t] = bk.add1 ? bk.add2[row * bk.ld2 + c] : 0.f;
+                }
         }
         keep_loads_above();
         bf16x4 a[KT];
@@ -238,8 +257,8 @@ __global__ __launch_bounds__(256) void k_gemm(const float *A, int64_t lda, const
             a[kt][3] = (short)f2bf(av[kt].w);
         }
 #pragma unroll
-        for (int nt = 0; nt < 8; nt++) {
-            if (nt >= NT) break;
+        for (int nt = 0; nt < (BACK ? 4 : 8); nt++) {
+            if (!BACK && nt >= NT) break;
             f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kt = 0; kt < KT; kt++)
@@ -248,9 +267,14 @@ __global__ __launch_bounds__(256) void k_gemm(const float *A, int64_t lda, const
                 const int64_t row = r0 + 4 * lg + t;
                 if (row >= M) continue;
                 const float v = acc[t] + bv[nt];
-                const float o = accumulate ? cv[nt][t] + v : v;
-                C[row * ldc + 16 * nt + lr] = o;
-                if (R) R[row * ldc + 16 * nt + lr] = fmaxf(o, 0.f);
+                if (BACK) {
+                    const float o = bk.add1 ? (c1[nt][t] + c2[nt][t]) + v : v;
+                    if (C) C[row * 64 + 16 * nt + lr] = o;
+                    bk.dU[row * 64 + 16 * nt + lr] = mk[nt][t] > 0.f ? o : 0.f;
+                    continue;
+                }
+                C[row * ldc + 16 * nt + lr] = v;
+                if (R) R[row * ldc + 16 * nt + lr] = fmaxf(v, 0.f);
             }
         }
     }
@@ -427,23 +451,6 @@ __global__ void k_int_entries(int64_t n, const int32_t *perm, const int32_t *inv
         icol[k0 + c] = inv[j];
         ef[k0 + c] = make_float4((float)(q.x / sW), sg * (float)q.y, sg * (float)q.z, sg * (float)q.w);
     }
-}
-
-// dst = src * (mask > 0)
-__global__ void k_mask(int64_t len, const float *src, const float *mask, float *dst)
-{
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < len) dst[t] = mask[t] > 0.f ? src[t] : 0.f;
-}
-
-// dst (row stride ldd) = a (row stride lda) + b (row stride ldb), 64 columns
-__global__ void k_add64(int64_t n, const float *a, int64_t lda, const float *b, int64_t ldb, float *dst, int64_t ldd)
-{
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n * 64) return;
-    int64_t i = t / 64;
-    int c = (int)(t % 64);
-    dst[i * ldd + c] = a[i * lda + c] + b[i * ldb + c];
 }
 
 // ---------------------------------------------------------------- messages (16 lanes per row, four features per lane)
@@ -902,18 +909,27 @@ Act carve(float *base, int64_t n)
 }
 
 int gemm(sgp_ctx ctx, const float *A, int64_t lda, const unsigned short *B, float *C, int64_t ldc, int64_t M, int K,
-         int N, const float *bias, int acc, float *relu_out = nullptr)
+         int N, const float *bias, float *relu_out = nullptr)
 {
     if (M <= 0) return SGP_OK;
     const int64_t nb = grid_for(M, GEMM_ROWS);
     hipStream_t st = ctx->stream;
     float *R = relu_out;
     switch (K) {
-    case 16: k_gemm<1><<<nb, 256, 0, st>>>(A, lda, B, C, ldc, M, N, bias, acc, R); break;
-    case 64: k_gemm<4><<<nb, 256, 0, st>>>(A, lda, B, C, ldc, M, N, bias, acc, R); break;
-    case 128: k_gemm<8><<<nb, 256, 0, st>>>(A, lda, B, C, ldc, M, N, bias, acc, R); break;
+    case 16: k_gemm<1, false><<<nb, 256, 0, st>>>(A, lda, B, C, ldc, M, N, bias, R, {}); break;
+    case 64: k_gemm<4, false><<<nb, 256, 0, st>>>(A, lda, B, C, ldc, M, N, bias, R, {}); break;
     default: return set_err(ctx, SGP_EINVAL, "mpnn gemm: unsupported K");
     }
+    LAUNCH_CHECK(ctx);
+    return SGP_OK;
+}
+
+// a product of the backward pass with N = 64 (GemmBack)
+template <int KT>
+int gemm_back(sgp_ctx ctx, const float *A, const unsigned short *B, float *C, int64_t M, const GemmBack &bk)
+{
+    if (M <= 0) return SGP_OK;
+    k_gemm<KT, true><<<grid_for(M, GEMM_ROWS), 256, 0, ctx->stream>>>(A, 16 * KT, B, C, 64, M, 64, nullptr, nullptr, bk);
     LAUNCH_CHECK(ctx);
     return SGP_OK;
 }
@@ -989,8 +1005,8 @@ int forward(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, Act &A, bool keep)
     const int32_t *rowptr = (const int32_t *)M->irow.p, *col = (const int32_t *)M->icol.p;   // internal order
     const float4 *ef = (const float4 *)M->efeat.p;
     // input layer: pre0 kept for the backward pass, h0 = relu(pre0) in the same pass
-    SGP_TRY(gemm(ctx, A.x16, 16, W + PK.in16, A.pre0, 64, n, 16, 64, wr + L.b_in, 0, A.h[0]));
-    SGP_TRY(gemm(ctx, A.h[0], 64, W + PK.ab[0], A.PQ, 128, n, 64, 128, nullptr, 0));
+    SGP_TRY(gemm(ctx, A.x16, 16, W + PK.in16, A.pre0, 64, n, 16, 64, wr + L.b_in, A.h[0]));
+    SGP_TRY(gemm(ctx, A.h[0], 64, W + PK.ab[0], A.PQ, 128, n, 64, 128, nullptr));
     // the layers gather from one PQ and write the next one's to the other
     // buffer (dPQ, free in a forward pass); the last layer's is in PQ
     static_assert(NL % 2 == 1, "the last layer reads A.PQ");
@@ -1025,16 +1041,16 @@ int backward(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, Act &A)
     // output layer: W_out rows 0..63 x columns 0..2 of h^T dout, b_out = column sums
     SGP_TRY((gemm_at<4, 0, 1>(ctx, M, A.h[NL], 64, nullptr, 0, A.dout16, 16, n,
                               {G + L.W_out, nullptr, G + L.b_out, 0, 0, 64, 3, 3, 3})));
-    SGP_TRY(gemm(ctx, A.dout16, 16, W + PK.out16T, A.dh, 64, n, 16, 64, nullptr, 0));
+    // dh of the last layer's output, and dU = dh where U > 0
+    SGP_TRY(gemm_back<1>(ctx, A.dout16, W + PK.out16T, A.dh, n, {nullptr, nullptr, 0, A.U[NL - 1], A.dU}));
     for (int l = NL - 1; l >= 0; l--) {
-        k_mask<<<grid_for(64 * n, 256), 256, 0, st>>>(64 * n, A.dh, A.U[l], A.dU);
         // W_u = [h | a]^T dU, b_u = column sums of dU
         SGP_TRY((gemm_at<4, 4, 4>(ctx, M, A.h[l], 64, A.a[l], 64, A.dU, 64, n,
                                   {G + L.W_u[l], nullptr, G + L.b_u[l], 0, 0, 128, 64, 64, 64})));
-        SGP_TRY(gemm(ctx, A.dU, 64, W + PK.uT[l], A.dcat, 128, n, 64, 128, nullptr, 0));   // [dh part | da]
+        SGP_TRY(gemm(ctx, A.dU, 64, W + PK.uT[l], A.dcat, 128, n, 64, 128, nullptr));   // [dh part | da]
         // messages: recompute PQ of this layer from h[l] (the last layer's is
         // still there from the forward pass)
-        if (l < NL - 1) SGP_TRY(gemm(ctx, A.h[l], 64, W + PK.ab[l], A.PQ, 128, n, 64, 128, nullptr, 0));
+        if (l < NL - 1) SGP_TRY(gemm(ctx, A.h[l], 64, W + PK.ab[l], A.PQ, 128, n, 64, 128, nullptr));
         const int nb = (int)std::min<int64_t>(grid_for(n, 16), MSG_BWD_GRID);
         float *wcp;
         SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP9], (size_t)nb * 256 + 64, &wcp));
@@ -1047,13 +1063,12 @@ int backward(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, Act &A)
         // W_a, W_b = h^T dP, h^T dQ; b_m = column sums of dP
         SGP_TRY((gemm_at<4, 0, 8>(ctx, M, A.h[l], 64, nullptr, 0, A.dPQ, 128, n,
                                   {G + L.W_a[l], G + L.W_b[l], G + L.b_m[l], 0, 0, 64, 64, 128, 64})));
-        // dh_l = dh (residual) + dcat[:, :64] + dPQ W_ab^T
-        k_add64<<<grid_for(64 * n, 256), 256, 0, st>>>(n, A.dh, 64, A.dcat, 128, A.tmp, 64);
-        LAUNCH_CHECK(ctx);
-        SGP_TRY(gemm(ctx, A.dPQ, 128, W + PK.abT[l], A.tmp, 64, n, 128, 64, nullptr, 1));
+        // dh_l = dh (residual) + dcat[:, :64] + dPQ W_ab^T, and its part where
+        // the activation before it passed (the input layer's for l = 0)
+        SGP_TRY(gemm_back<8>(ctx, A.dPQ, W + PK.abT[l], l > 0 ? A.tmp : nullptr, n,
+                             {A.dh, A.dcat, 128, l > 0 ? A.U[l - 1] : A.pre0, A.dU}));
         std::swap(A.dh, A.tmp);
     }
-    k_mask<<<grid_for(64 * n, 256), 256, 0, st>>>(64 * n, A.dh, A.pre0, A.dU);
     SGP_TRY((gemm_at<1, 0, 4>(ctx, M, A.x16, 16, nullptr, 0, A.dU, 64, n,
                               {G + L.W_in, nullptr, G + L.b_in, 0, 0, 6, 64, 64, 64})));
     return SGP_OK;
