@@ -235,6 +235,109 @@ __global__ __launch_bounds__(256) void k_sched_final(int nb, const int32_t *part
     if (threadIdx.x == 0) {
         out[0] = sa[0];
         out[1] = sm[0];
+        out[2] = 0;   // k_contract_list's count
+    }
+}
+
+// The rounds left once at most FINISH_MAX vertices are: the unscheduled ones
+// are listed (in any order: a round's outcome depends on ids alone) and one
+// workgroup runs every round on them in LDS, with the rules of
+// k_contract_select and k_contract_apply.  As launches the last rounds took
+// 4 to 7 us each for a handful of vertices, eight rounds to a host wait
+// (300k cells 2.91 -> 2.75 ms of setup, a step of 1000 cells 4.60 -> 4.41 ms).
+constexpr int FINISH_THREADS = 1024, FINISH_VPT = 3, FINISH_MAX = FINISH_THREADS * FINISH_VPT;
+
+// list[k] = v, up1[v] = k (up1 is set when v is scheduled, not before);
+// entries past FINISH_MAX are counted only
+__global__ void k_contract_list(int64_t n, const int32_t *stepv, int32_t *count, int32_t *list, int32_t *up1)
+{
+    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (v >= n || stepv[v] >= 0) return;
+    const int32_t k = atomicAdd(count, 1);
+    if (k >= FINISH_MAX) return;
+    list[k] = (int32_t)v;
+    up1[v] = k;
+}
+
+// list null: all n vertices, numbered by id.  out[0]: vertices left (0, or all
+// when there are more than FINISH_MAX: nothing was done), out[1]: the last step
+__global__ __launch_bounds__(FINISH_THREADS) void k_contract_finish(int32_t n, int32_t s0, const int32_t *count,
+                                                                    const int32_t *list, const int32_t *par,
+                                                                    const int32_t *nch, int32_t *stepv, int32_t *up0,
+                                                                    int32_t *up1, int32_t *out)
+{
+    __shared__ int32_t gid[FINISH_MAX], lnch[FINISH_MAX], lxch[FINISH_MAX], picked[2];
+    __shared__ int16_t lpar[FINISH_MAX], lup[FINISH_MAX], lst[FINISH_MAX];   // lst: step - s0, -1 open, -2 not ours
+    const int32_t tid = threadIdx.x, m = list ? *count : n;
+    if (m > FINISH_MAX) {
+        if (tid == 0) out[0] = m;
+        return;
+    }
+    int32_t open = 0;
+    for (int32_t l = tid; l < m; l += FINISH_THREADS) {
+        const int32_t v = list ? list[l] : l, p = par[v], k = p < 0 ? -1 : list ? up1[p] : p;
+        gid[l] = v;
+        lpar[l] = (int16_t)(k >= 0 && k < m ? k : -1);
+        lnch[l] = nch[v];
+        lxch[l] = 0;
+        lst[l] = stepv[v] < 0 ? -1 : -2;
+        open += lst[l] == -1;
+    }
+    if (tid < 2) picked[tid] = 0;
+    __syncthreads();
+    atomicAdd(&picked[0], open);
+    for (int32_t l = tid; l < m; l += FINISH_THREADS)
+        if (lst[l] == -1 && lpar[l] >= 0) atomicXor(&lxch[lpar[l]], l);
+    __syncthreads();
+    int32_t left = picked[0], s = 0;
+    // (every round of a forest schedules a leaf at least; m rounds at most)
+    for (; left > 0 && s < m; s++) {
+        int32_t mine = 0;
+        for (int32_t l = tid; l < m; l += FINISH_THREADS) {
+            if (lst[l] != -1) continue;
+            const int32_t p = lpar[l], c0 = lnch[l];
+            int32_t c = -1;
+            if (c0 != 0) {
+                if (c0 != 1 || p < 0) continue;
+                c = lxch[l];
+                if ((uint32_t)c >= (uint32_t)m || lnch[c] == 0) continue;   // (in range in a forest); its child is a leaf: it is raked first
+                const bool unary_p = lnch[p] == 1 && lpar[p] >= 0, unary_c = lnch[c] == 1 && lpar[c] >= 0;
+                if (unary_p && !beats(gid[l], gid[p], s0 + s)) continue;
+                if (unary_c && !beats(gid[l], gid[c], s0 + s)) continue;
+            }
+            lst[l] = (int16_t)s;
+            lup[l] = (int16_t)c;
+            mine++;
+        }
+        if (tid == 0) picked[(s + 1) & 1] = 0;
+        __syncthreads();
+        if (mine) atomicAdd(&picked[(s + 1) & 1], mine);
+        for (int32_t l = tid; l < m; l += FINISH_THREADS) {
+            if (lst[l] != s) continue;
+            const int32_t p = lpar[l], c = lup[l];
+            if (c >= 0) {
+                lpar[c] = (int16_t)p;
+                atomicXor(&lxch[p], l ^ c);
+            } else if (p >= 0) {
+                atomicSub(&lnch[p], 1);
+                atomicXor(&lxch[p], l);
+            }
+        }
+        __syncthreads();
+        const int32_t now = picked[(s + 1) & 1];
+        left -= now;
+        if (now == 0) break;
+    }
+    for (int32_t l = tid; l < m; l += FINISH_THREADS) {
+        if (lst[l] < 0) continue;
+        const int32_t v = gid[l];
+        stepv[v] = s0 + lst[l];
+        up0[v] = lpar[l] < 0 ? -1 : gid[lpar[l]];
+        up1[v] = lup[l] < 0 ? -1 : gid[lup[l]];
+    }
+    if (tid == 0) {
+        out[0] = left;
+        out[1] = s0 + s - 1;
     }
 }
 
@@ -2288,7 +2391,7 @@ extern "C" int sgp_factor_tree(sgp_ctx ctx, sgp_graph g, sgp_tree T, double g_pa
         SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP3], n + 1, &par));
         SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP4], n + 1, &nch));
         SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP5], n + 1, &xch));
-        SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP6], 2 * SCHED_STAT_BLOCKS + 4, &stat));   // per-block stats, then out[2]
+        SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP6], 2 * SCHED_STAT_BLOCKS + 4 + FINISH_MAX, &stat));   // per-block stats, out[3], a list
         SGP_TRY(fill_i32(ctx, nch, 0, n));
         SGP_TRY(fill_i32(ctx, xch, 0, n));
         k_contract_init<<<grid_for(n, 256), 256, 0, st>>>(n, parent, par, nch, xch, stepv);
@@ -2352,7 +2455,23 @@ extern "C" int sgp_factor_tree(sgp_ctx ctx, sgp_graph g, sgp_tree T, double g_pa
         // round before it schedules at least one vertex (a forest always has
         // a leaf), so the step count is the largest step given plus one
         constexpr int ROUNDS_PER_READ = 8;
+        // from at most FINISH_MAX vertices on (all of a small system) one launch
+        auto finish = [&](bool all) -> int {
+            if (!all) k_contract_list<<<grid_for(n, 256), 256, 0, st>>>(n, stepv, stat_out + 2, stat_out + 4, up1);
+            k_contract_finish<<<1, FINISH_THREADS, 0, st>>>((int32_t)n, S, stat_out + 2, all ? nullptr : stat_out + 4,
+                                                            par, nch, stepv, up0, up1, stat_out);
+            LAUNCH_CHECK(ctx);
+            SGP_TRY(readback(ctx, hbuf, stat_out, 8));
+            if (hbuf[0] != 0) return set_err(ctx, SGP_EINVAL, "factor_tree: contraction made no progress");
+            S = hbuf[1] + 1;
+            done = n;
+            return SGP_OK;
+        };
         while (done < n) {
+            if (n <= FINISH_MAX || n - done <= FINISH_MAX) {
+                SGP_TRY(finish(n <= FINISH_MAX));
+                break;
+            }
             if (S > 100000) return set_err(ctx, SGP_EINVAL, "factor_tree: contraction did not finish");
             for (int b = 0; b < ROUNDS_PER_READ; b++) {
                 const int32_t s = S + b;

@@ -42,3 +42,32 @@ def test_chain(n):
 def test_scan_tiles(n):
     c = sphere_cluster(n, 61)
     _check(c["pos"], c["radius"])
+
+
+@pytest.mark.parametrize("light", [0, 3])
+@pytest.mark.parametrize("n,chain", [(1, True), (2, True), (3072, True), (3073, True), (9001, True), (3071, False),
+                                     (3072, False), (3073, False), (20011, False)])
+def test_schedule_finish(n, chain, light):
+    """The rounds of the elimination schedule that one workgroup finishes (up to
+    3072 open vertices, listed or all): every vertex has a step, and the apply is
+    the oracle's P^-1 b (FP64 in another elimination order: 1e-10 as in the other
+    tests of the apply)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    if chain:
+        pos, R = np.zeros((n, 3)), np.ones(n)
+        pos[1:, 0] = np.cumsum(1.9 - 0.8 * np.arange(n - 1) / n)
+    else:
+        c = sphere_cluster(n, 62)
+        pos, R = c["pos"], c["radius"]
+    b = np.random.default_rng(n).normal(size=(n, 3))
+    og = O.collide(pos, R)
+    z = O.tree_solve(O.tree_factor(og, O.build_tree(og)), b)
+    ctx = P.Context()
+    ctx.tune("light_height", light)
+    g = ctx.collide(to_dev(pos), to_dev(R))
+    M = ctx.factor_tree(g, ctx.build_tree(g))
+    assert sum(M.info()["step_sizes"]) == n
+    zg = host(ctx.prec_apply(M, to_dev(b)))
+    assert np.linalg.norm(zg - z) <= 1e-10 * np.linalg.norm(z)
+    ctx.close()
