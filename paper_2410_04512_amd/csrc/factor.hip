@@ -1601,6 +1601,26 @@ __global__ __launch_bounds__(256) void k_top(int32_t Qt, int32_t nt, const int32
 #pragma unroll
         for (int u = 0; u < ROWS; u++) acc[u] = acc[u] + a[u][c] * bc;
     }
+    // The block holds the last vertices of every tree (of a batch: of every
+    // cluster), whose blocks are apart: the entries between two trees are
+    // exactly zero, but 0 Inf and 0 NaN are not.  So that a tree with such a
+    // right-hand side leaves the others alone, as in the steps below, the sums
+    // it reached are formed again without the zero entries.
+    bool finite = true;
+#pragma unroll
+    for (int u = 0; u < ROWS; u++) finite = finite && isfinite(acc[u]);
+    if (!__all(finite)) {
+#pragma unroll
+        for (int u = 0; u < ROWS; u++) acc[u] = 0;
+        for (int c = 0; c < NC; c++) {
+            const T bc = b[64 * c + lane];
+#pragma unroll
+            for (int u = 0; u < ROWS; u++) {
+                const T e = inv[(int64_t)min(row0 + u, N - 1) * (64 * NC) + 64 * c + lane];
+                acc[u] = e == (T)0 ? acc[u] : acc[u] + e * bc;
+            }
+        }
+    }
     T o = 0;
 #pragma unroll
     for (int u = 0; u < ROWS; u++) {
