@@ -121,7 +121,7 @@ extern "C" void sgp_prec_free(sgp_prec M)
     release(M->F); release(M->Dinv); release(M->y); release(M->F32); release(M->Dinv32); release(M->y32);
     release(M->tout); release(M->cs); release(M->cs32); release(M->step_ptr);
     release(M->elim_int); release(M->perm); release(M->inv); release(M->tail_iptr); release(M->tail_tslot);
-    release(M->tail_b); release(M->top_inv); release(M->top_inv32); release(M->light_ptr); release(M->mid_ptr); release(M->wu0); release(M->wu032);
+    release(M->tail_b); release(M->top_inv); release(M->top_inv32); release(M->top_root); release(M->light_ptr); release(M->mid_ptr); release(M->wu0); release(M->wu032);
     release(M->jdinv);
     release(M->aug_piece); release(M->aug_list); release(M->aug_tptr); release(M->aug_tadj); release(M->aug_twu);
     release(M->aug_ptr); release(M->aug_adj); release(M->aug_wu); release(M->small_ell); release(M->mid_tab); release(M->mid_pack);

@@ -1456,21 +1456,53 @@ static_assert((3 * TOP_MAX) % 256 == 0, "whole column chunks");
 // inverse, by the forward and the backward sweep of a unit vector over the
 // top steps (values and push slots in LDS).  The matrix is symmetric, so the
 // column is stored as a row; columns past 3 nt are zero.
+//
+// Roots apart.  A tree's root is its last vertex, and its pivot D is about
+// g_med times the tree's cells: with a small g_med all entries of the inverse
+// are about D^-1, and their rounding hides the differences that the friction
+// between cells makes (3000 cells, g_med = 1e-11: FP64 1085 -> 1259 iterations,
+// FP32 indefinite).  With the rest of the tree eliminated the root's right-hand
+// side is s = sum_j R_j^T b_j and
+//   x_i = (G b)_i + R_i D^-1 s,
+// G the inverse without the root's rows and columns (entries of the size of
+// the tree paths' resistances) and R the rows of L^T that lead there (about
+// the identity).  Where a root's pivot is TOP_APART times smaller than its
+// block of P (as the traces say), the matrix holds G, zero in the roots' rows
+// and columns, but for R^T in the roots' rows: [3 root + k][3 j + c] =
+// R_j[c][k].  These are the roots' values of the forward sweep; the backward
+// sweep starts with zeros there.  Below that ratio the whole inverse is the
+// better one: it takes one product less (5e4 cells 13.1 instead of 13.4 ms a
+// solve), and costs 1 % of the iterations at a ratio of about 1000 (3000 cells,
+// g_med = 1e-7: 1064 -> 1075), but 5 % at 1e4 (9000 cells, 1e-9: 2066 -> 2168);
+// in FP32 it rounds away 10 bits of the smallest eigenvalues at most.  root: the
+// root of every vertex (index in the block); apart: set where the roots are.
+constexpr double TOP_APART = 1024.0;
 constexpr int TOP_INV_THREADS = 192;
-static size_t top_inv_lds(int64_t nt, int64_t ni) { return 3 * 8 * 3 * (size_t)(nt + ni); }
+static size_t top_inv_lds(int64_t nt, int64_t ni) { return 3 * 8 * 3 * (size_t)(nt + ni) + 4 * (size_t)nt; }
 
 __global__ __launch_bounds__(TOP_INV_THREADS) void k_top_inverse(int32_t s0, int32_t S, const int32_t *sp, int32_t Qt,
                                                                  int32_t nt, int32_t ni, const int32_t *iptr,
                                                                  const int32_t *tslot, const int32_t *upq,
                                                                  const double *F, int64_t fs, const double *Dinv,
-                                                                 int32_t ld, double *out)
+                                                                 const int32_t *elim, const double *Pd, int32_t ld,
+                                                                 double *out, int32_t *root, int32_t *apart)
 {
     extern __shared__ unsigned char lds_raw[];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     double *sv = (double *)lds_raw + (size_t)wv * 3 * (nt + ni);
     double *slot = sv + 3 * nt;
+    int32_t *rt = (int32_t *)((double *)lds_raw + 9 * (size_t)(nt + ni));   // (the first wave's)
     const int32_t col = 3 * (int32_t)blockIdx.x + wv;
     for (int32_t i = lane; i < 3 * nt; i += 64) sv[i] = i == col ? 1.0 : 0.0;
+    bool mine = false;
+    for (int32_t i = lane; i < nt; i += 64) {
+        const int64_t q = Qt + i;
+        if (upq[2 * q] >= 0 || upq[2 * q + 1] >= 0) continue;
+        const double *d = Dinv + 6 * q, *D = Pd + 9 * (int64_t)elim[q];
+        mine = mine || ((d[0] + d[3]) + d[5]) * ((D[0] + D[4]) + D[8]) > 9.0 * TOP_APART;
+    }
+    const bool ap = __any(mine);
+    if (ap && blockIdx.x == 0 && threadIdx.x == 0) *apart = 1;
     lds_wave_barrier();
     for (int32_t k = s0; k < S; k++) {
         const int32_t hi = sp[k + 1] - Qt;
@@ -1492,6 +1524,16 @@ __global__ __launch_bounds__(TOP_INV_THREADS) void k_top_inverse(int32_t s0, int
         }
         lds_wave_barrier();
     }
+    for (int32_t i = lane; i < nt; i += 64) {
+        const int64_t q = Qt + i;
+        if (upq[2 * q] >= 0 || upq[2 * q + 1] >= 0) continue;
+        for (int m = 0; m < 3 && ap; m++) {
+            out[(int64_t)(3 * i + m) * ld + col] = sv[3 * i + m];
+            sv[3 * i + m] = 0.0;
+        }
+        if (wv == 0) rt[i] = i;
+    }
+    lds_wave_barrier();
     for (int32_t k = S - 1; k >= s0; k--) {
         const int32_t hi = sp[k + 1] - Qt;
         for (int32_t i = sp[k] - Qt + lane; i < hi; i += 64) {
@@ -1501,6 +1543,7 @@ __global__ __launch_bounds__(TOP_INV_THREADS) void k_top_inverse(int32_t s0, int
             for (int m = 0; m < 2; m++) {
                 const int32_t a = upq[2 * q + m];
                 if (a < 0) continue;
+                if (wv == 0) rt[i] = rt[a - Qt];
                 const double *xs = sv + 3 * (a - Qt);
                 pull3(x0, x1, x2, F + m * fs + 9 * q, xs[0], xs[1], xs[2]);
             }
@@ -1510,12 +1553,17 @@ __global__ __launch_bounds__(TOP_INV_THREADS) void k_top_inverse(int32_t s0, int
         }
         lds_wave_barrier();
     }
-    for (int32_t i = lane; i < ld; i += 64) out[(int64_t)col * ld + i] = i < 3 * nt ? sv[i] : 0.0;
+    // (a root's row of R^T: its first 3 nt columns are stored above)
+    const int64_t qj = Qt + blockIdx.x;
+    const bool theirs = ap && upq[2 * qj] < 0 && upq[2 * qj + 1] < 0;
+    for (int32_t i = lane + (theirs ? 3 * nt : 0); i < ld; i += 64) out[(int64_t)col * ld + i] = i < 3 * nt ? sv[i] : 0.0;
+    if (wv == 0 && lane == 0) root[blockIdx.x] = rt[blockIdx.x];
 }
 
-// x of the top block: the dense inverse (rows of 64 NC values) times the
+// x of the top block: the matrix above (rows of 64 NC values) times the
 // right-hand sides, r minus the pushes from vertices eliminated before (all
-// finished by the launch boundary).  Every workgroup forms all right-hand
+// finished by the launch boundary); APART: and R D^-1 s of the rows' root,
+// whose s the first three waves form for the root of the workgroup's first row.  Every workgroup forms all right-hand
 // sides while its ROWS rows per wave are in flight: TOP_LANES lanes per
 // vertex, since the last vertices have many slots and a lane's chunks of them
 // would be dependent rounds of loads.  x goes to y (for the steps below) and
@@ -1524,17 +1572,19 @@ __global__ __launch_bounds__(TOP_INV_THREADS) void k_top_inverse(int32_t s0, int
 // vertices have up to 23 slots at 1e6 cells, and two per lane left up to four
 // dependent rounds)
 constexpr int TOP_LANES = 4;
-template <class T, int NC, int ROWS>
+template <class T, int NC, int ROWS, bool APART>
 __global__ __launch_bounds__(256) void k_top(int32_t Qt, int32_t nt, const int32_t *elim, const int32_t *in_ptr,
-                                             const int32_t *iptr, const T *inv, const T *r, const T *cs, T *y, T *z,
-                                             const PcgScalars *s)
+                                             const int32_t *iptr, const int32_t *root, const T *inv, const T *Dinv,
+                                             const T *r, const T *cs, T *y, T *z, const PcgScalars *s)
 {
     constexpr int PER = 256 / TOP_LANES;                      // vertices per round
     constexpr int RND = (64 * NC / 3 + PER - 1) / PER;        // rounds
     constexpr int SLOTS = RND <= 4 ? 6 : RND <= 6 ? 4 : 2;
-    __shared__ T b[3 * PER * RND > 64 * NC ? 3 * PER * RND : 64 * NC];
-    const int tid = threadIdx.x, lane = tid & 63, sub = tid & (TOP_LANES - 1);
-    const int32_t N = 3 * nt, row0 = ((int32_t)blockIdx.x * 4 + (tid >> 6)) * ROWS;
+    constexpr int LD = 64 * NC;
+    __shared__ T b[3 * PER * RND > LD ? 3 * PER * RND : LD];
+    __shared__ T ssh[3];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, sub = tid & (TOP_LANES - 1);
+    const int32_t N = 3 * nt, row0 = ((int32_t)blockIdx.x * 4 + wv) * ROWS;
     const int32_t dn = done_flag(s);
     // ids first (the gathers wait for them), then the matrix rows (used last)
     int64_t v[RND];
@@ -1546,13 +1596,24 @@ __global__ __launch_bounds__(256) void k_top(int32_t Qt, int32_t nt, const int32
         t0[k] = in_ptr[q];
         t1[k] = in_ptr[q + 1] - (iptr[i + 1] - iptr[i]);
     }
-    const int64_t ov = elim[Qt + min(row0 + (lane & (ROWS - 1)), N - 1) / 3];
+    // lanes u < ROWS: row0 + u, its vertex and root; rb: the workgroup's root
+    const int32_t orow = min(row0 + (lane & (ROWS - 1)), N - 1), oi = orow / 3;
+    const int64_t ov = elim[Qt + oi];
+    const int32_t rb = APART ? root[(int32_t)blockIdx.x * 4 * ROWS / 3] : 0, ort = APART ? root[oi] : 0;
     keep_loads_above();
-    T a[ROWS][NC];
+    T a[ROWS][NC], sa[APART ? NC : 1], R[3], d[6];
 #pragma unroll
     for (int u = 0; u < ROWS; u++)
 #pragma unroll
-        for (int c = 0; c < NC; c++) a[u][c] = inv[(int64_t)min(row0 + u, N - 1) * (64 * NC) + 64 * c + lane];
+        for (int c = 0; c < NC; c++) a[u][c] = inv[(int64_t)min(row0 + u, N - 1) * LD + 64 * c + lane];
+    if (APART) {
+#pragma unroll
+        for (int c = 0; c < NC; c++) sa[c] = inv[(int64_t)(3 * rb + min(wv, 2)) * LD + 64 * c + lane];
+#pragma unroll
+        for (int k = 0; k < 3; k++) R[k] = inv[(int64_t)(3 * ort + k) * LD + orow];
+#pragma unroll
+        for (int k = 0; k < 6; k++) d[k] = Dinv[6 * (int64_t)(Qt + ort) + k];
+    }
     T g[RND], h[RND][SLOTS][3];
 #pragma unroll
     for (int k = 0; k < RND; k++) {
@@ -1589,10 +1650,10 @@ __global__ __launch_bounds__(256) void k_top(int32_t Qt, int32_t nt, const int32
             b[3 * i + sub] = i < nt ? w : (T)0;
         }
     }
-    for (int k = 3 * PER * RND + tid; k < 64 * NC; k += 256) b[k] = 0;
+    for (int k = 3 * PER * RND + tid; k < LD; k += 256) b[k] = 0;
     __syncthreads();
     if (dn) return;
-    T acc[ROWS];
+    T acc[ROWS], sacc = 0;
 #pragma unroll
     for (int u = 0; u < ROWS; u++) acc[u] = 0;
 #pragma unroll
@@ -1600,32 +1661,54 @@ __global__ __launch_bounds__(256) void k_top(int32_t Qt, int32_t nt, const int32
         const T bc = b[64 * c + lane];
 #pragma unroll
         for (int u = 0; u < ROWS; u++) acc[u] = acc[u] + a[u][c] * bc;
+        if (APART) sacc = sacc + sa[c] * bc;
     }
-    // The block holds the last vertices of every tree (of a batch: of every
-    // cluster), whose blocks are apart: the entries between two trees are
-    // exactly zero, but 0 Inf and 0 NaN are not.  So that a tree with such a
-    // right-hand side leaves the others alone, as in the steps below, the sums
-    // it reached are formed again without the zero entries.
-    bool finite = true;
+    // row `row` of the matrix times b without its zero entries: the block holds
+    // the last vertices of every tree (of a batch: of every cluster), and the
+    // entries between two trees are exactly zero, but 0 Inf and 0 NaN are not.
+    // So that a tree with such a right-hand side leaves the others alone, as in
+    // the steps below, sums that are not finite are formed again like this.
+    auto row_dot = [&](int32_t row) {
+        T t = 0;
+        for (int c = 0; c < NC; c++) {
+            const T e = inv[(int64_t)row * LD + 64 * c + lane];
+            t = e == (T)0 ? t : t + e * b[64 * c + lane];
+        }
+        return t;
+    };
+    bool finite = isfinite(sacc);
 #pragma unroll
     for (int u = 0; u < ROWS; u++) finite = finite && isfinite(acc[u]);
     if (!__all(finite)) {
+        if (APART) sacc = row_dot(3 * rb + min(wv, 2));
 #pragma unroll
-        for (int u = 0; u < ROWS; u++) acc[u] = 0;
-        for (int c = 0; c < NC; c++) {
-            const T bc = b[64 * c + lane];
-#pragma unroll
-            for (int u = 0; u < ROWS; u++) {
-                const T e = inv[(int64_t)min(row0 + u, N - 1) * (64 * NC) + 64 * c + lane];
-                acc[u] = e == (T)0 ? acc[u] : acc[u] + e * bc;
-            }
-        }
+        for (int u = 0; u < ROWS; u++) acc[u] = row_dot(min(row0 + u, N - 1));
     }
     T o = 0;
 #pragma unroll
     for (int u = 0; u < ROWS; u++) {
         const T w = wave_sum(acc[u]);
         o = lane == u ? w : o;
+    }
+    if (APART) {
+        sacc = wave_sum(sacc);
+        if (lane == 0 && wv < 3) ssh[wv] = sacc;
+        __syncthreads();
+        T s0 = ssh[0], s1 = ssh[1], s2 = ssh[2];
+        // rows of another tree than the workgroup's first
+        if (__any(ort != rb))
+            for (int u = 0; u < ROWS; u++) {
+                const int32_t ru = __shfl(ort, u, 64);
+                if (ru == rb) continue;
+                const T t0 = wave_sum(row_dot(3 * ru)), t1 = wave_sum(row_dot(3 * ru + 1)),
+                        t2 = wave_sum(row_dot(3 * ru + 2));
+                s0 = lane == u ? t0 : s0;
+                s1 = lane == u ? t1 : s1;
+                s2 = lane == u ? t2 : s2;
+            }
+        T x0, x1, x2;
+        sym_mv(d, s0, s1, s2, x0, x1, x2);
+        o = (oi == ort ? (T)0 : o) + (R[0] * x0 + R[1] * x1 + R[2] * x2);
     }
     if (lane < ROWS && row0 + lane < N) {
         y[3 * (int64_t)Qt + row0 + lane] = o;
@@ -2106,8 +2189,12 @@ static int tree_sweeps(sgp_ctx ctx, sgp_prec M, const T *F, const T *Dinv, T *y,
         // at most 32 matrix values per lane in flight
         auto top = [&](auto nc) {
             constexpr int NC = decltype(nc)::value, R = NC <= 8 ? 4 : NC <= 16 ? 2 : 1;
-            k_top<T, NC, R><<<(3 * nt + 4 * R - 1) / (4 * R), 256, 0, st>>>(sp[ts], nt, elim, in_ptr, iptr, inv, r, cs,
-                                                                           y, z, s);
+            const unsigned nb = (unsigned)((3 * nt + 4 * R - 1) / (4 * R));
+            const int32_t *root = (const int32_t *)M->top_root.p;
+            if (M->top_apart)
+                k_top<T, NC, R, true><<<nb, 256, 0, st>>>(sp[ts], nt, elim, in_ptr, iptr, root, inv, Dinv, r, cs, y, z, s);
+            else
+                k_top<T, NC, R, false><<<nb, 256, 0, st>>>(sp[ts], nt, elim, in_ptr, iptr, root, inv, Dinv, r, cs, y, z, s);
         };
         using std::integral_constant;
         switch (M->top_ld / 256) {
@@ -2352,16 +2439,18 @@ static int mid_pack(sgp_ctx ctx, sgp_prec M)
 }
 
 // the top block's inverse, after the factor and its tail tables
-static int top_block(sgp_ctx ctx, sgp_prec M)
+static int top_block(sgp_ctx ctx, sgp_prec M, const int32_t *elim, const double *Pd, int32_t *apart)
 {
     const int32_t ts = M->tail_step, S = M->steps, nt = M->tail_nt, ni = M->tail_ni;
     M->top_ld = (3 * nt + 255) / 256 * 256;
     double *inv;
+    int32_t *root;
     SGP_TRY(ensure_t(ctx, M->top_inv, 3 * (size_t)nt * M->top_ld, &inv));
+    SGP_TRY(ensure_t(ctx, M->top_root, (size_t)nt, &root));
     k_top_inverse<<<nt, TOP_INV_THREADS, top_inv_lds(nt, ni), ctx->stream>>>(
         ts, S, (const int32_t *)M->step_ptr.p, M->h_step_ptr[ts], nt, ni, (const int32_t *)M->tail_iptr.p,
         (const int32_t *)M->tail_tslot.p, (const int32_t *)M->up.p, (const double *)M->F.p, 9 * M->n,
-        (const double *)M->Dinv.p, M->top_ld, inv);
+        (const double *)M->Dinv.p, elim, Pd, M->top_ld, inv, root, apart);
     LAUNCH_CHECK(ctx);
     return SGP_OK;
 }
@@ -2680,7 +2769,7 @@ extern "C" int sgp_factor_tree(sgp_ctx ctx, sgp_graph g, sgp_tree T, double g_pa
     double *y;
     SGP_TRY(ensure_t(ctx, M->y, 3 * n + 3, &y));
     SGP_TRY(ensure_t(ctx, ctx->ws[WS_TMP9], 4, &status));
-    SGP_TRY(fill_i32(ctx, status, 0, 3));
+    SGP_TRY(fill_i32(ctx, status, 0, 4));
     SGP_TRY(fill_f64(ctx, F, 0.0, 18 * n));
     k_tree_blocks<<<grid_for(n, 256), 256, 0, st>>>(n, (const int32_t *)T->tptr.p, (const int32_t *)T->tadje.p,
                                                   (const int32_t *)T->pedge.p, (const double4 *)g->wu.p, g_par,
@@ -2723,11 +2812,12 @@ extern "C" int sgp_factor_tree(sgp_ctx ctx, sgp_graph g, sgp_tree T, double g_pa
     LAUNCH_CHECK(ctx);
     SGP_TRY(tail_tables(ctx, M, n, in_ptr, in_src, tout));
     SGP_TRY(mid_tables(ctx, M, in_ptr, in_src, status + 2));
-    if (M->top) SGP_TRY(top_block(ctx, M));
-    SGP_TRY(readback(ctx, hbuf, status, 12));
+    if (M->top) SGP_TRY(top_block(ctx, M, elim, Pd, status + 3));
+    SGP_TRY(readback(ctx, hbuf, status, 16));
     M->step0_sorted = M->n_wu0 > 0 && hbuf[1] == 0;
     M->mid.max_group = hbuf[2];
     M->mid.lds = M->mid.lds_built && hbuf[2] <= MID_LDS_MAX;
+    M->top_apart = hbuf[3] != 0;
     if (M->mid.lds) SGP_TRY(mid_pack(ctx, M));
     phase_end(ctx, 3);
     if (hbuf[0]) return set_err(ctx, SGP_ENOTSPD, "factor_tree: a pivot block is not positive definite");

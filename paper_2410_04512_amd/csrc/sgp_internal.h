@@ -226,11 +226,12 @@ struct sgp_prec_ {
     DevBuf mid_ptr;                                     // [mid.steps * mid.nwg + 1] first q of (step, workgroup)
     DevBuf mid_tab, mid_pack;                           // tables of the LDS mid sweeps (factor.hip, MidTab)
     int32_t tail_step = 0;                              // steps >= tail_step run in one launch (tail or top block)
-    // the top block: the steps >= tail_step as one dense symmetric product
-    // with the inverse of their Schur complement, [3 tail_nt][top_ld]
-    bool top = false;
+    // the top block: the steps >= tail_step as one dense product with the
+    // inverse of their Schur complement (top_apart: the trees' roots apart,
+    // factor.hip), [3 tail_nt][top_ld], and the root of each of its vertices
+    bool top = false, top_apart = false;
     int32_t top_ld = 0;
-    DevBuf top_inv, top_inv32;
+    DevBuf top_inv, top_inv32, top_root;
     int32_t tail_nt = 0, tail_ni = 0;                   // tail vertices, tail-internal push slots
     DevBuf tail_iptr, tail_tslot;                       // per tail target: first internal slot; per (q,k): its slot
     DevBuf tail_b;                                      // [tail_nt][3] right-hand sides entering the tail
