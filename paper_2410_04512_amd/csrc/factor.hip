@@ -830,8 +830,8 @@ SGP_DEV void bwd_vertex(int32_t q, const int32_t *elim, const int32_t *upq, cons
     if (dn) return;
     T n0, n1, n2;
     sym_mv(d, y0, y1, y2, n0, n1, n2);
-    if (w0 >= 0) pull3(n0, n1, n2, f0, p0, p1, p2);
-    if (w1 >= 0) pull3(n0, n1, n2, f1, x0, x1, x2);
+    if (w0 >= 0) pull3<0>(n0, n1, n2, f0, p0, p1, p2);
+    if (w1 >= 0) pull3<1>(n0, n1, n2, f1, x0, x1, x2);
     if (keep_x) {
         y[3 * (int64_t)q] = n0;
         y[3 * (int64_t)q + 1] = n1;
@@ -1371,12 +1371,11 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_tail(int32_t s0, int32_t S, in
         sym_mv(d, sv[3 * i], sv[3 * i + 1], sv[3 * i + 2], x0, x1, x2);
         if (a0 >= 0) {
             const T *xs = sv + 3 * (a0 - Qt);
-            const T g0[9] = {f0[6], f0[7], f0[8], f0[3], f0[4], f0[5], f0[0], f0[1], f0[2]};
-            pull3(x0, x1, x2, g0, xs[2], xs[1], xs[0]);
+            pull3<0>(x0, x1, x2, f0, xs[0], xs[1], xs[2]);
         }
         if (a1 >= 0) {
             const T *xs = sv + 3 * (a1 - Qt);
-            pull3(x0, x1, x2, f1, xs[0], xs[1], xs[2]);
+            pull3<1>(x0, x1, x2, f1, xs[0], xs[1], xs[2]);
         }
         sv[3 * i] = x0;
         sv[3 * i + 1] = x1;
@@ -1545,7 +1544,10 @@ __global__ __launch_bounds__(TOP_INV_THREADS) void k_top_inverse(int32_t s0, int
                 if (a < 0) continue;
                 if (wv == 0) rt[i] = rt[a - Qt];
                 const double *xs = sv + 3 * (a - Qt);
-                pull3(x0, x1, x2, F + m * fs + 9 * q, xs[0], xs[1], xs[2]);
+                if (m == 0)
+                    pull3<0>(x0, x1, x2, F + 9 * q, xs[0], xs[1], xs[2]);
+                else
+                    pull3<1>(x0, x1, x2, F + fs + 9 * q, xs[0], xs[1], xs[2]);
             }
             sv[3 * i] = x0;
             sv[3 * i + 1] = x1;
@@ -2020,7 +2022,10 @@ __global__ __launch_bounds__(THREADS) void k_bwd_mid(int32_t L, const T *F, int6
                     x1 = xs[1];
                     x2 = xs[2];
                 }
-                pull3(n0, n1, n2, m == 0 ? f0[u] : f1[u], x0, x1, x2);
+                if (m == 0)
+                    pull3<0>(n0, n1, n2, f0[u], x0, x1, x2);
+                else
+                    pull3<1>(n0, n1, n2, f1[u], x0, x1, x2);
             }
             const int32_t l = tid + THREADS * u;
             xl[3 * l] = n0;

@@ -567,9 +567,13 @@ SGP_DEV void sym_mv(const T *s, T x0, T x1, T x2, T &y0, T &y1, T &y2)
 }
 
 // One vertex of the tree sweeps: the push c = f o to an up-link's slot, and
-// x -= f^T p for an up-link's x.  Fused multiply-adds (the build forms none by
-// itself): one rounding less per term, and a shorter chain in the steps that
-// wait on each other.
+// x -= f^T p for the x of up-link K.  Fused multiply-adds (the build forms none
+// by itself): one rounding less per term, and a shorter chain in the steps that
+// wait on each other.  Every sweep subtracts up-link 0 from p's last component
+// to its first, then up-link 1 from its first to its last, so a vertex's bits do
+// not depend on the launch that its step runs in.  (Any one order would do; of
+// those tried this one stops a level-schedule solve of 2000 cells, whose
+// residual passes the tolerance within rounding of it, where the oracle stops.)
 template <class T>
 SGP_DEV void push3(T *c, const T *f, T o0, T o1, T o2)
 {
@@ -578,12 +582,14 @@ SGP_DEV void push3(T *c, const T *f, T o0, T o1, T o2)
     c[2] = __builtin_elementwise_fma(f[8], o2, __builtin_elementwise_fma(f[7], o1, f[6] * o0));
 }
 
-template <class T>
+template <int K, class T>
 SGP_DEV void pull3(T &x0, T &x1, T &x2, const T *f, T p0, T p1, T p2)
 {
-    x0 = __builtin_elementwise_fma(-f[6], p2, __builtin_elementwise_fma(-f[3], p1, __builtin_elementwise_fma(-f[0], p0, x0)));
-    x1 = __builtin_elementwise_fma(-f[7], p2, __builtin_elementwise_fma(-f[4], p1, __builtin_elementwise_fma(-f[1], p0, x1)));
-    x2 = __builtin_elementwise_fma(-f[8], p2, __builtin_elementwise_fma(-f[5], p1, __builtin_elementwise_fma(-f[2], p0, x2)));
+    constexpr int A = K == 0 ? 6 : 0, B = 6 - A;   // rows of f in the order taken
+    const T pa = K == 0 ? p2 : p0, pb = K == 0 ? p0 : p2;
+    x0 = __builtin_elementwise_fma(-f[B], pb, __builtin_elementwise_fma(-f[3], p1, __builtin_elementwise_fma(-f[A], pa, x0)));
+    x1 = __builtin_elementwise_fma(-f[B + 1], pb, __builtin_elementwise_fma(-f[4], p1, __builtin_elementwise_fma(-f[A + 1], pa, x1)));
+    x2 = __builtin_elementwise_fma(-f[B + 2], pb, __builtin_elementwise_fma(-f[5], p1, __builtin_elementwise_fma(-f[A + 2], pa, x2)));
 }
 
 // -W p for the block W = w (g_perp I + (g_par - g_perp) u u^T) of contact

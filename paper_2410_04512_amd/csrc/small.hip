@@ -261,8 +261,8 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_pcg(SmallArgs A)
             for (int t = 0; t < 9; t++) g1[t] = gs[t];
             double n0, n1, n2;
             sym_mv(c.d, y0, y1, y2, n0, n1, n2);
-            if (c.a0 >= 0) pull3(n0, n1, n2, c.f0, p0, p1, p2);
-            if (c.a1 >= 0) pull3(n0, n1, n2, g1, x0, x1, x2);
+            if (c.a0 >= 0) pull3<0>(n0, n1, n2, c.f0, p0, p1, p2);
+            if (c.a1 >= 0) pull3<1>(n0, n1, n2, g1, x0, x1, x2);
             pv[3 * qq] = n0;
             pv[3 * qq + 1] = n1;
             pv[3 * qq + 2] = n2;
