@@ -1,12 +1,14 @@
 """The one-workgroup tail where the sweeps have one: level schedules, light
 subtrees, and small contraction factors solved outside the one-workgroup solve.
 Where the tail begins (tail_max) changes no bit as long as the first elimination
-step stays outside it.  A factor has a tail if the step it begins
+step stays outside it, nor do the x update beside it (tail_side) and the
+prefetch of its constants (prefetch).  A factor has a tail if the step it begins
 at follows tail_max; the dense block of larger contraction factors does not."""
+import numpy as np
 import pytest
 import torch
 
-from workloads import sphere_cluster
+from workloads import sphere_cluster, batched_instance
 
 pytestmark = pytest.mark.gpu
 
@@ -31,6 +33,14 @@ def _system(ctx, n, seed):
     c = sphere_cluster(n, seed)
     g = ctx.collide(to_dev(c["pos"]), to_dev(c["radius"]))
     return g, ctx.assemble_gamma(g), ctx.build_tree(g), to_dev(c["force"])
+
+
+def _batch(ctx, sizes):
+    parts = [batched_instance(k + 41, n_override=s) for k, s in enumerate(sizes)]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    pos, R, F = (to_dev(np.concatenate([p[k] for p in parts])) for k in ("pos", "radius", "force"))
+    g = ctx.collide_batched(off, pos, R)
+    return off, g, ctx.assemble_gamma(g), ctx.build_tree(g), F
 
 
 def _factor(ctx, g, T, schedule, light, tail):
@@ -61,3 +71,56 @@ def test_tail_max_changes_no_bit(ctx, n, schedule, light, tails):
     for z, r in runs[1:]:
         assert torch.equal(z, runs[0][0])
         _same(r, runs[0][1])
+
+
+@pytest.mark.parametrize("knob", ["tail_side", "prefetch"])
+@pytest.mark.parametrize("n,schedule,light,tails", KINDS)
+def test_tail_launch_knobs_change_no_bit(ctx, n, schedule, light, tails, knob):
+    g, A, T, F = _system(ctx, n, 62)
+    M, start = _factor(ctx, g, T, schedule, light, tails[0])
+    assert start < M.steps()
+    x0 = 1e-3 * torch.randn_like(F)
+    runs = []
+    for on in (1, 0):
+        ctx.tune(knob, on)
+        r = [ctx.pcg_solve(A, M, F), ctx.pcg_solve(A, M, F, fixed_iters=7),
+             ctx.pcg_solve(A, M, F, x0.clone(), use_x0=True), ctx.pcg_solve(A, M, F, rtol=1e-6, stop="error"),
+             ctx.pcg_solve(A, M, F, precision="f32ir", inner_rtol=1e-4)]
+        ctx.tune("graph", 1)
+        r.append(ctx.pcg_solve(A, M, F, check_every=3))
+        ctx.tune("graph", 0)
+        runs.append((ctx.prec_apply(M, x0), r))
+    assert torch.equal(runs[0][0], runs[1][0])
+    _same(runs[0][1], runs[1][1])
+
+
+@pytest.mark.parametrize("knob", ["tail_side", "prefetch"])
+def test_tail_launch_knobs_batched(ctx, knob):
+    """Instances converge at different iterations: the side update stops with
+    each, as the CG's own pass does."""
+    off, g, A, T, F = _batch(ctx, [4000, 300, 7000, 50, 900])
+    M, start = _factor(ctx, g, T, "contract", 8, 2200)
+    assert start < M.steps()
+    runs = []
+    for on in (1, 0):
+        ctx.tune(knob, on)
+        v, info = ctx.pcg_solve_batched(A, M, off, F)
+        assert len({i["iters"] for i in info}) > 1
+        runs.append([(v, info)])
+    _same(*runs)
+
+
+def test_edge_product_waves(ctx):
+    """2, 4 and 8 waves per workgroup of the edge form (up to 8192 cells)
+    change the order of p.q's partials, not the product."""
+    g, A, T, F = _system(ctx, 8000, 63)
+    M = ctx.factor_tree(g, T)
+    x = torch.randn_like(F)
+    q, (ref, iref) = ctx.spmv(A, x), ctx.pcg_solve(A, M, F)
+    for waves in (2, 8):
+        ctx.tune("spmv_waves", waves)
+        assert torch.equal(ctx.spmv(A, x), q), waves
+        v, i = ctx.pcg_solve(A, M, F)
+        assert abs(i["iters"] - iref["iters"]) <= 1
+        if i["iters"] == iref["iters"]:
+            assert float(torch.linalg.vector_norm(v - ref) / torch.linalg.vector_norm(ref)) <= 1e-8
