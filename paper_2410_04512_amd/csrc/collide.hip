@@ -13,6 +13,7 @@
 //     the contact test defines them (same operation order, no FMA)
 //  6. each CSR entry records the id of its edge (used by assembly and forces)
 #include "sgp_internal.h"
+#include "grid.h"
 
 #include <cmath>
 
@@ -67,19 +68,6 @@ __global__ void k_bbox(const double *pos, const double *R, int64_t n, double *pa
 }
 
 // --------------------------------------------------------------- 2. keys
-
-struct Grid {
-    double lo[3];
-    double inv_h;
-    int32_t dim[3];
-    int64_t ncell;   // cell numbers per cluster
-    // Cell numbering: row by row, or (bricks) in cubes of 2^bits cells per
-    // axis, so that consecutive cells fill a cube: the product's tiles of a few
-    // hundred cells then have about as many outside neighbours as cells (2.5
-    // times as many in rows: 738 against 291 for 256 cells at 1e6)
-    int32_t bits[3], nb[3];
-    bool bricks;
-};
 
 SGP_DEV int64_t cell_number(const Grid &g, int cx, int cy, int cz)
 {
@@ -387,51 +375,8 @@ static int collide_impl(sgp_ctx ctx, int64_t n, const double *pos, const double 
     SGP_TRY(readback(ctx, hb, box, sizeof hb));
     if (hb[7] == 1.0) return set_err(ctx, SGP_ENONFINITE, "collide: non-finite position");
     if (hb[7] == 2.0) return set_err(ctx, SGP_EINVAL, "collide: negative or non-finite radius");
-    Grid gr;
-    double h = 2.0 * hb[6] * (1.0 + 0x1p-20);
-    if (!(h > 0.0)) h = 1.0;
-    gr.inv_h = 1.0 / h;
-    int64_t ncell = 1;
-    for (int a = 0; a < 3; a++) {
-        gr.lo[a] = hb[a];
-        double span = (hb[3 + a] - hb[a]) * gr.inv_h;
-        int64_t d = (int64_t)floor(span) + 1;
-        // a huge, sparse domain would need too many cells: coarsen uniformly
-        gr.dim[a] = (int32_t)std::min<int64_t>(d, 1 << 20);
-        ncell *= gr.dim[a];
-    }
-    int64_t budget = std::max<int64_t>(4 * n / std::max<int64_t>(n_inst, 1), 64);
-    while (ncell > budget || (double)ncell * n_inst > 4.0e9) {
-        // enlarge cells: still a correct cell list (side >= 2 max R)
-        h *= 1.25;
-        gr.inv_h = 1.0 / h;
-        ncell = 1;
-        for (int a = 0; a < 3; a++) {
-            gr.dim[a] = (int32_t)floor((hb[3 + a] - hb[a]) * gr.inv_h) + 1;
-            ncell *= gr.dim[a];
-        }
-    }
-    gr.bricks = n > TILE_MIN_CELLS;
-    if (gr.bricks) {
-        // six bits of brick: two per axis, less along an axis of fewer than
-        // four cells (a sheet or a thread), more along the others
-        int thin = 0, used = 0;
-        for (int a = 0; a < 3; a++) {
-            gr.bits[a] = -1;
-            if (gr.dim[a] >= 4) continue;
-            gr.bits[a] = gr.dim[a] > 2 ? 2 : gr.dim[a] > 1 ? 1 : 0;
-            used += gr.bits[a];
-            thin++;
-        }
-        ncell = 1;
-        for (int a = 0; a < 3; a++) {
-            if (gr.bits[a] < 0) gr.bits[a] = thin == 0 ? 2 : thin == 1 ? 3 : 6 - used;
-            gr.nb[a] = (gr.dim[a] + (1 << gr.bits[a]) - 1) >> gr.bits[a];
-            ncell *= (int64_t)gr.nb[a] << gr.bits[a];
-        }
-    }
-    gr.ncell = ncell;
-    int64_t nkeys = ncell * n_inst;
+    const Grid gr = size_grid(hb, hb + 3, hb[6], n, n_inst, n > TILE_MIN_CELLS);
+    int64_t nkeys = gr.ncell * n_inst;
     int key_bits = 1;
     while (((int64_t)1 << key_bits) < nkeys) key_bits++;
     // 2. keys + sort
