@@ -32,26 +32,28 @@ inline Grid size_grid(const double *lo, const double *hi, double rmax, int64_t n
     Grid g = {};
     double h = 2.0 * rmax * (1.0 + 0x1p-20);
     if (!(h > 0.0)) h = 1.0;
-    g.inv_h = 1.0 / h;
-    int64_t ncell = 1;
-    for (int a = 0; a < 3; a++) {
-        g.lo[a] = lo[a];
-        const int64_t d = (int64_t)std::floor((hi[a] - lo[a]) * g.inv_h) + 1;
-        // a huge, sparse domain would need too many cells: coarsen uniformly
-        g.dim[a] = (int32_t)std::min<int64_t>(d, 1 << 20);
-        ncell *= g.dim[a];
-    }
-    const int64_t budget = std::max<int64_t>(4 * n / std::max<int64_t>(n_inst, 1), 64);
-    while (ncell > budget || (double)ncell * n_inst > GRID_MAX_CELLS) {
-        h *= 1.25;
+    const double budget = (double)std::max<int64_t>(4 * n / std::max<int64_t>(n_inst, 1), 64);
+    double span[3], ncell;
+    // (counted in doubles: a cell far from the others makes more cubes than
+    // integers hold before they are enlarged)
+    for (;; h *= 1.25) {
         g.inv_h = 1.0 / h;
-        ncell = 1;
+        ncell = 1.0;
         for (int a = 0; a < 3; a++) {
-            g.dim[a] = (int32_t)std::floor((hi[a] - lo[a]) * g.inv_h) + 1;
-            ncell *= g.dim[a];
+            g.lo[a] = lo[a];
+            span[a] = std::floor((hi[a] - lo[a]) * g.inv_h) + 1.0;
+            ncell *= span[a];
+        }
+        const bool ints = std::max(std::max(span[0], span[1]), span[2]) <= 0x1p30;
+        if (ints && ncell <= budget && ncell * (double)n_inst <= GRID_MAX_CELLS) break;
+        if (!std::isfinite(h)) {   // a box wider than doubles: one cell
+            g.inv_h = 0.0;
+            span[0] = span[1] = span[2] = ncell = 1.0;
+            break;
         }
     }
-    g.ncell = ncell;
+    for (int a = 0; a < 3; a++) g.dim[a] = (int32_t)span[a];
+    g.ncell = (int64_t)ncell;
     if (bricks) {
         // six bits of brick: two per axis, less along an axis of fewer than
         // four cells (a sheet or a thread), more along the others

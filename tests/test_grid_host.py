@@ -80,6 +80,16 @@ def test_numbers_fit_their_keys(sizes):
             assert last[a] >= int((c[a]) * g["inv_h"]), (c, g)   # the box is covered
 
 
+@pytest.mark.parametrize("far", [1e7, 1e11, 1e15, 1e300])
+def test_far_cells(sizes, far):
+    """A cell far from the others: more cubes along an axis than 32 bits count."""
+    cases = [(far, 9.0, 9.0, 0.5, 20_000, 1, 1), (far, far, far, 0.5, 1_000_000, 1, 1), (5.0, far, far, 0.5, 100, 7, 0),
+             (far, 0.5, 0.5, 0.5, 2 ** 30 - 1, 1, 1)]
+    for c, g in zip(cases, sizes(cases)):
+        assert 1 <= min(g["dim"]) and max(g["dim"]) < 2 ** 31 and 0 < g["ncell"] < 2 ** 32, (c, g)
+        assert g["dim"][0] * g["dim"][1] * g["dim"][2] <= max(4 * c[4] // c[5], 64), (c, g)
+
+
 @pytest.mark.parametrize("bricks", [0, 1])
 def test_every_cell_has_its_own_number(sizes, bricks):
     boxes = [(a, b, c) for a, b, c in itertools.product((0.5, 1.5, 2.5, 4.5, 6.5), repeat=3)]
