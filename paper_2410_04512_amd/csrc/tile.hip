@@ -66,77 +66,113 @@ SGP_DEV void tile_range(const TileArgs &A, int64_t tile, int64_t &r0, int64_t &r
 
 // ---------------------------------------------------------------- assembly
 
+// squared distances that the plain square root iteration takes (tile_root)
+SGP_DEV bool tile_in_range(double d2) { return d2 > 0x1p-700 && d2 < 0x1p700; }
+
 SGP_DEV uint32_t tile_hash(int32_t j) { return ((uint32_t)j * 2654435761u) >> 21; }
 
 // One workgroup per tile: the columns of its rows (internal numbers), its halo
 // (distinct outside columns by a hash table in LDS, then in ascending order)
-// and the entries' LDS numbers.  Bound by the chains of gathers of a thread and
-// the ranks' LDS reads: with a row's gathers four at a time, the columns read
-// back instead of gathered again and the ranks four to a read, 300k cells 169
-// -> 70 us.
+// and the entries' LDS numbers.  Bound by the chains of gathers of a thread, so
+// BUILD_LANES lanes share a row and take eight entries of their TR / 64 rows
+// together, the next ones' columns with them: the longest row of a wave counts,
+// 40 entries where radii differ by 3.  The rows' positions stay in LDS, so that
+// four workgroups fit a CU.  200k cells 50 -> 43 us, radii in [0.3, 1] 86 -> 51,
+// 25 contacts a cell 139 -> 82, against one or two lanes a row.
+constexpr int BUILD_LANES = 4;
 template <int TR>
-__global__ __launch_bounds__(256) void k_tile_build(TileArgs A, const int32_t *grow, const int32_t *gcol,
+__global__ __launch_bounds__(256, 4) void k_tile_build(TileArgs A, const int32_t *grow, const int32_t *gcol,
                                                     const int32_t *perm, const int32_t *inv, int32_t *ecol,
                                                     uint16_t *idx, int32_t *halo, int32_t *hcnt)
 {
-    constexpr int TPR = 256 / TR, BATCH = 4;
+    constexpr int PASS = 256 / BUILD_LANES, RP = TR / PASS, EPR = 8 / RP, STEP = BUILD_LANES * EPR;
     __shared__ int32_t tab[TILE_HASH], where[1024];
     __shared__ alignas(16) int32_t list[1024];
     __shared__ uint16_t val[TILE_HASH];
-    __shared__ int32_t count, bad, fill;
-    const int tid = threadIdx.x, sub = tid % TPR;
+    __shared__ double own[3][TR];   // the rows' positions
+    __shared__ int32_t count, bad, fill, most;
+    const int tid = threadIdx.x, sub = tid % BUILD_LANES, lr = tid / BUILD_LANES;
     const int64_t tile = blockIdx.x;
     int64_t r0, r1;
     tile_range<TR>(A, tile, r0, r1);
+    // the thread's rows lr, lr + PASS, .. (a row past the tile's end: no entries)
+    int32_t u[RP], b[RP], deg[RP], k0[RP], longest = 0;
+#pragma unroll
+    for (int k = 0; k < RP; k++) {
+        const int64_t i = min(r0 + lr + PASS * k, A.n - 1);
+        u[k] = perm[i];
+        k0[k] = A.rowptr[i] - (int32_t)i;
+    }
+#pragma unroll
+    for (int k = 0; k < RP; k++) {
+        b[k] = grow[u[k]];
+        deg[k] = grow[u[k] + 1];
+    }
     for (int k = tid; k < TILE_HASH; k += 256) tab[k] = -1;
     for (int k = tid; k < 1024; k += 256) list[k] = INT_MAX;   // past the halo: below no cell
-    if (tid == 0) count = bad = fill = 0;
-    __syncthreads();
-    const int64_t i = r0 + tid / TPR;
-    const bool on = i < r1;
-    int32_t b = 0, deg = 0;
-    int64_t k0 = 0;
-    double4 me = {};
-    if (on) {
-        const int32_t u = perm[i];
-        b = grow[u];
-        deg = grow[u + 1] - b;
-        k0 = (int64_t)A.rowptr[i] - i;
-        me = A.pos[i];
+    if (tid == 0) count = bad = fill = most = 0;
+    if (tid < TR) {
+        const double4 me = A.pos[min(r0 + tid, A.n - 1)];
+        own[0][tid] = me.x;
+        own[1][tid] = me.y;
+        own[2][tid] = me.z;
     }
-    for (int32_t c0 = sub; c0 < deg; c0 += BATCH * TPR) {
-        // a batch's three dependent loads each together (clamped)
-        int32_t js[BATCH];
-        double ox[BATCH], oy[BATCH], oz[BATCH];
+    const int32_t any = u[0];   // (what a row without entries reads)
 #pragma unroll
-        for (int m = 0; m < BATCH; m++) js[m] = gcol[b + min(c0 + m * TPR, deg - 1)];
+    for (int k = 0; k < RP; k++) {
+        deg[k] = r0 + lr + PASS * k < r1 ? deg[k] - b[k] : 0;
+        longest = max(longest, deg[k]);
+    }
+    __syncthreads();
+    if (sub == 0 && longest > *(volatile int32_t *)&most) atomicMax(&most, longest);
+    // columns of entries c0 + sub + BUILD_LANES m (clamped; of a row without entries: any cell)
+    int32_t js[RP][EPR];
+    auto columns = [&](int32_t c0) {
 #pragma unroll
-        for (int m = 0; m < BATCH; m++) js[m] = inv[js[m]];
+        for (int k = 0; k < RP; k++)
 #pragma unroll
-        for (int m = 0; m < BATCH; m++) {
-            ox[m] = A.pos[js[m]].x;
-            oy[m] = A.pos[js[m]].y;
-            oz[m] = A.pos[js[m]].z;
-        }
+            for (int m = 0; m < EPR; m++)
+                js[k][m] = deg[k] > 0 ? gcol[b[k] + min(c0 + sub + BUILD_LANES * m, deg[k] - 1)] : any;
+    };
+    if (longest > 0) columns(0);
+    for (int32_t c0 = 0; c0 < longest; c0 += STEP) {
+        int32_t jj[RP][EPR];
+        double ox[RP][EPR], oy[RP][EPR], oz[RP][EPR];
+#pragma unroll
+        for (int k = 0; k < RP; k++)
+#pragma unroll
+            for (int m = 0; m < EPR; m++) jj[k][m] = inv[js[k][m]];
+        columns(c0 + STEP);
+#pragma unroll
+        for (int k = 0; k < RP; k++)
+#pragma unroll
+            for (int m = 0; m < EPR; m++) {
+                ox[k][m] = A.pos[jj[k][m]].x;
+                oy[k][m] = A.pos[jj[k][m]].y;
+                oz[k][m] = A.pos[jj[k][m]].z;
+            }
         keep_loads_above();
 #pragma unroll
-        for (int m = 0; m < BATCH; m++) {
-            const int32_t c = c0 + m * TPR, j = js[m];
-            if (c >= deg) break;
-            ecol[k0 + c] = j;
-            const double dx = ox[m] - me.x, dy = oy[m] - me.y, dz = oz[m] - me.z;
-            const double d2 = (dx * dx + dy * dy) + dz * dz;
-            if (!(d2 > 0x1p-700 && d2 < 0x1p700)) bad = 1;
-            if (j >= r0 && j < r1) continue;
-            // (past the cap the tile is marked and nothing more is inserted: at
-            // most 256 threads are beyond this test, so the table never fills)
-            if (*(volatile int32_t *)&count > A.cap) continue;
-            for (uint32_t h = tile_hash(j);; h = (h + 1) & (TILE_HASH - 1)) {
-                const int32_t old = atomicCAS(&tab[h], -1, j);
-                if (old == -1) atomicAdd(&count, 1);
-                if (old == -1 || old == j) break;
+        for (int k = 0; k < RP; k++)
+#pragma unroll
+            for (int m = 0; m < EPR; m++) {
+                const int32_t c = c0 + sub + BUILD_LANES * m, j = jj[k][m];
+                if (c >= deg[k]) continue;
+                ecol[k0[k] + c] = j;
+                const int l = lr + PASS * k;
+                const double dx = ox[k][m] - own[0][l], dy = oy[k][m] - own[1][l], dz = oz[k][m] - own[2][l];
+                const double d2 = (dx * dx + dy * dy) + dz * dz;
+                if (!tile_in_range(d2)) bad = 1;
+                if (j >= r0 && j < r1) continue;
+                // (past the cap the tile is marked and nothing more is inserted: at
+                // most 256 threads are beyond this test, so the table never fills)
+                if (*(volatile int32_t *)&count > A.cap) continue;
+                for (uint32_t h = tile_hash(j);; h = (h + 1) & (TILE_HASH - 1)) {
+                    const int32_t old = atomicCAS(&tab[h], -1, j);
+                    if (old == -1) atomicAdd(&count, 1);
+                    if (old == -1 || old == j) break;
+                }
             }
-        }
     }
     __syncthreads();
     const int32_t hc = count;
@@ -163,27 +199,35 @@ __global__ __launch_bounds__(256) void k_tile_build(TileArgs A, const int32_t *g
     }
     if (tid == 0) hcnt[tile] = hc;
     __syncthreads();
-    if (!on) return;
-    const int32_t own = sub < deg ? deg - 1 - (deg - 1 - sub) % TPR : 0;   // the last entry this thread stored
-    for (int32_t c0 = sub; c0 < A.W; c0 += BATCH * TPR) {
-        int32_t js[BATCH];   // (this thread's own stores above)
+    // groups of four entries, as far as the product reads them: the first four,
+    // and those up to the tile's longest row and one round of lanes beyond
+    constexpr int TPR = 256 / TR;
+    const int used = max(4, ((most + 3) / 4 + TPR - 1) / TPR * TPR) + TPR, groups = min(A.W / 4, used);
+    for (int g = sub; g < groups; g += BUILD_LANES) {
+        int32_t c[RP][4];
 #pragma unroll
-        for (int m = 0; m < BATCH; m++) js[m] = deg > 0 ? ecol[k0 + min(c0 + m * TPR, own)] : 0;
+        for (int k = 0; k < RP; k++)
 #pragma unroll
-        for (int m = 0; m < BATCH; m++) {
-            const int32_t c = c0 + m * TPR, j = js[m];
-            if (c >= A.W) break;
-            uint16_t l = 0xffff;
-            if (c < deg) {
+            for (int m = 0; m < 4; m++)   // (stored above by this workgroup)
+                c[k][m] = 4 * g + m < deg[k] ? ecol[k0[k] + 4 * g + m] : -1;
+#pragma unroll
+        for (int k = 0; k < RP; k++) {
+            const int64_t i = r0 + lr + PASS * k;
+            uint16_t l[4];
+#pragma unroll
+            for (int m = 0; m < 4; m++) {
+                const int32_t j = c[k][m];
+                l[m] = 0xffff;
+                if (j < 0) continue;
                 if (j >= r0 && j < r1) {
-                    l = (uint16_t)(j - r0);
+                    l[m] = (uint16_t)(j - r0);
                 } else {
                     uint32_t h = tile_hash(j);
                     while (tab[h] != j) h = (h + 1) & (TILE_HASH - 1);
-                    l = val[h];
+                    l[m] = val[h];
                 }
             }
-            idx[i * A.W + c] = l;
+            if (i < r1) *(ushort4 *)(idx + i * A.W + 4 * g) = make_ushort4(l[0], l[1], l[2], l[3]);
         }
     }
 }
