@@ -39,6 +39,16 @@ constexpr int TILE_HALO_MAX = 474;   // (256 + 474) x 56 B of LDS: four workgrou
 // lanes), 128 and 256 rows: 2e4 cells 15.7, 15.2, 16.3; 5e4 16.1, 15.9, 16.2;
 // 2e5 14.1, 13.3, 12.9; 5e5 (FP32) 27.4, 26.1, 25.3; 1e6 61.7, 57.4, 55.6.
 static int tile_rows_for(int64_t n) { return n >= 150000 ? 256 : 128; }
+
+// Tiles are cut at the clusters of a batch, so that a product forms p.q per
+// cluster, unless that makes more than TILE_CUT times as many (clusters much
+// smaller than a tile): then they are cut straight through, and p.q takes a pass
+// of its own.  us per product and ms per block Jacobi solve, cut at the clusters
+// and straight: 7000 clusters of 30 cells (8.5 times the tiles) 37.1, 19.8 and
+// 7.48, 6.04; 3000 of 64 (4) 24.0, 18.3 and 4.64, 4.19; 2000 of 100 (2.6) 23.5,
+// 20.7 and 4.20, 4.05; 300 of 64 (2) 9.3, 9.0 and 1.65, 1.74; 1000 of 200 (1.3)
+// 21.4, 21.4 and 3.61, 3.94.
+constexpr double TILE_CUT = 2.5;
 constexpr int tile_halo_cap(int rows) { return rows == 256 ? TILE_HALO_MAX : 384; }
 
 struct TileArgs {
@@ -504,7 +514,11 @@ int tile_assemble(sgp_ctx ctx, sgp_graph g, sgp_bsr A)
     A->tile_w = (std::max(g->max_deg, 1) + 3) / 4 * 4;
     A->tile_hertz = g->hertz;
     A->tile_off = g->h_inst_off;
-    if (g->n_inst > 1) {
+    int64_t tiles = 0;
+    for (int64_t k = 0; k < g->n_inst; k++)
+        tiles += std::max<int64_t>((A->tile_off[k + 1] - A->tile_off[k] + A->tile_rows - 1) / A->tile_rows, 1);
+    if ((double)tiles > TILE_CUT * (double)((n + A->tile_rows - 1) / A->tile_rows)) A->tile_off = {0, n};
+    if (A->tile_off.size() > 2) {
         std::vector<int32_t> buf;
         build_tab(A->tile_off, A->tile_rows, buf, A->n_tiles);
         int32_t *d;
