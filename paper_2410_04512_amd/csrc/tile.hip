@@ -252,26 +252,32 @@ SGP_DEV double contact_area(double ri, double rj, double d, bool hertz)
     return hertz ? (TILE_PI * ((ri * rj) / s)) * a : a;
 }
 
-// q += W e of one contact, dx = b - a and radii ra, rb; nothing where !on.  The
-// square root by Goldschmidt's iteration from the hardware's reciprocal square
-// root estimate, with two residual corrections (Markstein), which round
-// correctly in the range the tile build has checked; 1 / d by one Newton step
-// from the same half reciprocal.
-template <bool HERTZ>
-SGP_DEV void tile_entry(bool on, double dx, double dy, double dz, double ra, double rb, double e0, double e1, double e2,
-                        double gperp, double gdif, double &q0, double &q1, double &q2)
+// d = sqrt(d2) and v = 1 / d, for d2 in the range that the tile build checks.
+// The root by Goldschmidt's iteration from the hardware's reciprocal square root
+// estimate, with two residual corrections (Markstein), which round correctly in
+// that range; v by one Newton step from the same half reciprocal.
+SGP_DEV void tile_root(double d2, double &d, double &v)
 {
-    double d2 = (dx * dx + dy * dy) + dz * dz;
-    d2 = on ? d2 : 1.0;
     const double y = __builtin_amdgcn_rsq(d2);
     double g = d2 * y, h = 0.5 * y;
     const double r = __builtin_fma(-h, g, 0.5);
     g = __builtin_fma(g, r, g);
     h = __builtin_fma(h, r, h);
     g = __builtin_fma(__builtin_fma(-g, g, d2), h, g);
-    const double d = __builtin_fma(__builtin_fma(-g, g, d2), h, g);
-    double v = h + h;
+    d = __builtin_fma(__builtin_fma(-g, g, d2), h, g);
+    v = h + h;
     v = __builtin_fma(__builtin_fma(-d, v, 1.0), v, v);
+}
+
+// q += W e of one contact, dx = b - a and radii ra, rb; nothing where !on.
+template <bool HERTZ>
+SGP_DEV void tile_entry(bool on, double dx, double dy, double dz, double ra, double rb, double e0, double e1, double e2,
+                        double gperp, double gdif, double &q0, double &q1, double &q2)
+{
+    double d2 = (dx * dx + dy * dy) + dz * dz;
+    d2 = on ? d2 : 1.0;
+    double d, v;
+    tile_root(d2, d, v);
     double w = contact_area(ra, rb, d, HERTZ);
     w = on ? w : 0.0;
     const double s = __builtin_fma(dz, e2, __builtin_fma(dy, e1, dx * e0));
@@ -450,8 +456,9 @@ __global__ __launch_bounds__(256) void k_spmv_tile(TileArgs A, const T *__restri
 }
 
 // Gamma's diagonal blocks (64-row groups of 6 planes), summed over the row's
-// contacts in neighbour order with the operations of the assembly, so the
-// same bits.
+// contacts in neighbour order: the assembly's sums, with u to the last place.
+// Bound by the FP64 operations and a row's chain of gathers: four entries at a
+// time and no library root or division.
 template <bool HERTZ>
 __global__ void k_tile_diag(TileArgs A, double *dg)
 {
@@ -461,16 +468,40 @@ __global__ void k_tile_diag(TileArgs A, double *dg)
     double D[9];
     for (int t = 0; t < 9; t++) D[t] = t % 4 == 0 ? A.gmed : 0.0;
     const int64_t b = (int64_t)A.rowptr[i] - i, e = (int64_t)A.rowptr[i + 1] - (i + 1);
-    for (int64_t k = b; k < e; k++) {
-        const double4 o = A.pos[A.ecol[k]];
-        const double dx = o.x - me.x, dy = o.y - me.y, dz = o.z - me.z;
-        const double d = sqrt((dx * dx + dy * dy) + dz * dz);
-        const double w = contact_area(me.w, o.w, d, HERTZ), u[3] = {dx / d, dy / d, dz / d};
-        for (int a = 0; a < 3; a++)
-            for (int c = a; c < 3; c++) {
-                const double uu = u[a] * u[c], id = a == c ? 1.0 : 0.0;
-                D[3 * a + c] = D[3 * a + c] + w * (A.gpar * uu + A.gperp * (id - uu));
+    constexpr int BATCH = 4;
+    int32_t nx[BATCH];
+#pragma unroll
+    for (int m = 0; m < BATCH; m++) nx[m] = b < e ? A.ecol[min(b + m, e - 1)] : (int32_t)i;
+    for (int64_t k0 = b; k0 < e; k0 += BATCH) {
+        double4 o[BATCH];
+#pragma unroll
+        for (int m = 0; m < BATCH; m++) o[m] = A.pos[nx[m]];
+#pragma unroll
+        for (int m = 0; m < BATCH; m++) nx[m] = A.ecol[min(k0 + BATCH + m, e - 1)];
+        keep_loads_above();
+#pragma unroll
+        for (int m = 0; m < BATCH; m++) {
+            if (k0 + m >= e) break;
+            const double dx = o[m].x - me.x, dy = o[m].y - me.y, dz = o[m].z - me.z;
+            const double d2 = (dx * dx + dy * dy) + dz * dz;
+            double d, v, u[3] = {dx, dy, dz};
+            if (tile_in_range(d2)) {
+                tile_root(d2, d, v);
+                for (int a = 0; a < 3; a++) {   // u / d with one residual correction
+                    const double t = u[a] * v;
+                    u[a] = __builtin_fma(__builtin_fma(-t, d, u[a]), v, t);
+                }
+            } else {
+                d = sqrt(d2);
+                for (int a = 0; a < 3; a++) u[a] = u[a] / d;
             }
+            const double w = contact_area(me.w, o[m].w, d, HERTZ);
+            for (int a = 0; a < 3; a++)
+                for (int c = a; c < 3; c++) {
+                    const double uu = u[a] * u[c], id = a == c ? 1.0 : 0.0;
+                    D[3 * a + c] = D[3 * a + c] + w * (A.gpar * uu + A.gperp * (id - uu));
+                }
+        }
     }
     double *g = dg + (i >> 6) * 384 + (i & 63);
     g[0] = D[0];
