@@ -295,10 +295,21 @@ struct alignas(2 * sizeof(T)) Pair {
     T a, b;
 };
 
+// How marked tiles without a halo (hc -1) are multiplied: the gathers of two
+// entries together, so that no tile pays registers for it and four workgroups
+// fit a CU, or (WIDE) of four with the next four's numbers ahead, in up to 168
+// registers, three workgroups.  Where a cell has more than TILE_WIDE contacts in
+// the mean few tiles have a halo that fits.  us per product: 25 contacts, 200k
+// cells 50.6 so (stored contacts 53.0; four entries without the numbers ahead
+// 63.5), 20k cells 13.5 (12.3; one entry behind the other, with the library's
+// root and divisions, 17.8); 10 contacts, tiles with halos 26.3 as WIDE, 25.2 not;
+// radii in [0.2, 1], 200k, 31.0 (31.7; one behind the other 35.3).
+constexpr int64_t TILE_WIDE = 16;
+
 // Partials of p.q per tile (mode 1).  S: the solve's scalars (null: always
 // run), inst: the cluster of each tile (null: cluster 0).
-template <class T, int TR, bool HERTZ>
-__global__ __launch_bounds__(256) void k_spmv_tile(TileArgs A, const T *__restrict__ x, T *__restrict__ y,
+template <class T, int TR, bool HERTZ, bool WIDE>
+__global__ __launch_bounds__(256, WIDE ? 3 : 4) void k_spmv_tile(TileArgs A, const T *__restrict__ x, T *__restrict__ y,
                                                    const PcgScalars *S, const int32_t *inst, double *part, int mode)
 {
     constexpr int TPR = 256 / TR, CAP = tile_halo_cap(TR), HR = (CAP + 255) / 256, PRE = 4 / TPR > 0 ? 4 / TPR : 1;
@@ -391,45 +402,54 @@ __global__ __launch_bounds__(256) void k_spmv_tile(TileArgs A, const T *__restri
         }
     } else if (on) {
         // marked tiles (hc -1: the halo does not fit, -2: distances): columns and
-        // cells from global memory, four entries at a time, their numbers a group
-        // ahead.  One entry behind the other, with the library's root and
-        // divisions for all, 25 contacts a cell took 17.8 us instead of 13.0
-        // (20k cells; stored contacts: 12.6), radii in [0.2, 1] 35.3 instead of
-        // 30.9 (200k; 31.7).
-        const int64_t b = (int64_t)A.rowptr[i] - i, e = (int64_t)A.rowptr[i + 1] - (i + 1);
-        int64_t g = b + 4 * sub;
-        int32_t nx[4];
-        if (g < e)
+        // cells from global memory
+        const int32_t b = A.rowptr[i] - (int32_t)i, e = A.rowptr[i + 1] - (int32_t)(i + 1);
+        if (hc == -1) {
+            constexpr int GRP = WIDE ? 4 : 2;
+            int32_t nx[4];
+            auto numbers = [&](int32_t g) {
 #pragma unroll
-            for (int m = 0; m < 4; m++) nx[m] = A.ecol[min(g + m, e - 1)];
-        for (; g < e; g += 4 * TPR) {
-            double o[4][4];
-            T px[4][3];
+                for (int m = 0; m < 4; m++) nx[m] = A.ecol[min(g + m, e - 1)];
+            };
+            if (WIDE && b + 4 * sub < e) numbers(b + 4 * sub);
+            for (int32_t g4 = b + 4 * sub; g4 < e; g4 += 4 * TPR) {
+                if (!WIDE) numbers(g4);
 #pragma unroll
-            for (int m = 0; m < 4; m++) {
-                const int64_t jj = nx[m];
-                for (int t = 0; t < 4; t++) o[m][t] = pos[4 * jj + t];
-                for (int t = 0; t < 3; t++) px[m][t] = x[3 * jj + t];
+                for (int g = 0; g < 4; g += GRP) {
+                    double o[GRP][4];
+                    T px[GRP][3];
+#pragma unroll
+                    for (int m = 0; m < GRP; m++) {
+                        const int64_t jj = nx[g + m];
+                        for (int t = 0; t < 4; t++) o[m][t] = pos[4 * jj + t];
+                        for (int t = 0; t < 3; t++) px[m][t] = x[3 * jj + t];
+                    }
+                    if (WIDE) numbers(g4 + 4 * TPR);
+                    keep_loads_above();
+#pragma unroll
+                    for (int m = 0; m < GRP; m++) {
+                        if (!WIDE) __builtin_amdgcn_sched_barrier(0);
+                        tile_entry<HERTZ>(g4 + g + m < e, o[m][0] - ax, o[m][1] - ay, o[m][2] - az, ar, o[m][3],
+                                          (double)p0 - (double)px[m][0], (double)p1 - (double)px[m][1],
+                                          (double)p2 - (double)px[m][2], A.gperp, gdif, q0, q1, q2);
+                    }
+                }
             }
-#pragma unroll
-            for (int m = 0; m < 4; m++) nx[m] = A.ecol[min(g + 4 * TPR + m, e - 1)];
-            keep_loads_above();
-#pragma unroll
-            for (int m = 0; m < 4; m++) {
-                const double dx = o[m][0] - ax, dy = o[m][1] - ay, dz = o[m][2] - az;
-                const double e0 = (double)p0 - (double)px[m][0], e1 = (double)p1 - (double)px[m][1],
-                             e2 = (double)p2 - (double)px[m][2];
-                if (hc == -1) {
-                    tile_entry<HERTZ>(g + m < e, dx, dy, dz, ar, o[m][3], e0, e1, e2, A.gperp, gdif, q0, q1, q2);
-                } else if (g + m < e) {   // library square root and division
+        } else {
+            for (int32_t g = b + 4 * sub; g < e; g += 4 * TPR)
+                for (int32_t k = g; k < min(g + 4, e); k++) {
+                    const int64_t jj = A.ecol[k];
+                    const double4 o = A.pos[jj];
+                    const double dx = o.x - ax, dy = o.y - ay, dz = o.z - az;
                     const double d = sqrt((dx * dx + dy * dy) + dz * dz);
-                    const double w = contact_area(ar, o[m][3], d, HERTZ), u0 = dx / d, u1 = dy / d, u2 = dz / d;
+                    const double w = contact_area(ar, o.w, d, HERTZ), u0 = dx / d, u1 = dy / d, u2 = dz / d;
+                    const double e0 = (double)p0 - (double)x[3 * jj], e1 = (double)p1 - (double)x[3 * jj + 1],
+                                 e2 = (double)p2 - (double)x[3 * jj + 2];
                     const double cu = (w * gdif) * ((u0 * e0 + u1 * e1) + u2 * e2), cp = w * A.gperp;
                     q0 += cp * e0 + cu * u0;
                     q1 += cp * e1 + cu * u1;
                     q2 += cp * e2 + cu * u2;
                 }
-            }
         }
     }
 #pragma unroll
@@ -597,12 +617,14 @@ static void tile_launch(sgp_ctx ctx, sgp_bsr A, const T *x, T *y, const PcgScala
                         double *part, int mode)
 {
     const TileArgs t = tile_args(A);
+    const bool wide = A->nnzb - A->n > TILE_WIDE * A->n;
+    const auto kernel = wide ? k_spmv_tile<T, TR, HERTZ, true> : k_spmv_tile<T, TR, HERTZ, false>;
     if (ctx->kt_start) {   // a timed launch carries the kernel timer's events (ktimer_begin)
-        hipExtLaunchKernelGGL(k_spmv_tile<T, TR, HERTZ>, dim3(A->n_tiles), dim3(256), 0, ctx->stream, ctx->kt_start,
-                              ctx->kt_stop, 0, t, x, y, S, inst, part, mode);
+        hipExtLaunchKernelGGL(kernel, dim3(A->n_tiles), dim3(256), 0, ctx->stream, ctx->kt_start, ctx->kt_stop, 0, t,
+                              x, y, S, inst, part, mode);
         ctx->kt_used = true;
     } else {
-        k_spmv_tile<T, TR, HERTZ><<<A->n_tiles, 256, 0, ctx->stream>>>(t, x, y, S, inst, part, mode);
+        kernel<<<A->n_tiles, 256, 0, ctx->stream>>>(t, x, y, S, inst, part, mode);
     }
 }
 
