@@ -1678,22 +1678,21 @@ __global__ __launch_bounds__(256) void k_top(int32_t Qt, int32_t nt, const int32
         }
         return t;
     };
-    bool finite = isfinite(sacc);
-#pragma unroll
-    for (int u = 0; u < ROWS; u++) finite = finite && isfinite(acc[u]);
-    if (!__all(finite)) {
-        if (APART) sacc = row_dot(3 * rb + min(wv, 2));
-#pragma unroll
-        for (int u = 0; u < ROWS; u++) acc[u] = row_dot(min(row0 + u, N - 1));
-    }
     T o = 0;
 #pragma unroll
     for (int u = 0; u < ROWS; u++) {
         const T w = wave_sum(acc[u]);
         o = lane == u ? w : o;
     }
+    if (APART) sacc = wave_sum(sacc);
+    if (__any(!isfinite(o) || (APART && !isfinite(sacc)))) {
+        if (APART) sacc = wave_sum(row_dot(3 * rb + min(wv, 2)));
+        for (int u = 0; u < ROWS; u++) {
+            const T w = wave_sum(row_dot(min(row0 + u, N - 1)));
+            o = lane == u ? w : o;
+        }
+    }
     if (APART) {
-        sacc = wave_sum(sacc);
         if (lane == 0 && wv < 3) ssh[wv] = sacc;
         __syncthreads();
         T s0 = ssh[0], s1 = ssh[1], s2 = ssh[2];
