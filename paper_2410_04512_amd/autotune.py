@@ -62,10 +62,14 @@ def tune(ctx, g, T, A, F, offsets=None, fixed_iters=20, repeats=3, rtol=1e-8, lo
     for sched in SCHEDULES:
         for lh in (LIGHT_HEIGHT if sched == "contract" else (0,)):
             ctx.tune("light_height", lh)
+            timed = {}   # by the step the tail begins at: the same step is the same factor
             for tm in TAIL_MAX:
                 ctx.tune("tail_max", tm)
                 M = ctx.factor_tree(g, T, schedule=sched)
-                t = _timed(ctx, lambda: solve(M, fixed_iters), repeats)
+                start_step = M.info()["tail_step"]
+                if start_step not in timed:
+                    timed[start_step] = _timed(ctx, lambda: solve(M, fixed_iters), repeats)
+                t = timed[start_step]
                 table[f"schedule={sched},light_height={lh},tail_max={tm}"] = t
                 if log:
                     log(f"autotune: schedule {sched} light_height {lh} tail_max {tm}: "
