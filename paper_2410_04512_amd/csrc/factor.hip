@@ -1670,8 +1670,11 @@ __global__ __launch_bounds__(256) void k_top(int32_t Qt, int32_t nt, const int32
     // entries between two trees are exactly zero, but 0 Inf and 0 NaN are not.
     // So that a tree with such a right-hand side leaves the others alone, as in
     // the steps below, sums that are not finite are formed again like this.
+    // (Rolled: unrolled, its loads took registers from the sums above, 9.2 ->
+    // 10.2 us at 303 vertices.)
     auto row_dot = [&](int32_t row) {
         T t = 0;
+#pragma unroll 1
         for (int c = 0; c < NC; c++) {
             const T e = inv[(int64_t)row * LD + 64 * c + lane];
             t = e == (T)0 ? t : t + e * b[64 * c + lane];
@@ -1687,6 +1690,7 @@ __global__ __launch_bounds__(256) void k_top(int32_t Qt, int32_t nt, const int32
     if (APART) sacc = wave_sum(sacc);
     if (__any(!isfinite(o) || (APART && !isfinite(sacc)))) {
         if (APART) sacc = wave_sum(row_dot(3 * rb + min(wv, 2)));
+#pragma unroll 1
         for (int u = 0; u < ROWS; u++) {
             const T w = wave_sum(row_dot(min(row0 + u, N - 1)));
             o = lane == u ? w : o;
