@@ -463,8 +463,10 @@ int sgp_mpnn_warm_start(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, sgp_bsr Gamma, con
  *                 (0..65536, 0 disables, default 2200; used by factors built
  *                 afterwards).  CONTRACT factors of more than 2200 cells
  *                 (without light steps or a local forest) have no such
- *                 steps: their last ones, of at most 256 vertices, are one
- *                 dense product with the inverse of their Schur complement
+ *                 steps, whatever the value: their last ones, of at most 256
+ *                 vertices (up to 512 where the components of the mid steps
+ *                 would be too large otherwise), are one dense product with
+ *                 the inverse of their Schur complement
  *  "graph"        1: each chunk of check_every CG iterations is captured once
  *                 per solve into a hipGraph and replayed (default 0)
  *  "spmv_waves"   waves per workgroup of the product: 2, 4 or 8 (default 4;
@@ -486,8 +488,8 @@ int sgp_mpnn_warm_start(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, sgp_bsr Gamma, con
  *                 mid steps' components (CONTRACT without light steps: the
  *                 steps between the first one or two and the dense last
  *                 ones, from the first with at most 2^17 vertices left, are
- *                 swept one workgroup per group of components, in one or two
- *                 launches per sweep)
+ *                 swept one workgroup per group of components, in one launch
+ *                 per sweep)
  *  "fuse_step0"   1: in sgp_pcg_solve* with a tree preconditioner whose
  *                 first elimination step runs as launches of its own, that
  *                 step's forward substitution runs inside the CG's
@@ -514,7 +516,8 @@ int sgp_mpnn_warm_start(sgp_ctx ctx, sgp_mpnn M, sgp_graph g, sgp_bsr Gamma, con
  *  "prefetch"     1: the launch before the one-workgroup tail of the tree
  *                 sweeps also loads the tail's constants, from the XCD that
  *                 runs the tail, so that its start-up loads hit in the caches
- *                 (default 1; 0: off)
+ *                 (default 1; 0: off; no effect, like tail_side, on factors
+ *                 without such a tail)
  * Unknown keys or values out of range give SGP_EINVAL.  check_every,
  * graph, fuse_step0, mid_lds, tail_side and prefetch leave every result bitwise
  * unchanged, and so does tail_max as long as the tail does not reach the first elimination

@@ -327,8 +327,9 @@ __global__ __launch_bounds__(FIN_THREADS) void k_fin(int op, const double *part,
 // Whole solves: 50k cells, tree 16.1 -> 13.6 ms; 32 clusters of 1k to 40k 23.5
 // -> 22.1 ms; 200k cells, block Jacobi (with its passes joined) 13.0 -> 9.4 ms;
 // 500k cells, FP32 in refinement, 1954 partials from as many blocks, 25.1 ->
-// 24.5 ms.  The reading grows with the square of the size (244 MB an iteration
-// at 1e6 cells, for two launches of 4.8 us), so there k_fin stays.
+// 24.5 ms.  The reading grows with the square of the size (366 MB an iteration
+// at 1e6 cells, three arrays of 3907 partials by as many blocks, for two launches
+// of 4.7 us), so there k_fin stays.
 constexpr int FOLD_MAX = 2048;
 struct FinIn {
     const double *part;           // NA arrays of stride `stride`

@@ -7,7 +7,7 @@
 // so a row needs its cell's position and radius (32 B) and its neighbours'
 // numbers, not 24 B per entry of stored contact vectors and a diagonal block:
 // 1e6 cells, ~10.5 contacts each: 418 MB -> 140 MB of memory traffic a product
-// by the counters, 88.8 -> 37.4 us (3.7 TB/s).  The price, a square root and
+// by the counters, 87.1 -> 34.7 us alone (4.0 TB/s), 89.1 -> 35.5 in a solve.  The price, a square root and
 // ~45 FP64 operations per entry, keeps the vector units busy for half of that
 // time and the LDS for a third; two lanes per contact, each row its own, cost
 // less than sums that meet from both sides.  w is bit for bit the collide's
