@@ -30,6 +30,7 @@
 #include <hip/hip_ext.h>
 
 #include <climits>
+#include <type_traits>
 
 constexpr int TILE_HASH = 2048;
 constexpr int TILE_HALO_MAX = 474;   // (256 + 474) x 56 B of LDS: four workgroups per CU
@@ -38,8 +39,17 @@ constexpr int TILE_HALO_MAX = 474;   // (256 + 474) x 56 B of LDS: four workgrou
 // workgroups, 128 rows of two lanes below.  ms per solve or step with 64 (four
 // lanes), 128 and 256 rows: 2e4 cells 15.7, 15.2, 16.3; 5e4 16.1, 15.9, 16.2;
 // 2e5 14.1, 13.3, 12.9; 5e5 (FP32) 27.4, 26.1, 25.3; 1e6 61.7, 57.4, 55.6.
-static int tile_rows_for(int64_t n) { return n >= 150000 ? 256 : 128; }
-
+// With more than TILE_DENSE contacts a cell in the mean the halos of larger tiles
+// do not fit, so 64: us per product (and per iteration with block Jacobi) at 200k
+// cells with 256 and with 64 rows: 14 contacts 29.0, 30.6 (34.0, 38.6), 18 contacts
+// 36.9, 31.7 (42.1, 39.5), 25 contacts 57.6, 34.0 (63.3, 41.6; stored contacts
+// 53.0, 69.1); 20k cells with 128 and with 64: 25 contacts 12.6, 10.6 (17.4, 15.5;
+// stored 12.2, 27.5).
+constexpr int64_t TILE_DENSE = 16;
+static int tile_rows_for(int64_t n, int64_t entries)
+{
+    return entries > TILE_DENSE * n ? 64 : n >= 150000 ? 256 : 128;
+}
 // Tiles are cut at the clusters of a batch, so that a product forms p.q per
 // cluster, unless that makes more than TILE_CUT times as many (clusters much
 // smaller than a tile): then they are cut straight through, and p.q takes a pass
@@ -49,7 +59,7 @@ static int tile_rows_for(int64_t n) { return n >= 150000 ? 256 : 128; }
 // 20.7 and 4.20, 4.05; 300 of 64 (2) 9.3, 9.0 and 1.65, 1.74; 1000 of 200 (1.3)
 // 21.4, 21.4 and 3.61, 3.94.
 constexpr double TILE_CUT = 2.5;
-constexpr int tile_halo_cap(int rows) { return rows == 256 ? TILE_HALO_MAX : 384; }
+constexpr int tile_halo_cap(int rows) { return rows == 256 ? TILE_HALO_MAX : rows == 128 ? 384 : 512; }
 
 struct TileArgs {
     int64_t n;
@@ -295,21 +305,10 @@ struct alignas(2 * sizeof(T)) Pair {
     T a, b;
 };
 
-// How marked tiles without a halo (hc -1) are multiplied: the gathers of two
-// entries together, so that no tile pays registers for it and four workgroups
-// fit a CU, or (WIDE) of four with the next four's numbers ahead, in up to 168
-// registers, three workgroups.  Where a cell has more than TILE_WIDE contacts in
-// the mean few tiles have a halo that fits.  us per product: 25 contacts, 200k
-// cells 50.6 so (stored contacts 53.0; four entries without the numbers ahead
-// 63.5), 20k cells 13.5 (12.3; one entry behind the other, with the library's
-// root and divisions, 17.8); 10 contacts, tiles with halos 26.3 as WIDE, 25.2 not;
-// radii in [0.2, 1], 200k, 31.0 (31.7; one behind the other 35.3).
-constexpr int64_t TILE_WIDE = 16;
-
 // Partials of p.q per tile (mode 1).  S: the solve's scalars (null: always
 // run), inst: the cluster of each tile (null: cluster 0).
-template <class T, int TR, bool HERTZ, bool WIDE>
-__global__ __launch_bounds__(256, WIDE ? 3 : 4) void k_spmv_tile(TileArgs A, const T *__restrict__ x, T *__restrict__ y,
+template <class T, int TR, bool HERTZ>
+__global__ __launch_bounds__(256, 4) void k_spmv_tile(TileArgs A, const T *__restrict__ x, T *__restrict__ y,
                                                    const PcgScalars *S, const int32_t *inst, double *part, int mode)
 {
     constexpr int TPR = 256 / TR, CAP = tile_halo_cap(TR), HR = (CAP + 255) / 256, PRE = 4 / TPR > 0 ? 4 / TPR : 1;
@@ -405,31 +404,30 @@ __global__ __launch_bounds__(256, WIDE ? 3 : 4) void k_spmv_tile(TileArgs A, con
         // cells from global memory
         const int32_t b = A.rowptr[i] - (int32_t)i, e = A.rowptr[i + 1] - (int32_t)(i + 1);
         if (hc == -1) {
-            constexpr int GRP = WIDE ? 4 : 2;
-            int32_t nx[4];
-            auto numbers = [&](int32_t g) {
+            // the gathers of two entries together: 116 registers, so that the path
+            // costs no tile a workgroup per CU (four together: 150, 25.2 -> 26.3 us
+            // for 32 clusters with halos; one behind the other, with the library's
+            // root and divisions: radii in [0.2, 1], 200k cells, 35.3 us instead of
+            // 31.0, stored contacts 31.7)
+            for (int32_t g = b + 4 * sub; g < e; g += 4 * TPR) {
+                int32_t nx[4];
 #pragma unroll
                 for (int m = 0; m < 4; m++) nx[m] = A.ecol[min(g + m, e - 1)];
-            };
-            if (WIDE && b + 4 * sub < e) numbers(b + 4 * sub);
-            for (int32_t g4 = b + 4 * sub; g4 < e; g4 += 4 * TPR) {
-                if (!WIDE) numbers(g4);
 #pragma unroll
-                for (int g = 0; g < 4; g += GRP) {
-                    double o[GRP][4];
-                    T px[GRP][3];
+                for (int h = 0; h < 4; h += 2) {
+                    double o[2][4];
+                    T px[2][3];
 #pragma unroll
-                    for (int m = 0; m < GRP; m++) {
-                        const int64_t jj = nx[g + m];
+                    for (int m = 0; m < 2; m++) {
+                        const int64_t jj = nx[h + m];
                         for (int t = 0; t < 4; t++) o[m][t] = pos[4 * jj + t];
                         for (int t = 0; t < 3; t++) px[m][t] = x[3 * jj + t];
                     }
-                    if (WIDE) numbers(g4 + 4 * TPR);
                     keep_loads_above();
 #pragma unroll
-                    for (int m = 0; m < GRP; m++) {
-                        if (!WIDE) __builtin_amdgcn_sched_barrier(0);
-                        tile_entry<HERTZ>(g4 + g + m < e, o[m][0] - ax, o[m][1] - ay, o[m][2] - az, ar, o[m][3],
+                    for (int m = 0; m < 2; m++) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        tile_entry<HERTZ>(g + h + m < e, o[m][0] - ax, o[m][1] - ay, o[m][2] - az, ar, o[m][3],
                                           (double)p0 - (double)px[m][0], (double)p1 - (double)px[m][1],
                                           (double)p2 - (double)px[m][2], A.gperp, gdif, q0, q1, q2);
                     }
@@ -561,7 +559,7 @@ int tile_assemble(sgp_ctx ctx, sgp_graph g, sgp_bsr A)
 {
     hipStream_t st = ctx->stream;
     const int64_t n = A->n;
-    A->tile_rows = tile_rows_for(n);
+    A->tile_rows = tile_rows_for(n, 2 * g->m);
     A->tile_w = (std::max(g->max_deg, 1) + 3) / 4 * 4;
     A->tile_hertz = g->hertz;
     A->tile_off = g->h_inst_off;
@@ -593,8 +591,10 @@ int tile_assemble(sgp_ctx ctx, sgp_graph g, sgp_bsr A)
     int32_t *ecol = (int32_t *)A->ecol.p;
     if (A->tile_rows == 256)
         k_tile_build<256><<<A->n_tiles, 256, 0, st>>>(t, gr, gc, perm, inv, ecol, idx, halo, hcnt);
-    else
+    else if (A->tile_rows == 128)
         k_tile_build<128><<<A->n_tiles, 256, 0, st>>>(t, gr, gc, perm, inv, ecol, idx, halo, hcnt);
+    else
+        k_tile_build<64><<<A->n_tiles, 256, 0, st>>>(t, gr, gc, perm, inv, ecol, idx, halo, hcnt);
     LAUNCH_CHECK(ctx);
     return SGP_OK;
 }
@@ -617,8 +617,7 @@ static void tile_launch(sgp_ctx ctx, sgp_bsr A, const T *x, T *y, const PcgScala
                         double *part, int mode)
 {
     const TileArgs t = tile_args(A);
-    const bool wide = A->nnzb - A->n > TILE_WIDE * A->n;
-    const auto kernel = wide ? k_spmv_tile<T, TR, HERTZ, true> : k_spmv_tile<T, TR, HERTZ, false>;
+    const auto kernel = k_spmv_tile<T, TR, HERTZ>;
     if (ctx->kt_start) {   // a timed launch carries the kernel timer's events (ktimer_begin)
         hipExtLaunchKernelGGL(kernel, dim3(A->n_tiles), dim3(256), 0, ctx->stream, ctx->kt_start, ctx->kt_stop, 0, t,
                               x, y, S, inst, part, mode);
@@ -632,13 +631,14 @@ template <class T>
 int spmv_tile(sgp_ctx ctx, sgp_bsr A, const T *x, T *y, const PcgScalars *S, bool per_inst, double *part, int mode)
 {
     const int32_t *inst = per_inst ? tile_args(A).inst : nullptr;
-    if (A->tile_hertz) {
-        if (A->tile_rows == 256) tile_launch<T, 256, true>(ctx, A, x, y, S, inst, part, mode);
-        else tile_launch<T, 128, true>(ctx, A, x, y, S, inst, part, mode);
-    } else {
-        if (A->tile_rows == 256) tile_launch<T, 256, false>(ctx, A, x, y, S, inst, part, mode);
-        else tile_launch<T, 128, false>(ctx, A, x, y, S, inst, part, mode);
-    }
+    auto rows = [&](auto hertz) {
+        constexpr bool H = decltype(hertz)::value;
+        if (A->tile_rows == 256) tile_launch<T, 256, H>(ctx, A, x, y, S, inst, part, mode);
+        else if (A->tile_rows == 128) tile_launch<T, 128, H>(ctx, A, x, y, S, inst, part, mode);
+        else tile_launch<T, 64, H>(ctx, A, x, y, S, inst, part, mode);
+    };
+    if (A->tile_hertz) rows(std::true_type{});
+    else rows(std::false_type{});
     LAUNCH_CHECK(ctx);
     return SGP_OK;
 }
