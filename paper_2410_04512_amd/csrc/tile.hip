@@ -562,11 +562,15 @@ int tile_assemble(sgp_ctx ctx, sgp_graph g, sgp_bsr A)
     A->tile_rows = tile_rows_for(n, 2 * g->m);
     A->tile_w = (std::max(g->max_deg, 1) + 3) / 4 * 4;
     A->tile_hertz = g->hertz;
-    A->tile_off = g->h_inst_off;
+    const std::vector<int64_t> &off = g->h_inst_off;
+    const double most = TILE_CUT * (double)((n + A->tile_rows - 1) / A->tile_rows);
     int64_t tiles = 0;
-    for (int64_t k = 0; k < g->n_inst; k++)
-        tiles += std::max<int64_t>((A->tile_off[k + 1] - A->tile_off[k] + A->tile_rows - 1) / A->tile_rows, 1);
-    if ((double)tiles > TILE_CUT * (double)((n + A->tile_rows - 1) / A->tile_rows)) A->tile_off = {0, n};
+    for (int64_t k = 0; k < g->n_inst && (double)tiles <= most; k++)
+        tiles += std::max<int64_t>((off[k + 1] - off[k] + A->tile_rows - 1) / A->tile_rows, 1);
+    if ((double)tiles > most)
+        A->tile_off = {0, n};
+    else
+        A->tile_off = off;
     if (A->tile_off.size() > 2) {
         std::vector<int32_t> buf;
         build_tab(A->tile_off, A->tile_rows, buf, A->n_tiles);
